@@ -49,23 +49,16 @@ constexpr int kPairBytes = 2 * kPageBytes;      // K page followed by V page
 constexpr int kRowsPerWg = 256;
 constexpr int kMaxSeg = kMaxInflight;
 
-// Rotary embedding of the queries inside the kernel's Q load.  Angles are formed in revolutions:
-// pair j turns by pos * freq[j] / 2pi; that factor is split into a 12-bit head and a tail so that
-// pos * head is exact in fp32 for pos < 4096 and only its fractional part meets the hardware
-// sin / cos (measured: cos and sin within 4.2e-7 of fp64 for every pos < 4096 and every pair).
-struct QRope {
-  float rev_hi[kMaxPairs], rev_lo[kMaxPairs];
-  int32_t pairs_t, pairs_h;            // pairs [0, pairs_t): frame axis, then pairs_h: row axis, rest: column axis
-  int32_t grid_w, plane, block_tokens; // plane = grid_h * grid_w
-  int32_t first_frame[kMaxInflight];   // of the launch's query blocks
-  int64_t tok_stride, head_stride;     // of q, in elements
-};
-
+// Everything a launch needs, in the order the kernel reads it.  A workgroup starts with nothing but
+// this block's address, which the first reads of a launch fetch over the bus: the scalars of the
+// first part come in a few wide loads issued together, the per-segment and per-block tables as one
+// dword per lane of `lanes` (a lane's entry is picked with v_readlane later), the rotation factors
+// as two vectors per lane.  Divisions by launch constants are a multiplication and a correction.
 struct AttnArgs {
-  const uint16_t* q;
+  const uint16_t* q;                   // [row, head, dim] with the strides below; unrotated for attn_bf16_kernel<true>
   uint16_t* o;
   const uint8_t* pool;
-  int32_t heads, pages_per_block, last_valid;
+  float* partials;                     // [xcd][split item][chunk][kPartialFloats]
   // Query segments: rows that share one visible prefix (one segment in a bidirectional cascade,
   // one per query block in a block-causal one, longest prefix first); all have tiles_per_seg row
   // tiles.  A "column" is a (head, row tile) pair; XCD x owns columns [x*cols_per_xcd,
@@ -73,45 +66,69 @@ struct AttnArgs {
   // i / cols_per_xcd of column i % cols_per_xcd.  Workgroups that run together on an XCD then
   // walk KV prefixes of one length, start and finish together, and stay in step on the same pages
   // of the same few heads, which is what keeps those pages in the XCD's L2.
-  int32_t n_seg, tiles_per_seg, total_cols, cols_per_xcd;
-  int32_t seg_row0[kMaxSeg], seg_rows[kMaxSeg], seg_nvis[kMaxSeg];
-  int32_t kv_slot[kMaxKvBlocks];
-  int32_t work_per_xcd;                // = cols_per_xcd * n_seg
-  // Tail balancing: the last `split_items` work items of every XCD's range have their KV walk cut
-  // into `split` page ranges, one workgroup each, so that the launch's last, partly filled round
-  // of workgroups is shorter; their partial results meet in merge_partials_kernel.
+  int32_t heads, pages_per_block, last_valid, n_seg;
+  int32_t tiles_per_seg, total_cols, cols_per_xcd, work_per_xcd;   // work_per_xcd = cols_per_xcd * n_seg
+  // Splitting: the last `split_items` work items of every XCD's range have their KV walk cut
+  // into `split` page ranges, one workgroup each; their partial results meet in
+  // merge_partials_kernel.
   int32_t split, split_items, full_items;   // per XCD: full_items + split_items == work_per_xcd
-  float* partials;                     // [xcd][split item][chunk][kPartialFloats]
   float c;                             // log2(e) / sqrt(head_dim)
-  // Only read by the instantiation that rotates Q itself (attn_bf16_kernel<true>): q is then the
-  // unrotated [row, head, dim] tensor with the caller's strides.
-  QRope rq;
+  float inv_cols, inv_tiles, inv_pages, inv_split, inv_split_items;
+  int64_t q_tok_stride, q_head_stride;
+  // Rotary embedding of the queries (attn_bf16_kernel<true> only).  Angles are formed in revolutions:
+  // pair j turns by pos * freq[j] / 2pi; that factor is split into a 12-bit head and a tail so that
+  // pos * head is exact in fp32 for pos < 4096 and only its fractional part meets the hardware
+  // sin / cos (measured: cos and sin within 4.2e-7 of fp64 for every pos < 4096 and every pair).
+  int32_t pairs_t, pairs_h;            // pairs [0, pairs_t): frame axis, then pairs_h: row axis, rest: column axis
+  int32_t block_tokens, plane, grid_w; // plane = grid_h * grid_w
+  float inv_block, inv_plane, inv_grid_w;
+  int32_t lanes[64];                   // kLane*: first row, rows, visible blocks per segment; first frame per query block; KV slots
+  float rev_hi[kMaxPairs], rev_lo[kMaxPairs];
 };
+constexpr int kLaneRow0 = 0, kLaneRows = 8, kLaneNvis = 16, kLaneFrame = 24, kLaneSlot = 32;
+static_assert(kMaxInflight == 8 && kMaxKvBlocks == 32, "AttnArgs::lanes");
 
-// one partial result of a 256-row tile: O^T contributions [row][128] (fp32, not normalised),
-// then the row's exponent reference (log2 units) and row sum
-constexpr int kPartialRow = 132;                 // floats per row: 128 + reference + sum, padded to 16 B
-constexpr int kPartialFloats = kRowsPerWg * kPartialRow;
+// one partial result of a 256-row tile, in the order the accumulators leave the registers: O^T
+// contributions [slab of 32 rows][group of 8 dims][lane] as fp32 x 4 (not normalised), then (exponent
+// reference in log2 units, row sum) per row
+constexpr int kPartialMl = kRowsPerWg * 128;
+constexpr int kPartialFloats = kRowsPerWg * 132;
 static_assert(size_t(kMaxPartials) * kPartialFloats * 4 == kAttnScratchBytes, "scratch size");
+
+// n / d and n % d for 0 <= n < 2^31, n / d < 2^22, with inv = 1.0f / d: the product is off by less
+// than one, so the quotient needs at most one correction
+__device__ __forceinline__ int div_by(int n, int d, float inv, int* rem) {
+  int q = int(float(n) * inv), r = n - q * d;
+  if (r < 0) {
+    --q;
+    r += d;
+  }
+  if (r >= d) {
+    ++q;
+    r -= d;
+  }
+  *rem = r;
+  return q;
+}
+
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
 struct WorkItem {
   int h, row0, rows_end, n_kvb;     // h < 0: no such item (the last XCD may own fewer columns)
 };
 
-__device__ __forceinline__ WorkItem decode_item(const AttnArgs& a, int xcd, int item) {
+// lane_tab: this lane's entry of AttnArgs::lanes
+__device__ __forceinline__ WorkItem decode_item(const AttnArgs& a, int lane_tab, int xcd, int item) {
   WorkItem w;
-  const int seg = item / a.cols_per_xcd;
-  const int col = xcd * a.cols_per_xcd + (item - seg * a.cols_per_xcd);
-  if (seg >= a.n_seg || col >= a.total_cols) {
-    w.h = -1;
-    w.row0 = w.rows_end = w.n_kvb = 0;
-    return w;
-  }
-  w.h = col / a.tiles_per_seg;
-  const int t = col - w.h * a.tiles_per_seg;
-  w.row0 = a.seg_row0[seg] + t * kRowsPerWg;
-  w.rows_end = a.seg_row0[seg] + a.seg_rows[seg];
-  w.n_kvb = a.seg_nvis[seg];
+  int in_seg, t;
+  const int seg = uniform(div_by(item, a.cols_per_xcd, a.inv_cols, &in_seg));
+  const int col = xcd * a.cols_per_xcd + uniform(in_seg);
+  w.h = uniform(div_by(col, a.tiles_per_seg, a.inv_tiles, &t));
+  const int row0 = __builtin_amdgcn_readlane(lane_tab, kLaneRow0 + seg);
+  w.row0 = row0 + uniform(t) * kRowsPerWg;
+  w.rows_end = row0 + __builtin_amdgcn_readlane(lane_tab, kLaneRows + seg);
+  w.n_kvb = __builtin_amdgcn_readlane(lane_tab, kLaneNvis + seg);
+  if (col >= a.total_cols) w.h = -1;
   return w;
 }
 
@@ -124,123 +141,177 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
 // value of the partner lane (lane ^ 32)
 __device__ __forceinline__ float other_half(float x) { return __shfl_xor(x, 32, 64); }
 
+// what a wave wrote to LDS is there for its other lanes
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 #include "attn_core_clobbers.inc"
 
-// LDS map: K ring (2 pages) then V ring (2 pages); the main loop lives in attn_core_gfx950.inc
-// (generated by gen_attn_core.py, which also documents the pipeline and the register map).
+// LDS map: K ring (2 pages), V ring (2 pages), token positions of the tile's rows; the main loop lives
+// in attn_core_gfx950.inc (generated by gen_attn_core.py, which also documents the pipeline and the
+// register map).  Before the loop the second slots of the two rings hold the tile's Q rows.
 constexpr uint32_t kVRing = 2 * kPageBytes;
+constexpr uint32_t kPosArea = 4 * kPageBytes;
+constexpr int kAttnLds = 4 * kPageBytes + kRowsPerWg * 16;
 
+// What a workgroup spends outside the loop is paid once per item, and one workgroup per CU means that
+// nothing overlaps it: 31 000 cycles (timestamps of a probe build; 7 pages of walk) when a thread rotated a
+// whole row, scalars were fetched one by one and results left in 8-byte pieces, 23 000 now.  So the
+// first K and V page are requested as soon as the item is known, Q is read and the results are
+// written as whole 256-byte rows (through LDS; the matrix layouts hold 16-byte pieces of 32 rows), and
+// the rotation is shared out so that a thread needs the factors of four pairs only (8 700 -> 5 500
+// cycles, the largest part left).  Whole steps: 15 workgroups with 20 pages each 72 -> 67 us, 300 with
+// 70..110 pages 383 -> 366 us; nothing at the 14B shape, where an item walks 407 pages.
 template <bool kRopeQ>
 __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l31 = lane & 31, hi = lane >> 5, sw = lane & 15;
+  const int lane_tab = a.lanes[lane];
+  const int my_slot = a.lanes[kLaneSlot + l31];
+  const int c16 = lane & 15, r4 = lane >> 4;               // 16-byte chunk and row (mod 4) of Q / O this lane moves
+  float rev_hi[4], rev_lo[4];
+  if (kRopeQ) {
+    *reinterpret_cast<float4*>(rev_hi) = *reinterpret_cast<const float4*>(a.rev_hi + 4 * c16);
+    *reinterpret_cast<float4*>(rev_lo) = *reinterpret_cast<const float4*>(a.rev_lo + 4 * c16);
+  }
 
-  // ---- which (head, row tile, page range): XCD x takes its own work_per_xcd items;
-  // inside an XCD the full items come first, then `split` workgroups per split item
+  // ---- which (head, row tile, page range): XCD x takes its own work_per_xcd items; inside an XCD
+  // the full items come first, then the split ones, all their first page ranges, then the second ...
   const int xcd = blockIdx.x & 7, nth = blockIdx.x >> 3;
   int item = nth, chunk = 0, n_chunks = 1;
   if (nth >= a.full_items) {
-    item = a.full_items + (nth - a.full_items) / a.split;
-    chunk = (nth - a.full_items) % a.split;
+    int in_chunk;
+    chunk = uniform(div_by(nth - a.full_items, a.split_items, a.inv_split_items, &in_chunk));
+    item = a.full_items + uniform(in_chunk);
     n_chunks = a.split;
   }
-  if (item >= a.work_per_xcd) return;
-  const WorkItem wi = decode_item(a, xcd, item);
+  const WorkItem wi = decode_item(a, lane_tab, xcd, item);
   if (wi.h < 0) return;
   const int h = wi.h, row0 = wi.row0, rows_end = wi.rows_end, n_kvb = wi.n_kvb;
   const int all_pages = n_kvb * a.pages_per_block;
-  const int page_lo = int(int64_t(all_pages) * chunk / n_chunks);
-  const int page_hi = int(int64_t(all_pages) * (chunk + 1) / n_chunks);
+  int page_lo = 0, page_hi = all_pages, in_block, rem;
+  if (n_chunks > 1) {
+    page_lo = uniform(div_by(all_pages * chunk, n_chunks, a.inv_split, &rem));
+    page_hi = uniform(div_by(all_pages * (chunk + 1), n_chunks, a.inv_split, &rem));
+  }
+  const int kb0 = uniform(div_by(page_lo, a.pages_per_block, a.inv_pages, &in_block)), pg0 = uniform(in_block);
   const int n_pages = page_hi - page_lo;
-  const int kb0 = page_lo / a.pages_per_block, pg0 = page_lo - kb0 * a.pages_per_block;
 
-  // ---- Q fragments: B operand of S^T = K Q^T.  Lane holds dims 16ks + 8hi .. +7 of query l31
-  // of column tile nt; fragment (nt, ks) goes to a[128 + 4*(8nt + ks) ..].
-  // The instantiation that rotates Q itself does so in a pass of its own: thread t rotates row t of
-  // the workgroup's 256 rows, scales, rounds once and parks the row in LDS, which the page rings do
-  // not use yet; the fragment loads below then read LDS.
+  // ---- Q rows: a wave takes its own 64, 16 lanes to a row
+  u32x4 v[16];
+  {
+    const uint16_t* qp = a.q + int64_t(h) * a.q_head_stride + c16 * 8;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int r = min(row0 + wave * 64 + r4 + 4 * i, rows_end - 1);
+      v[i] = *reinterpret_cast<const u32x4*>(qp + int64_t(r) * a.q_tok_stride);
+    }
+  }
+  // ---- the first K and V page on their way into the first slots of their rings
+  const uint32_t lane_off = wave * 1024 + lane * 16;   // this lane's 16 bytes inside each 4 KB slice of a page
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
+  {
+    const int slot0 = __builtin_amdgcn_readlane(lane_tab, kLaneSlot + kb0);
+    const uint64_t k0 = reinterpret_cast<uint64_t>(a.pool) +
+                        ((uint64_t(slot0) * a.pages_per_block + pg0) * a.heads + h) * uint64_t(kPairBytes);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const uint32_t m0 = lds0 + wave * 1024 + (i & 7) * 4096 + (i >> 3) * kVRing;
+      asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+                   :: "s"(m0), "v"(lane_off + (i & 7) * 4096), "s"(k0 + (i >> 3) * uint64_t(kPageBytes)) : "memory", "m0");
+    }
+  }
+  // ---- rotate, scale by c (scores then leave the matrix pipe in log2 units), round once, park the rows
+  // in the second ring slots (rows 0..127 in K's, the others in V's), chunks swizzled as in a page
+  uint8_t* const parked = lds + kPageBytes + (wave >> 1) * kPageBytes + wave * 64 * 256;
   if (kRopeQ) {
-    const int r = row0 + tid;
-    const bool ok = r < rows_end;
-    const int rr = ok ? r : row0;
-    const int blk = rr / a.rq.block_tokens, n = rr - blk * a.rq.block_tokens;
-    const int fr = n / a.rq.plane, in_plane = n - fr * a.rq.plane;
-    const int y = in_plane / a.rq.grid_w;
-    const float pos_f = float(a.rq.first_frame[blk] + fr), pos_y = float(y), pos_x = float(in_plane - y * a.rq.grid_w);
-    const uint16_t* qp = a.q + int64_t(rr) * a.rq.tok_stride + int64_t(h) * a.rq.head_stride;
-    u32x4 v[16];                                            // the row's 16 chunks, all loads in flight at once
+    float4* const pos = reinterpret_cast<float4*>(lds + kPosArea) + wave * 64;
+    {
+      int n, in_plane, x;
+      const int r = min(row0 + tid, rows_end - 1);
+      const int blk = div_by(r, a.block_tokens, a.inv_block, &n);
+      const int fr = div_by(n, a.plane, a.inv_plane, &in_plane);
+      const int y = div_by(in_plane, a.grid_w, a.inv_grid_w, &x);
+      pos[lane] = make_float4(float(__shfl(lane_tab, kLaneFrame + blk) + fr), float(y), float(x), 0.f);
+    }
+    wave_lds_fence();
+    bool on_t[4], on_y[4];
 #pragma unroll
-    for (int c = 0; c < 16; ++c) v[c] = *reinterpret_cast<const u32x4*>(qp + 8 * c);
-    // the per-pair factors go through LDS (behind the 64 KB the rotated rows will take): read from
-    // the argument block with compile-time indices they would sit in 128 scalar registers
-    float* tab = reinterpret_cast<float*>(lds + 65536);
-    if (tid < 2 * kMaxPairs) tab[tid] = tid < kMaxPairs ? a.rq.rev_hi[tid] : a.rq.rev_lo[tid - kMaxPairs];
-    __syncthreads();
+    for (int j = 0; j < 4; ++j) {
+      on_t[j] = 4 * c16 + j < a.pairs_t;
+      on_y[j] = 4 * c16 + j < a.pairs_t + a.pairs_h;
+    }
 #pragma unroll
-    for (int c = 0; c < 16; ++c) {                          // chunk c: dims 8c .. 8c+7, pairs 4c .. 4c+3
+    for (int i = 0; i < 16; ++i) {
+      const int r = r4 + 4 * i;
+      const float4 p = pos[r];
       u32x4 out;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int pair = 4 * c + j;
-        const float pos = pair < a.rq.pairs_t ? pos_f : (pair < a.rq.pairs_t + a.rq.pairs_h ? pos_y : pos_x);
-        const float rev = __builtin_amdgcn_fractf(pos * tab[pair]) + pos * tab[kMaxPairs + pair];
+        const float at = on_t[j] ? p.x : (on_y[j] ? p.y : p.z);
+        const float rev = __builtin_amdgcn_fractf(at * rev_hi[j]) + at * rev_lo[j];
         const float cs = __builtin_amdgcn_cosf(rev), sn = __builtin_amdgcn_sinf(rev);
-        const uint32_t x = ok ? v[c][j] : 0u;
+        const uint32_t x = v[i][j];
         const float u = __uint_as_float(x << 16), w = __uint_as_float(x & 0xffff0000u);
-        // scores come out of the matrix pipe in log2 units: Q is scaled by c = log2(e)/sqrt(D) here
         out[j] = pack2((u * cs - w * sn) * a.c, (u * sn + w * cs) * a.c);
       }
-      *reinterpret_cast<u32x4*>(lds + tid * 256 + ((c ^ (tid & 15)) << 4)) = out;
+      if (row0 + wave * 64 + r >= rows_end) out = u32x4{0, 0, 0, 0};
+      *reinterpret_cast<u32x4*>(parked + r * 256 + ((c16 ^ (r & 15)) << 4)) = out;
     }
-    __syncthreads();
+  } else {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int r = r4 + 4 * i;
+      u32x4 out;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        out[j] = pack2(__uint_as_float(v[i][j] << 16) * a.c, __uint_as_float(v[i][j] & 0xffff0000u) * a.c);
+      if (row0 + wave * 64 + r >= rows_end) out = u32x4{0, 0, 0, 0};
+      *reinterpret_cast<u32x4*>(parked + r * 256 + ((c16 ^ (r & 15)) << 4)) = out;
+    }
   }
-  int qrow[2];
+  wave_lds_fence();
+  // ---- Q fragments: B operand of S^T = K Q^T.  Lane holds dims 16ks + 8hi .. +7 of query l31
+  // of column tile nt; fragment (nt, ks) goes to a[128 + 4*(8nt + ks) ..].
   f32x16 qt[4];
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt) {
-    const int lrow = wave * 64 + nt * 32 + l31;              // row inside the workgroup's tile
-    qrow[nt] = row0 + lrow;
-    const bool ok = qrow[nt] < rows_end;
-    const uint16_t* qp = a.q + (int64_t(ok ? qrow[nt] : row0) * a.heads + h) * 128 + hi * 8;
+  for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
-      if (kRopeQ) {
-        const u32x4 v = *reinterpret_cast<const u32x4*>(lds + lrow * 256 + (((2 * ks + hi) ^ (lrow & 15)) << 4));
+      const u32x4 f = *reinterpret_cast<const u32x4*>(parked + (nt * 32 + l31) * 256 + (((2 * ks + hi) ^ sw) << 4));
 #pragma unroll
-        for (int j = 0; j < 4; ++j) qt[2 * nt + (ks >> 2)][4 * (ks & 3) + j] = __uint_as_float(v[j]);
-      } else {
-        u32x4 v = *reinterpret_cast<const u32x4*>(qp + ks * 16);
-        if (!ok) v = u32x4{0, 0, 0, 0};
-        // scores come out of the matrix pipe in log2 units: Q is scaled by c = log2(e)/sqrt(D) here
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const uint32_t w = pack2(__uint_as_float(v[j] << 16) * a.c, __uint_as_float(v[j] & 0xffff0000u) * a.c);
-          qt[2 * nt + (ks >> 2)][4 * (ks & 3) + j] = __uint_as_float(w);
-        }
-      }
+      for (int j = 0; j < 4; ++j) qt[2 * nt + (ks >> 2)][4 * (ks & 3) + j] = __uint_as_float(f[j]);
     }
-  }
-  if (kRopeQ) __syncthreads();        // every fragment is in registers before the first page lands in LDS
+  __syncthreads();                    // every fragment is in registers: the second slots are free
 
   // address of page 0 of KV block i for this head: lane i of (tbl_lo, tbl_hi)
-  const int my_slot = a.kv_slot[lane & (kMaxKvBlocks - 1)];
   const uint64_t my_off = reinterpret_cast<uint64_t>(a.pool) +
                           (uint64_t(my_slot) * a.pages_per_block * a.heads + h) * uint64_t(kPairBytes);
   const uint32_t tbl_lo = uint32_t(my_off), tbl_hi = uint32_t(my_off >> 32);
   const uint32_t xo0 = l31 * 256 + ((hi ^ sw) << 4);    // row offset + swizzled chunk 0 (or 1 for hi)
-  const uint32_t lane_off = wave * 1024 + lane * 16;   // this lane's 16 bytes inside each 4 KB slice of a page
   const uint32_t kidx = 4 * hi;
   const uint32_t xlane = 4 * (lane ^ 32);
   const uint32_t stride = uint32_t(a.heads) * kPairBytes;
-  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
-  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
 
-  // The first PV product multiplies an all-zero P tile with whatever the second V ring slot
-  // holds: make that finite.
+  // The first PV product multiplies an all-zero P tile with the last 32 keys (chunks 12..15 of every
+  // row) of whatever the second V ring slot holds: make that finite.
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
-    *reinterpret_cast<u32x4*>(lds + kVRing + kPageBytes + (i * 256 + tid) * 16) = u32x4{0, 0, 0, 0};
+  for (int i = 0; i < 2; ++i) {
+    const int row = tid >> 1, ch = 12 + 2 * (tid & 1) + i;
+    *reinterpret_cast<u32x4*>(lds + kVRing + kPageBytes + row * 256 + ((ch ^ (row & 15)) << 4)) = u32x4{0, 0, 0, 0};
+  }
+
+  // The loop leaves few scalar registers: what the epilogue needs waits in LDS, or is read again from
+  // the arguments, through a pointer the compiler cannot see to be the same.
+  if (tid == 0) {
+    const int part_index = n_chunks > 1 ? (xcd * a.split_items + (item - a.full_items)) * n_chunks + chunk : -1;
+    *reinterpret_cast<int4*>(lds + kPosArea) = make_int4(h, row0, rows_end, part_index);
+  }
+  typedef const __attribute__((address_space(4))) AttnArgs* ArgPtr;
+  ArgPtr ap = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
 
   // o6/o7 are not early-clobber: the block reads every VGPR input in its first instructions,
   // before it writes v[96:127], and the inputs need somewhere to live (it uses all of v[128:255])
@@ -255,87 +326,107 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
         [xo0] "v"(xo0), [lane_off] "v"(lane_off), [tbl_lo] "v"(tbl_lo), [tbl_hi] "v"(tbl_hi),
         [kidx] "v"(kidx), [xlane] "v"(xlane), [n_pages] "s"(n_pages), [n_kvb] "s"(n_kvb), [kb0] "s"(kb0), [pg0] "s"(pg0),
         [ppb] "s"(a.pages_per_block), [stride] "s"(stride), [last_valid] "s"(a.last_valid),
-        [wave] "s"(wave_s), [lds0] "s"(lds0)
+        [wave] "s"(wave), [lds0] "s"(lds0)
       : "memory", "vcc", "scc", "m0", CA_CORE_CLOBBERS);
 
+  asm volatile("" : "+s"(ap));
+  const int4 kept = *reinterpret_cast<const int4*>(lds + kPosArea);
+  const int o_head = uniform(kept.x), o_row0 = uniform(kept.y), o_end = uniform(kept.z), part_index = uniform(kept.w);
   // ---- normalise and store: lane holds, for its query, dims 32mt + 8(i/4) + 4hi + (i%4)
   const f32x16 oacc[4][2] = {{o0, o1}, {o2, o3}, {o4, o5}, {o6, o7}};
   const float l_lane[2] = {l0a + l0b, l1a + l1b};
-  if (n_chunks > 1) {
+  if (part_index >= 0) {
     // partial result: accumulators as they are, plus (m_ref, row sum) per row
-    float* part = a.partials + (size_t(xcd * a.split_items + (item - a.full_items)) * a.split + chunk) * kPartialFloats;
+    float* part = ap->partials + size_t(part_index) * kPartialFloats;
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) {
       const float l_tot = l_lane[nt] + other_half(l_lane[nt]);
-      const int r = wave * 64 + nt * 32 + l31;
-      float* rp = part + r * kPartialRow;
+      float4* slab = reinterpret_cast<float4*>(part) + (wave * 2 + nt) * 16 * 64 + lane;
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const f32x16& o = oacc[mt][nt];
           const float x0 = o[4 * g + 0], x1 = o[4 * g + 1], x2 = o[4 * g + 2], x3 = o[4 * g + 3];
-          *reinterpret_cast<float4*>(rp + 32 * mt + 8 * g + 4 * hi) = make_float4(x0, x1, x2, x3);
+          slab[(4 * mt + g) * 64] = make_float4(x0, x1, x2, x3);
         }
-      if (hi == 0) {
-        rp[128] = -(nt ? negm1 : negm0);
-        rp[129] = l_tot;
-      }
+      if (hi == 0)
+        *reinterpret_cast<float2*>(part + kPartialMl + 2 * (wave * 64 + nt * 32 + l31)) = make_float2(-(nt ? negm1 : negm0), l_tot);
     }
     return;
   }
+  // rows leave through LDS: a wave's 64 rows in 16 KB of its own, chunks swizzled, then 16 lanes to a row
+  __syncthreads();                    // no wave reads pages any more, no page load is in flight
+  uint8_t* const mine = lds + wave * 64 * 256;
 #pragma unroll
   for (int nt = 0; nt < 2; ++nt) {
     const float l_tot = l_lane[nt] + other_half(l_lane[nt]);
     const float inv = 1.0f / l_tot;
-    if (qrow[nt] < rows_end) {
-      uint16_t* op = a.o + (int64_t(qrow[nt]) * a.heads + h) * 128 + 4 * hi;
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
+    for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x16& o = oacc[mt][nt];
-          u32x2 w;
-          w[0] = pack2(o[4 * g + 0] * inv, o[4 * g + 1] * inv);
-          w[1] = pack2(o[4 * g + 2] * inv, o[4 * g + 3] * inv);
-          *reinterpret_cast<u32x2*>(op + 32 * mt + 8 * g) = w;
-        }
-    }
+      for (int g = 0; g < 4; ++g) {
+        const f32x16& o = oacc[mt][nt];
+        u32x2 w;
+        w[0] = pack2(o[4 * g + 0] * inv, o[4 * g + 1] * inv);
+        w[1] = pack2(o[4 * g + 2] * inv, o[4 * g + 3] * inv);
+        *reinterpret_cast<u32x2*>(mine + (nt * 32 + l31) * 256 + (((4 * mt + g) ^ sw) << 4) + 8 * hi) = w;
+      }
+  }
+  wave_lds_fence();
+  uint16_t* op = ap->o + int64_t(o_head) * 128 + c16 * 8;
+  const int64_t o_stride = int64_t(ap->heads) * 128;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int r = r4 + 4 * i, row = o_row0 + wave * 64 + r;
+    const u32x4 w = *reinterpret_cast<const u32x4*>(mine + r * 256 + ((c16 ^ (r & 15)) << 4));
+    if (row < o_end) *reinterpret_cast<u32x4*>(op + row * o_stride) = w;
   }
 }
 
 
 // Combines the partial results of the split work items: for every row, the partials are brought
 // to the largest of their exponent references, summed and normalised.  Eight workgroups per tile
-// (blockIdx.y picks 32 of its rows); 32 threads share a row (four dims each), so that a row of a
-// partial tile is read as 512 contiguous bytes and a result row is written as 256.
+// (blockIdx.y picks a slab of 32 rows), a wave per 32 dims; a lane keeps the place it had in the attention
+// kernel, so that every read of a partial tile is 1 KB of contiguous memory.
 __global__ __launch_bounds__(256) void merge_partials_kernel(AttnArgs a) {
+  const int lane = threadIdx.x & 63, mt = threadIdx.x >> 6, l31 = lane & 31, hi = lane >> 5;
+  const int lane_tab = a.lanes[lane];
   const int xcd = blockIdx.x / a.split_items, sidx = blockIdx.x % a.split_items;
-  const WorkItem wi = decode_item(a, xcd, a.full_items + sidx);
-  if (wi.h < 0) return;
-  const int sub = threadIdx.x >> 5, d = 4 * (threadIdx.x & 31);
+  const int slab = blockIdx.y;
   const float* tile = a.partials + size_t(xcd * a.split_items + sidx) * a.split * kPartialFloats;
+  const float* ml = tile + kPartialMl + 2 * (slab * 32 + l31);
+  const float4* part = reinterpret_cast<const float4*>(tile) + (slab * 16 + 4 * mt) * 64 + lane;
+  const WorkItem wi = decode_item(a, lane_tab, xcd, a.full_items + sidx);
+  if (wi.h < 0) return;
+  const int row = wi.row0 + slab * 32 + l31;
+  if (wi.row0 + slab * 32 >= wi.rows_end) return;
+  float m = -INFINITY;
+  for (int c = 0; c < a.split; ++c) m = fmaxf(m, ml[c * kPartialFloats]);
+  float l = 0.f;
+  float4 acc[4];
 #pragma unroll
-  for (int pass = 0; pass < 4; ++pass) {
-    const int r = int(blockIdx.y) * 32 + pass * 8 + sub;
-    const int row = wi.row0 + r;
-    if (row >= wi.rows_end) break;                       // rows only grow from here
-    const float* part = tile + r * kPartialRow;
-    float m = -INFINITY;
-    for (int c = 0; c < a.split; ++c) m = fmaxf(m, part[c * kPartialFloats + 128]);
-    float l = 0.f;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int c = 0; c < a.split; ++c) {
-      const float wgt = __builtin_amdgcn_exp2f(part[c * kPartialFloats + 128] - m);
-      l += wgt * part[c * kPartialFloats + 129];
-      const float4 x = *reinterpret_cast<const float4*>(part + c * kPartialFloats + d);
-      acc.x += wgt * x.x; acc.y += wgt * x.y; acc.z += wgt * x.z; acc.w += wgt * x.w;
+  for (int g = 0; g < 4; ++g) acc[g] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 2
+  for (int c = 0; c < a.split; ++c) {
+    const float2 y = *reinterpret_cast<const float2*>(ml + c * kPartialFloats);
+    const float wgt = __builtin_amdgcn_exp2f(y.x - m);
+    l += wgt * y.y;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const float4 x = part[c * (kPartialFloats / 4) + g * 64];
+      acc[g].x += wgt * x.x; acc[g].y += wgt * x.y; acc[g].z += wgt * x.z; acc[g].w += wgt * x.w;
     }
-    const float inv = 1.0f / l;
+  }
+  if (row >= wi.rows_end) return;
+  const float inv = 1.0f / l;
+  uint16_t* op = a.o + (int64_t(row) * a.heads + wi.h) * 128 + 32 * mt + 4 * hi;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
     u32x2 w;
-    w[0] = pack2(acc.x * inv, acc.y * inv);
-    w[1] = pack2(acc.z * inv, acc.w * inv);
-    *reinterpret_cast<u32x2*>(a.o + (int64_t(row) * a.heads + wi.h) * 128 + d) = w;
+    w[0] = pack2(acc[g].x * inv, acc[g].y * inv);
+    w[1] = pack2(acc[g].z * inv, acc[g].w * inv);
+    *reinterpret_cast<u32x2*>(op + 8 * g) = w;
   }
 }
 
@@ -361,24 +452,24 @@ int32_t plan_attn_bf16(const AttnPlan& p, int variant, const void* q, void* out,
   a.heads = p.heads;
   a.pages_per_block = p.pages_per_block;
   a.last_valid = p.block_tokens - (p.pages_per_block - 1) * 128;
-  for (int i = 0; i < p.n_kv; ++i) a.kv_slot[i] = p.kv_slot[i];
+  for (int i = 0; i < p.n_kv; ++i) a.lanes[kLaneSlot + i] = p.kv_slot[i];
   // Query segments: rows sharing one visible prefix are tiled together.  A bidirectional
   // cascade is one segment; block-causal gives one segment per in-flight block.
   int tiles = 0;
   if (p.uniform) {
     a.n_seg = 1;
-    a.seg_row0[0] = 0;
-    a.seg_rows[0] = p.n_q_blocks * p.block_tokens;
-    a.seg_nvis[0] = p.n_vis[0];
-    tiles = (a.seg_rows[0] + kRowsPerWg - 1) / kRowsPerWg;
+    a.lanes[kLaneRow0] = 0;
+    a.lanes[kLaneRows] = p.n_q_blocks * p.block_tokens;
+    a.lanes[kLaneNvis] = p.n_vis[0];
+    tiles = (a.lanes[kLaneRows] + kRowsPerWg - 1) / kRowsPerWg;
   } else {
     // one segment per query block, the longest prefix (latest block) first
     a.n_seg = p.n_q_blocks;
     for (int j = 0; j < p.n_q_blocks; ++j) {
       const int i = p.n_q_blocks - 1 - j;
-      a.seg_row0[j] = i * p.block_tokens;
-      a.seg_rows[j] = p.block_tokens;
-      a.seg_nvis[j] = p.n_vis[i];
+      a.lanes[kLaneRow0 + j] = i * p.block_tokens;
+      a.lanes[kLaneRows + j] = p.block_tokens;
+      a.lanes[kLaneNvis + j] = p.n_vis[i];
     }
     tiles = (p.block_tokens + kRowsPerWg - 1) / kRowsPerWg;
   }
@@ -387,6 +478,8 @@ int32_t plan_attn_bf16(const AttnPlan& p, int variant, const void* q, void* out,
   a.cols_per_xcd = (a.total_cols + 7) / 8;
   a.work_per_xcd = a.cols_per_xcd * a.n_seg;
   a.c = 1.4426950408889634f / sqrtf(float(p.head_dim));
+  a.q_tok_stride = int64_t(p.heads) * 128;       // rotated queries are contiguous
+  a.q_head_stride = 128;
   // Tail balancing.  One workgroup occupies a CU, an XCD has n_cu/8 of them, and all items of a
   // launch take about the same time: after floor(items / cus) full rounds, `rem` items would run
   // alone while the other CUs idle.  Their KV walks are cut into split = floor(cus / rem) ranges.
@@ -413,6 +506,11 @@ int32_t plan_attn_bf16(const AttnPlan& p, int variant, const void* q, void* out,
       *partials_needed = 8 * rem * split;
     }
   }
+  a.inv_cols = 1.0f / float(a.cols_per_xcd);
+  a.inv_tiles = 1.0f / float(a.tiles_per_seg);
+  a.inv_pages = 1.0f / float(a.pages_per_block);
+  a.inv_split = 1.0f / float(a.split);
+  a.inv_split_items = 1.0f / float(a.split_items > 0 ? a.split_items : 1);
   return CA_OK;
 }
 
@@ -420,11 +518,11 @@ int32_t enqueue_attn_bf16(const AttnArgs& a, bool rope_q, void* stream) {
   const dim3 grid((unsigned)((a.full_items + a.split_items * a.split) * 8));
   const void* kernel = rope_q ? reinterpret_cast<const void*>(attn_bf16_kernel<true>)
                               : reinterpret_cast<const void*>(attn_bf16_kernel<false>);
-  if (const int32_t rc = ensure_dynamic_lds(kernel, 4 * kPageBytes, rope_q ? 2 : 0); rc != CA_OK) return rc;
+  if (const int32_t rc = ensure_dynamic_lds(kernel, kAttnLds, rope_q ? 2 : 0); rc != CA_OK) return rc;
   if (rope_q)
-    hipLaunchKernelGGL(attn_bf16_kernel<true>, grid, dim3(256), 4 * kPageBytes, static_cast<hipStream_t>(stream), a);
+    hipLaunchKernelGGL(attn_bf16_kernel<true>, grid, dim3(256), kAttnLds, static_cast<hipStream_t>(stream), a);
   else
-    hipLaunchKernelGGL(attn_bf16_kernel<false>, grid, dim3(256), 4 * kPageBytes, static_cast<hipStream_t>(stream), a);
+    hipLaunchKernelGGL(attn_bf16_kernel<false>, grid, dim3(256), kAttnLds, static_cast<hipStream_t>(stream), a);
   if (a.split > 1)
     hipLaunchKernelGGL(merge_partials_kernel, dim3((unsigned)(8 * a.split_items), kRowsPerWg / 32), dim3(256), 0,
                        static_cast<hipStream_t>(stream), a);
@@ -456,22 +554,25 @@ int32_t launch_attn_bf16_rope(const AttnPlan& p, const QRopePlan& rp, int varian
     int e = 0;
     const double m = std::frexp(rev, &e);                       // rev = m 2^e, 0.5 <= m < 1
     const double head = std::ldexp(std::floor(std::ldexp(m, 12)), e - 12);
-    a.rq.rev_hi[j] = float(head);
-    a.rq.rev_lo[j] = float(rev - head);
+    a.rev_hi[j] = float(head);
+    a.rev_lo[j] = float(rev - head);
   }
-  a.rq.pairs_t = rp.geom.pairs_t;
-  a.rq.pairs_h = rp.geom.pairs_h;
-  a.rq.grid_w = rp.geom.grid_w;
-  a.rq.plane = rp.geom.grid_h * rp.geom.grid_w;
-  a.rq.block_tokens = p.block_tokens;
+  a.pairs_t = rp.geom.pairs_t;
+  a.pairs_h = rp.geom.pairs_h;
+  a.grid_w = rp.geom.grid_w;
+  a.plane = rp.geom.grid_h * rp.geom.grid_w;
+  a.block_tokens = p.block_tokens;
+  a.inv_block = 1.0f / float(a.block_tokens);
+  a.inv_plane = 1.0f / float(a.plane);
+  a.inv_grid_w = 1.0f / float(a.grid_w);
   for (int i = 0; i < p.n_q_blocks; ++i) {
     // positions must stay below 4096 for the exact head product (frames are the only axis that grows)
-    if (rp.first_frame[i] < 0 || rp.first_frame[i] + p.block_tokens / a.rq.plane >= 4096) return CA_EUNSUPPORTED;
-    a.rq.first_frame[i] = int32_t(rp.first_frame[i]);
+    if (rp.first_frame[i] < 0 || rp.first_frame[i] + p.block_tokens / a.plane >= 4096) return CA_EUNSUPPORTED;
+    a.lanes[kLaneFrame + i] = int32_t(rp.first_frame[i]);
   }
   if (rp.geom.grid_h >= 4096 || rp.geom.grid_w >= 4096) return CA_EUNSUPPORTED;
-  a.rq.tok_stride = rp.tok_stride;
-  a.rq.head_stride = rp.head_stride;
+  a.q_tok_stride = rp.tok_stride;
+  a.q_head_stride = rp.head_stride;
   return enqueue_attn_bf16(a, true, stream);
 }
 

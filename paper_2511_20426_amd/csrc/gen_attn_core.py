@@ -494,6 +494,19 @@ def generate():
         E.e(f"v_xor_b32 {V(XOK + j)}, {j << 5}, %[xo0]")
         E.e(f"v_add_u32 {V(XOK + j)}, s{S_LDS0}, {V(XOK + j)}")
         E.e(f"v_add_u32 {V(XOV + j)}, {VRING}, {V(XOK + j)}")
+    # the walk starts at page pg0 of visible block kb0 (0, 0 unless the KV range of a tile is split)
+    E.e(f"s_mov_b32 s{S_PGCUR}, %[pg0]")
+    E.e(f"s_add_u32 s{S_T}, s{S_PGCUR}, 1")
+    E.e(f"s_cmp_eq_u32 s{S_T}, s{S_P}")
+    E.e(f"s_cselect_b32 s{S_PGNEXT}, 0, s{S_T}")
+    E.e(f"s_mov_b32 s{S_KKB}, %[kb0]")
+    E.e(f"s_mov_b32 s{S_KPG}, %[pg0]")
+    # ---- K(0) and V(0) are in flight already (requested by the code around this block, oldest first);
+    # K(1) joins them, the accumulators are cleared meanwhile; wait for the first two, publish
+    for grp in page_advance_lines():
+        for ln in grp:
+            E.e(ln)
+    emit_issue_page(E, 0, PAGE)
     for r in range(128):
         E.e(f"v_accvgpr_write_b32 {A(r)}, 0")
     for r in range(4):
@@ -505,23 +518,6 @@ def generate():
             E.e(f"v_mov_b32 {V(NT[nt] + i)}, 0")
     for r in range(16):
         E.e(f"v_mov_b32 {V(P_TILE['B'] + r)}, 0")
-    # the walk starts at page pg0 of visible block kb0 (0, 0 unless the KV range of a tile is split)
-    E.e(f"s_mov_b32 s{S_PGCUR}, %[pg0]")
-    E.e(f"s_add_u32 s{S_T}, s{S_PGCUR}, 1")
-    E.e(f"s_cmp_eq_u32 s{S_T}, s{S_P}")
-    E.e(f"s_cselect_b32 s{S_PGNEXT}, 0, s{S_T}")
-    E.e(f"s_mov_b32 s{S_KKB}, %[kb0]")
-    E.e(f"s_mov_b32 s{S_KPG}, %[pg0]")
-    # ---- K(0), V(0), K(1) in flight; wait for the first two, publish
-    for grp in page_address_lines() + v_address_lines():
-        for ln in grp:
-            E.e(ln)
-    emit_issue_page(E, 0, 0)
-    emit_issue_page(E, 1, VRING)
-    for grp in page_advance_lines():
-        for ln in grp:
-            E.e(ln)
-    emit_issue_page(E, 0, PAGE)
     E.e("s_waitcnt vmcnt(8) lgkmcnt(0)")
     E.e("s_barrier")
     # ---- S tile of step 0 into tile A, its mask, max and reference
