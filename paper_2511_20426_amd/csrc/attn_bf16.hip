@@ -407,7 +407,7 @@ __global__ __launch_bounds__(256) void merge_partials_kernel(AttnArgs a) {
   float4 acc[4];
 #pragma unroll
   for (int g = 0; g < 4; ++g) acc[g] = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 2
+#pragma unroll 4
   for (int c = 0; c < a.split; ++c) {
     const float2 y = *reinterpret_cast<const float2*>(ml + c * kPartialFloats);
     const float wgt = __builtin_amdgcn_exp2f(y.x - m);
@@ -437,7 +437,27 @@ int32_t attn_bf16_variant_ok(int variant) { return variant == 0 || variant == 1 
 
 namespace {
 
-// Fills the kernel arguments for one forward.  Tail balancing: `capacity` partial results fit in
+// How many page ranges the items of a launch that leaves CUs idle are cut into.  A walk of n pages cut
+// in s takes ceil(n / s) page times of 1.95 us; against that stand the merge launch, about one page time,
+// and every partial result that is written and read again (135 KB), 1/40 of one.  Measured, whole
+// forwards: 1 item of 14 pages 37.7 us whole, 26.7 in two, 18.8 in seven; 15 of 20 pages 54.8 whole, 41.1 / 30.1 /
+// 32.3 in 2 / 5 / 8; 64 of 14 pages 42.0 whole, 33.9 in four; 38 of 259 pages 473 whole, 141 in six; 120 of 14 pages
+// 44.9 whole, 44.2 in two.
+int split_of_small_launch(int items_per_xcd, int cus_per_xcd, int items, int min_pages, int max_pages, int capacity) {
+  constexpr int kMaxSplit = 16;
+  int best = 1, best_cost = 40 * max_pages;                    // in 40ths of a page time
+  for (int s = 2; s <= kMaxSplit && s * items_per_xcd <= cus_per_xcd && s <= min_pages; ++s) {
+    if (8 * items_per_xcd * s > capacity) break;
+    const int cost = 40 * ((max_pages + s - 1) / s + 1) + items * s;
+    if (cost < best_cost) {
+      best = s;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
+// Fills the kernel arguments for one forward.  Splitting: `capacity` partial results fit in
 // the scratch area; with adapt the split is reduced until the partials fit, without it the split
 // the device's CU count asks for is kept and *partials_needed tells the caller how many it takes.
 int32_t plan_attn_bf16(const AttnPlan& p, int variant, const void* q, void* out, const void* pool, void* partials_dev,
@@ -480,9 +500,10 @@ int32_t plan_attn_bf16(const AttnPlan& p, int variant, const void* q, void* out,
   a.c = 1.4426950408889634f / sqrtf(float(p.head_dim));
   a.q_tok_stride = int64_t(p.heads) * 128;       // rotated queries are contiguous
   a.q_head_stride = 128;
-  // Tail balancing.  One workgroup occupies a CU, an XCD has n_cu/8 of them, and all items of a
+  // Splitting.  One workgroup occupies a CU, an XCD has n_cu/8 of them, and all items of a
   // launch take about the same time: after floor(items / cus) full rounds, `rem` items would run
   // alone while the other CUs idle.  Their KV walks are cut into split = floor(cus / rem) ranges.
+  // A launch that does not give every CU an item has all of them cut.
   int n_cu = 0;
   if (const int32_t rc = device_cu_count(&n_cu); rc != CA_OK) return rc;
   const int cus_per_xcd = n_cu >= 8 ? n_cu / 8 : 1;
@@ -493,12 +514,19 @@ int32_t plan_attn_bf16(const AttnPlan& p, int variant, const void* q, void* out,
   const int rem = a.work_per_xcd % cus_per_xcd;
   int min_vis = p.n_vis[0];                                    // shortest KV walk of the launch
   for (int i = 1; i < p.n_q_blocks; ++i) min_vis = p.n_vis[i] < min_vis ? p.n_vis[i] : min_vis;
-  const int min_pages = min_vis * p.pages_per_block;
+  int max_vis = p.n_vis[0];
+  for (int i = 1; i < p.n_q_blocks; ++i) max_vis = p.n_vis[i] > max_vis ? p.n_vis[i] : max_vis;
+  const int min_pages = min_vis * p.pages_per_block, max_pages = max_vis * p.pages_per_block;
   *partials_needed = 0;
-  if (partials_dev && variant == 0 && rem > 0 && a.work_per_xcd > cus_per_xcd) {
-    int split = cus_per_xcd / rem;
-    if (split > 8) split = 8;
-    while (split > 1 && (min_pages < 8 * split || (adapt && 8 * rem * split > capacity))) --split;
+  if (partials_dev && variant == 0 && rem > 0) {
+    int split = 1;
+    if (a.work_per_xcd > cus_per_xcd) {
+      split = cus_per_xcd / rem;
+      if (split > 8) split = 8;
+      while (split > 1 && (min_pages < 8 * split || (adapt && 8 * rem * split > capacity))) --split;
+    } else {
+      split = split_of_small_launch(rem, cus_per_xcd, a.total_cols * a.n_seg, min_pages, max_pages, capacity);
+    }
     if (split > 1) {
       a.split = split;
       a.split_items = rem;

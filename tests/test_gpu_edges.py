@@ -28,3 +28,19 @@ def test_f32_key_tiles(head_dim, fpb, gh, gw, page, nc, ni):
         out = Hn.gpu_forward(w, pool, q, infl, mode)
         ref = np.concatenate(Hn.oracle_forward(w, q, k, v, cached, infl, mode))
         Hn.assert_close(out, ref, "f32", f"f32 tiles D={head_dim} L={w.block_tokens} page={page} mode={mode}")
+
+
+# bf16 attention of launches that leave CUs idle: every KV walk cut into page ranges.  One item in as many
+# ranges as it has pages (the last one ragged), items absent on some XCDs, walks of different lengths
+# (block-causal) in ranges that begin and end inside blocks.
+@pytest.mark.parametrize("heads,gh,gw,nc,ni", [(1, 4, 11, 1, 1), (1, 9, 10, 3, 1), (3, 9, 13, 1, 3), (9, 5, 9, 5, 1), (2, 20, 30, 0, 2)])
+def test_bf16_split_small_launch(heads, gh, gw, nc, ni):
+    w = W.small_variant(W.CONFIGS["c3_wan1p3b_cascade5"], heads=heads, grid_h=gh, grid_w=gw, n_cached=nc, n_inflight=ni)
+    cached, infl = list(range(nc)), list(range(nc, nc + ni))
+    q, k, v = W.draw_config(w, seed=6)
+    pool = Hn.gpu_setup(w, k, v, cached, infl)
+    for mode in (BI, CA):
+        pool.pool[pool.pool.numel() - (256 * 256 * 132 * 4):].fill_(0xFF)       # partial results start as NaN
+        out = Hn.gpu_forward(w, pool, q, infl, mode)
+        ref, bound = (np.concatenate(x) for x in Hn.oracle_forward_bounded(w, q, k, v, cached, infl, mode))
+        Hn.assert_close(out, ref, "bf16", f"split heads={heads} grid={gh}x{gw} nc={nc} ni={ni} mode={mode}", bound=bound)
