@@ -236,8 +236,8 @@ int32_t ca_debug_visibility(const ca_ctx* ctx, const int64_t* inflight_block_ids
  * nothing is allocated and nothing but y[0..m_rows) x [0..n_out) is written.  The QKV projection
  * writes [tokens][3][heads][head_dim] rows that rope3d_apply and kv_cache_append take as strided
  * views.  Supported shapes: n_out a multiple of 8, k_in a multiple of 128 (CA_EUNSUPPORTED
- * otherwise); m_rows is free (0: nothing is done, CA_OK).  Tiles are 256 x 256: an n_out that is not
- * a multiple of 256 costs the padding of its last column tile. */
+ * otherwise); m_rows is free (0: nothing is done, CA_OK).  Tiles are 64 x 64 to 256 x 256, by the size
+ * of the product; the result does not depend on the choice. */
 int32_t layer_linear_bf16(const void* x_dev, const void* w_dev, void* y_dev, int64_t m_rows, int32_t n_out,
                           int32_t k_in, int64_t ldx, int64_t ldw, int64_t ldy, void* hip_stream);
 
@@ -253,8 +253,8 @@ int32_t layer_linear_bf16(const void* x_dev, const void* w_dev, void* y_dev, int
  * kv_cache_append_batch: entries NOISY(timestep, epoch), all or none; slots_out optional.
  * The pool bytes are those that layer_linear_bf16 followed by kv_cache_append_batch on its k and v
  * columns would write, byte for byte.  bf16 contexts with an even number of heads and k_in a
- * multiple of 128 (CA_EUNSUPPORTED otherwise); row tiles are counted per block, so the launch
- * computes ceil(L / 256) * 256 rows per block. */
+ * multiple of 128 (CA_EUNSUPPORTED otherwise); row tiles (128 or 256 rows) are counted per
+ * block. */
 int32_t layer_qkv_publish(ca_ctx* ctx, int32_t n_blocks, const int64_t* block_ids, const int32_t* timesteps,
                           int32_t prompt_epoch, const void* x_dev, int64_t ldx, const void* w_qkv_dev,
                           int64_t ldw, int32_t k_in, void* q_out_dev, void* hip_stream, int32_t* slots_out);

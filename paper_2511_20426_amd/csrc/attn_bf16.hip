@@ -546,7 +546,7 @@ int32_t enqueue_attn_bf16(const AttnArgs& a, bool rope_q, void* stream) {
   const dim3 grid((unsigned)((a.full_items + a.split_items * a.split) * 8));
   const void* kernel = rope_q ? reinterpret_cast<const void*>(attn_bf16_kernel<true>)
                               : reinterpret_cast<const void*>(attn_bf16_kernel<false>);
-  if (const int32_t rc = ensure_dynamic_lds(kernel, kAttnLds, rope_q ? 2 : 0); rc != CA_OK) return rc;
+  if (const int32_t rc = ensure_dynamic_lds(kernel, kAttnLds, rope_q ? kLdsAttnRope : kLdsAttn); rc != CA_OK) return rc;
   if (rope_q)
     hipLaunchKernelGGL(attn_bf16_kernel<true>, grid, dim3(256), kAttnLds, static_cast<hipStream_t>(stream), a);
   else

@@ -130,7 +130,9 @@ int32_t launch_gemm_qkv_publish(const RopeGeom& g, int32_t n_blocks, int32_t blo
 // safe: the cached values are idempotent and written with relaxed atomics).
 constexpr int kMaxDevices = 64;
 int32_t device_cu_count(int* n_cu);                                   // of the current device
-int32_t ensure_dynamic_lds(const void* kernel, int bytes, int slot);  // slot: 0 attention, 1 GEMM, 2 attention rotating Q, 3 publishing GEMM
+enum LdsSlot { kLdsAttn, kLdsAttnRope, kLdsGemm256, kLdsGemm256Publish, kLdsGemm256x128, kLdsGemm256x128Publish, kLdsGemm128,
+               kLdsGemm128Publish, kLdsGemm64, kLdsGemm64Wide, kLdsSlots };
+int32_t ensure_dynamic_lds(const void* kernel, int bytes, LdsSlot slot);
 int32_t finish_launch(const char* what);   // launchers end with this: CA_OK, or CA_EDEVICE after recording HIP's last error
 int32_t device_failure(const char* what, int hip_error);   // records the text, clears HIP's last error, returns CA_EDEVICE
 const char* last_device_error();

@@ -1,6 +1,7 @@
 // Y[M,N] = X[M,K] . W[N,K]^T in bf16 with fp32 accumulation: the linear maps either side of the
 // attention inside a DiT layer (QKV projection before it, output projection after it).
 //
+//   gemm_bf16_kernel, for products that fill the chip with 256 x 256 tiles (pick_gemm_tile; the others: gemm_tile_kernel).
 //   Workgroup = 4 waves = a 256 x 256 tile of Y, one wave per SIMD; the main loop (K in stages of
 //   64, both operands through rings in LDS that together fill its 160 KB) is the assembly
 //   emitted by gen_gemm_core.py, which documents the pipeline and the register map.  This file
@@ -27,6 +28,8 @@ namespace {
 
 typedef __attribute__((ext_vector_type(16))) uint32_t u32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int kTile = 256;
 constexpr int kSbRows = 8, kSbCols = 4;           // tiles of one XCD's block
@@ -54,7 +57,7 @@ struct GemmArgs {
   uint16_t* y;                                    // publishing: the packed queries [M][heads * 128]
   int32_t M, N, K;
   int64_t ldx, ldw, ldy;                          // row strides in elements
-  int32_t tiles_m, tiles_n, sb_cols, n_sb;
+  int32_t tiles_m, tiles_n, sb_cols, n_sb;        // gemm_tile_kernel: n_sb = tiles of an XCD
   // Row tiles are counted inside row blocks of block_rows rows, tiles_per_block each (the last
   // one ragged): one block spanning all of M for the plain product, one per in-flight block when
   // publishing.
@@ -65,6 +68,88 @@ struct GemmArgs {
 constexpr int kTrigBytes = 12288;                 // per 128-token page; two pages per workgroup behind the staging area
 
 #include "gemm_core_clobbers.inc"
+
+// ---- publishing epilogue.  A 128 x 128 tile in LDS (`tile`, rows of kEpiRow bytes, kEpiRowV in the v section) is one
+// head of q, k or v (output rows are ordered q|k|v, head, dim: `col` is its first) for the 128 tokens of page `page`
+// of block `blk`, rows m0 .. of the product.  kThreads threads share it, this one is number t; a page's cos / sin table
+// is filled by fill_n threads, this one number fill_t.  Every thread of the workgroup calls this (there is a barrier in
+// it) and all tiles of a workgroup are of one section.
+template <int kThreads>
+__device__ __forceinline__ void publish_tile(const GemmArgs& a, const uint8_t* tile, int col, int blk, int page, int m0,
+                                             float2* trig, int t, int fill_t, int fill_n) {
+  constexpr int kRowsPerTrip = kThreads / 16;
+  const PublishArgs& pb = a.pub;
+  const int width = pb.heads * 128;
+  const int section = col / width, head = (col - section * width) >> 7;
+  const int tok0 = page * 128;                                                // first token of the page in its block
+  const int c = t & 15, r4 = t >> 4;
+  if (section == 0) {                      // q: as it is (the attention kernel rotates it), packed rows
+#pragma unroll 4
+    for (int it = 0; it < 128 / kRowsPerTrip; ++it) {
+      const int row = it * kRowsPerTrip + r4;
+      const u32x4 v = *reinterpret_cast<const u32x4*>(tile + row * kEpiRow + c * 16);
+      if (tok0 + row < a.block_rows)
+        __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(a.y + int64_t(m0 + row) * a.ldy + head * 128 + c * 8));
+    }
+    return;
+  }
+  const bool has_page = page < pb.pages_per_block;
+  uint8_t* kpage = pb.pool + ((int64_t(pb.slot[blk]) * pb.pages_per_block + (has_page ? page : 0)) * pb.heads + head) *
+                                 int64_t(2 * 128 * 128 * 2);
+  if (section == 1) {                      // k: rotate by the token's position, K page rows, pad rows zero
+    TrigLayout lay{};
+    if (pb.tab.n_f > 0) {
+      lay = trig_layout(pb.g, pb.tab, tok0, a.block_rows, pb.first_frame[blk]);
+      if (has_page) trig_fill(pb.g, lay, trig, fill_t, fill_n);
+    }
+    __syncthreads();
+    if (!has_page) return;
+    // the thread's rows are tokens tok0 + r4 + kRowsPerTrip it
+    TokenPos p = token_pos(min(tok0 + r4, a.block_rows - 1), pb.first_frame[blk], pb.g.grid_h, pb.g.grid_w);
+#pragma unroll 2
+    for (int it = 0; it < 128 / kRowsPerTrip; ++it, p = token_advance(p, kRowsPerTrip, pb.g.grid_h, pb.g.grid_w)) {
+      const int row = it * kRowsPerTrip + r4;
+      U4 kk = {0, 0, 0, 0};
+      if (tok0 + row < a.block_rows) {
+        float cs[4], sn[4];
+        if (pb.tab.n_f > 0) {
+          trig_pick(pb.g, lay, trig, p, c, cs, sn);
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) pair_cs<false>(pb.g, p, c * 4 + j, &cs[j], &sn[j]);
+        }
+        const U4 raw = *reinterpret_cast<const U4*>(tile + row * kEpiRow + c * 16);
+        Vec8<uint16_t> e;
+        e.v[0] = bf16_lo(raw.x); e.v[1] = bf16_hi(raw.x); e.v[2] = bf16_lo(raw.y); e.v[3] = bf16_hi(raw.y);
+        e.v[4] = bf16_lo(raw.z); e.v[5] = bf16_hi(raw.z); e.v[6] = bf16_lo(raw.w); e.v[7] = bf16_hi(raw.w);
+        rotate8(e, cs, sn);
+        kk.x = pack_bf16(e.v[0], e.v[1]); kk.y = pack_bf16(e.v[2], e.v[3]);
+        kk.z = pack_bf16(e.v[4], e.v[5]); kk.w = pack_bf16(e.v[6], e.v[7]);
+      }
+      store_once(kpage + row * 256 + ((c ^ (row & 15)) << 4), kk);
+    }
+    return;
+  }
+  // v: V page rows are dims; chunk c of a row holds tokens 16 (c / 2) + 4 (c % 2) + {0..3, 8..11}
+  if (!has_page) return;
+  uint8_t* vpage = kpage + 128 * 128 * 2;
+  const int tb = 16 * (c >> 1) + 4 * (c & 1);
+#pragma unroll 2
+  for (int it = 0; it < 128 / kRowsPerTrip; ++it) {
+    const int d = it * kRowsPerTrip + r4;
+    uint32_t e[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int tok = tb + (j & 3) + 8 * (j >> 2);
+      const uint32_t w = *reinterpret_cast<const uint16_t*>(tile + tok * kEpiRowV + d * 2);
+      e[j] = tok0 + tok < a.block_rows ? w : 0u;
+    }
+    U4 o;
+    o.x = e[0] | (e[1] << 16); o.y = e[2] | (e[3] << 16);
+    o.z = e[4] | (e[5] << 16); o.w = e[6] | (e[7] << 16);
+    store_once(vpage + d * 256 + ((c ^ (d & 15)) << 4), o);
+  }
+}
 
 template <bool kPublish>
 __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(GemmArgs a) {
@@ -148,81 +233,154 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(GemmArgs a) {
     }
     return;
   }
-  // ---- publishing epilogue.  The wave's sub-tile is one head of q, k or v (output rows are
-  // ordered q|k|v, head, dim) for the 128 tokens of page 2 * tile_in_blk + wm of block blk.
-  const PublishArgs& pb = a.pub;
-  const int width = pb.heads * 128;
-  const int col = n0 + wn * 128;
-  const int section = col / width, head = (col - section * width) >> 7;      // the same for all four waves' section
+  // ---- publishing epilogue: the wave's sub-tile is one head of q, k or v for one page of a block
   const int page = 2 * tile_in_blk + wm;
-  const int tok0 = page * 128;                                                // first token of the page in its block
-  const int c = lane & 15, r4 = lane >> 4;
-  if (section == 0) {                      // q: as it is (the attention kernel rotates it), packed rows
+  float2* trig = reinterpret_cast<float2*>(lds + 4 * kEpiWave + wm * kTrigBytes);
+  publish_tile<64>(a, mine, n0 + wn * 128, blk, page, m0 + wm * 128, trig, lane, wn * 64 + lane, 128);
+}
+
+
+// Smaller tiles, for products whose 256 x 256 tiles would leave CUs idle: K walked in the same stages of 64, through a
+// ring of kStages in LDS filled by global -> LDS loads, kWavesM x kWavesN waves of 16 x 16 tiles, operands read one k-step
+// ahead.  What bounds them: LDS reads and fills (128 x 128 in eight waves: 128 KB a stage = 1024 cycles, 1000 measured, for
+// 512 of the matrix pipe), at 64 x 64 with few workgroups the latency of a stage; that is why the smallest takes eight
+// waves and six stages.
+template <int BM, int BN, int kWavesM, int kWavesN, int kStages>
+struct TileShape {
+  static constexpr int kWaves = kWavesM * kWavesN, kThreads = 64 * kWaves;
+  static constexpr int kTm = BM / kWavesM / 16, kTn = BN / kWavesN / 16;   // 16 x 16 tiles of a wave
+  static constexpr int kStageBytes = (BM + BN) * 128;
+  static constexpr int kLoadsW = BN / 8 / kWaves, kLoadsX = BM / 8 / kWaves;   // 1 KB loads of a wave per stage
+  static constexpr int kPitch = BN * 2 + 16;
+  static constexpr int kEpi = BM * kPitch + (BN == 128 ? BM / 128 * kTrigBytes : 0);
+  static constexpr int kLds = kStages * kStageBytes > kEpi ? kStages * kStageBytes : kEpi;
+  static_assert(kLoadsW * 8 * kWaves == BN && kLoadsX * 8 * kWaves == BM && kLds <= kGemmLds, "shape");
+};
+
+template <int BM, int BN, int kWavesM, int kWavesN, int kStages, bool kPublish>
+__global__ __launch_bounds__(64 * kWavesM * kWavesN) void gemm_tile_kernel(GemmArgs a) {
+  using T = TileShape<BM, BN, kWavesM, kWavesN, kStages>;
+  extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l15 = lane & 15, grp = lane >> 4;
+  const int wm = wave % kWavesM, wn = wave / kWavesM;
+  // XCD x takes a contiguous range of the tiles, which are numbered down bands of eight row tiles: its workgroups
+  // share a few row slabs of X and of W in that XCD's L2
+  const int nth = int(blockIdx.x & 7) * a.n_sb + int(blockIdx.x >> 3);
+  if (nth >= a.tiles_m * a.tiles_n) return;
+  const int band = nth / (kSbRows * a.tiles_n), in_band = nth - band * kSbRows * a.tiles_n;
+  const int height = min(kSbRows, a.tiles_m - band * kSbRows);
+  const int tn = in_band / height, tm = band * kSbRows + in_band - tn * height;
+  const int blk = tm / a.tiles_per_block, tile_in_blk = tm - blk * a.tiles_per_block;
+  const int m0 = blk * a.block_rows + tile_in_blk * BM, n0 = tn * BN;
+  const int m_end = min((blk + 1) * a.block_rows, a.M);
+
+  // as in gemm_bf16_kernel: load i of a wave brings 8 whole 128-byte rows, chunks swizzled by the row
+  uint32_t offw[T::kLoadsW], offx[T::kLoadsX];
+#pragma unroll
+  for (int i = 0; i < T::kLoadsW; ++i) {
+    const int row = (wave * T::kLoadsW + i) * 8 + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
+    offw[i] = uint32_t(int64_t(min(n0 + row, a.N - 1) - n0) * a.ldw * 2 + c * 16);
+  }
+#pragma unroll
+  for (int i = 0; i < T::kLoadsX; ++i) {
+    const int row = (wave * T::kLoadsX + i) * 8 + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
+    offx[i] = uint32_t(int64_t(min(m0 + row, m_end - 1) - m0) * a.ldx * 2 + c * 16);
+  }
+  uint64_t base_w = reinterpret_cast<uint64_t>(a.w + int64_t(n0) * a.ldw);
+  uint64_t base_x = reinterpret_cast<uint64_t>(a.x + int64_t(m0) * a.ldx);
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
+  const int n_stages = a.K / 64;
+  int issued = 0;
+  uint32_t fill = lds0;                       // ring slot the next stage goes to
+  auto issue = [&]() {
+#pragma unroll
+    for (int i = 0; i < T::kLoadsW; ++i)
+      asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+                   :: "s"(fill + (wave * T::kLoadsW + i) * 1024), "v"(offw[i]), "s"(base_w) : "memory", "m0");
+#pragma unroll
+    for (int i = 0; i < T::kLoadsX; ++i)
+      asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+                   :: "s"(fill + BN * 128 + (wave * T::kLoadsX + i) * 1024), "v"(offx[i]), "s"(base_x) : "memory", "m0");
+    // past the last stage the loads repeat it, into slots nothing reads any more: the wait counts stay exact
+    ++issued;
+    base_w += issued < n_stages ? 128 : 0;
+    base_x += issued < n_stages ? 128 : 0;
+    fill += T::kStageBytes;
+    fill = fill == lds0 + kStages * T::kStageBytes ? lds0 : fill;
+  };
+  const uint32_t swz = (l15 >> 1) & 7;
+  const uint32_t aw0 = uint32_t((wn * T::kTn * 16 + l15) * 128) + ((uint32_t(grp) ^ swz) << 4);
+  const uint32_t ax0 = uint32_t(BN * 128 + (wm * T::kTm * 16 + l15) * 128) + ((uint32_t(grp) ^ swz) << 4);
+
+  f32x4 acc[T::kTn][T::kTm];
+#pragma unroll
+  for (int i = 0; i < T::kTn; ++i)
+#pragma unroll
+    for (int j = 0; j < T::kTm; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 fw[2][T::kTn], fx[2][T::kTm];
+  uint32_t slot = 0;
+  auto read = [&](int kk) {
+#pragma unroll
+    for (int i = 0; i < T::kTn; ++i) fw[kk][i] = *reinterpret_cast<const bf16x8*>(lds + slot + (aw0 ^ (kk << 6)) + i * 2048);
+#pragma unroll
+    for (int j = 0; j < T::kTm; ++j) fx[kk][j] = *reinterpret_cast<const bf16x8*>(lds + slot + (ax0 ^ (kk << 6)) + j * 2048);
+    __builtin_amdgcn_sched_barrier(0);        // reads stay ahead of the products they run beside
+  };
+  auto multiply = [&](int kk) {
+#pragma unroll
+    for (int i = 0; i < T::kTn; ++i)
+#pragma unroll
+      for (int j = 0; j < T::kTm; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[kk][i], fx[kk][j], acc[i][j], 0, 0, 0);
+  };
+#pragma unroll
+  for (int s = 0; s < kStages; ++s) issue();
+  constexpr int kFlying = (kStages - 1) * (T::kLoadsW + T::kLoadsX);
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(kFlying) : "memory");
+  read(0);
+  // operands are read one k-step ahead of their products, across stages too: the barrier stands before a
+  // stage's second k-step
+  for (int s = 0; s < n_stages; ++s) {
+    read(1);
+    multiply(0);
+    __builtin_amdgcn_sched_barrier(0);
+    // the next stage has landed; every wave has this one in registers: its slot takes the next loads
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(kFlying - T::kLoadsW - T::kLoadsX) : "memory");
+    issue();
+    slot += T::kStageBytes;
+    slot = slot == kStages * T::kStageBytes ? 0 : slot;
+    read(0);
+    multiply(1);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");     // the ring is free
+
+  const bool v_section = kPublish && n0 / (a.pub.heads * 128) == 2;
+  const int pitch = kPublish ? (v_section ? kEpiRowV : kEpiRow) : T::kPitch;
+#pragma unroll
+  for (int i = 0; i < T::kTn; ++i)
+#pragma unroll
+    for (int j = 0; j < T::kTm; ++j) {
+      uint32_t* to = reinterpret_cast<uint32_t*>(lds + ((wm * T::kTm + j) * 16 + l15) * pitch +
+                                                 ((wn * T::kTn + i) * 16 + 4 * grp) * 2);
+      to[0] = pack_bf16(acc[i][j][0], acc[i][j][1]);
+      to[1] = pack_bf16(acc[i][j][2], acc[i][j][3]);
+    }
+  __syncthreads();
+  if constexpr (kPublish) {
+    constexpr int kPages = BM / 128, kShare = T::kThreads / kPages;      // threads of a page
+    const int part = wave / (kShare / 64), t = tid % kShare;
+    publish_tile<kShare>(a, lds + part * 128 * pitch, n0, blk, kPages * tile_in_blk + part, m0 + part * 128,
+                         reinterpret_cast<float2*>(lds + BM * kEpiRow + part * kTrigBytes), t, t, kShare);
+    return;
+  }
+  constexpr int kChunks = BN / 8, kRows = T::kThreads / kChunks;
+  const int c = tid % kChunks;
 #pragma unroll 4
-    for (int it = 0; it < 32; ++it) {
-      const int row = it * 4 + r4;
-      const u32x4 v = *reinterpret_cast<const u32x4*>(mine + row * kEpiRow + c * 16);
-      if (tok0 + row < a.block_rows)
-        __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(a.y + int64_t(m0 + wm * 128 + row) * a.ldy + head * 128 + c * 8));
-    }
-    return;
-  }
-  const bool has_page = page < pb.pages_per_block;
-  uint8_t* kpage = pb.pool + ((int64_t(pb.slot[blk]) * pb.pages_per_block + (has_page ? page : 0)) * pb.heads + head) *
-                                 int64_t(2 * 128 * 128 * 2);
-  if (section == 1) {                      // k: rotate by the token's position, K page rows, pad rows zero
-    float2* trig = reinterpret_cast<float2*>(lds + 4 * kEpiWave + wm * kTrigBytes);
-    TrigLayout lay{};
-    if (pb.tab.n_f > 0) {                  // the two waves of a page (wn = 0, 1) fill its table together
-      lay = trig_layout(pb.g, pb.tab, tok0, a.block_rows, pb.first_frame[blk]);
-      if (has_page) trig_fill(pb.g, lay, trig, wn * 64 + lane, 128);
-    }
-    __syncthreads();
-    if (!has_page) return;
-    // the lane's rows are tokens tok0 + r4 + 4 it: positions move on by four tokens per trip
-    TokenPos p = token_pos(min(tok0 + r4, a.block_rows - 1), pb.first_frame[blk], pb.g.grid_h, pb.g.grid_w);
-#pragma unroll 2
-    for (int it = 0; it < 32; ++it, p = token_advance(p, 4, pb.g.grid_h, pb.g.grid_w)) {
-      const int row = it * 4 + r4;
-      U4 kk = {0, 0, 0, 0};
-      if (tok0 + row < a.block_rows) {
-        float cs[4], sn[4];
-        if (pb.tab.n_f > 0) {
-          trig_pick(pb.g, lay, trig, p, c, cs, sn);
-        } else {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) pair_cs<false>(pb.g, p, c * 4 + j, &cs[j], &sn[j]);
-        }
-        const U4 raw = *reinterpret_cast<const U4*>(mine + row * kEpiRow + c * 16);
-        Vec8<uint16_t> e;
-        e.v[0] = bf16_lo(raw.x); e.v[1] = bf16_hi(raw.x); e.v[2] = bf16_lo(raw.y); e.v[3] = bf16_hi(raw.y);
-        e.v[4] = bf16_lo(raw.z); e.v[5] = bf16_hi(raw.z); e.v[6] = bf16_lo(raw.w); e.v[7] = bf16_hi(raw.w);
-        rotate8(e, cs, sn);
-        kk.x = pack_bf16(e.v[0], e.v[1]); kk.y = pack_bf16(e.v[2], e.v[3]);
-        kk.z = pack_bf16(e.v[4], e.v[5]); kk.w = pack_bf16(e.v[6], e.v[7]);
-      }
-      store_once(kpage + row * 256 + ((c ^ (row & 15)) << 4), kk);
-    }
-    return;
-  }
-  // v: V page rows are dims; chunk c of a row holds tokens 16 (c / 2) + 4 (c % 2) + {0..3, 8..11}
-  if (!has_page) return;
-  uint8_t* vpage = kpage + 128 * 128 * 2;
-  const int tb = 16 * (c >> 1) + 4 * (c & 1);
-#pragma unroll 2
-  for (int it = 0; it < 32; ++it) {
-    const int d = it * 4 + r4;
-    uint32_t e[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int tok = tb + (j & 3) + 8 * (j >> 2);
-      const uint32_t w = *reinterpret_cast<const uint16_t*>(mine + tok * kEpiRowV + d * 2);
-      e[j] = tok0 + tok < a.block_rows ? w : 0u;
-    }
-    U4 o;
-    o.x = e[0] | (e[1] << 16); o.y = e[2] | (e[3] << 16);
-    o.z = e[4] | (e[5] << 16); o.w = e[6] | (e[7] << 16);
-    store_once(vpage + d * 256 + ((c ^ (d & 15)) << 4), o);
+  for (int row = tid / kChunks; row < BM; row += kRows) {
+    const u32x4 v = *reinterpret_cast<const u32x4*>(lds + row * T::kPitch + c * 16);
+    if (m0 + row < m_end && n0 + c * 8 < a.N)
+      __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(a.y + int64_t(m0 + row) * a.ldy + n0 + c * 8));
   }
 }
 
@@ -240,17 +398,79 @@ int32_t check_gemm_shape(int64_t M, int32_t N, int32_t K, int64_t ldx, int64_t l
 
 template <bool kPublish>
 int32_t enqueue_gemm(GemmArgs& a, void* stream) {
+  a.tiles_per_block = (a.block_rows + kTile - 1) / kTile;
+  a.tiles_m = (a.M / a.block_rows) * a.tiles_per_block;
   a.tiles_n = (a.N + kTile - 1) / kTile;
   a.sb_cols = (a.tiles_n + kSbCols - 1) / kSbCols;
   a.n_sb = ((a.tiles_m + kSbRows - 1) / kSbRows) * a.sb_cols;
   const unsigned rounds = unsigned((a.n_sb + 7) / 8);
   if (const int32_t rc = ensure_dynamic_lds(reinterpret_cast<const void*>(gemm_bf16_kernel<kPublish>), kGemmLds,
-                                            kPublish ? 3 : 1);
+                                            kPublish ? kLdsGemm256Publish : kLdsGemm256);
       rc != CA_OK)
     return rc;
   hipLaunchKernelGGL(gemm_bf16_kernel<kPublish>, dim3(rounds * 8 * 32), dim3(256), kGemmLds,
                      static_cast<hipStream_t>(stream), a);
   return finish_launch("gemm_bf16.hip");
+}
+
+template <int BM, int BN, int kWavesM, int kWavesN, int kStages, bool kPublish>
+int32_t enqueue_gemm_tiles(GemmArgs& a, LdsSlot slot, void* stream) {
+  using T = TileShape<BM, BN, kWavesM, kWavesN, kStages>;
+  a.tiles_per_block = (a.block_rows + BM - 1) / BM;
+  a.tiles_m = (a.M / a.block_rows) * a.tiles_per_block;
+  a.tiles_n = (a.N + BN - 1) / BN;
+  a.n_sb = (a.tiles_m * a.tiles_n + 7) / 8;                  // tiles of an XCD
+  const auto kernel = gemm_tile_kernel<BM, BN, kWavesM, kWavesN, kStages, kPublish>;
+  if (const int32_t rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), T::kLds, slot); rc != CA_OK) return rc;
+  hipLaunchKernelGGL(kernel, dim3(unsigned(a.n_sb) * 8), dim3(T::kThreads), T::kLds, static_cast<hipStream_t>(stream), a);
+  return finish_launch("gemm_bf16.hip");
+}
+
+// Which tile a product takes.  Outputs are the same to the last bit with every one of them (each is one chain of the
+// same matrix instruction over k in steps of 32), so the choice is the cheapest by a model of what was measured: rounds
+// of workgroups over the CUs times (stages of 64 k x time of a stage + set-up and epilogue), in microseconds:
+//   256 x 256 (asm loop)   stage 1.25, fixed 8      128 x 128   stage 0.43, fixed 5
+//   256 x 128              stage 0.85, fixed 6       64 x 64 two a CU 0.31, 4; one a CU 0.165, 4
+// Whole calls, us, 256 x 256 first and then what is taken: 257 x 768 x 1024 (6 tiles of 256 x 256) 22.7 -> 8.1, 64 x 128 x 5120
+// 80 -> 17, 1200 x 1400 x 1152 27.7 -> 10.1, 4680 x 1536 x 1536 36.7 -> 25.1 (256 x 128; 28.8 with 128 x 128, 39 with 64 x 64),
+// 23400 x 128 x 5120 93 -> 41 (128 x 128); 256 x 256 stays where its tiles fill the chip: 23400 x 5120 x 5120 901 against 1120.
+// The publishing epilogue needs whole pages and heads: 128 columns, 128 or 256 rows.
+enum GemmTile { kTile256, kTile256x128, kTile128, kTile64, kTile64Wide };
+
+int32_t pick_gemm_tile(const GemmArgs& a, bool publish, GemmTile* tile) {
+  static constexpr struct { int bm, bn, per_cu, threads, stage, fixed; } kModel[] = {
+      {256, 256, 1, 256, 1250, 8000}, {256, 128, 1, 512, 850, 6000}, {128, 128, 1, 512, 430, 5000},
+      {64, 64, 2, 256, 310, 4000}, {64, 64, 1, 512, 165, 4000}};
+  int n_cu = 0;
+  if (const int32_t rc = device_cu_count(&n_cu); rc != CA_OK) return rc;
+  const int64_t blocks = a.M / a.block_rows, stages = a.K / 64;
+  int64_t best = 0;
+  for (int i = 0; i < (publish ? 3 : 5); ++i) {
+    const auto& m = kModel[i];
+    const int64_t tiles = blocks * ((a.block_rows + m.bm - 1) / m.bm) * ((a.N + m.bn - 1) / m.bn);
+    if (i > 0 && tiles * m.threads >= (int64_t(1) << 31)) continue;      // a launch may have 2^32 threads
+    const int64_t slots = int64_t(n_cu) * m.per_cu;
+    const int64_t cost = (tiles + slots - 1) / slots * (stages * m.stage + m.fixed);
+    if (i == 0 || cost < best) {
+      best = cost;
+      *tile = GemmTile(i);
+    }
+  }
+  return CA_OK;
+}
+
+template <bool kPublish>
+int32_t dispatch_gemm(GemmArgs& a, void* stream) {
+  GemmTile tile = kTile256;
+  if (const int32_t rc = pick_gemm_tile(a, kPublish, &tile); rc != CA_OK) return rc;
+  if constexpr (!kPublish) {
+    if (tile == kTile64) return enqueue_gemm_tiles<64, 64, 2, 2, 4, false>(a, kLdsGemm64, stream);
+    if (tile == kTile64Wide) return enqueue_gemm_tiles<64, 64, 2, 4, 6, false>(a, kLdsGemm64Wide, stream);
+  }
+  if (tile == kTile128) return enqueue_gemm_tiles<128, 128, 2, 4, 4, kPublish>(a, kPublish ? kLdsGemm128Publish : kLdsGemm128, stream);
+  if (tile == kTile256x128)
+    return enqueue_gemm_tiles<256, 128, 4, 2, 3, kPublish>(a, kPublish ? kLdsGemm256x128Publish : kLdsGemm256x128, stream);
+  return enqueue_gemm<kPublish>(a, stream);
 }
 
 }  // namespace
@@ -266,10 +486,8 @@ int32_t launch_gemm_bf16(const void* x, const void* w, void* y, int64_t M, int32
   a.y = static_cast<uint16_t*>(y);
   a.M = int32_t(M); a.N = N; a.K = K;
   a.ldx = ldx; a.ldw = ldw; a.ldy = ldy;
-  a.tiles_m = int32_t((M + kTile - 1) / kTile);
   a.block_rows = a.M;                             // one row block: tiles run through all of M
-  a.tiles_per_block = a.tiles_m;
-  return enqueue_gemm<false>(a, stream);
+  return dispatch_gemm<false>(a, stream);
 }
 
 int32_t launch_gemm_qkv_publish(const RopeGeom& g, int32_t n_blocks, int32_t block_tokens, int32_t pages_per_block,
@@ -288,8 +506,6 @@ int32_t launch_gemm_qkv_publish(const RopeGeom& g, int32_t n_blocks, int32_t blo
   a.M = int32_t(M); a.N = N; a.K = K;
   a.ldx = ldx; a.ldw = ldw; a.ldy = int64_t(g.heads) * 128;
   a.block_rows = block_tokens;
-  a.tiles_per_block = (block_tokens + kTile - 1) / kTile;
-  a.tiles_m = n_blocks * a.tiles_per_block;
   a.pub.g = g;
   a.pub.pool = static_cast<uint8_t*>(pool);
   a.pub.heads = g.heads;
@@ -300,7 +516,7 @@ int32_t launch_gemm_qkv_publish(const RopeGeom& g, int32_t n_blocks, int32_t blo
   }
   size_t tab_bytes = 0;
   a.pub.tab = trig_table_for(g, 128, kTrigBytes, &tab_bytes);
-  return enqueue_gemm<true>(a, stream);
+  return dispatch_gemm<true>(a, stream);
 }
 
 }  // namespace ca

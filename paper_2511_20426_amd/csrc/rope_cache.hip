@@ -218,7 +218,7 @@ const char* last_device_error() { return g_last_error; }
 
 namespace {
 std::atomic<int> g_cu_count[kMaxDevices];
-std::atomic<int> g_lds_set[4][kMaxDevices];
+std::atomic<int> g_lds_set[kLdsSlots][kMaxDevices];
 }  // namespace
 
 int32_t device_cu_count(int* n_cu) {
@@ -236,7 +236,7 @@ int32_t device_cu_count(int* n_cu) {
   return CA_OK;
 }
 
-int32_t ensure_dynamic_lds(const void* kernel, int bytes, int slot) {
+int32_t ensure_dynamic_lds(const void* kernel, int bytes, LdsSlot slot) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return finish_launch("hipGetDevice");
   const bool cached = dev >= 0 && dev < kMaxDevices;

@@ -44,3 +44,50 @@ def test_bf16_split_small_launch(heads, gh, gw, nc, ni):
         out = Hn.gpu_forward(w, pool, q, infl, mode)
         ref, bound = (np.concatenate(x) for x in Hn.oracle_forward_bounded(w, q, k, v, cached, infl, mode))
         Hn.assert_close(out, ref, "bf16", f"split heads={heads} grid={gh}x{gw} nc={nc} ni={ni} mode={mode}", bound=bound)
+
+
+# Every tile of the linear map: one row, a tile and one row, column counts that end inside a tile, the shortest and
+# longer walks over k, several tiles per band and XCD.  (Two stages are fewer than any ring holds.)
+@pytest.mark.parametrize("M,N,K", [(1, 8, 128), (65, 72, 128), (129, 200, 768), (1100, 1400, 256), (2050, 1160, 128), (1345, 3000, 256),
+                                   (1300, 4104, 128), (4680, 1544, 384), (9001, 136, 1024), (4100, 4104, 128)])
+def test_linear_tiles(M, N, K):
+    import torch
+    from paper_2511_20426_amd.runner import linear
+    x, w = W.draw_linear(M, N, K, seed=M + N)
+    yt = torch.full((M + 2, N + 8), 7.0, dtype=torch.bfloat16, device="cuda:0")
+    print(f"linear tiles {M}x{N}x{K}", flush=True)
+    linear(Hn.to_torch(x, "bf16"), Hn.to_torch(w, "bf16"), out=yt[:M, :N])
+    torch.cuda.synchronize()
+    got = Hn.from_torch(yt, "bf16")
+    assert (got[M:] == 7.0).all() and (got[:, N:] == 7.0).all()
+    # one rounding to bf16 and fp32 accumulation: half an ulp is 2^-9 relative, 2^-8 and 1e-5 of sum |x||w| allowed
+    rows = np.unique(np.concatenate([np.arange(0, M, max(1, M // 300)), [M - 1]]))
+    xf, wf = W.to_f64(x[rows]), W.to_f64(w)
+    ref = orc.layer_linear(xf, wf)
+    bound = np.abs(ref) * 2.0 ** -8 + 1e-5 * orc.layer_linear(np.abs(xf), np.abs(wf)) + 1e-30
+    assert (np.abs(got[rows, :N].astype(np.float64) - ref) <= bound).all(), f"linear {M}x{N}x{K}"
+
+
+# The publishing projection in each of its tiles writes the bytes that projection and cache write do: blocks of one page,
+# a ragged page, an odd number of pages (256-row tiles whose second page does not exist).
+@pytest.mark.parametrize("heads,fpb,gh,gw,ids,k_in", [(2, 1, 4, 8, (1,), 128), (2, 3, 13, 17, (0, 1, 2), 256), (4, 3, 19, 27, (2, 3), 128),
+                                                      (24, 3, 10, 12, (0, 1, 2), 128), (12, 3, 30, 52, (4,), 256)])
+def test_publish_tiles(heads, fpb, gh, gw, ids, k_in):
+    import torch
+    from paper_2511_20426_amd.runner import CascadePool, linear
+    w = W.small_variant(W.CONFIGS["c3_wan1p3b_cascade5"], heads=heads, frames_per_block=fpb, grid_h=gh, grid_w=gw)
+    L, n, width = w.block_tokens, len(ids) * w.block_tokens, heads * 128
+    x, wq = W.draw_linear(n, 3 * width, k_in, seed=17)
+    xt, wt = Hn.to_torch(x, "bf16"), Hn.to_torch(wq, "bf16")
+    two, one = CascadePool.for_workload(w), CascadePool.for_workload(w)
+    pages = two.pool.numel() - (256 * 256 * 132 * 4)
+    two.pool.fill_(0xAB); one.pool.fill_(0xAB)
+    print(f"publish tiles heads={heads} L={L} blocks={ids} k_in={k_in}", flush=True)
+    qkv = linear(xt, wt).view(n, 3, heads, 128)
+    ts = [250] * len(ids)
+    two.append_batch(list(ids), ts, 1, [qkv[i * L:(i + 1) * L, 1] for i in range(len(ids))],
+                     [qkv[i * L:(i + 1) * L, 2] for i in range(len(ids))])
+    q = one.qkv_publish(xt, wt, list(ids), ts, 1)
+    torch.cuda.synchronize()
+    assert torch.equal(q.view(torch.int16), qkv[:, 0].contiguous().view(torch.int16))
+    assert torch.equal(one.pool[:pages], two.pool[:pages])
