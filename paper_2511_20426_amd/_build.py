@@ -28,13 +28,10 @@ def build(verbose: bool = False, extra=(), bdir: str | None = None) -> str:
     objs = []
     bdir = bdir or os.path.join(PKG, "_build")
     os.makedirs(bdir, exist_ok=True)
-    # the hand-scheduled attention main loop is emitted as an inline-assembly include
-    subprocess.run([sys.executable, os.path.join(CSRC, "gen_attn_core.py"),
-                    os.path.join(bdir, "attn_core_gfx950.inc")], check=True,
-                   stdout=None if verbose else subprocess.DEVNULL)
-    subprocess.run([sys.executable, os.path.join(CSRC, "gen_gemm_core.py"),
-                    os.path.join(bdir, "gemm_core_gfx950.inc")], check=True,
-                   stdout=None if verbose else subprocess.DEVNULL)
+    # the hand-scheduled main loops are emitted as inline-assembly includes
+    for core in ("attn_core", "attn_core16", "gemm_core"):
+        subprocess.run([sys.executable, os.path.join(CSRC, f"gen_{core}.py"), os.path.join(bdir, f"{core}_gfx950.inc")],
+                       check=True, stdout=None if verbose else subprocess.DEVNULL)
     common = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-I", os.path.join(ROOT, "include"),
               "-I", CSRC, "-I", bdir, "-Wno-unused-command-line-argument", "-Wno-unknown-warning-option"] + DEVICE_FLAGS + list(extra)
     procs = []

@@ -7,26 +7,29 @@
 // pages of invisible blocks are never loaded.
 //
 // Shape of the kernel
-//   workgroup = 4 waves, one per SIMD; a wave owns 64 query rows (two 32-wide MFMA column
-//   tiles), a workgroup 256 rows of one head.  K and V pages (32 KB each) stream global -> LDS
-//   without passing through registers into two 2-page rings shared by the four waves.
-//   S^T = K Q^T   : v_mfma_f32_32x32x16_bf16, A = K rows from LDS, B = Q (AGPRs).
-//                   In the 32x32 accumulator layout a lane then holds 16 of the 32 keys of ONE
-//                   query, so row max / row sum need a single cross-lane step (lane ^ 32), and
-//                   only on the rare steps where the exponent reference moves.
+//   workgroup = 4 waves, one per SIMD; a wave owns 64 query rows, a workgroup 256 rows of one head.
+//   K and V pages (32 KB each) stream global -> LDS without passing through registers into two
+//   2-page rings shared by the four waves.
+//   S^T = K Q^T   : A = K rows from LDS, B = Q (AGPRs).  A lane then holds keys of ONE query per column
+//                   tile, so a row reduction is a cross-lane step or two, and only on the rare steps
+//                   where the exponent reference moves.
 //   O^T += V^T P^T: A = V^T rows from LDS, B = P^T straight from the S^T accumulator
 //                   registers (rounded to bf16).  V pages are stored transposed and with the
-//                   key order the accumulator hands over, so no data movement is needed
+//                   key order the accumulators hand over, so no data movement is needed
 //                   between the two products (see cascade_attn.h for the page format).
 //   Softmax is the running-reference form in base 2: p = exp2(s*c - m_ref), c = log2(e)/sqrt(D);
-//   m_ref moves (and the accumulators are rescaled) only when the probabilities of a step sum past 2^16.
+//   m_ref moves (and the accumulators are rescaled) only when the probabilities of a step grow past a limit.
+//   The loop exists on two matrix instructions, picked per launch by takes_core16: 32x32x16 (two column tiles
+//   of 32 queries, row sums by the VALU; fewer cycles) and 16x16x32 (four tiles of 16, row sums by the matrix pipe; less
+//   power).  Errors against fp64 over seven shapes and logit scales: 2.4066e-3 .. 5.3026e-3 with the first,
+//   2.4058e-3 .. 5.2881e-3 with the second.
 //   The 256-byte page rows are stored with their 16-byte chunks XOR-swizzled by (row & 15),
-//   which makes every ds_read_b128 of an MFMA operand bank-conflict free.
+//   which makes every ds_read_b128 of an MFMA operand bank-conflict free (K with 16x16x32: two lanes to a bank).
 //   Workgroups are numbered so that the eight XCDs each take a contiguous range of
 //   (head, row tile) work: workgroups running together on an XCD stream the same head's pages
 //   and share them in that XCD's L2.
 //   This file holds the set-up and the epilogue; the software-pipelined main loop is the
-//   hand-scheduled assembly emitted by gen_attn_core.py.
+//   hand-scheduled assembly emitted by gen_attn_core.py and gen_attn_core16.py.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -89,7 +92,7 @@ constexpr int kLaneRow0 = 0, kLaneRows = 8, kLaneNvis = 16, kLaneFrame = 24, kLa
 static_assert(kMaxInflight == 8 && kMaxKvBlocks == 32, "AttnArgs::lanes");
 
 // one partial result of a 256-row tile, in the order the accumulators leave the registers: O^T
-// contributions [slab of 32 rows][group of 8 dims][lane] as fp32 x 4 (not normalised), then (exponent
+// contributions [wave][register group][lane] as fp32 x 4 (not normalised), then (exponent
 // reference in log2 units, row sum) per row
 constexpr int kPartialMl = kRowsPerWg * 128;
 constexpr int kPartialFloats = kRowsPerWg * 132;
@@ -148,6 +151,7 @@ __device__ __forceinline__ void wave_lds_fence() {
 }
 
 #include "attn_core_clobbers.inc"
+#include "attn_core16_clobbers.inc"
 
 // LDS map: K ring (2 pages), V ring (2 pages), token positions of the tile's rows; the main loop lives
 // in attn_core_gfx950.inc (generated by gen_attn_core.py, which also documents the pipeline and the
@@ -164,13 +168,16 @@ constexpr int kAttnLds = 4 * kPageBytes + kRowsPerWg * 16;
 // the rotation is shared out so that a thread needs the factors of four pairs only (8 700 -> 5 500
 // cycles, the largest part left).  Whole steps: 15 workgroups with 20 pages each 72 -> 67 us, 300 with
 // 70..110 pages 383 -> 366 us; nothing at the 14B shape, where an item walks 407 pages.
-template <bool kRopeQ>
+//
+// kCore16: which of the two main loops.  Both walk the same pages the same way; they differ in the matrix instruction, and
+// so in where a lane's part of Q, of the accumulators and of a row sum is.
+template <bool kRopeQ, bool kCore16>
 __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l31 = lane & 31, hi = lane >> 5, sw = lane & 15;
+  const int l31 = lane & 31, hi = lane >> 5, l15 = lane & 15, grp = lane >> 4;
   const int lane_tab = a.lanes[lane];
-  const int my_slot = a.lanes[kLaneSlot + l31];
+  const int my_slot = a.lanes[kLaneSlot + (lane & 31)];
   const int c16 = lane & 15, r4 = lane >> 4;               // 16-byte chunk and row (mod 4) of Q / O this lane moves
   float rev_hi[4], rev_lo[4];
   if (kRopeQ) {
@@ -274,26 +281,35 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
     }
   }
   wave_lds_fence();
-  // ---- Q fragments: B operand of S^T = K Q^T.  Lane holds dims 16ks + 8hi .. +7 of query l31
-  // of column tile nt; fragment (nt, ks) goes to a[128 + 4*(8nt + ks) ..].
+  // ---- Q fragments: B operand of S^T = K Q^T, a[128:191].  16x16x32: lane holds dims 32ks + 8grp .. +7 of query l15 of query
+  // tile t, fragment (t, ks) at a[128 + 4*(4t + ks) ..]; 32x32x16: dims 16ks + 8hi .. +7 of query l31 of column tile
+  // nt, fragment (nt, ks) at a[128 + 4*(8nt + ks) ..].
   f32x16 qt[4];
+  if constexpr (kCore16) {
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const u32x4 f = *reinterpret_cast<const u32x4*>(parked + (t * 16 + l15) * 256 + (((4 * ks + grp) ^ l15) << 4));
+#pragma unroll
+      for (int j = 0; j < 4; ++j) qt[t][4 * ks + j] = __uint_as_float(f[j]);
+    }
+  } else {
 #pragma unroll
   for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
-      const u32x4 f = *reinterpret_cast<const u32x4*>(parked + (nt * 32 + l31) * 256 + (((2 * ks + hi) ^ sw) << 4));
+      const u32x4 f = *reinterpret_cast<const u32x4*>(parked + (nt * 32 + l31) * 256 + (((2 * ks + hi) ^ l15) << 4));
 #pragma unroll
       for (int j = 0; j < 4; ++j) qt[2 * nt + (ks >> 2)][4 * (ks & 3) + j] = __uint_as_float(f[j]);
     }
+  }
   __syncthreads();                    // every fragment is in registers: the second slots are free
 
   // address of page 0 of KV block i for this head: lane i of (tbl_lo, tbl_hi)
   const uint64_t my_off = reinterpret_cast<uint64_t>(a.pool) +
                           (uint64_t(my_slot) * a.pages_per_block * a.heads + h) * uint64_t(kPairBytes);
   const uint32_t tbl_lo = uint32_t(my_off), tbl_hi = uint32_t(my_off >> 32);
-  const uint32_t xo0 = l31 * 256 + ((hi ^ sw) << 4);    // row offset + swizzled chunk 0 (or 1 for hi)
-  const uint32_t kidx = 4 * hi;
-  const uint32_t xlane = 4 * (lane ^ 32);
   const uint32_t stride = uint32_t(a.heads) * kPairBytes;
 
   // The first PV product multiplies an all-zero P tile with the last 32 keys (chunks 12..15 of every
@@ -316,63 +332,101 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
   // o6/o7 are not early-clobber: the block reads every VGPR input in its first instructions,
   // before it writes v[96:127], and the inputs need somewhere to live (it uses all of v[128:255])
   f32x16 o0, o1, o2, o3, o4, o5, o6, o7;
-  float l0a, l0b, l1a, l1b, negm0, negm1;
-  asm volatile(
+  float l0, l1, l2, l3, negm0, negm1, negm2 = 0.f, negm3 = 0.f;
+  if constexpr (kCore16) {
+    // K rows of a key tile: lanes 0..7 hold keys 0..7, lanes 8..15 keys 16..23 (the second tile: 8 further), so that
+    // the accumulators of the two tiles hand a lane group exactly the keys of one chunk of a V row
+    const uint32_t xk0 = (16 * (l15 >> 3) + (l15 & 7)) * 256 + ((grp ^ (l15 & 7)) << 4);
+    const uint32_t xv0 = l15 * 256 + ((grp ^ l15) << 4);
+    const uint32_t kidx = 16 * (grp >> 1) + 4 * (grp & 1);
+    const uint32_t xl16 = 4 * (lane ^ 16), xl32 = 4 * (lane ^ 32);
+    asm volatile(
+#include "attn_core16_gfx950.inc"
+      : "=&{v[0:15]}"(o0), "=&{v[16:31]}"(o1), "=&{v[32:47]}"(o2), "=&{v[48:63]}"(o3), "=&{v[64:79]}"(o4),
+        "=&{v[80:95]}"(o5), "={v[96:111]}"(o6), "={v[112:127]}"(o7), "=&{v148}"(l0), "=&{v149}"(l1),
+        "=&{v150}"(l2), "=&{v151}"(l3), "=&{v184}"(negm0), "=&{v188}"(negm1), "=&{v192}"(negm2), "=&{v196}"(negm3)
+      : "{a[128:143]}"(qt[0]), "{a[144:159]}"(qt[1]), "{a[160:175]}"(qt[2]), "{a[176:191]}"(qt[3]),
+        [xk0] "v"(xk0), [xv0] "v"(xv0), [lane_off] "v"(lane_off), [tbl_lo] "v"(tbl_lo), [tbl_hi] "v"(tbl_hi),
+        [kidx] "v"(kidx), [xl16] "v"(xl16), [xl32] "v"(xl32), [ones] "v"(l15 == 0 ? 0x3f803f80u : 0u),
+        [n_pages] "s"(n_pages), [n_kvb] "s"(n_kvb), [kb0] "s"(kb0), [pg0] "s"(pg0),
+        [ppb] "s"(a.pages_per_block), [stride] "s"(stride), [last_valid] "s"(a.last_valid),
+        [wave] "s"(wave), [lds0] "s"(lds0)
+      : "memory", "vcc", "scc", "m0", CA_CORE16_CLOBBERS);
+  } else {
+    const uint32_t xo0 = l31 * 256 + ((hi ^ l15) << 4);    // row offset + swizzled chunk 0 (or 1 for hi)
+    const uint32_t kidx = 4 * hi, xlane = 4 * (lane ^ 32);
+    asm volatile(
 #include "attn_core_gfx950.inc"
       : "=&{v[0:15]}"(o0), "=&{v[16:31]}"(o1), "=&{v[32:47]}"(o2), "=&{v[48:63]}"(o3), "=&{v[64:79]}"(o4),
-        "=&{v[80:95]}"(o5), "={v[96:111]}"(o6), "={v[112:127]}"(o7), "=&{v148}"(l0a), "=&{v149}"(l0b),
-        "=&{v150}"(l1a), "=&{v151}"(l1b), "=&{v184}"(negm0), "=&{v200}"(negm1)
+        "=&{v[80:95]}"(o5), "={v[96:111]}"(o6), "={v[112:127]}"(o7), "=&{v148}"(l0), "=&{v149}"(l1),
+        "=&{v150}"(l2), "=&{v151}"(l3), "=&{v184}"(negm0), "=&{v200}"(negm1)
       : "{a[128:143]}"(qt[0]), "{a[144:159]}"(qt[1]), "{a[160:175]}"(qt[2]), "{a[176:191]}"(qt[3]),
         [xo0] "v"(xo0), [lane_off] "v"(lane_off), [tbl_lo] "v"(tbl_lo), [tbl_hi] "v"(tbl_hi),
         [kidx] "v"(kidx), [xlane] "v"(xlane), [n_pages] "s"(n_pages), [n_kvb] "s"(n_kvb), [kb0] "s"(kb0), [pg0] "s"(pg0),
         [ppb] "s"(a.pages_per_block), [stride] "s"(stride), [last_valid] "s"(a.last_valid),
         [wave] "s"(wave), [lds0] "s"(lds0)
       : "memory", "vcc", "scc", "m0", CA_CORE_CLOBBERS);
+  }
 
   asm volatile("" : "+s"(ap));
   const int4 kept = *reinterpret_cast<const int4*>(lds + kPosArea);
   const int o_head = uniform(kept.x), o_row0 = uniform(kept.y), o_end = uniform(kept.z), part_index = uniform(kept.w);
-  // ---- normalise and store: lane holds, for its query, dims 32mt + 8(i/4) + 4hi + (i%4)
-  const f32x16 oacc[4][2] = {{o0, o1}, {o2, o3}, {o4, o5}, {o6, o7}};
-  const float l_lane[2] = {l0a + l0b, l1a + l1b};
+  // ---- normalise and store.  The lane's accumulators are 32 groups of four consecutive dims of a row of the wave: group
+  // g of o_j is register 4g of it.  16x16x32: o_j has dims 16j + 4grp .. of query l15 of tile g; 32x32x16: o_j, j = 2mt + nt, has
+  // dims 32mt + 8g + 4hi .. of query l31 of tile nt.
+  const f32x16 oacc[8] = {o0, o1, o2, o3, o4, o5, o6, o7};
+  const float negm[4] = {negm0, negm1, negm2, negm3};
+  float l_tot[4];                     // row sums per tile
+  if constexpr (kCore16) {            // lane l15 has that of query l15
+    const float l[4] = {l0, l1, l2, l3};
+#pragma unroll
+    for (int t = 0; t < 4; ++t) l_tot[t] = __shfl(l[t], l15, 64);
+  } else {
+    const float a0 = l0 + l1, a1 = l2 + l3;
+    l_tot[0] = a0 + other_half(a0);
+    l_tot[1] = a1 + other_half(a1);
+    l_tot[2] = l_tot[3] = 0.f;
+  }
   if (part_index >= 0) {
     // partial result: accumulators as they are, plus (m_ref, row sum) per row
     float* part = ap->partials + size_t(part_index) * kPartialFloats;
+    float4* slab = reinterpret_cast<float4*>(part) + wave * 32 * 64 + lane;
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      const float l_tot = l_lane[nt] + other_half(l_lane[nt]);
-      float4* slab = reinterpret_cast<float4*>(part) + (wave * 2 + nt) * 16 * 64 + lane;
+    for (int j = 0; j < 8; ++j)
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
+      for (int g = 0; g < 4; ++g)
+        slab[(4 * j + g) * 64] = make_float4(oacc[j][4 * g + 0], oacc[j][4 * g + 1], oacc[j][4 * g + 2], oacc[j][4 * g + 3]);
+    float2* ml = reinterpret_cast<float2*>(part + kPartialMl) + wave * 64;
+    if constexpr (kCore16) {
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x16& o = oacc[mt][nt];
-          const float x0 = o[4 * g + 0], x1 = o[4 * g + 1], x2 = o[4 * g + 2], x3 = o[4 * g + 3];
-          slab[(4 * mt + g) * 64] = make_float4(x0, x1, x2, x3);
-        }
-      if (hi == 0)
-        *reinterpret_cast<float2*>(part + kPartialMl + 2 * (wave * 64 + nt * 32 + l31)) = make_float2(-(nt ? negm1 : negm0), l_tot);
+      for (int t = 0; t < 4; ++t)
+        if (grp == 0) ml[t * 16 + l15] = make_float2(-negm[t], l_tot[t]);
+    } else {
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt)
+        if (hi == 0) ml[nt * 32 + l31] = make_float2(-negm[nt], l_tot[nt]);
     }
     return;
   }
   // rows leave through LDS: a wave's 64 rows in 16 KB of its own, chunks swizzled, then 16 lanes to a row
   __syncthreads();                    // no wave reads pages any more, no page load is in flight
   uint8_t* const mine = lds + wave * 64 * 256;
+  float inv[4];
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt) {
-    const float l_tot = l_lane[nt] + other_half(l_lane[nt]);
-    const float inv = 1.0f / l_tot;
+  for (int t = 0; t < 4; ++t) inv[t] = 1.0f / l_tot[t];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+  for (int j = 0; j < 8; ++j)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x16& o = oacc[mt][nt];
-        u32x2 w;
-        w[0] = pack2(o[4 * g + 0] * inv, o[4 * g + 1] * inv);
-        w[1] = pack2(o[4 * g + 2] * inv, o[4 * g + 3] * inv);
-        *reinterpret_cast<u32x2*>(mine + (nt * 32 + l31) * 256 + (((4 * mt + g) ^ sw) << 4) + 8 * hi) = w;
-      }
-  }
+    for (int g = 0; g < 4; ++g) {
+      const f32x16& o = oacc[j];
+      const float f = inv[kCore16 ? g : j & 1];
+      const int row = kCore16 ? g * 16 + l15 : (j & 1) * 32 + l31;
+      const int piece = kCore16 ? 4 * j + grp : 8 * (j >> 1) + 2 * g + hi;          // of 8 bytes
+      u32x2 w;
+      w[0] = pack2(o[4 * g + 0] * f, o[4 * g + 1] * f);
+      w[1] = pack2(o[4 * g + 2] * f, o[4 * g + 3] * f);
+      *reinterpret_cast<u32x2*>(mine + row * 256 + (((piece >> 1) ^ l15) << 4) + 8 * (piece & 1)) = w;
+    }
   wave_lds_fence();
   uint16_t* op = ap->o + int64_t(o_head) * 128 + c16 * 8;
   const int64_t o_stride = int64_t(ap->heads) * 128;
@@ -386,21 +440,28 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
 
 
 // Combines the partial results of the split work items: for every row, the partials are brought
-// to the largest of their exponent references, summed and normalised.  Eight workgroups per tile
-// (blockIdx.y picks a slab of 32 rows), a wave per 32 dims; a lane keeps the place it had in the attention
-// kernel, so that every read of a partial tile is 1 KB of contiguous memory.
+// to the largest of their exponent references, summed and normalised.  Eight workgroups per tile: a wave takes
+// four register groups of one row of the attention kernel's tiles, and a lane keeps the place it had
+// there, so that every read of a partial tile is 1 KB of contiguous memory.
+template <bool kCore16>
 __global__ __launch_bounds__(256) void merge_partials_kernel(AttnArgs a) {
-  const int lane = threadIdx.x & 63, mt = threadIdx.x >> 6, l31 = lane & 31, hi = lane >> 5;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l31 = lane & 31, hi = lane >> 5, l15 = lane & 15, grp = lane >> 4;
   const int lane_tab = a.lanes[lane];
   const int xcd = blockIdx.x / a.split_items, sidx = blockIdx.x % a.split_items;
-  const int slab = blockIdx.y;
+  const int wrow = blockIdx.y >> 1;                            // the attention kernel's wave
+  // 16x16x32: query tile t, accumulators j0 .. j0+3 (dims 16 j0 ..); 32x32x16: column tile nt, accumulator 2 mt + nt
+  const int t = 2 * (blockIdx.y & 1) + (wave & 1), j0 = 4 * (wave >> 1);
+  const int nt = blockIdx.y & 1, mt = wave;
+  const int first = kCore16 ? 16 * t : 32 * nt;
+  const int row_in_tile = wrow * 64 + first + (kCore16 ? l15 : l31);
   const float* tile = a.partials + size_t(xcd * a.split_items + sidx) * a.split * kPartialFloats;
-  const float* ml = tile + kPartialMl + 2 * (slab * 32 + l31);
-  const float4* part = reinterpret_cast<const float4*>(tile) + (slab * 16 + 4 * mt) * 64 + lane;
+  const float* ml = tile + kPartialMl + 2 * row_in_tile;
+  constexpr int kStep = kCore16 ? 4 * 64 : 64;                 // from one of the four groups to the next
+  const float4* part = reinterpret_cast<const float4*>(tile) + (wrow * 32 + (kCore16 ? 4 * j0 + t : 4 * (2 * mt + nt))) * 64 + lane;
   const WorkItem wi = decode_item(a, lane_tab, xcd, a.full_items + sidx);
   if (wi.h < 0) return;
-  const int row = wi.row0 + slab * 32 + l31;
-  if (wi.row0 + slab * 32 >= wi.rows_end) return;
+  const int row = wi.row0 + row_in_tile;
+  if (wi.row0 + wrow * 64 + first >= wi.rows_end) return;
   float m = -INFINITY;
   for (int c = 0; c < a.split; ++c) m = fmaxf(m, ml[c * kPartialFloats]);
   float l = 0.f;
@@ -414,19 +475,19 @@ __global__ __launch_bounds__(256) void merge_partials_kernel(AttnArgs a) {
     l += wgt * y.y;
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      const float4 x = part[c * (kPartialFloats / 4) + g * 64];
+      const float4 x = part[c * (kPartialFloats / 4) + g * kStep];
       acc[g].x += wgt * x.x; acc[g].y += wgt * x.y; acc[g].z += wgt * x.z; acc[g].w += wgt * x.w;
     }
   }
   if (row >= wi.rows_end) return;
   const float inv = 1.0f / l;
-  uint16_t* op = a.o + (int64_t(row) * a.heads + wi.h) * 128 + 32 * mt + 4 * hi;
+  uint16_t* op = a.o + (int64_t(row) * a.heads + wi.h) * 128 + (kCore16 ? 16 * j0 + 4 * grp : 32 * mt + 4 * hi);
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
     u32x2 w;
     w[0] = pack2(acc[g].x * inv, acc[g].y * inv);
     w[1] = pack2(acc[g].z * inv, acc[g].w * inv);
-    *reinterpret_cast<u32x2*>(op + 8 * g) = w;
+    *reinterpret_cast<u32x2*>(op + (kCore16 ? 16 : 8) * g) = w;
   }
 }
 
@@ -457,11 +518,21 @@ int split_of_small_launch(int items_per_xcd, int cus_per_xcd, int items, int min
   return best;
 }
 
+// The loop on the 16x16x32 instruction draws less power a flop, the one on 32x32x16 needs fewer cycles: where most CUs
+// work at once and long enough, power decides.  Whole forwards, us, 32x32x16 / 16x16x32, by workgroups of a round x
+// pages of a walk: 171 x 259 563 / 536, 228 x 259 685 / 634, 200 x 14 50.4 / 49.3, 200 x 10 37.3 / 36.6; 152 x 259 515 / 520, 160 x 14
+// 46.6 / 47.1, 240 x 7 44.6 / 45.5, 240 x 5 36.1 / 36.7, 8 x 14 20.2 / 21.6.
+bool takes_core16(const AttnArgs& a, int max_pages, int n_cu) {
+  const bool alone = a.full_items == 0;                        // all items cut
+  const int64_t workgroups = int64_t(a.total_cols) * a.n_seg * (alone ? a.split : 1);
+  return 3 * workgroups >= 2 * int64_t(n_cu) && max_pages / (alone ? a.split : 1) >= 10;
+}
+
 // Fills the kernel arguments for one forward.  Splitting: `capacity` partial results fit in
 // the scratch area; with adapt the split is reduced until the partials fit, without it the split
 // the device's CU count asks for is kept and *partials_needed tells the caller how many it takes.
 int32_t plan_attn_bf16(const AttnPlan& p, int variant, const void* q, void* out, const void* pool, void* partials_dev,
-                       int capacity, bool adapt, AttnArgs* args, int* partials_needed) {
+                       int capacity, bool adapt, AttnArgs* args, int* partials_needed, bool* core16) {
   if (p.head_dim != 128 || p.page_tokens != 128) return CA_EUNSUPPORTED;
   if (attn_bf16_variant_ok(variant) != CA_OK) return CA_EINVAL;
   AttnArgs& a = *args;
@@ -534,6 +605,7 @@ int32_t plan_attn_bf16(const AttnPlan& p, int variant, const void* q, void* out,
       *partials_needed = 8 * rem * split;
     }
   }
+  *core16 = takes_core16(a, max_pages, n_cu);
   a.inv_cols = 1.0f / float(a.cols_per_xcd);
   a.inv_tiles = 1.0f / float(a.tiles_per_seg);
   a.inv_pages = 1.0f / float(a.pages_per_block);
@@ -542,19 +614,22 @@ int32_t plan_attn_bf16(const AttnPlan& p, int variant, const void* q, void* out,
   return CA_OK;
 }
 
-int32_t enqueue_attn_bf16(const AttnArgs& a, bool rope_q, void* stream) {
+template <bool kRopeQ, bool kCore16>
+int32_t enqueue_attn_bf16(const AttnArgs& a, void* stream) {
   const dim3 grid((unsigned)((a.full_items + a.split_items * a.split) * 8));
-  const void* kernel = rope_q ? reinterpret_cast<const void*>(attn_bf16_kernel<true>)
-                              : reinterpret_cast<const void*>(attn_bf16_kernel<false>);
-  if (const int32_t rc = ensure_dynamic_lds(kernel, kAttnLds, rope_q ? kLdsAttnRope : kLdsAttn); rc != CA_OK) return rc;
-  if (rope_q)
-    hipLaunchKernelGGL(attn_bf16_kernel<true>, grid, dim3(256), kAttnLds, static_cast<hipStream_t>(stream), a);
-  else
-    hipLaunchKernelGGL(attn_bf16_kernel<false>, grid, dim3(256), kAttnLds, static_cast<hipStream_t>(stream), a);
+  const auto kernel = attn_bf16_kernel<kRopeQ, kCore16>;
+  const LdsSlot slot = kRopeQ ? (kCore16 ? kLdsAttnRope16 : kLdsAttnRope) : (kCore16 ? kLdsAttn16 : kLdsAttn);
+  if (const int32_t rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), kAttnLds, slot); rc != CA_OK) return rc;
+  hipLaunchKernelGGL(kernel, grid, dim3(256), kAttnLds, static_cast<hipStream_t>(stream), a);
   if (a.split > 1)
-    hipLaunchKernelGGL(merge_partials_kernel, dim3((unsigned)(8 * a.split_items), kRowsPerWg / 32), dim3(256), 0,
+    hipLaunchKernelGGL(merge_partials_kernel<kCore16>, dim3((unsigned)(8 * a.split_items), kRowsPerWg / 32), dim3(256), 0,
                        static_cast<hipStream_t>(stream), a);
   return finish_launch("attn_bf16.hip");
+}
+
+template <bool kRopeQ>
+int32_t enqueue_attn_bf16(const AttnArgs& a, bool core16, void* stream) {
+  return core16 ? enqueue_attn_bf16<kRopeQ, true>(a, stream) : enqueue_attn_bf16<kRopeQ, false>(a, stream);
 }
 
 }  // namespace
@@ -563,17 +638,19 @@ int32_t launch_attn_bf16(const AttnPlan& p, int variant, const void* q, void* ou
                          void* partials_dev, int max_partials, void* stream) {
   AttnArgs a;
   int needed = 0;
-  if (const int32_t rc = plan_attn_bf16(p, variant, q, out, pool, partials_dev, max_partials, true, &a, &needed);
+  bool core16 = false;
+  if (const int32_t rc = plan_attn_bf16(p, variant, q, out, pool, partials_dev, max_partials, true, &a, &needed, &core16);
       rc != CA_OK)
     return rc;
-  return enqueue_attn_bf16(a, false, stream);
+  return enqueue_attn_bf16<false>(a, core16, stream);
 }
 
 int32_t launch_attn_bf16_rope(const AttnPlan& p, const QRopePlan& rp, int variant, const void* q, void* out,
                               const void* pool, void* partials_dev, int max_partials, void* stream) {
   AttnArgs a;
   int needed = 0;
-  if (const int32_t rc = plan_attn_bf16(p, variant, q, out, pool, partials_dev, max_partials, true, &a, &needed);
+  bool core16 = false;
+  if (const int32_t rc = plan_attn_bf16(p, variant, q, out, pool, partials_dev, max_partials, true, &a, &needed, &core16);
       rc != CA_OK)
     return rc;
   const double two_pi = 6.283185307179586476925286766559;
@@ -601,7 +678,7 @@ int32_t launch_attn_bf16_rope(const AttnPlan& p, const QRopePlan& rp, int varian
   if (rp.geom.grid_h >= 4096 || rp.geom.grid_w >= 4096) return CA_EUNSUPPORTED;
   a.q_tok_stride = rp.tok_stride;
   a.q_head_stride = rp.head_stride;
-  return enqueue_attn_bf16(a, true, stream);
+  return enqueue_attn_bf16<true>(a, core16, stream);
 }
 
 // ---- the same launch with the partial results in device memory this library holds itself, for
@@ -644,12 +721,13 @@ int32_t launch_attn_bf16_static(const AttnPlan& p, int variant, const void* q, v
   if (const int32_t rc = static_scratch_on_current_device(&ptr); rc != CA_OK) return rc;
   AttnArgs a;
   int needed = 0;
+  bool core16 = false;
   // the split the device's CU count asks for, as launch_attn_bf16 takes it when its area is large
   // enough; what does not fit the static area is refused, not shrunk
-  if (const int32_t rc = plan_attn_bf16(p, variant, q, out, pool, ptr, kStaticPartials, false, &a, &needed); rc != CA_OK)
+  if (const int32_t rc = plan_attn_bf16(p, variant, q, out, pool, ptr, kStaticPartials, false, &a, &needed, &core16); rc != CA_OK)
     return rc;
   if (needed > kStaticPartials) return CA_ETOOBIG;
-  return enqueue_attn_bf16(a, false, stream);
+  return enqueue_attn_bf16<false>(a, core16, stream);
 }
 
 }  // namespace ca

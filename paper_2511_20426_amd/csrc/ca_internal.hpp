@@ -130,7 +130,7 @@ int32_t launch_gemm_qkv_publish(const RopeGeom& g, int32_t n_blocks, int32_t blo
 // safe: the cached values are idempotent and written with relaxed atomics).
 constexpr int kMaxDevices = 64;
 int32_t device_cu_count(int* n_cu);                                   // of the current device
-enum LdsSlot { kLdsAttn, kLdsAttnRope, kLdsGemm256, kLdsGemm256Publish, kLdsGemm256x128, kLdsGemm256x128Publish, kLdsGemm128,
+enum LdsSlot { kLdsAttn, kLdsAttnRope, kLdsAttn16, kLdsAttnRope16, kLdsGemm256, kLdsGemm256Publish, kLdsGemm256x128, kLdsGemm256x128Publish, kLdsGemm128,
                kLdsGemm128Publish, kLdsGemm64, kLdsGemm64Wide, kLdsSlots };
 int32_t ensure_dynamic_lds(const void* kernel, int bytes, LdsSlot slot);
 int32_t finish_launch(const char* what);   // launchers end with this: CA_OK, or CA_EDEVICE after recording HIP's last error

@@ -50,6 +50,7 @@ from __future__ import annotations
 
 import os
 import sys
+from types import SimpleNamespace
 
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 from issue_sched import Atom, quanta, schedule  # noqa: E402
@@ -418,22 +419,23 @@ def emit_cold(E, s_cur, s_next, p_cur, cold, back, valid_sreg):
     c.append(f"s_branch {back}")
 
 
-def emit_step(E, R, par, vmcnt):
-    slots, cold_args = build_step(R, par)
+def emit_step(E, R, par, vmcnt, core):
+    slots, cold_args = core.build_step(R, par)
     E.e(f"; ---- step R={R} parity={par}")
     for m, lines in slots:
         E.e(m)
         for ln in lines:
             E.e(ln.replace("@VMCNT_V@", str(vmcnt[0])).replace("@VMCNT_K@", str(vmcnt[1])))
-    emit_cold(E, *cold_args)
+    core.emit_cold(E, *cold_args)
 
 
-def wait_counts():
+def wait_counts(core=None):
     """vmcnt operands of the two page barriers: loads complete in issue order, so waiting for
     page X means allowing as many loads in flight as are issued after X's last one."""
+    core = core or CORE
     order = []                                            # (R, slot, stream) of every load of one page period
     for R in range(4):
-        slots, _ = build_step(R, 0)
+        slots, _ = core.build_step(R, 0)
         for i, (_, lines) in enumerate(slots):
             for ln in lines:
                 if ln.startswith("s_add_u32 m0"):
@@ -445,8 +447,8 @@ def wait_counts():
         n_prev = len(order) - 1 - last
         n_now = sum(1 for o in order if (o[0], o[1]) <= until)
         return n_prev + n_now
-    vm_v = after_last(1, (0, 31))                         # barrier in the tail of step 0
-    vm_k = after_last(0, (2, K_BARRIER_SLOT - 1))
+    vm_v = after_last(1, (0, core.SLOTS - 1))             # barrier in the tail of step 0
+    vm_k = after_last(0, (2, core.K_BARRIER_SLOT - 1))
     assert vm_v < 60 and vm_k < 60
     return vm_v, vm_k
 
@@ -464,7 +466,60 @@ def emit_drain(E, par_last):
             E.e(mfma_pv(g & 3, nt, g, P_TILE["B"], g >> 2))
 
 
-def generate():
+def emit_operand_setup(E):
+    E.e(f"v_mov_b32 {V(KIDX)}, %[kidx]")
+    E.e(f"v_mov_b32 {V(XLANE)}, %[xlane]")
+    for j in range(8):
+        E.e(f"v_xor_b32 {V(XOK + j)}, {j << 5}, %[xo0]")
+        E.e(f"v_add_u32 {V(XOK + j)}, s{S_LDS0}, {V(XOK + j)}")
+        E.e(f"v_add_u32 {V(XOV + j)}, {VRING}, {V(XOK + j)}")
+
+
+def emit_clear(E):
+    for r in range(4):
+        E.e(f"v_mov_b32 {V(LACC + r)}, 0")
+    for nt in range(2):
+        E.e(f"v_mov_b32 {V(TS[nt])}, 0")
+    for nt in range(2):                                   # m_ref = 0 until tile 0 has been seen
+        for i in range(16):
+            E.e(f"v_mov_b32 {V(NT[nt] + i)}, 0")
+
+
+def emit_first_tile(E):
+    """S tile of step 0 into tile A, its mask, max and reference"""
+    for f in range(8):
+        E.e(f"ds_read_b128 {V(FR + 4 * f, 4)}, {V(XOK + f)} offset:0")
+    E.e("s_waitcnt lgkmcnt(0)")
+    for f in range(8):
+        for nt in range(2):
+            E.e(mfma_qk(f == 0, S_TILE["A"], nt, f, f))
+    E.e("s_nop 15\ns_nop 15\ns_nop 15")
+    for op in tile_max_ops(S_TILE["A"]):
+        E.e(op)
+    emit_mask_check(E, S_TILE["A"], S_PGCUR, 0)
+    emit_first_reference(E, S_TILE["A"])
+
+
+def emit_first_reads(E):
+    """first operand fragments of step (R=0, parity 0)"""
+    for f in range(D_AHEAD):
+        E.e(ds_read_frag(f, frag_source(0, 0, f)))
+    E.e(f"s_waitcnt lgkmcnt({D_AHEAD - 2})")
+
+
+def emit_results(E):
+    for r in range(128):                                   # results leave in v[0:127]
+        E.e(f"v_accvgpr_read_b32 {V(r)}, {A(r)}")
+
+
+CORE = SimpleNamespace(SLOTS=32, K_BARRIER_SLOT=K_BARRIER_SLOT, build_step=build_step, emit_cold=emit_cold, emit_drain=emit_drain,
+                       emit_operand_setup=emit_operand_setup, emit_clear=emit_clear, emit_first_tile=emit_first_tile,
+                       emit_first_reads=emit_first_reads, emit_results=emit_results)
+
+
+def generate(core=None):
+    """The whole block; what depends on the shape of the matrix instruction comes from `core`."""
+    core = core or CORE
     E = Emitter()
     # ---- set-up: inputs to fixed registers
     E.e(f"s_mov_b32 s{S_NLEFT}, %[n_pages]")
@@ -488,12 +543,7 @@ def generate():
         E.e(f"v_add_u32 {V(DMAOFF + i)}, {4096 * i}, %[lane_off]")
     E.e(f"v_mov_b32 {V(TBLLO)}, %[tbl_lo]")
     E.e(f"v_mov_b32 {V(TBLHI)}, %[tbl_hi]")
-    E.e(f"v_mov_b32 {V(KIDX)}, %[kidx]")
-    E.e(f"v_mov_b32 {V(XLANE)}, %[xlane]")
-    for j in range(8):
-        E.e(f"v_xor_b32 {V(XOK + j)}, {j << 5}, %[xo0]")
-        E.e(f"v_add_u32 {V(XOK + j)}, s{S_LDS0}, {V(XOK + j)}")
-        E.e(f"v_add_u32 {V(XOV + j)}, {VRING}, {V(XOK + j)}")
+    core.emit_operand_setup(E)
     # the walk starts at page pg0 of visible block kb0 (0, 0 unless the KV range of a tile is split)
     E.e(f"s_mov_b32 s{S_PGCUR}, %[pg0]")
     E.e(f"s_add_u32 s{S_T}, s{S_PGCUR}, 1")
@@ -509,53 +559,33 @@ def generate():
     emit_issue_page(E, 0, PAGE)
     for r in range(128):
         E.e(f"v_accvgpr_write_b32 {A(r)}, 0")
-    for r in range(4):
-        E.e(f"v_mov_b32 {V(LACC + r)}, 0")
-    for nt in range(2):
-        E.e(f"v_mov_b32 {V(TS[nt])}, 0")
-    for nt in range(2):                                   # m_ref = 0 until tile 0 has been seen
-        for i in range(16):
-            E.e(f"v_mov_b32 {V(NT[nt] + i)}, 0")
+    core.emit_clear(E)
     for r in range(16):
         E.e(f"v_mov_b32 {V(P_TILE['B'] + r)}, 0")
     E.e("s_waitcnt vmcnt(8) lgkmcnt(0)")
     E.e("s_barrier")
-    # ---- S tile of step 0 into tile A, its mask, max and reference
-    for f in range(8):
-        E.e(f"ds_read_b128 {V(FR + 4 * f, 4)}, {V(XOK + f)} offset:0")
-    E.e("s_waitcnt lgkmcnt(0)")
-    for f in range(8):
-        for nt in range(2):
-            E.e(mfma_qk(f == 0, S_TILE["A"], nt, f, f))
-    E.e("s_nop 15\ns_nop 15\ns_nop 15")
-    for op in tile_max_ops(S_TILE["A"]):
-        E.e(op)
-    emit_mask_check(E, S_TILE["A"], S_PGCUR, 0)
-    emit_first_reference(E, S_TILE["A"])
-    # first operand fragments of step (R=0, parity 0)
-    for f in range(D_AHEAD):
-        E.e(ds_read_frag(f, frag_source(0, 0, f)))
-    E.e(f"s_waitcnt lgkmcnt({D_AHEAD - 2})")
+    core.emit_first_tile(E)
+    core.emit_first_reads(E)
 
     # ---- main loop, two pages per trip (ring parity is compile-time)
     loop, exit_even, exit_odd, done = (E.label("LOOP"), E.label("EXIT_EVEN"), E.label("EXIT_ODD"),
                                         E.label("DONE"))
-    vmcnt = wait_counts()
+    vmcnt = wait_counts(core)
     E.e(f"{loop}:")
     for par in range(2):
         for R in range(4):
-            emit_step(E, R, par, vmcnt)
+            emit_step(E, R, par, vmcnt, core)
         E.e(f"s_cmp_eq_u32 s{S_NLEFT}, 0")
         E.e("s_nop 0")
         E.e(f"s_cbranch_scc1 {exit_even if par == 0 else exit_odd}")
     E.e(f"s_branch {loop}")
     E.e(f"{exit_even}:")
     E.e("s_waitcnt lgkmcnt(0)")
-    emit_drain(E, 0)
+    core.emit_drain(E, 0)
     E.e(f"s_branch {done}")
     E.e(f"{exit_odd}:")
     E.e("s_waitcnt lgkmcnt(0)")
-    emit_drain(E, 1)
+    core.emit_drain(E, 1)
     E.e(f"s_branch {done}")
     # ---- out-of-line blocks
     for ln in E.cold:
@@ -563,30 +593,32 @@ def generate():
     E.e(f"{done}:")
     E.e("s_waitcnt vmcnt(0)")                              # trailing (unused) page loads have landed
     E.e("s_nop 15\ns_nop 15\ns_nop 15")                    # the last MFMAs have written back
-    for r in range(128):                                   # results leave in v[0:127]
-        E.e(f"v_accvgpr_read_b32 {V(r)}, {A(r)}")
+    core.emit_results(E)
     return E.lines
 
 
-def main(out_path):
-    lines = generate()
+def write_include(out_path, lines, clob, macro):
     text = []
     for ln in lines:
         for part in ln.split("\n"):
             text.append(part)
+    by = f"// Generated by {os.path.basename(sys.argv[0])} -- do not edit.\n"
     with open(out_path, "w") as f:
-        f.write("// Generated by gen_attn_core.py -- do not edit.\n")
+        f.write(by)
         for t in text:
             f.write('"' + t.replace("\\", "\\\\").replace('"', '\\"') + '\\n"\n')
-    # registers the block uses beyond its operands (v148..v151 are outputs)
-    clob = [f"v{i}" for i in range(128, 256) if not 148 <= i <= 151 and i not in (184, 200)] + [f"a{i}" for i in range(0, 128)] + [f"s{i}" for i in range(36, 96)]
-    clob_path = out_path.replace("attn_core_gfx950.inc", "attn_core_clobbers.inc")
-    with open(clob_path, "w") as f:
-        f.write("// Generated by gen_attn_core.py -- do not edit.\n#define CA_CORE_CLOBBERS \\\n")
+    with open(out_path.replace("_gfx950.inc", "_clobbers.inc"), "w") as f:
+        f.write(f"{by}#define {macro} \\\n")
         for i in range(0, len(clob), 12):
             chunk = ", ".join(f'"{c}"' for c in clob[i:i + 12])
             f.write("  " + chunk + (", \\\n" if i + 12 < len(clob) else "\n"))
     print(f"{out_path}: {len(text)} lines")
+
+
+def main(out_path):
+    # registers the block uses beyond its operands (v148..v151 are outputs)
+    clob = [f"v{i}" for i in range(128, 256) if not 148 <= i <= 151 and i not in (184, 200)] + [f"a{i}" for i in range(0, 128)] + [f"s{i}" for i in range(36, 96)]
+    write_include(out_path, generate(), clob, "CA_CORE_CLOBBERS")
 
 
 if __name__ == "__main__":

@@ -1,0 +1,440 @@
+#!/usr/bin/env python3
+"""Emits attn_core16_gfx950.inc: the main loop of gen_attn_core.py on the 16x16x32 matrix instruction, for launches that
+fill the chip.  Walk, page traffic, barriers and scalar registers are that generator's.
+
+Why 16x16x32 and not 32x32x16: a launch that fills the chip is limited by power, and per flop the smaller
+shape moves half as many accumulator registers.  An MFMA-only loop over random operands reaches 1943 TFLOP/s with
+it against 1715 with 32x32x16 in one session, 2060 if four consecutive MFMAs share their accumulator (as QK does below).  The
+price is issue room (64 MFMAs a step for 32): row sums are therefore taken by the matrix pipe as well, and a slot is dealt out
+by its own model (schedule16; with the other one's the loop took 1190 cycles a step).  Cycles a step
+1062 -> 1135 at the highest clock, but 1.84 GHz for 1.62 where power decides: 14B step of five blocks 16.45 ->
+15.33 ms, 1.3B one block 688 -> 636 us, one device's share 2.91 -> 2.77 ms.
+
+Pipeline (a "step" is 32 keys, a page is 4 steps; t counts steps):
+    QK(t+1): 32 MFMAs  S_next = K_frag x Q                      (K fragments from LDS)
+    SM(t)  : p = exp2(S_cur), bf16 pack                          (VALU; S_cur already holds
+             s*c - m_ref: Q is pre-scaled by c = log2(e)/sqrt(D) and QK starts from -m_ref)
+    PV(t-1): 32 MFMAs  O^T   += V_frag x P_prev                  (V fragments from LDS)
+             4 MFMAs   l     += ones x P_prev                    (the row sums, fp32, of the weights PV uses)
+
+Keys in the accumulators.  A 16x16 accumulator tile gives lane group g (of 16 lanes) its rows 4g..4g+3.  A 32-key
+step has two such tiles; their 16 rows are keys 0..7 and 16..23 (second tile: 8..15 and 24..31), so that what a
+lane group holds in both, keys 16 (g/2) + 4 (g%2) + {0..3, 8..11}, is one 16-byte chunk of a V row and P goes from accumulator
+to operand without movement.  The K rows a read touches then meet in pairs in an LDS bank; LDS has the room
+(31 % busy).
+
+The exponent reference m_ref of a row is lazy: it starts 15 above the maximum of the row's first tile (log2 units: P is
+floating point, so the offset costs nothing) and moves only when it has to.  No maximum is taken in the loop; instead the
+packed words of a step are or'ed together, and an exponent bit that only numbers from 2 on have (or inf: exp2 against a stale
+reference may overflow) sends the wave to an out-of-line block at the end of the step, which
+takes the tile's maximum, forms the step's probabilities again from the S tile (still in
+registers) against the raised reference and rescales what earlier steps left.  The same branch
+serves the rare step whose S tile needs its ragged tail masked.
+
+Register map (fixed):
+  a[0:127]    O^T accumulators, (dt, qt) at a[16 dt + 4 qt ..]: dims 16 dt + 4 (lane/16) + i of query lane%16 of tile qt
+  a[128:191]  Q fragments, (qt, ks) at a[128 + 4*(4*qt+ks) ..]
+  a[192:207]  row sums, query tile qt at a[192 + 4 qt ..] (row 0: first register of lanes 0..15)
+  v[0:31]     S tile A, (kt, qt) at v[16 kt + 4 qt ..]     v[32:63]  S tile B
+  v[64:79]    P^T tile A, qt at v[64 + 4 qt ..]      v[80:95]  P^T tile B
+  v[96:127]   ring of 8 operand fragments
+  v[128:131]  LDS address in the K ring for chunks 4j.., v[132:135] in the V ring for 32-key step j of a page
+  v[136:139]  ones in lanes 0, 16, 32, 48
+  v[148:151]  row sums on leaving
+  v156..v175  temporaries of the out-of-line blocks
+  v[184:199]  -m_ref per query tile, replicated 4 times: the C operand of the
+              first MFMA of every S tile, so a tile comes out of the matrix pipe as s*c - m_ref
+  v[216:223]  lane's byte offset inside a page for page load i = 0..7
+  v[224:255]  the 32 probabilities of the step before they are packed
+  v177,v178   address of page 0 of each KV block for this head (lane i = block i), low / high word
+  v179        first key this lane holds in a step: 16 (g/2) + 4 (g%2)
+  v180, v181  4*(lane ^ 16), 4*(lane ^ 32): ds_bpermute addresses of the lanes that share this query
+"""
+from __future__ import annotations
+
+import os
+import sys
+
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+import gen_attn_core as base  # noqa: E402
+from gen_attn_core import (A, FR, P_TILE, PAGE, S_LDS0, S_NLEFT, S_P, S_PGCUR, S_PGNEXT, S_PM1, S_RG, S_T, S_TILE,  # noqa: E402
+                           S_VLAST, S_VLP, V, VRING, Emitter, page_advance_lines, page_load_lines, v_address_lines)
+from issue_sched import Atom, is_vector, schedule16, split_cost  # noqa: E402
+
+QT = 4               # query tiles of 16 per wave
+SLOTS = 68           # MFMAs of a step: 32 QK, 4 row sums, 32 PV
+
+XOK, XOV = 128, 132
+ONES = 136           # 136..139: one row of ones (lanes 0, 16, 32, 48), the A operand that sums P over the keys
+LSUM = 192           # a192..a207: row sums per query tile (row 0 of a tile of 16: first register of lanes 0..15)
+LOUT = 148           # 148..151: the same on leaving
+NT = [184 + 4 * qt for qt in range(QT)]      # -m_ref of the tile's query, four times: C operand of a tile's first MFMA
+MX = [156, 157, 158, 159]
+PX = 224             # 224..255: the 32 probabilities of the step, before packing
+RT = list(range(160, 176))     # rare-path temporaries
+KIDX, XL16, XL32 = 179, 180, 181
+
+
+def s_reg(s_base, kt, qt, i=0):
+    return s_base + 16 * kt + 4 * qt + i
+
+
+def o_reg(dt, qt, i=0):
+    return 16 * dt + 4 * qt + i
+
+
+def mfma_qk(s_base, kt, qt, ks):
+    d = V(s_reg(s_base, kt, qt), 4)
+    c = V(NT[qt], 4) if ks == 0 else d
+    return f"v_mfma_f32_16x16x32_bf16 {d}, {V(FR + 4 * (4 * kt + ks), 4)}, {A(128 + 4 * (4 * qt + ks), 4)}, {c}"
+
+
+def mfma_pv(dt, qt, p_base):
+    o = A(o_reg(dt, qt), 4)
+    return f"v_mfma_f32_16x16x32_bf16 {o}, {V(FR + 4 * dt, 4)}, {V(p_base + 4 * qt, 4)}, {o}"
+
+
+def mfma_sum(qt, p_base):
+    l = A(LSUM + 4 * qt, 4)
+    return f"v_mfma_f32_16x16x32_bf16 {l}, {V(ONES, 4)}, {V(p_base + 4 * qt, 4)}, {l}"
+
+
+def pv_order(p_base):
+    return [mfma_sum(qt, p_base) for qt in range(QT)] + [mfma_pv(dt, qt, p_base) for dt in range(8) for qt in range(QT)]
+
+
+def qk_order():
+    """the four k-steps of a tile back to back: an accumulator that stays in the pipe costs less power"""
+    return [(kt, qt, ks) for kt in range(2) for qt in range(QT) for ks in range(4)]
+
+
+def k_source(page_sub, par, f):
+    """(address register, immediate) of K fragment f = 4 kt + ks of a 32-key step of a page."""
+    kt, ks = f >> 2, f & 3
+    return XOK + (ks ^ (2 * kt)), par * PAGE + page_sub * 8192 + kt * 2048
+
+
+def frag_source(R, par, f):
+    """(address register, immediate) of operand fragment f of step (R, par): 0..7 K, 8..15 V."""
+    if f < 8:                                   # K fragment of step t+1
+        return k_source(R + 1, par, f) if R < 3 else k_source(0, 1 - par, f)   # (first step of page q+1)
+    dt = f - 8
+    if R == 0:                                  # V of the last step of page q-1
+        return XOV + 3, (1 - par) * PAGE + dt * 4096
+    return XOV + R - 1, par * PAGE + dt * 4096
+
+
+def ds_read_frag(f, src):
+    reg, imm = src
+    return f"ds_read_b128 {V(FR + 4 * (f % 8), 4)}, {V(reg)} offset:{imm}"
+
+
+def row_max_lines(m, regs):
+    """m = max over eight registers"""
+    return [f"v_max3_f32 {m}, {V(regs[0])}, {V(regs[1])}, {V(regs[2])}",
+            f"v_max3_f32 {m}, {m}, {V(regs[3])}, {V(regs[4])}",
+            f"v_max3_f32 {m}, {m}, {V(regs[5])}, {V(regs[6])}",
+            f"v_max_f32 {m}, {m}, {V(regs[7])}"]
+
+
+def row_regs(s_base, qt):
+    """the eight scores of a query of tile qt that a lane holds"""
+    return [s_reg(s_base, kt, qt, i) for kt in range(2) for i in range(4)]
+
+
+def across_lanes_lines(m, other):
+    """m = its maximum over the four lanes that share a query"""
+    out = []
+    for x in (XL16, XL32):
+        out += [f"ds_bpermute_b32 {other}, {V(x)}, {m}", "s_waitcnt lgkmcnt(0)", f"v_max_f32 {m}, {m}, {other}"]
+    return out
+
+
+def tile_max_ops(s_base):
+    """ops leaving the maximum over a lane's eight scores of each query tile in MX[qt]."""
+    return [ln for qt in range(QT) for ln in row_max_lines(V(MX[qt]), row_regs(s_base, qt))]
+
+
+def emit_mask(E, s_base, valid_sreg):
+    """Scores of keys at or past `valid` (keys of this 32-key step) become -inf, all query tiles."""
+    E.e(f"v_mov_b32 {V(RT[0])}, 0xff800000")
+    for kt in range(2):
+        for i in range(4):
+            E.e(f"s_sub_i32 s{S_T}, s{valid_sreg}, {8 * kt + i}")
+            E.e(f"v_cmp_lt_i32 vcc, {V(KIDX)}, s{S_T}")             # key row < valid
+            for qt in range(QT):
+                r = V(s_reg(s_base, kt, qt, i))
+                E.e(f"v_cndmask_b32 {r}, {V(RT[0])}, {r}, vcc")
+
+
+def emit_first_reference(E, s_base):
+    """The exponent reference of a row starts as the maximum of its first tile (at s_base, its
+    per-lane maxima in MX): the tile and the -m_ref operand move by it.  Nothing has been
+    accumulated yet, so there is nothing to rescale."""
+    E.e("s_nop 15\ns_nop 15\ns_nop 15")                   # every MFMA issued so far has written back
+    for qt in range(QT):
+        m = V(MX[qt])
+        for ln in across_lanes_lines(m, V(RT[3])):
+            E.e(ln)
+        E.e(f"v_add_f32 {m}, {HEADROOM}, {m}")
+        for i in range(4):
+            E.e(f"v_sub_f32 {V(NT[qt] + i)}, {V(NT[qt] + i)}, {m}")
+        for r in row_regs(s_base, qt):
+            E.e(f"v_sub_f32 {V(r)}, {V(r)}, {m}")
+
+
+def emit_mask_check(E, s_base, pg_sreg, sub):
+    """If the tile at s_base is the ragged tail of a block's last page: mask it and redo its max."""
+    cold, back = E.label("MASK"), E.label("MBACK")
+    E.e(f"s_cmp_eq_u32 s{pg_sreg}, s{S_PM1}")
+    E.e(f"s_cselect_b32 s{S_T + 8}, s{S_VLAST + sub}, 32")
+    E.e(f"s_cmp_lt_u32 s{S_T + 8}, 32")
+    E.e(f"s_cbranch_scc1 {cold}")
+    E.e(f"{back}:")
+    sub_e = Emitter()
+    emit_mask(sub_e, s_base, S_T + 8)
+    E.cold.append(f"{cold}:")
+    E.cold.append("s_nop 15\ns_nop 15\ns_nop 15")
+    E.cold.extend(sub_e.lines)
+    E.cold.extend(tile_max_ops(s_base))
+    E.cold.append(f"s_branch {back}")
+
+
+def p_word(p_base, j):
+    """VGPR of the packed pair that ends at element j (odd) of the tile being exponentiated; element
+    16 kt + 4 qt + i."""
+    return p_base + 4 * ((j & 15) >> 2) + 2 * (j >> 4) + ((j & 3) >> 1)
+
+
+CAP = 4.0            # issue quanta per MFMA slot the scheduler may fill
+E_SPREAD = 40        # the 32 exponentials of a step are due by this slot
+HEADROOM = "0x41700000"   # 15: the reference is taken this far above the maximum it is taken from (log2 units)
+TOO_LARGE = "0x40004000"  # exponent bit that a bf16 number (a pair of them) has from 2 on
+K_BARRIER_SLOT = 32  # step 2: K(q+1) visible, slot of K(q) free
+N_KLOADS_R2 = 3      # of the 8 loads of K(q+2), how many issue in step 2 (the rest in step 3)
+
+# Operand reads: fragment -> slot it is read in.  Fragment f goes to registers FR + 4 (f % 8): V's take the place of
+# K's as those have been multiplied, and the next step's K's the place of V's; K fragment 7 of a step
+# is read in its own slot 1.
+V_READS = {8 + i: 16 + 2 * i for i in range(4)} | {12 + i: 32 + 2 * i for i in range(4)}
+K_READS = {0: 41, 1: 44, 2: 49, 3: 52, 4: 57, 5: 60, 6: 64}
+# lgkmcnt of the waits before the slots that first use a fragment: what was read later may still be on its way
+WAITS = {15: 0, 35: 2, 51: 3, 67: 3}
+
+
+def build_step(R, par):
+    """One 32-key step as a list of SLOTS slots: (MFMA line, [lines issued after it])."""
+    cur, nxt = ("A", "B") if R % 2 == 0 else ("B", "A")
+    s_cur, s_next = S_TILE[cur], S_TILE[nxt]
+    p_prev, p_cur = (P_TILE["B"], P_TILE["A"]) if R % 2 == 0 else (P_TILE["A"], P_TILE["B"])
+    nR, npar = ((R + 1) & 3, par if R < 3 else 1 - par)
+    cold, back = f"COLD_{R}_{par}_%=", f"BACK_{R}_{par}_%="
+
+    head, tail = [[] for _ in range(SLOTS)], [[] for _ in range(SLOTS)]
+    mfma = [mfma_qk(s_next, *x) for x in qk_order()] + pv_order(p_prev)
+    head[1].append(ds_read_frag(7, frag_source(R, par, 7)))
+    for f, at in V_READS.items():
+        head[at].append(ds_read_frag(f, frag_source(R, par, f)))
+    for f, at in K_READS.items():
+        head[at].append(ds_read_frag(f, frag_source(nR, npar, f)))
+    for at, n in WAITS.items():
+        tail[at].append(f"s_waitcnt lgkmcnt({n})")
+    if R == 0:                                             # before step 1: V(q) visible, V(q-1)'s slot free
+        tail[SLOTS - 1] += ["s_waitcnt vmcnt(@VMCNT_V@)", "s_barrier"]
+    if R == 2:
+        tail[K_BARRIER_SLOT - 1] += ["s_waitcnt vmcnt(@VMCNT_K@)", "s_barrier"]
+
+    atoms = []
+    exps = [Atom([f"v_exp_f32 {V(PX + e)}, {V(s_cur + e)}"], 0, (e * E_SPREAD) // 32, hard=54) for e in range(32)]
+    atoms += exps
+    packs = []
+    for j in range(1, 32, 2):
+        packs.append(Atom([f"v_cvt_pk_bf16_f32 {V(p_word(p_cur, j))}, {V(PX + j - 1)}, {V(PX + j)}"],
+                          0, (j * E_SPREAD) // 32 + 6, [exps[j - 1], exps[j]], 2, hard=60))
+        packs[-1].word = p_word(p_cur, j)
+    atoms += packs
+    # all the step's words or'ed together: has any probability reached 2?
+    acc, last = V(RT[1]), None
+    for k in range(0, 15, 2):
+        more = packs[:3] if k == 0 else packs[k + 1:k + 3]
+        srcs = [V(x.word) for x in more]
+        op = f"v_or3_b32 {acc}, " + ", ".join(srcs if k == 0 else [acc] + srcs) if len(srcs) + (k > 0) == 3 else f"v_or_b32 {acc}, {acc}, {srcs[0]}"
+        last = Atom([op], 0, ((2 * k + 7) * E_SPREAD) // 32 + 12, more + ([last] if last else []), 1, hard=62)
+        atoms.append(last)
+    # is the tile just produced the ragged tail of a block's last page?
+    pg, sub = (S_PGCUR, R + 1) if R < 3 else (S_PGNEXT, 0)
+    rag = Atom([f"s_cmp_eq_u32 s{pg}, s{S_PM1}",
+                f"s_cselect_b64 s[{S_RG}:{S_RG + 1}], s[{S_VLP + 2 * sub}:{S_VLP + 2 * sub + 1}], 0"], 0, 12, hard=48)
+    det = Atom([f"v_and_b32 {acc}, {TOO_LARGE}, {acc}", f"v_cmp_ne_u32 vcc, 0, {acc}"], 0, 62, [last], 0, hard=63)
+    # scc travels from here to the branch after the last MFMA: nothing that writes scc may
+    # issue behind it (every such atom has hard <= 60)
+    orr = Atom([f"s_or_b64 s[{S_T + 8}:{S_T + 9}], vcc, s[{S_RG}:{S_RG + 1}]"], 65, 65, [det, rag], 1, hard=65)
+    atoms += [rag, det, orr]
+    tail[SLOTS - 1].insert(0, f"{back}:")
+    tail[SLOTS - 1].insert(0, f"s_cbranch_scc1 {cold}")
+    # page traffic
+    loads = []
+    if R == 0:                                             # address of V(q+1), then of K(q+2)
+        prev = None
+        for k, grp in enumerate(v_address_lines() + page_advance_lines()):
+            prev = Atom(grp, 4, 12 + 6 * k, [prev] if prev else [], 1, hard=59)
+            atoms.append(prev)
+    if R == 1:                                             # V(q+1) into the slot V(q-1) left
+        for i in range(8):
+            loads.append(Atom(page_load_lines(i, VRING + (1 - par) * PAGE, 1), 0, 3 + 7 * i, tag=("load", 1), hard=59))
+    if R == 2:                                             # K(q+2) into the slot K(q) left
+        for i in range(N_KLOADS_R2):
+            loads.append(Atom(page_load_lines(i, par * PAGE, 0), K_BARRIER_SLOT,
+                              K_BARRIER_SLOT + 4 + (i * (54 - K_BARRIER_SLOT)) // N_KLOADS_R2, tag=("load", 0), hard=59))
+    if R == 3:
+        n = 8 - N_KLOADS_R2
+        for i in range(n):
+            loads.append(Atom(page_load_lines(N_KLOADS_R2 + i, par * PAGE, 0), 0, 4 + (i * 56) // n, tag=("load", 0), hard=59))
+        # page-in-block counters of pages q and q+1 move on; one page less to go
+        pe = Atom([f"s_mov_b32 s{S_PGCUR}, s{S_PGNEXT}", f"s_add_u32 s{S_T}, s{S_PGNEXT}, 1",
+                   f"s_cmp_eq_u32 s{S_T}, s{S_P}", f"s_cselect_b32 s{S_PGNEXT}, 0, s{S_T}",
+                   f"s_sub_u32 s{S_NLEFT}, s{S_NLEFT}, 1"], 0, 40, [rag], 1, hard=59)
+        atoms.append(pe)
+    atoms += loads
+
+    fixed = [split_cost(head[i] + tail[i]) for i in range(SLOTS)]
+    placed = schedule16(fixed, atoms, CAP)
+    for i in range(65, SLOTS):
+        for a in placed[i]:
+            assert not any(l.split()[0].startswith(("s_add", "s_sub", "s_cmp", "s_and", "s_mul")) for l in a.lines), a.lines
+    slots = []
+    for i in range(SLOTS):
+        # what is not vector work goes first; nothing of the step may stand behind the branch at its end
+        atom_lines = [[l for a in placed[i] for l in a.lines if is_vector(l) == vec] for vec in (False, True)]
+        if i == SLOTS - 1:
+            lines = atom_lines[0] + atom_lines[1] + tail[i]
+        else:
+            lines = tail[i] + head[i] + atom_lines[0] + atom_lines[1]
+        slots.append((mfma[i], lines))
+    return slots, (s_cur, s_next, p_cur, cold, back, (S_VLAST + (R + 1 if R < 3 else 0)))
+
+
+def emit_cold(E, s_cur, s_next, p_cur, cold, back, valid_sreg):
+    """Out-of-line end of a step, entered when some lane's row sum of the step crossed THRESH
+    (vcc) or the tile just produced needs its ragged tail masked (s[S_RG]).
+
+    Moving the reference: the probabilities of the step were formed against a reference that
+    turned out too low (they may even have overflowed), so they are formed again from the S tile,
+    which is still in registers: the row maximum relative to the old reference gives the shift
+    delta >= 0; row sums and accumulators (all from earlier steps) are scaled by 2^-delta, the
+    tile just produced and the -m_ref operand move by delta."""
+    c = E.cold
+    skip_ovf, done = E.label("NOOVF"), E.label("CDONE")
+    c.append(f"{cold}:")
+    c.append("s_nop 15\ns_nop 15\ns_nop 15")            # every MFMA issued so far has written back
+    c.append(f"s_cbranch_vccz {skip_ovf}")
+    for qt in range(QT):
+        m, delta, alpha = V(MX[qt]), V(MX[qt]), V(RT[6])
+        regs = row_regs(s_cur, qt)
+        c += row_max_lines(m, regs)
+        c += across_lanes_lines(m, V(RT[3]))
+        c.append(f"v_add_f32 {m}, {HEADROOM}, {m}")
+        c.append(f"v_max_f32 {delta}, 0, {delta}")                  # the reference never moves down
+        c.append(f"v_exp_f32_e64 {alpha}, -{delta}")
+        c.append("s_nop 3")                              # a trans result is not forwarded to the next VALU op
+        c += [f"v_accvgpr_read_b32 {V(RT[8])}, {A(LSUM + 4 * qt)}", f"v_mul_f32 {V(RT[8])}, {V(RT[8])}, {alpha}",
+              f"v_accvgpr_write_b32 {A(LSUM + 4 * qt)}, {V(RT[8])}"]
+        for dt in range(8):
+            for i in range(4):
+                acc = A(o_reg(dt, qt, i))
+                tmp = V(RT[8 + (4 * dt + i) % 8])
+                c.append(f"v_accvgpr_read_b32 {tmp}, {acc}")
+                c.append(f"v_mul_f32 {tmp}, {tmp}, {alpha}")
+                c.append(f"v_accvgpr_write_b32 {acc}, {tmp}")
+        for r in regs:                                   # the step's probabilities again
+            c.append(f"v_sub_f32 {V(r)}, {V(r)}, {delta}")
+        es = [r - s_cur for r in regs]
+        for e in es:
+            c.append(f"v_exp_f32 {V(PX + e)}, {V(s_cur + e)}")
+        c.append("s_nop 3")
+        for j in es[1::2]:
+            c.append(f"v_cvt_pk_bf16_f32 {V(p_word(p_cur, j))}, {V(PX + j - 1)}, {V(PX + j)}")
+        for i in range(4):                               # -m_ref operand and the tile just produced
+            c.append(f"v_sub_f32 {V(NT[qt] + i)}, {V(NT[qt] + i)}, {delta}")
+        for r in row_regs(s_next, qt):
+            c.append(f"v_sub_f32 {V(r)}, {V(r)}, {delta}")
+    c.append(f"{skip_ovf}:")
+    c.append(f"s_cmp_eq_u32 s{S_RG}, 0")
+    c.append(f"s_cbranch_scc1 {done}")
+    sub_e = Emitter()
+    emit_mask(sub_e, s_next, valid_sreg)
+    c.extend(sub_e.lines)
+    c.append(f"{done}:")
+    c.append("s_nop 7")
+    c.append(f"s_branch {back}")
+
+
+def emit_drain(E, par_last):
+    """PV of the final step: V page (parity par_last), keys 96..127, P tile B."""
+    for dt in range(8):
+        E.e(f"ds_read_b128 {V(FR + 4 * dt, 4)}, {V(XOV + 3)} offset:{par_last * PAGE + dt * 4096}")
+    E.e("s_waitcnt lgkmcnt(0)")
+    for ln in pv_order(P_TILE["B"]):
+        E.e(ln)
+
+
+def emit_operand_setup(E):
+    E.e(f"v_mov_b32 {V(KIDX)}, %[kidx]")
+    E.e(f"v_mov_b32 {V(XL16)}, %[xl16]")
+    E.e(f"v_mov_b32 {V(XL32)}, %[xl32]")
+    for r in range(4):
+        E.e(f"v_mov_b32 {V(ONES + r)}, %[ones]")
+    for j in range(4):
+        E.e(f"v_xor_b32 {V(XOK + j)}, {j << 6}, %[xk0]")
+        E.e(f"v_add_u32 {V(XOK + j)}, s{S_LDS0}, {V(XOK + j)}")
+        E.e(f"v_xor_b32 {V(XOV + j)}, {j << 6}, %[xv0]")
+        E.e(f"v_add_u32 {V(XOV + j)}, s{S_LDS0}, {V(XOV + j)}")
+        E.e(f"v_add_u32 {V(XOV + j)}, {VRING}, {V(XOV + j)}")
+
+
+def emit_clear(E):
+    for r in range(4 * QT):
+        E.e(f"v_accvgpr_write_b32 {A(LSUM + r)}, 0")
+        E.e(f"v_mov_b32 {V(NT[0] + r)}, 0")               # m_ref = 0 until tile 0 has been seen
+
+
+def emit_first_tile(E):
+    """S tile of step 0 into tile A, its mask, max and reference"""
+    for f in range(8):
+        E.e(ds_read_frag(f, k_source(0, 0, f)))
+    E.e("s_waitcnt lgkmcnt(0)")
+    for x in qk_order():
+        E.e(mfma_qk(S_TILE["A"], *x))
+    E.e("s_nop 15\ns_nop 15\ns_nop 15")
+    for op in tile_max_ops(S_TILE["A"]):
+        E.e(op)
+    emit_mask_check(E, S_TILE["A"], S_PGCUR, 0)
+    emit_first_reference(E, S_TILE["A"])
+
+
+def emit_first_reads(E):
+    """first operand fragments of step (R=0, parity 0)"""
+    for f in K_READS:
+        E.e(ds_read_frag(f, frag_source(0, 0, f)))
+    E.e(f"s_waitcnt lgkmcnt({WAITS[SLOTS - 1]})")
+
+
+def emit_results(E):
+    base.emit_results(E)
+    for qt in range(QT):
+        E.e(f"v_accvgpr_read_b32 {V(LOUT + qt)}, {A(LSUM + 4 * qt)}")
+
+
+def generate():
+    return base.generate(sys.modules[__name__])
+
+
+def main(out_path):
+    # registers the block uses beyond its operands (v148..v151 and NT are outputs)
+    clob = [f"v{i}" for i in range(128, 256) if not 148 <= i <= 151 and i not in NT]
+    clob += [f"a{i}" for i in range(0, 128)] + [f"a{i}" for i in range(LSUM, LSUM + 4 * QT)] + [f"s{i}" for i in range(36, 96)]
+    base.write_include(out_path, generate(), clob, "CA_CORE16_CLOBBERS")
+
+
+if __name__ == "__main__":
+    main(sys.argv[1] if len(sys.argv) > 1 else "attn_core16_gfx950.inc")

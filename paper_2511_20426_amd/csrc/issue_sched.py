@@ -79,3 +79,61 @@ def schedule(fixed_load, atoms, cap):
             room -= pick.cost
     assert not pending, [a.lines for a in pending]
     return placed
+
+
+# ---- 16-cycle MFMAs (v_mfma_f32_16x16x32): a slot is four quanta.  Measured the same way (cycles per MFMA with fillers):
+# the MFMA takes one quantum of the issue port but keeps vector instructions out for two, so that one other
+# instruction (scalar, wait, LDS or memory) fits in between for nothing if it stands first; behind it there is room
+# for two quanta of vector work.  MFMA + s + s + v: 17 cycles; + v + v: 17; + v + v + s: 21 (the scalar one behind); + exp: 17;
+# + exp + s: 21; + ds_read + v: 17; + ds_read + 2 v: 21 -- a ds_read takes two quanta, an exp two.
+
+def is_vector(line):
+    return line.startswith("v_")
+
+
+def quanta16(line):
+    op = line.split()[0]
+    if op.endswith(":") or op.startswith(";"):
+        return 0.0
+    if op.startswith(("v_exp", "v_readlane", "ds_read", "ds_write", "global_load")):
+        return 2.0
+    if op.startswith("s_cbranch"):
+        return 2.5
+    return 1.0
+
+
+def slot_end(other, vector):
+    """quanta from an MFMA to the next one's earliest issue"""
+    return max(1.0 + other, 2.0 if vector else 0.0) + vector
+
+
+def split_cost(lines):
+    return (sum(quanta16(l) for l in lines if not is_vector(l)), sum(quanta16(l) for l in lines if is_vector(l)))
+
+
+def schedule16(fixed, atoms, cap=4.0):
+    """As schedule(), with the slot model above; fixed[i]: (other, vector) quanta pinned to slot i.  Atoms whose
+    hard limit has come are placed whatever they cost."""
+    n = len(fixed)
+    placed = [[] for _ in range(n)]
+    pending = list(atoms)
+    for i in range(n):
+        other, vector = fixed[i]
+        while True:
+            pick = None
+            for a in sorted((a for a in pending if a.ready_slot() is not None and a.ready_slot() <= i), key=lambda a: a.deadline):
+                o, v = split_cost(a.lines)
+                # what fits no slot takes one that holds nothing else
+                alone = slot_end(o, v) > cap and not placed[i] and not vector
+                if slot_end(other + o, vector + v) <= cap or a.hard <= i or alone:
+                    pick = a
+                    break
+            if pick is None:
+                break
+            o, v = split_cost(pick.lines)
+            pick.slot = i
+            placed[i].append(pick)
+            pending.remove(pick)
+            other, vector = other + o, vector + v
+    assert not pending, [a.lines for a in pending]
+    return placed

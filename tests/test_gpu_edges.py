@@ -91,3 +91,33 @@ def test_publish_tiles(heads, fpb, gh, gw, ids, k_in):
     torch.cuda.synchronize()
     assert torch.equal(q.view(torch.int16), qkv[:, 0].contiguous().view(torch.int16))
     assert torch.equal(one.pool[:pages], two.pool[:pages])
+
+
+# bf16 attention on the 16x16x32 instruction (launches of many workgroups and ten pages or more): every class of ragged
+# last page, blocks that begin inside a step, rows past the last query; two heads checked whole.
+@pytest.mark.parametrize("gh,gw,nc", [(3, 43, 4), (3, 53, 4), (10, 16, 4), (7, 23, 4), (12, 16, 4), (223, 1, 4), (14, 16, 4), (15, 15, 4),
+                                      (15, 17, 5), (16, 16, 4), (1, 40, 14)])
+def test_bf16_many_workgroups(gh, gw, nc):
+    w = W.small_variant(W.CONFIGS["c5_wan1p3b_rollout"], heads=181, grid_h=gh, grid_w=gw, frames_per_block=1, n_cached=nc, n_inflight=1,
+                        sink_blocks=0, window_blocks=16)
+    cached, infl = list(range(nc)), [nc]
+    q, k, v = W.draw_config(w, seed=8)
+    print(f"many workgroups L={w.block_tokens}", flush=True)
+    pool = Hn.gpu_setup(w, k, v, cached, infl)
+    heads = [0, 180]
+    ref, bound = (np.concatenate(x) for x in Hn.oracle_forward_bounded(w, q, k, v, cached, infl, BI, heads=heads))
+    Hn.assert_close(Hn.gpu_forward(w, pool, q, infl, BI)[:, heads], ref, "bf16", f"many workgroups L={w.block_tokens}", bound=bound)
+
+
+# ... and its moving exponent reference: rising, falling, past the fp32 exponent range, from one key to the next.  The bars are
+# those of the same ramps on few workgroups (the bf16 rounding of K moves logits of 25 by 5e-2, of 400 by 0.8).
+@pytest.mark.parametrize("ramp,bar", [((1.0, 24.0), 2e-2), ((24.0, 1.0), 2e-2), ((1.0, 400.0), 8e-2), ((1.0, 400.0, "step"), 8e-2)])
+def test_bf16_many_workgroups_moving_maximum(ramp, bar):
+    w = W.small_variant(W.CONFIGS["c3_wan1p3b_cascade5"], heads=90, grid_h=10, grid_w=13, n_cached=2, n_inflight=1)
+    q, k, v = W.draw_config(w, seed=31, k_ramp=ramp)
+    pool = Hn.gpu_setup(w, k, v, [0, 1], [2])
+    heads = [0, 89]
+    got = Hn.gpu_forward(w, pool, q, [2], BI)
+    ref = np.concatenate(Hn.oracle_forward(w, q, k, v, [0, 1], [2], BI, heads=heads))
+    assert np.isfinite(got).all()
+    Hn.assert_close(got[:, heads], ref, "bf16", f"many workgroups, ramp {ramp}", max_abs=bar * float(np.abs(ref).max()) * 4, rel=bar)
