@@ -350,7 +350,7 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
         [kidx] "v"(kidx), [xl16] "v"(xl16), [xl32] "v"(xl32), [ones] "v"(l15 == 0 ? 0x3f803f80u : 0u),
         [n_pages] "s"(n_pages), [n_kvb] "s"(n_kvb), [kb0] "s"(kb0), [pg0] "s"(pg0),
         [ppb] "s"(a.pages_per_block), [stride] "s"(stride), [last_valid] "s"(a.last_valid),
-        [wave] "s"(wave), [lds0] "s"(lds0)
+        [wave] "s"(wave), [lds0] "s"(lds0), [idle] "s"(uniform(row0 + wave * 64 - rows_end))
       : "memory", "vcc", "scc", "m0", CA_CORE16_CLOBBERS);
   } else {
     const uint32_t xo0 = l31 * 256 + ((hi ^ l15) << 4);    // row offset + swizzled chunk 0 (or 1 for hi)

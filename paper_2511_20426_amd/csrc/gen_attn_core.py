@@ -564,13 +564,15 @@ def generate(core=None):
         E.e(f"v_mov_b32 {V(P_TILE['B'] + r)}, 0")
     E.e("s_waitcnt vmcnt(8) lgkmcnt(0)")
     E.e("s_barrier")
+    done = E.label("DONE")
+    vmcnt = wait_counts(core)
+    if hasattr(core, "emit_idle"):
+        core.emit_idle(E, done, vmcnt)
     core.emit_first_tile(E)
     core.emit_first_reads(E)
 
     # ---- main loop, two pages per trip (ring parity is compile-time)
-    loop, exit_even, exit_odd, done = (E.label("LOOP"), E.label("EXIT_EVEN"), E.label("EXIT_ODD"),
-                                        E.label("DONE"))
-    vmcnt = wait_counts(core)
+    loop, exit_even, exit_odd = E.label("LOOP"), E.label("EXIT_EVEN"), E.label("EXIT_ODD")
     E.e(f"{loop}:")
     for par in range(2):
         for R in range(4):

@@ -378,6 +378,28 @@ def emit_drain(E, par_last):
         E.e(ln)
 
 
+def emit_idle(E, done, vmcnt):
+    """A wave without a single query row (the last tile of a segment has up to three) only takes its part in
+    moving pages: the lines of a step that do so, and the barriers, in a loop of their own.  Its matrix
+    work would cost power that the others can use (half-size 1.3B grid, five blocks: one wave in twenty)."""
+    idle = E.label("IDLE")
+    E.e("s_cmp_ge_i32 %[idle], 0")
+    E.e("s_nop 0")
+    E.e(f"s_cbranch_scc1 {idle}")
+    c = E.cold
+    c.append(f"{idle}:")
+    for par in range(2):
+        for R in range(4):
+            for _, lines in build_step(R, par)[0]:
+                for ln in lines:
+                    if ln.startswith(("global_load", "v_readlane", "s_")) and not ln.startswith(("s_cbranch", "s_or", "s_waitcnt lgkmcnt")):
+                        c.append(ln.replace("@VMCNT_V@", str(vmcnt[0])).replace("@VMCNT_K@", str(vmcnt[1])))
+        c.append(f"s_cmp_eq_u32 s{S_NLEFT}, 0")
+        c.append("s_nop 0")
+        c.append(f"s_cbranch_scc1 {done}")
+    c.append(f"s_branch {idle}")
+
+
 def emit_operand_setup(E):
     E.e(f"v_mov_b32 {V(KIDX)}, %[kidx]")
     E.e(f"v_mov_b32 {V(XL16)}, %[xl16]")
