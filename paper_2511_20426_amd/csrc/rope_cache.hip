@@ -47,7 +47,7 @@ __global__ __launch_bounds__(256) void rope_generic_kernel(RopeGeom g, GenericAr
   const int c8 = lane % chunks;
   const int hs = lane / chunks;
   const bool pad = MODE == 1 && n >= a.valid_tokens;
-  const TokenPos p = token_pos(pad ? 0 : n, a.first_frame, g.grid_h, g.grid_w);
+  const TokenPos p = token_pos_any(pad ? 0 : n, a.first_frame, g.grid_h, g.grid_w);
   float cs[4], sn[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) pair_cs<sizeof(T) == 4>(g, p, c8 * 4 + j, &cs[j], &sn[j]);
@@ -82,6 +82,9 @@ __global__ __launch_bounds__(256) void rope_generic_kernel(RopeGeom g, GenericAr
 // K page: row = token, sixteen 16-byte chunks, chunk c kept at position c ^ (row & 15).
 // V page: row = dim, chunk c = eight tokens in MFMA hand-over order, same swizzle.
 // V goes through LDS to be transposed; rows of 65 dwords keep the column reads conflict-free.
+// What bounds it: memory at size, the length of one workgroup's chain when small.  A head's 16 loads per thread are
+// requested together, a head ahead: with loads issued row by row behind the angles, five 14B blocks took 204.6 us (4.7 TB/s) and
+// a block of 12 heads 19.5; now 196 (4.9) and 15.0.
 constexpr int kPage = 128;
 constexpr int kVRowWords = 65;
 
@@ -126,6 +129,21 @@ __global__ __launch_bounds__(256) void cache_write_bf16_kernel(RopeGeom g, Paged
   const int r0 = t >> 4;             // first row; rows r0, r0+16, ..., r0+112
   const int tok0 = page * kPage;
 
+  // K and V of the first head are on their way while the angles are evaluated, those of the next head while
+  // this one's V is transposed; rows past the block's end re-read its last one and are stored as zeros
+  const int h0 = blockIdx.y * a.heads_per_group;
+  const int h1 = min(h0 + a.heads_per_group, g.heads);
+  U4 kin[8], vin[8];
+  auto request = [&](int h) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int64_t src = int64_t(min(tok0 + r0 + 16 * i, a.block_tokens - 1)) * a.tok_stride + int64_t(h) * a.head_stride + c * 8;
+      kin[i] = load_once(a.k + src);
+      vin[i] = load_once(a.v + src);
+    }
+  };
+  request(h0);
+
   // cos/sin of this thread's 4 pairs at its 8 tokens
   float cs[8][4], sn[8][4];
   if (a.tab.n_f > 0) {
@@ -148,8 +166,6 @@ __global__ __launch_bounds__(256) void cache_write_bf16_kernel(RopeGeom g, Paged
     }
   }
 
-  const int h0 = blockIdx.y * a.heads_per_group;
-  const int h1 = min(h0 + a.heads_per_group, g.heads);
   for (int h = h0; h < h1; ++h) {
     const int64_t pair = (int64_t(a.slot) * a.pages_per_block + page) * g.heads + h;
     uint8_t* kpage = a.pool + pair * (2 * kPage * 128 * 2);
@@ -158,21 +174,20 @@ __global__ __launch_bounds__(256) void cache_write_bf16_kernel(RopeGeom g, Paged
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int r = r0 + 16 * i;
-      const int n = tok0 + r;
-      U4 kk = {0, 0, 0, 0}, vv = {0, 0, 0, 0};
-      if (n < a.block_tokens) {
-        const int64_t src = int64_t(n) * a.tok_stride + int64_t(h) * a.head_stride + c * 8;
-        Vec8<uint16_t> e;
-        e.load(a.k + src);
-        rotate8(e, cs[i], sn[i]);
-        kk.x = pack_bf16(e.v[0], e.v[1]); kk.y = pack_bf16(e.v[2], e.v[3]);
-        kk.z = pack_bf16(e.v[4], e.v[5]); kk.w = pack_bf16(e.v[6], e.v[7]);
-        vv = load_once(a.v + src);
-      }
+      const bool pad = tok0 + r >= a.block_tokens;
+      const U4 raw = kin[i];
+      Vec8<uint16_t> e;
+      e.v[0] = bf16_lo(raw.x); e.v[1] = bf16_hi(raw.x); e.v[2] = bf16_lo(raw.y); e.v[3] = bf16_hi(raw.y);
+      e.v[4] = bf16_lo(raw.z); e.v[5] = bf16_hi(raw.z); e.v[6] = bf16_lo(raw.w); e.v[7] = bf16_hi(raw.w);
+      rotate8(e, cs[i], sn[i]);
+      U4 kk;
+      kk.x = pad ? 0u : pack_bf16(e.v[0], e.v[1]); kk.y = pad ? 0u : pack_bf16(e.v[2], e.v[3]);
+      kk.z = pad ? 0u : pack_bf16(e.v[4], e.v[5]); kk.w = pad ? 0u : pack_bf16(e.v[6], e.v[7]);
       *reinterpret_cast<U4*>(kpage + r * 256 + ((c ^ (r & 15)) << 4)) = kk;
       uint32_t* row = vt + r * kVRowWords + c * 4;
-      row[0] = vv.x; row[1] = vv.y; row[2] = vv.z; row[3] = vv.w;
+      row[0] = pad ? 0u : vin[i].x; row[1] = pad ? 0u : vin[i].y; row[2] = pad ? 0u : vin[i].z; row[3] = pad ? 0u : vin[i].w;
     }
+    if (h + 1 < h1) request(h + 1);
     __syncthreads();
     // ---- V: thread builds chunk c of dim rows r0 + 16 i: tokens 16*(c/2) + perm[8*(c%2) + e]
 #pragma unroll
@@ -290,10 +305,13 @@ int32_t launch_cache_write(const RopeGeom& g, int dtype, int32_t n_blocks, const
     a.pool = static_cast<uint8_t*>(pool);
     a.tok_stride = tok_stride; a.head_stride = head_stride;
     a.block_tokens = block_tokens; a.pages_per_block = pages_per_block;
-    int groups = 1;
-    while (pages_per_block * n_blocks * groups < 1024 && groups < g.heads) groups *= 2;
-    groups = groups > g.heads ? g.heads : groups;
-    a.heads_per_group = (g.heads + groups - 1) / groups;
+    // A CU holds two of these workgroups (250 registers).  Heads are shared out so that one round of 512 takes
+    // all of up to 2048 pages, and twice as many workgroups beyond.  Measured: 1480 pages in 370 workgroups 37.4 us, in 740 43;
+    // 600 in 600 22.1, in 300 23.0; 7400 in 925 or more 196, in 555 217.
+    const int64_t all_pages = int64_t(pages_per_block) * n_blocks * g.heads;
+    const int target = all_pages > 1024 && all_pages <= 2048 ? 512 : 1024;
+    const int64_t per_group = (all_pages + target - 1) / target;
+    a.heads_per_group = int32_t(per_group < g.heads ? per_group : g.heads);
     const dim3 grid((unsigned)pages_per_block,
                     (unsigned)((g.heads + a.heads_per_group - 1) / a.heads_per_group), (unsigned)n_blocks);
     size_t tab_bytes = 0;

@@ -32,14 +32,17 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 
 struct TokenPos { int f, y, x; };
 
-__device__ __forceinline__ TokenPos token_pos(int64_t n, int64_t first_frame, int gh, int gw) {
+// (32-bit division wherever it does: a 64-bit one is some hundred instructions)
+__device__ __forceinline__ TokenPos token_pos(uint32_t n, int64_t first_frame, int gh, int gw) {
+  const uint32_t plane = uint32_t(gh) * uint32_t(gw), f = n / plane, r = n - f * plane, y = r / uint32_t(gw);
+  return TokenPos{int(first_frame + f), int(y), int(r - y * uint32_t(gw))};
+}
+
+__device__ __forceinline__ TokenPos token_pos_any(int64_t n, int64_t first_frame, int gh, int gw) {
+  if (n >> 32 == 0) return token_pos(uint32_t(n), first_frame, gh, gw);
   const int plane = gh * gw;
-  TokenPos p;
-  p.f = int(first_frame + n / plane);
   const int r = int(n % plane);
-  p.y = r / gw;
-  p.x = r % gw;
-  return p;
+  return TokenPos{int(first_frame + n / plane), r / gw, r % gw};
 }
 
 // cos/sin of pair `pair` at a token position.  The angle pos * freq is formed and reduced to
