@@ -23,18 +23,26 @@ namespace {
 // ----------------------------------------------------------------------------- generic path
 // One thread owns 4 consecutive pairs (8 elements) of one token and walks a range of heads; the 64
 // lanes of a wave cover one token: 64/chunks neighbouring heads x all chunks, i.e. up to 1 KB of
-// contiguous memory per load when heads are adjacent in memory.
+// contiguous memory per load when heads are adjacent in memory.  A token has at most 64 pairs: a lane evaluates
+// sin / cos of one and takes its four from the others (small fp32 launches are one such evaluation long, in fp64:
+// 5.3 us with four, 3.4 with one).
 // MODE 0: y[token][head][dim] (rope3d_apply).  MODE 1: K/V pages of the fp32 pool layout
-// (row-major [token][dim] pages), V copied unrotated.
-struct GenericArgs {
+// (row-major [token][dim] pages), V copied unrotated; grid.z picks the block.
+struct GenericBlock {
   const void* x;        // MODE 0: input; MODE 1: K
   const void* v;        // MODE 1: V
+  int64_t first_frame;
+  int32_t slot;         // MODE 1
+};
+
+struct GenericArgs {
+  GenericBlock b[kMaxInflight];
   void* y;              // MODE 0: output; MODE 1: pool
-  int64_t n_tokens, first_frame, tok_stride, head_stride;
+  int64_t n_tokens, tok_stride, head_stride;
   int64_t y_tok_stride, y_head_stride;   // MODE 0: strides of the output
   int32_t heads_per_group;
   // MODE 1 only: n_tokens covers whole pages, tokens >= valid_tokens are stored as zeros
-  int32_t page_tokens, pages_per_block, slot, valid_tokens;
+  int32_t page_tokens, pages_per_block, valid_tokens;
 };
 
 template <typename T, int MODE>
@@ -43,17 +51,25 @@ __global__ __launch_bounds__(256) void rope_generic_kernel(RopeGeom g, GenericAr
   const int head_slots = 64 / chunks;             // heads a wave touches per load
   const int64_t n = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
   if (n >= a.n_tokens) return;
+  const GenericBlock& blk = a.b[MODE == 1 ? blockIdx.z : 0];
   const int lane = threadIdx.x & 63;
   const int c8 = lane % chunks;
   const int hs = lane / chunks;
   const bool pad = MODE == 1 && n >= a.valid_tokens;
-  const TokenPos p = token_pos_any(pad ? 0 : n, a.first_frame, g.grid_h, g.grid_w);
+  const TokenPos p = token_pos_any(pad ? 0 : n, blk.first_frame, g.grid_h, g.grid_w);
   float cs[4], sn[4];
+  {
+    float c1, s1;
+    pair_cs<sizeof(T) == 4>(g, p, lane % (g.head_dim / 2), &c1, &s1);
 #pragma unroll
-  for (int j = 0; j < 4; ++j) pair_cs<sizeof(T) == 4>(g, p, c8 * 4 + j, &cs[j], &sn[j]);
+    for (int j = 0; j < 4; ++j) {
+      cs[j] = __shfl(c1, c8 * 4 + j, 64);
+      sn[j] = __shfl(s1, c8 * 4 + j, 64);
+    }
+  }
   const int h0 = blockIdx.y * a.heads_per_group;
   const int h1 = min(h0 + a.heads_per_group, g.heads);
-  const T* x = static_cast<const T*>(a.x);
+  const T* x = static_cast<const T*>(blk.x);
   for (int h = h0 + hs; h < h1; h += head_slots) {
     const int64_t src = n * a.tok_stride + int64_t(h) * a.head_stride + c8 * 8;
     Vec8<T> e, w;
@@ -68,10 +84,10 @@ __global__ __launch_bounds__(256) void rope_generic_kernel(RopeGeom g, GenericAr
     } else {
       const int64_t page = n / a.page_tokens, row = n % a.page_tokens;
       const int64_t page_elems = int64_t(a.page_tokens) * g.head_dim;
-      const int64_t pair = (int64_t(a.slot) * a.pages_per_block + page) * g.heads + h;
+      const int64_t pair = (int64_t(blk.slot) * a.pages_per_block + page) * g.heads + h;
       T* kdst = static_cast<T*>(a.y) + pair * 2 * page_elems + row * g.head_dim + c8 * 8;
       e.store(kdst);
-      if (!pad) w.load(static_cast<const T*>(a.v) + src);
+      if (!pad) w.load(static_cast<const T*>(blk.v) + src);
       w.store(kdst + page_elems);
     }
   }
@@ -267,8 +283,9 @@ int32_t launch_rope_apply(const RopeGeom& g, int dtype, const void* x, void* y, 
                           int64_t y_tok_stride, int64_t y_head_stride, void* stream) {
   if (n_tokens == 0) return CA_OK;
   GenericArgs a{};
-  a.x = x; a.v = nullptr; a.y = y;
-  a.n_tokens = n_tokens; a.first_frame = first_frame;
+  a.b[0].x = x; a.b[0].first_frame = first_frame;
+  a.y = y;
+  a.n_tokens = n_tokens;
   a.tok_stride = tok_stride; a.head_stride = head_stride;
   a.y_tok_stride = y_tok_stride; a.y_head_stride = y_head_stride;
   const int64_t gx = (n_tokens + 3) / 4;           // one wave per token, four per workgroup
@@ -319,17 +336,20 @@ int32_t launch_cache_write(const RopeGeom& g, int dtype, int32_t n_blocks, const
     a.tab = tab;
     hipLaunchKernelGGL(cache_write_bf16_kernel, grid, dim3(256), tab_bytes, s, g, a);
   } else {
-    for (int i = 0; i < n_blocks; ++i) {           // the fp32 path is for tiny cases: one launch per block
-      GenericArgs a{};
-      a.x = k[i]; a.v = v[i]; a.y = pool;
-      a.n_tokens = int64_t(pages_per_block) * page_tokens; a.first_frame = first_frame[i];
-      a.valid_tokens = block_tokens;
-      a.tok_stride = tok_stride; a.head_stride = head_stride;
-      a.page_tokens = page_tokens; a.pages_per_block = pages_per_block; a.slot = slot[i];
-      a.heads_per_group = g.heads;
-      const dim3 grid((unsigned)((a.n_tokens + 3) / 4), 1);
-      hipLaunchKernelGGL((rope_generic_kernel<float, 1>), grid, dim3(256), 0, s, g, a);
+    GenericArgs a{};
+    for (int i = 0; i < n_blocks; ++i) {
+      a.b[i].x = k[i]; a.b[i].v = v[i];
+      a.b[i].first_frame = first_frame[i];
+      a.b[i].slot = slot[i];
     }
+    a.y = pool;
+    a.n_tokens = int64_t(pages_per_block) * page_tokens;
+    a.valid_tokens = block_tokens;
+    a.tok_stride = tok_stride; a.head_stride = head_stride;
+    a.page_tokens = page_tokens; a.pages_per_block = pages_per_block;
+    a.heads_per_group = g.heads;
+    const dim3 grid((unsigned)((a.n_tokens + 3) / 4), 1, (unsigned)n_blocks);
+    hipLaunchKernelGGL((rope_generic_kernel<float, 1>), grid, dim3(256), 0, s, g, a);
   }
   return finish_launch("rope_cache.hip");
 }
