@@ -15,9 +15,13 @@
 // (2m + c at head_dim 32), so that one 16-byte load per key feeds four tiles.  The next tile's rows are
 // requested before the present one is multiplied.
 //
+// A row's exponent reference stays until a score exceeds it by kSlack: the common tile needs no cross-lane maximum and no
+// rescaling (219 -> 120 vector instructions a tile beside its 64 products).
+//
 // Measured (2 heads x 144 rows x 432 keys, head_dim 64): 318 -> 11 us; (4 heads x 3 blocks of 576 rows,
-// 3..5 KV blocks of 576, head_dim 128): 12.2 ms -> 126 us = 65 TFLOP/s of the 157 the fp32 matrix
-// instruction has; one thread per query row walked every key before.
+// 3..5 KV blocks of 576, head_dim 128): 12.2 ms -> 117 us = 70 TFLOP/s of the 157 the fp32 matrix
+// instruction has; one thread per query row walked every key before.  A CU takes 3200 cycles per round of four tiles
+// with one wave a SIMD as with two (2048 of them products): what bounds it now is the 16 KB a tile fetches from L2.
 //
 // Visibility per block pair follows Sec. 3.1 (a block is bidirectional inside), Sec. 3.3
 // (cached blocks visible to all) and Sec. 3.4 / 4.2 (bidirectional or block-causal cascade).
@@ -55,13 +59,27 @@ struct TilePos {
   size_t page_step, v_off;                     // to the same head's next page; from a K page to its V page
   int row0, page_tokens, valid;                // first key's row in its page; keys of the tile that exist
   float inv_page;                              // 1 / page_tokens
-  // keys past the block's end re-read its last one
+  // keys past the block's end re-read its last one; pages of 16 tokens or more: a tile crosses into one more at most
+  template <bool kTinyPages>
   __device__ __forceinline__ const float* row(int key, int d) const {
     const int r = row0 + min(key, valid - 1);                 // < page_tokens + 16
+    if (!kTinyPages) return page + (r >= page_tokens ? page_step - size_t(page_tokens * d) : 0) + uint32_t(r * d);
     const int pg = int((float(r) + 0.5f) * inv_page);         // r / page_tokens: at most 16, 0.5 / 4096 from an integer
     return page + uint32_t(pg) * page_step + uint32_t((r - pg * page_tokens) * d);
   }
 };
+
+// exp(x) for x <= kSlack + a little, the softmax's range: 2^t with t = x log2 e in two parts, the second one applied to the
+// result to first order.  v_exp_f32 is within an ulp; expf spends its further instructions on the rest of the range.
+__device__ __forceinline__ float softmax_exp(float x) {
+  const float t = x * 1.44269504f;
+  const float e = fmaf(x, 1.44269504f, -t) + x * 1.92596299e-8f;         // log2 e = 1.44269504 + 1.92596299e-8
+  const float r = __builtin_amdgcn_exp2f(t);
+  return x > -126.f ? fmaf(r, e * 0.693147181f, r) : r;                   // far below (or -inf): r is 0 or next to it
+}
+
+// A row's exponent reference moves only when a score exceeds it by more than this: weights up to e^8 cost a 32-bit sum nothing
+constexpr float kSlack = 8.f;
 
 __device__ __forceinline__ TilePos tile_pos(const AttnPlan& p, const float* pool, int h, int kb, int n0, int d) {
   TilePos t;
@@ -76,7 +94,7 @@ __device__ __forceinline__ TilePos tile_pos(const AttnPlan& p, const float* pool
   return t;
 }
 
-template <int D>
+template <int D, bool kTinyPages>
 __global__ __launch_bounds__(64 * kMaxWaves) void attn_f32_kernel(F32Args a) {
   using T = Shape<D>;
   const AttnPlan& p = a.p;
@@ -111,7 +129,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void attn_f32_kernel(F32Args a) {
   f32x4 k[T::kVecs];
   TilePos pos = tile_pos(p, a.pool, h, min(kb, p.n_vis[qb] - 1), in_blk * kTileKeys, D);
   auto load_k = [&]() {
-    const float* kr = pos.row(r, D) + 4 * g;
+    const float* kr = pos.row<kTinyPages>(r, D) + 4 * g;
 #pragma unroll
     for (int j = 0; j < T::kVecs; ++j) k[j] = *reinterpret_cast<const f32x4*>(kr + 16 * j);
   };
@@ -121,7 +139,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void attn_f32_kernel(F32Args a) {
     float v[4][T::kPieces][T::kW];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float* vr = pos.row(4 * g + i, D) + pos.v_off + T::kW * r;
+      const float* vr = pos.row<kTinyPages>(4 * g + i, D) + pos.v_off + T::kW * r;
 #pragma unroll
       for (int c = 0; c < T::kPieces; ++c) {
         if (T::kW == 4) {
@@ -154,19 +172,22 @@ __global__ __launch_bounds__(64 * kMaxWaves) void attn_f32_kernel(F32Args a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) s[i] = 4 * g + i < valid ? (s0[i] + s1[i]) * scale : -INFINITY;
     float tm = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
-    tm = fmaxf(tm, __shfl_xor(tm, 16));
-    tm = fmaxf(tm, __shfl_xor(tm, 32));
-    const float m_new = fmaxf(m, tm);                         // a tile has at least one key: finite
-    const float alpha = expf(m - m_new);                      // 0 on the first tile (m = -inf)
+    if (__builtin_expect(__any(tm > m + kSlack), 0)) {        // always on the first tile (m = -inf)
+      tm = fmaxf(tm, __shfl_xor(tm, 16));
+      tm = fmaxf(tm, __shfl_xor(tm, 32));
+      const float m_new = fmaxf(m, tm);                       // a tile has at least one key: finite
+      const float alpha = expf(m - m_new);                    // 0 on the first tile
+      l *= alpha;
+      m = m_new;
+#pragma unroll
+      for (int c = 0; c < D / 16; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[c][i] *= alpha;
+    }
     float w[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) w[i] = expf(s[i] - m_new);
-    l = l * alpha + ((w[0] + w[1]) + (w[2] + w[3]));
-    m = m_new;
-#pragma unroll
-    for (int c = 0; c < D / 16; ++c)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) o[c][i] *= alpha;
+    for (int i = 0; i < 4; ++i) w[i] = softmax_exp(s[i] - m);
+    l += (w[0] + w[1]) + (w[2] + w[3]);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -219,7 +240,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) void attn_f32_kernel(F32Args a) {
 
 template <int D>
 void enqueue_attn_f32(const F32Args& a, dim3 grid, int waves, hipStream_t s) {
-  hipLaunchKernelGGL(attn_f32_kernel<D>, grid, dim3(unsigned(64 * waves)), 0, s, a);
+  const auto kernel = a.p.page_tokens < kTileKeys ? attn_f32_kernel<D, true> : attn_f32_kernel<D, false>;
+  hipLaunchKernelGGL(kernel, grid, dim3(unsigned(64 * waves)), 0, s, a);
 }
 
 }  // namespace
