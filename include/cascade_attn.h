@@ -43,7 +43,7 @@
  *          is copied to LDS linearly).  K page: row = token, chunk c = dims 8c..8c+7.
  *          V page: row = dim, chunk c = eight tokens: element e of chunk c is token
  *          16*(c/2) + perm[8*(c%2) + e], perm = {0,1,2,3,8,9,10,11,4,5,6,7,12,13,14,15}
- *          (the order in which an MFMA 32x32 accumulator hands P to the next MFMA).
+ *          (the order in which the matrix accumulators hand P to the next MFMA).
  *   Rows/tokens past the end of a block's last page are stored as zeros.
  * For bf16 the pool ends with a fixed scratch area (about 35 MB) that cascade_attn_forward uses
  * for partial results; forwards on one context must therefore not overlap on the GPU.

@@ -618,8 +618,6 @@ template <bool kRopeQ, bool kCore16>
 int32_t enqueue_attn_bf16(const AttnArgs& a, void* stream) {
   const dim3 grid((unsigned)((a.full_items + a.split_items * a.split) * 8));
   const auto kernel = attn_bf16_kernel<kRopeQ, kCore16>;
-  const LdsSlot slot = kRopeQ ? (kCore16 ? kLdsAttnRope16 : kLdsAttnRope) : (kCore16 ? kLdsAttn16 : kLdsAttn);
-  if (const int32_t rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), kAttnLds, slot); rc != CA_OK) return rc;
   hipLaunchKernelGGL(kernel, grid, dim3(256), kAttnLds, static_cast<hipStream_t>(stream), a);
   if (a.split > 1)
     hipLaunchKernelGGL(merge_partials_kernel<kCore16>, dim3((unsigned)(8 * a.split_items), kRowsPerWg / 32), dim3(256), 0,
@@ -629,6 +627,9 @@ int32_t enqueue_attn_bf16(const AttnArgs& a, void* stream) {
 
 template <bool kRopeQ>
 int32_t enqueue_attn_bf16(const AttnArgs& a, bool core16, void* stream) {
+  const KernelLds kernels[] = {{reinterpret_cast<const void*>(attn_bf16_kernel<kRopeQ, false>), kAttnLds},
+                               {reinterpret_cast<const void*>(attn_bf16_kernel<kRopeQ, true>), kAttnLds}};
+  if (const int32_t rc = ensure_dynamic_lds(kernels, 2, kRopeQ ? kLdsAttnRope : kLdsAttn); rc != CA_OK) return rc;
   return core16 ? enqueue_attn_bf16<kRopeQ, true>(a, stream) : enqueue_attn_bf16<kRopeQ, false>(a, stream);
 }
 

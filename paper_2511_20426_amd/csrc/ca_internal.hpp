@@ -130,9 +130,14 @@ int32_t launch_gemm_qkv_publish(const RopeGeom& g, int32_t n_blocks, int32_t blo
 // safe: the cached values are idempotent and written with relaxed atomics).
 constexpr int kMaxDevices = 64;
 int32_t device_cu_count(int* n_cu);                                   // of the current device
-enum LdsSlot { kLdsAttn, kLdsAttnRope, kLdsAttn16, kLdsAttnRope16, kLdsGemm256, kLdsGemm256Publish, kLdsGemm256x128, kLdsGemm256x128Publish, kLdsGemm128,
-               kLdsGemm128Publish, kLdsGemm64, kLdsGemm64Wide, kLdsSlots };
-int32_t ensure_dynamic_lds(const void* kernel, int bytes, LdsSlot slot);
+// A call may take one of several kernels by its size.  All of them get their LDS attribute with the first call of
+// any size, so that one eager call readies every later one for stream capture.
+struct KernelLds {
+  const void* kernel;
+  int bytes;
+};
+enum LdsSlot { kLdsAttn, kLdsAttnRope, kLdsGemm, kLdsGemmPublish, kLdsSlots };
+int32_t ensure_dynamic_lds(const KernelLds* kernels, int n, LdsSlot slot);   // slot: which set of kernels
 int32_t finish_launch(const char* what);   // launchers end with this: CA_OK, or CA_EDEVICE after recording HIP's last error
 int32_t device_failure(const char* what, int hip_error);   // records the text, clears HIP's last error, returns CA_EDEVICE
 const char* last_device_error();

@@ -247,6 +247,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(GemmArgs a) {
 // waves and six stages.
 template <int BM, int BN, int kWavesM, int kWavesN, int kStages>
 struct TileShape {
+  static constexpr int kBm = BM, kBn = BN, kWavesAlongM = kWavesM, kRing = kStages;
   static constexpr int kWaves = kWavesM * kWavesN, kThreads = 64 * kWaves;
   static constexpr int kTm = BM / kWavesM / 16, kTn = BN / kWavesN / 16;   // 16 x 16 tiles of a wave
   static constexpr int kStageBytes = (BM + BN) * 128;
@@ -257,9 +258,14 @@ struct TileShape {
   static_assert(kLoadsW * 8 * kWaves == BN && kLoadsX * 8 * kWaves == BM && kLds <= kGemmLds, "shape");
 };
 
-template <int BM, int BN, int kWavesM, int kWavesN, int kStages, bool kPublish>
-__global__ __launch_bounds__(64 * kWavesM * kWavesN) void gemm_tile_kernel(GemmArgs a) {
-  using T = TileShape<BM, BN, kWavesM, kWavesN, kStages>;
+using Tile256x128 = TileShape<256, 128, 4, 2, 3>;
+using Tile128 = TileShape<128, 128, 2, 4, 4>;
+using Tile64 = TileShape<64, 64, 2, 2, 4>;
+using Tile64Wide = TileShape<64, 64, 2, 4, 6>;
+
+template <typename T, bool kPublish>
+__global__ __launch_bounds__(T::kThreads) void gemm_tile_kernel(GemmArgs a) {
+  constexpr int BM = T::kBm, BN = T::kBn, kWavesM = T::kWavesAlongM, kStages = T::kRing;
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l15 = lane & 15, grp = lane >> 4;
@@ -404,25 +410,19 @@ int32_t enqueue_gemm(GemmArgs& a, void* stream) {
   a.sb_cols = (a.tiles_n + kSbCols - 1) / kSbCols;
   a.n_sb = ((a.tiles_m + kSbRows - 1) / kSbRows) * a.sb_cols;
   const unsigned rounds = unsigned((a.n_sb + 7) / 8);
-  if (const int32_t rc = ensure_dynamic_lds(reinterpret_cast<const void*>(gemm_bf16_kernel<kPublish>), kGemmLds,
-                                            kPublish ? kLdsGemm256Publish : kLdsGemm256);
-      rc != CA_OK)
-    return rc;
   hipLaunchKernelGGL(gemm_bf16_kernel<kPublish>, dim3(rounds * 8 * 32), dim3(256), kGemmLds,
                      static_cast<hipStream_t>(stream), a);
   return finish_launch("gemm_bf16.hip");
 }
 
-template <int BM, int BN, int kWavesM, int kWavesN, int kStages, bool kPublish>
-int32_t enqueue_gemm_tiles(GemmArgs& a, LdsSlot slot, void* stream) {
-  using T = TileShape<BM, BN, kWavesM, kWavesN, kStages>;
+template <typename T, bool kPublish>
+int32_t enqueue_gemm_tiles(GemmArgs& a, void* stream) {
+  constexpr int BM = T::kBm, BN = T::kBn;
   a.tiles_per_block = (a.block_rows + BM - 1) / BM;
   a.tiles_m = (a.M / a.block_rows) * a.tiles_per_block;
   a.tiles_n = (a.N + BN - 1) / BN;
   a.n_sb = (a.tiles_m * a.tiles_n + 7) / 8;                  // tiles of an XCD
-  const auto kernel = gemm_tile_kernel<BM, BN, kWavesM, kWavesN, kStages, kPublish>;
-  if (const int32_t rc = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), T::kLds, slot); rc != CA_OK) return rc;
-  hipLaunchKernelGGL(kernel, dim3(unsigned(a.n_sb) * 8), dim3(T::kThreads), T::kLds, static_cast<hipStream_t>(stream), a);
+  hipLaunchKernelGGL((gemm_tile_kernel<T, kPublish>), dim3(unsigned(a.n_sb) * 8), dim3(T::kThreads), T::kLds, static_cast<hipStream_t>(stream), a);
   return finish_launch("gemm_bf16.hip");
 }
 
@@ -463,13 +463,18 @@ template <bool kPublish>
 int32_t dispatch_gemm(GemmArgs& a, void* stream) {
   GemmTile tile = kTile256;
   if (const int32_t rc = pick_gemm_tile(a, kPublish, &tile); rc != CA_OK) return rc;
+  const KernelLds kernels[] = {{reinterpret_cast<const void*>(gemm_bf16_kernel<kPublish>), kGemmLds},
+                               {reinterpret_cast<const void*>(gemm_tile_kernel<Tile256x128, kPublish>), Tile256x128::kLds},
+                               {reinterpret_cast<const void*>(gemm_tile_kernel<Tile128, kPublish>), Tile128::kLds},
+                               {reinterpret_cast<const void*>(gemm_tile_kernel<Tile64, false>), Tile64::kLds},
+                               {reinterpret_cast<const void*>(gemm_tile_kernel<Tile64Wide, false>), Tile64Wide::kLds}};
+  if (const int32_t rc = ensure_dynamic_lds(kernels, kPublish ? 3 : 5, kPublish ? kLdsGemmPublish : kLdsGemm); rc != CA_OK) return rc;
   if constexpr (!kPublish) {
-    if (tile == kTile64) return enqueue_gemm_tiles<64, 64, 2, 2, 4, false>(a, kLdsGemm64, stream);
-    if (tile == kTile64Wide) return enqueue_gemm_tiles<64, 64, 2, 4, 6, false>(a, kLdsGemm64Wide, stream);
+    if (tile == kTile64) return enqueue_gemm_tiles<Tile64, false>(a, stream);
+    if (tile == kTile64Wide) return enqueue_gemm_tiles<Tile64Wide, false>(a, stream);
   }
-  if (tile == kTile128) return enqueue_gemm_tiles<128, 128, 2, 4, 4, kPublish>(a, kPublish ? kLdsGemm128Publish : kLdsGemm128, stream);
-  if (tile == kTile256x128)
-    return enqueue_gemm_tiles<256, 128, 4, 2, 3, kPublish>(a, kPublish ? kLdsGemm256x128Publish : kLdsGemm256x128, stream);
+  if (tile == kTile128) return enqueue_gemm_tiles<Tile128, kPublish>(a, stream);
+  if (tile == kTile256x128) return enqueue_gemm_tiles<Tile256x128, kPublish>(a, stream);
   return enqueue_gemm<kPublish>(a, stream);
 }
 

@@ -267,14 +267,15 @@ int32_t device_cu_count(int* n_cu) {
   return CA_OK;
 }
 
-int32_t ensure_dynamic_lds(const void* kernel, int bytes, LdsSlot slot) {
+int32_t ensure_dynamic_lds(const KernelLds* kernels, int n, LdsSlot slot) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return finish_launch("hipGetDevice");
   const bool cached = dev >= 0 && dev < kMaxDevices;
-  if (cached && g_lds_set[slot][dev].load(std::memory_order_relaxed) == bytes) return CA_OK;
-  if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess)
-    return finish_launch("hipFuncSetAttribute");
-  if (cached) g_lds_set[slot][dev].store(bytes, std::memory_order_relaxed);
+  if (cached && g_lds_set[slot][dev].load(std::memory_order_relaxed)) return CA_OK;
+  for (int i = 0; i < n; ++i)
+    if (hipFuncSetAttribute(kernels[i].kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kernels[i].bytes) != hipSuccess)
+      return finish_launch("hipFuncSetAttribute");
+  if (cached) g_lds_set[slot][dev].store(1, std::memory_order_relaxed);
   return CA_OK;
 }
 

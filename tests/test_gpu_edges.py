@@ -121,3 +121,44 @@ def test_bf16_many_workgroups_moving_maximum(ramp, bar):
     ref = np.concatenate(Hn.oracle_forward(w, q, k, v, [0, 1], [2], BI, heads=heads))
     assert np.isfinite(got).all()
     Hn.assert_close(got[:, heads], ref, "bf16", f"many workgroups, ramp {ramp}", max_abs=bar * float(np.abs(ref).max()) * 4, rel=bar)
+
+
+# One eager call of any size readies the others for capture: products of several tiles and a forward of each loop recorded
+# after small eager calls, replayed three times on new inputs.
+def test_capture_of_other_sizes_than_the_eager_call():
+    import torch
+    from paper_2511_20426_amd.runner import CascadePool, linear
+    gen = torch.Generator(device="cuda:0").manual_seed(3)
+
+    def draw(*shape):
+        return (torch.randn(shape, generator=gen, device="cuda:0") * 0.3).to(torch.bfloat16)
+
+    linear(draw(8, 128), draw(8, 128))
+    xs = [(draw(m, k), draw(n, k), torch.empty((m, n), dtype=torch.bfloat16, device="cuda:0"))
+          for m, n, k in ((1100, 1400, 256), (1300, 4104, 128), (4100, 4104, 128))]
+    small, large = (CascadePool.for_workload(W.small_variant(W.CONFIGS["c3_wan1p3b_cascade5"], heads=h, grid_h=10, grid_w=13, n_cached=2,
+                                                             n_inflight=1)) for h in (2, 90))
+    for p in (small, large):
+        for g in range(3):
+            p.append(g, 0, 0, draw(390, p.heads, 128), draw(390, p.heads, 128))
+            if g < 2:
+                p.ctx.kv_cache_promote(g)
+    small.forward_rope(draw(390, 2, 128), [2], BI)
+    q, o = draw(390, 90, 128), torch.empty((390, 90, 128), dtype=torch.bfloat16, device="cuda:0")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for x, w, y in xs:
+            linear(x, w, out=y)
+        large.forward_rope(q, [2], BI, out=o)
+    for _ in range(3):
+        for x, _w, y in xs:
+            x.copy_(draw(*x.shape))
+            y.zero_()
+        q.copy_(draw(*q.shape))
+        o.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        for x, w, y in xs:
+            assert torch.equal(linear(x, w), y)
+        assert torch.equal(large.forward_rope(q, [2], BI), o)
