@@ -227,7 +227,7 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const uint32_t m0 = lds0 + wave * 1024 + (i & 7) * 4096 + (i >> 3) * kVRing;
-      asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                    :: "s"(m0), "v"(lane_off + (i & 7) * 4096), "s"(k0 + (i >> 3) * uint64_t(kPageBytes)) : "memory", "m0");
     }
   }

@@ -302,11 +302,11 @@ __global__ __launch_bounds__(T::kThreads) void gemm_tile_kernel(GemmArgs a) {
   auto issue = [&]() {
 #pragma unroll
     for (int i = 0; i < T::kLoadsW; ++i)
-      asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                    :: "s"(fill + (wave * T::kLoadsW + i) * 1024), "v"(offw[i]), "s"(base_w) : "memory", "m0");
 #pragma unroll
     for (int i = 0; i < T::kLoadsX; ++i)
-      asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                    :: "s"(fill + BN * 128 + (wave * T::kLoadsX + i) * 1024), "v"(offx[i]), "s"(base_x) : "memory", "m0");
     // past the last stage the loads repeat it, into slots nothing reads any more: the wait counts stay exact
     ++issued;

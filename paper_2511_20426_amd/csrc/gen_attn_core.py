@@ -185,15 +185,28 @@ def v_address_lines():
 
 def page_load_lines(i, lds_slot_off, which):
     """Load number i (0..7) of a page: 64 lanes x 16 B -> 1 KB of LDS at slot + 4096 i + 1024 wave
-    (M0 carries the LDS address, the VGPR the byte offset in the page)."""
+    (M0 carries the LDS address, the VGPR the byte offset in the page).  The two may not follow each other
+    directly: a load to LDS takes M0 one wait state after a scalar instruction wrote it."""
     a = S_ADDRV if which else S_ADDR
     return [f"s_add_u32 m0, s{S_M0B}, {lds_slot_off + 4096 * i}",
             f"global_load_lds_dwordx4 {V(DMAOFF + i)}, s[{a}:{a + 1}]"]
 
 
+def page_load_atoms(loads, ready, hard):
+    """loads: (page_load_lines, slot due by) of a step in issue order.  M0 is written in an earlier slot than its load, so that an
+    MFMA stands between, and behind the load before."""
+    atoms, prev = [], None
+    for (m0, load), due in loads:
+        at = Atom([m0], max(ready - 1, 0), due - 1, [prev] if prev else [], 0, hard=hard - 1)
+        prev = Atom([load], ready, due, [at], 1, tag="load", hard=hard)
+        atoms += [at, prev]
+    return atoms
+
+
 def emit_issue_page(E, which, lds_slot_off):
     for i in range(8):
-        for ln in page_load_lines(i, lds_slot_off, which):
+        m0, load = page_load_lines(i, lds_slot_off, which)
+        for ln in (m0, "s_nop 0", load):
             E.e(ln)
 
 
@@ -321,29 +334,24 @@ def build_step(R, par):
     tail[31].insert(0, f"{back}:")
     tail[31].insert(0, f"s_cbranch_scc1 {cold}")
     # page traffic
-    loads = []
     if R == 0:                                             # address of V(q+1), then of K(q+2)
         prev = None
         for k, grp in enumerate(v_address_lines() + page_advance_lines()):
             prev = Atom(grp, 2, 6 + 3 * k, [prev] if prev else [], 0, hard=29)
             atoms.append(prev)
     if R == 1:                                             # V(q+1) into the slot V(q-1) left
-        for i in range(8):
-            loads.append(Atom(page_load_lines(i, VRING + (1 - par) * PAGE, 1), 0, 2 + 4 * i, tag=("load", 1), hard=29))
+        atoms += page_load_atoms([(page_load_lines(i, VRING + (1 - par) * PAGE, 1), 2 + (i * 26) // 8) for i in range(8)], 0, 29)
     if R == 2:                                             # K(q+2) into the slot K(q) left
-        for i in range(N_KLOADS_R2):
-            loads.append(Atom(page_load_lines(i, par * PAGE, 0), K_BARRIER_SLOT,
-                              K_BARRIER_SLOT + 2 + (i * (26 - K_BARRIER_SLOT)) // N_KLOADS_R2, tag=("load", 0), hard=29))
+        atoms += page_load_atoms([(page_load_lines(i, par * PAGE, 0), K_BARRIER_SLOT + 2 + (i * (26 - K_BARRIER_SLOT)) // N_KLOADS_R2)
+                                  for i in range(N_KLOADS_R2)], K_BARRIER_SLOT, 29)
     if R == 3:
         n = 8 - N_KLOADS_R2
-        for i in range(n):
-            loads.append(Atom(page_load_lines(N_KLOADS_R2 + i, par * PAGE, 0), 0, 2 + (i * 28) // n, tag=("load", 0), hard=29))
+        atoms += page_load_atoms([(page_load_lines(N_KLOADS_R2 + i, par * PAGE, 0), 2 + (i * 26) // n) for i in range(n)], 0, 29)
         # page-in-block counters of pages q and q+1 move on; one page less to go
         pe = Atom([f"s_mov_b32 s{S_PGCUR}, s{S_PGNEXT}", f"s_add_u32 s{S_T}, s{S_PGNEXT}, 1",
                    f"s_cmp_eq_u32 s{S_T}, s{S_P}", f"s_cselect_b32 s{S_PGNEXT}, 0, s{S_T}",
                    f"s_sub_u32 s{S_NLEFT}, s{S_NLEFT}, 1"], 0, 20, [rag], 1, hard=29)
         atoms.append(pe)
-    atoms += loads
 
     fixed = [2.0 + sum(quanta(l) for l in head[i] + tail[i]) for i in range(32)]
     placed = schedule(fixed, atoms, CAP)
@@ -438,7 +446,7 @@ def wait_counts(core=None):
         slots, _ = core.build_step(R, 0)
         for i, (_, lines) in enumerate(slots):
             for ln in lines:
-                if ln.startswith("s_add_u32 m0"):
+                if ln.startswith("global_load_lds"):
                     order.append((R, i, 1 if R == 1 else 0))
     assert len(order) == 16, order
     def after_last(stream, until):

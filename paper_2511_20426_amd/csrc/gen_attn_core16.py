@@ -58,7 +58,7 @@ import sys
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 import gen_attn_core as base  # noqa: E402
 from gen_attn_core import (A, FR, P_TILE, PAGE, S_LDS0, S_NLEFT, S_P, S_PGCUR, S_PGNEXT, S_PM1, S_RG, S_T, S_TILE,  # noqa: E402
-                           S_VLAST, S_VLP, V, VRING, Emitter, page_advance_lines, page_load_lines, v_address_lines)
+                           S_VLAST, S_VLP, V, VRING, Emitter, page_advance_lines, page_load_atoms, page_load_lines, v_address_lines)
 from issue_sched import Atom, is_vector, schedule16, split_cost  # noqa: E402
 
 QT = 4               # query tiles of 16 per wave
@@ -273,29 +273,24 @@ def build_step(R, par):
     tail[SLOTS - 1].insert(0, f"{back}:")
     tail[SLOTS - 1].insert(0, f"s_cbranch_scc1 {cold}")
     # page traffic
-    loads = []
     if R == 0:                                             # address of V(q+1), then of K(q+2)
         prev = None
         for k, grp in enumerate(v_address_lines() + page_advance_lines()):
             prev = Atom(grp, 4, 12 + 6 * k, [prev] if prev else [], 1, hard=59)
             atoms.append(prev)
     if R == 1:                                             # V(q+1) into the slot V(q-1) left
-        for i in range(8):
-            loads.append(Atom(page_load_lines(i, VRING + (1 - par) * PAGE, 1), 0, 3 + 7 * i, tag=("load", 1), hard=59))
+        atoms += page_load_atoms([(page_load_lines(i, VRING + (1 - par) * PAGE, 1), 3 + 7 * i) for i in range(8)], 0, 59)
     if R == 2:                                             # K(q+2) into the slot K(q) left
-        for i in range(N_KLOADS_R2):
-            loads.append(Atom(page_load_lines(i, par * PAGE, 0), K_BARRIER_SLOT,
-                              K_BARRIER_SLOT + 4 + (i * (54 - K_BARRIER_SLOT)) // N_KLOADS_R2, tag=("load", 0), hard=59))
+        atoms += page_load_atoms([(page_load_lines(i, par * PAGE, 0), K_BARRIER_SLOT + 4 + (i * (54 - K_BARRIER_SLOT)) // N_KLOADS_R2)
+                                  for i in range(N_KLOADS_R2)], K_BARRIER_SLOT, 59)
     if R == 3:
         n = 8 - N_KLOADS_R2
-        for i in range(n):
-            loads.append(Atom(page_load_lines(N_KLOADS_R2 + i, par * PAGE, 0), 0, 4 + (i * 56) // n, tag=("load", 0), hard=59))
+        atoms += page_load_atoms([(page_load_lines(N_KLOADS_R2 + i, par * PAGE, 0), 4 + (i * 56) // n) for i in range(n)], 0, 59)
         # page-in-block counters of pages q and q+1 move on; one page less to go
         pe = Atom([f"s_mov_b32 s{S_PGCUR}, s{S_PGNEXT}", f"s_add_u32 s{S_T}, s{S_PGNEXT}, 1",
                    f"s_cmp_eq_u32 s{S_T}, s{S_P}", f"s_cselect_b32 s{S_PGNEXT}, 0, s{S_T}",
                    f"s_sub_u32 s{S_NLEFT}, s{S_NLEFT}, 1"], 0, 40, [rag], 1, hard=59)
         atoms.append(pe)
-    atoms += loads
 
     fixed = [split_cost(head[i] + tail[i]) for i in range(SLOTS)]
     placed = schedule16(fixed, atoms, CAP)
@@ -393,6 +388,8 @@ def emit_idle(E, done, vmcnt):
             for _, lines in build_step(R, par)[0]:
                 for ln in lines:
                     if ln.startswith(("global_load", "v_readlane", "s_")) and not ln.startswith(("s_cbranch", "s_or", "s_waitcnt lgkmcnt")):
+                        if ln.startswith("global_load") and " m0," in c[-1]:
+                            c.append("s_nop 0")           # (what stands between in a working wave is left out here)
                         c.append(ln.replace("@VMCNT_V@", str(vmcnt[0])).replace("@VMCNT_K@", str(vmcnt[1])))
         c.append(f"s_cmp_eq_u32 s{S_NLEFT}, 0")
         c.append("s_nop 0")

@@ -82,7 +82,8 @@ def read_frag(b, op, t, stage, kk):
 
 def load_lines(op, stage, i):
     """Load i (0..7) of this wave's share of a stage of W (op 0) or X (op 1): 8 rows x 128 bytes
-    -> 1 KB of LDS."""
+    -> 1 KB of LDS.  The two lines may not follow each other directly: a load to LDS takes M0 one wait state
+    after a scalar instruction wrote it."""
     ring = (stage % NW) * PART if op == 0 else XBASE + (stage % NX) * PART
     base, off = (S_BW, OFFW) if op == 0 else (S_BX, OFFX)
     return [f"s_add_u32 m0, s{S_M0B}, {ring + 1024 * i}",
@@ -127,15 +128,14 @@ def build_stage(P):
     for grp in advance_lines(S_BX, S_XISS) + advance_lines(S_BW, S_ISS):
         prev = Atom(grp, half, half, [prev] if prev else [], 0, hard=half + 6)
         atoms.append(prev)
+    # (M0 is written in an earlier slot than its load, so that an MFMA stands between, and behind the load before)
     last = prev
-    for i in range(8):
-        at = half + 4 + (i * X_BY) // 8
-        last = Atom(load_lines(1, P + 2, i), at, at, [last], 0, hard=half + X_BY + 6)
-        atoms.append(last)
-    for i in range(8):
-        at = half + 6 + 7 * i
-        last = Atom(load_lines(0, P + 3, i), at, at, [last] if i == 0 else [prev], 0, hard=SLOTS - 3)
-        atoms.append(last)
+    for op, stage, i, at, hard in ([(1, P + 2, i, half + 4 + (i * X_BY) // 8, half + X_BY + 6) for i in range(8)] +
+                                   [(0, P + 3, i, half + 6 + 7 * i, SLOTS - 3) for i in range(8)]):
+        m0, load = load_lines(op, stage, i)
+        write = Atom([m0], at - 1, at - 1, [last], 0, hard=hard - 1)
+        last = Atom([load], at, at, [write], 1, hard=hard)
+        atoms += [write, last]
     fixed = [2.0 + sum(quanta(l) for l in tail[i]) for i in range(SLOTS)]
     placed = schedule(fixed, atoms, CAP)
     out = []
@@ -183,13 +183,15 @@ def generate():
             for grp in advance_lines(S_BW, S_ISS):
                 L.extend(grp)
         for i in range(8):
-            L.extend(load_lines(0, st, i))
+            m0, load = load_lines(0, st, i)
+            L.extend([m0, "s_nop 0", load])
     for st in range(NX):
         if st:
             for grp in advance_lines(S_BX, S_XISS):
                 L.extend(grp)
         for i in range(8):
-            L.extend(load_lines(1, st, i))
+            m0, load = load_lines(1, st, i)
+            L.extend([m0, "s_nop 0", load])
     e("s_waitcnt vmcnt(0)")
     e("s_barrier")
     for op, t in READ_ORDER:

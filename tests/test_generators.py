@@ -5,6 +5,7 @@ run here; the GPU parity tests cover what the code computes."""
 import importlib.util
 import os
 import re
+import sys
 
 import numpy as np
 import pytest
@@ -15,16 +16,47 @@ CSRC = os.path.join(ROOT, "paper_2511_20426_amd", "csrc")
 
 def _load(name):
     spec = importlib.util.spec_from_file_location(name, os.path.join(CSRC, name + ".py"))
-    mod = importlib.util.module_from_spec(spec)
+    mod = sys.modules[name] = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(mod)
     return mod
 
 
 sched = _load("issue_sched")
 attn = _load("gen_attn_core")
+attn16 = _load("gen_attn_core16")
 gemm = _load("gen_gemm_core")
 
 SCC_WRITERS = ("s_add", "s_sub", "s_cmp", "s_and", "s_or", "s_mul", "s_lsh", "s_min", "s_max")
+
+
+def _m0_writes(text):
+    """Lines that write M0, by place, after checking that writes and loads to LDS alternate and that a load never follows its
+    write directly: it takes M0 one wait state after a scalar instruction wrote it."""
+    writes, open_write = {}, None
+    for k, ln in enumerate(text):
+        if " m0," in ln:
+            assert open_write is None, (k, ln)
+            writes[k] = ln
+            open_write = k
+        elif ln.startswith("global_load_lds"):
+            assert open_write is not None and k >= open_write + 2, (k, ln)
+            open_write = None
+    assert open_write is None
+    return writes
+
+
+def test_loads_to_lds_keep_their_distance_from_the_m0_write():
+    for gen, n in ((attn, 8 + 2 * 16), (attn16, 8 + 2 * 2 * 16), (gemm, 40 + 16 * gemm.PERIOD)):
+        assert len(_m0_writes([p for ln in gen.generate() for p in ln.split("\n")])) == n
+    # the inline assembly of the kernels around the loops
+    found = 0
+    for name in sorted(os.listdir(CSRC)):
+        if name.endswith((".hip", ".hpp")):
+            with open(os.path.join(CSRC, name)) as f:
+                for body in re.findall(r'asm volatile\("((?:[^"\\]|\\.)*)"', f.read()):
+                    lines = [x.strip() for x in body.replace("\\t", "").split("\\n")]
+                    found += len(_m0_writes(lines))
+    assert found == 3
 
 
 def test_scheduler_respects_ready_order_gaps_and_hard_deadlines():
@@ -106,10 +138,7 @@ def test_attention_step_invariants():
                 while text[back].split()[0] in ("s_cselect_b32", "s_cselect_b64"):
                     back -= 1
                 assert text[back].split()[0].startswith(("s_cmp", "s_add_u32", "s_addc_u32")), (R, text[back], ln)
-        # every M0 write is directly followed by its load
-        for k, ln in enumerate(text):
-            if ln.startswith("s_add_u32 m0"):
-                assert text[k + 1].startswith("global_load_lds_dwordx4")
+        assert _m0_writes(text) == {k: text[k] for k, ln in enumerate(text) if ln.startswith("s_add_u32 m0")}
 
 
 def test_attention_page_traffic_bookkeeping():
@@ -164,12 +193,13 @@ def test_gemm_stage_invariants():
         assert len(reads) == 32 and len(loads) == 16
         assert sum(1 for ln in text if ln == "s_barrier") == 1
         k_bar = text.index("s_barrier")
-        # all loads sit behind the barrier that frees their buffers; every M0 write is directly
-        # followed by its load; W goes to ring slot (P+3) % 3, X to ring slot (P+2) % 2
+        # all loads sit behind the barrier that frees their buffers, each with an M0 write of its own;
+        # W goes to ring slot (P+3) % 3, X to ring slot (P+2) % 2
         assert min(loads) > k_bar
+        writes = _m0_writes(text)
         for k in loads:
-            m0 = re.match(r"s_add_u32 m0, s\d+, (\d+)$", text[k - 1])
-            assert m0, text[k - 1]
+            m0 = re.match(r"s_add_u32 m0, s\d+, (\d+)$", writes[max(w for w in writes if w < k)])
+            assert m0
             off = int(m0.group(1))
             if f"s[{gemm.S_BX}:" in text[k]:
                 assert gemm.XBASE + ((P + 2) % gemm.NX) * gemm.PART <= off < gemm.XBASE + ((P + 2) % gemm.NX + 1) * gemm.PART
