@@ -20,9 +20,9 @@
 //   Softmax is the running-reference form in base 2: p = exp2(s*c - m_ref), c = log2(e)/sqrt(D);
 //   m_ref moves (and the accumulators are rescaled) only when the probabilities of a step grow past a limit.
 //   The loop exists on two matrix instructions, picked per launch by takes_core16: 32x32x16 (two column tiles
-//   of 32 queries, row sums by the VALU; fewer cycles) and 16x16x32 (four tiles of 16, row sums by the matrix pipe; less
-//   power).  Errors against fp64 over seven shapes and logit scales: 2.4066e-3 .. 5.3026e-3 with the first,
-//   2.4058e-3 .. 5.2881e-3 with the second.
+//   of 32 queries; fewer cycles) and 16x16x32 (four tiles of 16; less power).  Row sums are taken in fp32 over the probabilities
+//   before their rounding to bf16 in both.  Errors against fp64 over seven shapes and logit scales, flat rows and peaked ones: 2.4066e-3 ..
+//   5.3026e-3 with either; rows with one key of weight 0.9 whose V is zero: 1.5e-4 off as a whole, with either.
 //   The 256-byte page rows are stored with their 16-byte chunks XOR-swizzled by (row & 15),
 //   which makes every ds_read_b128 of an MFMA operand bank-conflict free (K with 16x16x32: two lanes to a bank).
 //   Workgroups are numbered so that the eight XCDs each take a contiguous range of
@@ -347,7 +347,7 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
         "=&{v150}"(l2), "=&{v151}"(l3), "=&{v184}"(negm0), "=&{v188}"(negm1), "=&{v192}"(negm2), "=&{v196}"(negm3)
       : "{a[128:143]}"(qt[0]), "{a[144:159]}"(qt[1]), "{a[160:175]}"(qt[2]), "{a[176:191]}"(qt[3]),
         [xk0] "v"(xk0), [xv0] "v"(xv0), [lane_off] "v"(lane_off), [tbl_lo] "v"(tbl_lo), [tbl_hi] "v"(tbl_hi),
-        [kidx] "v"(kidx), [xl16] "v"(xl16), [xl32] "v"(xl32), [ones] "v"(l15 == 0 ? 0x3f803f80u : 0u),
+        [kidx] "v"(kidx), [xl16] "v"(xl16), [xl32] "v"(xl32),
         [n_pages] "s"(n_pages), [n_kvb] "s"(n_kvb), [kb0] "s"(kb0), [pg0] "s"(pg0),
         [ppb] "s"(a.pages_per_block), [stride] "s"(stride), [last_valid] "s"(a.last_valid),
         [wave] "s"(wave), [lds0] "s"(lds0), [idle] "s"(uniform(row0 + wave * 64 - rows_end))
@@ -377,10 +377,13 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
   const f32x16 oacc[8] = {o0, o1, o2, o3, o4, o5, o6, o7};
   const float negm[4] = {negm0, negm1, negm2, negm3};
   float l_tot[4];                     // row sums per tile
-  if constexpr (kCore16) {            // lane l15 has that of query l15
+  if constexpr (kCore16) {            // four lanes share a query
     const float l[4] = {l0, l1, l2, l3};
 #pragma unroll
-    for (int t = 0; t < 4; ++t) l_tot[t] = __shfl(l[t], l15, 64);
+    for (int t = 0; t < 4; ++t) {
+      const float half = l[t] + __shfl_xor(l[t], 16, 64);
+      l_tot[t] = half + other_half(half);
+    }
   } else {
     const float a0 = l0 + l1, a1 = l2 + l3;
     l_tot[0] = a0 + other_half(a0);

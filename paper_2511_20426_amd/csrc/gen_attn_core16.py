@@ -5,17 +5,16 @@ fill the chip.  Walk, page traffic, barriers and scalar registers are that gener
 Why 16x16x32 and not 32x32x16: a launch that fills the chip is limited by power, and per flop the smaller
 shape moves half as many accumulator registers.  An MFMA-only loop over random operands reaches 1943 TFLOP/s with
 it against 1715 with 32x32x16 in one session, 2060 if four consecutive MFMAs share their accumulator (as QK does below).  The
-price is issue room (64 MFMAs a step for 32): row sums are therefore taken by the matrix pipe as well, and a slot is dealt out
-by its own model (schedule16; with the other one's the loop took 1190 cycles a step).  Cycles a step
-1062 -> 1135 at the highest clock, but 1.84 GHz for 1.62 where power decides: 14B step of five blocks 16.45 ->
-15.33 ms, 1.3B one block 688 -> 636 us, one device's share 2.91 -> 2.77 ms.
+price is issue room (64 MFMAs a step for 32): a slot is dealt out by its own model (schedule16), and by it a step takes 1096
+cycles, 1024 of them of the matrix pipe: what is left over is vector work that finds no room.  14B step of five blocks 16.45 ->
+15.6 ms, 1.3B one block 688 -> 643 us, one device's share 2.91 -> 2.8 ms.  (Row sums taken by the matrix pipe, ones x P, would
+be 1 % faster, but of probabilities already rounded to bf16: a row with one heavy key was then off by up to 2.5e-3 as a whole.)
 
 Pipeline (a "step" is 32 keys, a page is 4 steps; t counts steps):
     QK(t+1): 32 MFMAs  S_next = K_frag x Q                      (K fragments from LDS)
-    SM(t)  : p = exp2(S_cur), bf16 pack                          (VALU; S_cur already holds
+    SM(t)  : p = exp2(S_cur), bf16 pack, row sums                (VALU; S_cur already holds
              s*c - m_ref: Q is pre-scaled by c = log2(e)/sqrt(D) and QK starts from -m_ref)
     PV(t-1): 32 MFMAs  O^T   += V_frag x P_prev                  (V fragments from LDS)
-             4 MFMAs   l     += ones x P_prev                    (the row sums, fp32, of the weights PV uses)
 
 Keys in the accumulators.  A 16x16 accumulator tile gives lane group g (of 16 lanes) its rows 4g..4g+3.  A 32-key
 step has two such tiles; their 16 rows are keys 0..7 and 16..23 (second tile: 8..15 and 24..31), so that what a
@@ -23,9 +22,9 @@ lane group holds in both, keys 16 (g/2) + 4 (g%2) + {0..3, 8..11}, is one 16-byt
 to operand without movement.  The K rows a read touches then meet in pairs in an LDS bank; LDS has the room
 (31 % busy).
 
-The exponent reference m_ref of a row is lazy: it starts 15 above the maximum of the row's first tile (log2 units: P is
-floating point, so the offset costs nothing) and moves only when it has to.  No maximum is taken in the loop; instead the
-packed words of a step are or'ed together, and an exponent bit that only numbers from 2 on have (or inf: exp2 against a stale
+The exponent reference m_ref of a row is lazy: it starts as the maximum of the row's first tile
+and moves only when it has to.  No maximum is taken in the loop; instead the 8 probabilities of a row that a
+lane forms in a step are summed on their own, and a sum above 2^16 (or inf: exp2 against a stale
 reference may overflow) sends the wave to an out-of-line block at the end of the step, which
 takes the tile's maximum, forms the step's probabilities again from the S tile (still in
 registers) against the raised reference and rescales what earlier steps left.  The same branch
@@ -34,13 +33,12 @@ serves the rare step whose S tile needs its ragged tail masked.
 Register map (fixed):
   a[0:127]    O^T accumulators, (dt, qt) at a[16 dt + 4 qt ..]: dims 16 dt + 4 (lane/16) + i of query lane%16 of tile qt
   a[128:191]  Q fragments, (qt, ks) at a[128 + 4*(4*qt+ks) ..]
-  a[192:207]  row sums, query tile qt at a[192 + 4 qt ..] (row 0: first register of lanes 0..15)
   v[0:31]     S tile A, (kt, qt) at v[16 kt + 4 qt ..]     v[32:63]  S tile B
   v[64:79]    P^T tile A, qt at v[64 + 4 qt ..]      v[80:95]  P^T tile B
   v[96:127]   ring of 8 operand fragments
   v[128:131]  LDS address in the K ring for chunks 4j.., v[132:135] in the V ring for 32-key step j of a page
-  v[136:139]  ones in lanes 0, 16, 32, 48
-  v[148:151]  row sums on leaving
+  v[148:151]  running row sums of this lane's keys, per query tile
+  v[152:155]  row sums of the current step
   v156..v175  temporaries of the out-of-line blocks
   v[184:199]  -m_ref per query tile, replicated 4 times: the C operand of the
               first MFMA of every S tile, so a tile comes out of the matrix pipe as s*c - m_ref
@@ -62,12 +60,11 @@ from gen_attn_core import (A, FR, P_TILE, PAGE, S_LDS0, S_NLEFT, S_P, S_PGCUR, S
 from issue_sched import Atom, is_vector, schedule16, split_cost  # noqa: E402
 
 QT = 4               # query tiles of 16 per wave
-SLOTS = 68           # MFMAs of a step: 32 QK, 4 row sums, 32 PV
+SLOTS = 64           # MFMAs of a step: 32 QK, 32 PV
 
 XOK, XOV = 128, 132
-ONES = 136           # 136..139: one row of ones (lanes 0, 16, 32, 48), the A operand that sums P over the keys
-LSUM = 192           # a192..a207: row sums per query tile (row 0 of a tile of 16: first register of lanes 0..15)
-LOUT = 148           # 148..151: the same on leaving
+LACC = 148           # 148..151: running row sums per query tile
+TS = [152, 153, 154, 155]      # row sums of the current step
 NT = [184 + 4 * qt for qt in range(QT)]      # -m_ref of the tile's query, four times: C operand of a tile's first MFMA
 MX = [156, 157, 158, 159]
 PX = 224             # 224..255: the 32 probabilities of the step, before packing
@@ -94,13 +91,8 @@ def mfma_pv(dt, qt, p_base):
     return f"v_mfma_f32_16x16x32_bf16 {o}, {V(FR + 4 * dt, 4)}, {V(p_base + 4 * qt, 4)}, {o}"
 
 
-def mfma_sum(qt, p_base):
-    l = A(LSUM + 4 * qt, 4)
-    return f"v_mfma_f32_16x16x32_bf16 {l}, {V(ONES, 4)}, {V(p_base + 4 * qt, 4)}, {l}"
-
-
 def pv_order(p_base):
-    return [mfma_sum(qt, p_base) for qt in range(QT)] + [mfma_pv(dt, qt, p_base) for dt in range(8) for qt in range(QT)]
+    return [mfma_pv(dt, qt, p_base) for dt in range(8) for qt in range(QT)]
 
 
 def qk_order():
@@ -176,7 +168,6 @@ def emit_first_reference(E, s_base):
         m = V(MX[qt])
         for ln in across_lanes_lines(m, V(RT[3])):
             E.e(ln)
-        E.e(f"v_add_f32 {m}, {HEADROOM}, {m}")
         for i in range(4):
             E.e(f"v_sub_f32 {V(NT[qt] + i)}, {V(NT[qt] + i)}, {m}")
         for r in row_regs(s_base, qt):
@@ -207,19 +198,19 @@ def p_word(p_base, j):
 
 
 CAP = 4.0            # issue quanta per MFMA slot the scheduler may fill
-E_SPREAD = 40        # the 32 exponentials of a step are due by this slot
-HEADROOM = "0x41700000"   # 15: the reference is taken this far above the maximum it is taken from (log2 units)
-TOO_LARGE = "0x40004000"  # exponent bit that a bf16 number (a pair of them) has from 2 on
+E_SPREAD = 54        # the 32 exponentials of a step are due by this slot
+E_HARD = 56          # ... and issue by this one
+THRESH = "0x47800000"     # 2^16: a step's sum of 8 probabilities above this moves the reference
 K_BARRIER_SLOT = 32  # step 2: K(q+1) visible, slot of K(q) free
 N_KLOADS_R2 = 3      # of the 8 loads of K(q+2), how many issue in step 2 (the rest in step 3)
 
 # Operand reads: fragment -> slot it is read in.  Fragment f goes to registers FR + 4 (f % 8): V's take the place of
 # K's as those have been multiplied, and the next step's K's the place of V's; K fragment 7 of a step
 # is read in its own slot 1.
-V_READS = {8 + i: 16 + 2 * i for i in range(4)} | {12 + i: 32 + 2 * i for i in range(4)}
-K_READS = {0: 41, 1: 44, 2: 49, 3: 52, 4: 57, 5: 60, 6: 64}
+V_READS = {8 + i: 16 + 2 * i for i in range(4)} | {12: 32, 13: 34, 14: 36, 15: 37}
+K_READS = {0: 38, 1: 41, 2: 45, 3: 48, 4: 53, 5: 56, 6: 60}
 # lgkmcnt of the waits before the slots that first use a fragment: what was read later may still be on its way
-WAITS = {15: 0, 35: 2, 51: 3, 67: 3}
+WAITS = {15: 0, 31: 0, 47: 3, 63: 3}
 
 
 def build_step(R, par):
@@ -245,30 +236,34 @@ def build_step(R, par):
         tail[K_BARRIER_SLOT - 1] += ["s_waitcnt vmcnt(@VMCNT_K@)", "s_barrier"]
 
     atoms = []
-    exps = [Atom([f"v_exp_f32 {V(PX + e)}, {V(s_cur + e)}"], 0, (e * E_SPREAD) // 32, hard=54) for e in range(32)]
+    # row sums of the previous step join the running sums; this step's start afresh
+    lacc = [Atom([f"v_add_f32 {V(LACC + qt)}, {V(LACC + qt)}, {V(TS[qt])}"], 0, qt, hard=6) for qt in range(QT)]
+    atoms += lacc
+    exps = [Atom([f"v_exp_f32 {V(PX + e)}, {V(s_cur + e)}"], 0, (e * E_SPREAD) // 32, hard=E_HARD) for e in range(32)]
     atoms += exps
-    packs = []
-    for j in range(1, 32, 2):
-        packs.append(Atom([f"v_cvt_pk_bf16_f32 {V(p_word(p_cur, j))}, {V(PX + j - 1)}, {V(PX + j)}"],
-                          0, (j * E_SPREAD) // 32 + 6, [exps[j - 1], exps[j]], 2, hard=60))
-        packs[-1].word = p_word(p_cur, j)
-    atoms += packs
-    # all the step's words or'ed together: has any probability reached 2?
-    acc, last = V(RT[1]), None
-    for k in range(0, 15, 2):
-        more = packs[:3] if k == 0 else packs[k + 1:k + 3]
-        srcs = [V(x.word) for x in more]
-        op = f"v_or3_b32 {acc}, " + ", ".join(srcs if k == 0 else [acc] + srcs) if len(srcs) + (k > 0) == 3 else f"v_or_b32 {acc}, {acc}, {srcs[0]}"
-        last = Atom([op], 0, ((2 * k + 7) * E_SPREAD) // 32 + 12, more + ([last] if last else []), 1, hard=62)
-        atoms.append(last)
+    last_sum = [None] * QT
+    for j in range(1, 32, 2):                              # the pair (j - 1, j) of query tile qt
+        qt, deps, dl = (j & 15) >> 2, [exps[j - 1], exps[j]], (j * E_SPREAD) // 32 + 6
+        atoms.append(Atom([f"v_cvt_pk_bf16_f32 {V(p_word(p_cur, j))}, {V(PX + j - 1)}, {V(PX + j)}"], 0, dl, deps, 2, hard=E_HARD + 4))
+        if last_sum[qt] is None:
+            sums = [Atom([f"v_add_f32 {V(TS[qt])}, {V(PX + j - 1)}, {V(PX + j)}"], 0, dl + 2, deps, 2, hard=E_HARD + 4)]
+            sums[0].after.append((lacc[qt], 0))
+        else:
+            sums = [Atom([f"v_add_f32 {V(TS[qt])}, {V(TS[qt])}, {V(PX + k)}"], 0, dl + 2, deps, 2, hard=E_HARD + 4) for k in (j - 1, j)]
+            sums[0].after.append((last_sum[qt], 0))
+            sums[1].after.append((sums[0], 0))
+        atoms += sums
+        last_sum[qt] = sums[-1]
     # is the tile just produced the ragged tail of a block's last page?
     pg, sub = (S_PGCUR, R + 1) if R < 3 else (S_PGNEXT, 0)
     rag = Atom([f"s_cmp_eq_u32 s{pg}, s{S_PM1}",
-                f"s_cselect_b64 s[{S_RG}:{S_RG + 1}], s[{S_VLP + 2 * sub}:{S_VLP + 2 * sub + 1}], 0"], 0, 12, hard=48)
-    det = Atom([f"v_and_b32 {acc}, {TOO_LARGE}, {acc}", f"v_cmp_ne_u32 vcc, 0, {acc}"], 0, 62, [last], 0, hard=63)
+                f"s_cselect_b64 s[{S_RG}:{S_RG + 1}], s[{S_VLP + 2 * sub}:{S_VLP + 2 * sub + 1}], 0"], 0, 12, hard=44)
+    top = V(RT[1])
+    det = Atom([f"v_max3_f32 {top}, {V(TS[0])}, {V(TS[1])}, {V(TS[2])}", f"v_max_f32 {top}, {top}, {V(TS[3])}",
+                f"v_cmp_lt_f32 vcc, {THRESH}, {top}"], 0, E_HARD + 5, last_sum, 0, hard=E_HARD + 5)
     # scc travels from here to the branch after the last MFMA: nothing that writes scc may
-    # issue behind it (every such atom has hard <= 60)
-    orr = Atom([f"s_or_b64 s[{S_T + 8}:{S_T + 9}], vcc, s[{S_RG}:{S_RG + 1}]"], 65, 65, [det, rag], 1, hard=65)
+    # issue behind it (every such atom has hard <= 55)
+    orr = Atom([f"s_or_b64 s[{S_T + 8}:{S_T + 9}], vcc, s[{S_RG}:{S_RG + 1}]"], 62, 62, [det, rag], 1, hard=62)
     atoms += [rag, det, orr]
     tail[SLOTS - 1].insert(0, f"{back}:")
     tail[SLOTS - 1].insert(0, f"s_cbranch_scc1 {cold}")
@@ -276,25 +271,25 @@ def build_step(R, par):
     if R == 0:                                             # address of V(q+1), then of K(q+2)
         prev = None
         for k, grp in enumerate(v_address_lines() + page_advance_lines()):
-            prev = Atom(grp, 4, 12 + 6 * k, [prev] if prev else [], 1, hard=59)
+            prev = Atom(grp, 4, 12 + 6 * k, [prev] if prev else [], 1, hard=55)
             atoms.append(prev)
     if R == 1:                                             # V(q+1) into the slot V(q-1) left
-        atoms += page_load_atoms([(page_load_lines(i, VRING + (1 - par) * PAGE, 1), 3 + 7 * i) for i in range(8)], 0, 59)
+        atoms += page_load_atoms([(page_load_lines(i, VRING + (1 - par) * PAGE, 1), 3 + (i * 52) // 8) for i in range(8)], 0, 55)
     if R == 2:                                             # K(q+2) into the slot K(q) left
-        atoms += page_load_atoms([(page_load_lines(i, par * PAGE, 0), K_BARRIER_SLOT + 4 + (i * (54 - K_BARRIER_SLOT)) // N_KLOADS_R2)
-                                  for i in range(N_KLOADS_R2)], K_BARRIER_SLOT, 59)
+        atoms += page_load_atoms([(page_load_lines(i, par * PAGE, 0), K_BARRIER_SLOT + 4 + (i * (52 - K_BARRIER_SLOT)) // N_KLOADS_R2)
+                                  for i in range(N_KLOADS_R2)], K_BARRIER_SLOT, 55)
     if R == 3:
         n = 8 - N_KLOADS_R2
-        atoms += page_load_atoms([(page_load_lines(N_KLOADS_R2 + i, par * PAGE, 0), 4 + (i * 56) // n) for i in range(n)], 0, 59)
+        atoms += page_load_atoms([(page_load_lines(N_KLOADS_R2 + i, par * PAGE, 0), 4 + (i * 52) // n) for i in range(n)], 0, 55)
         # page-in-block counters of pages q and q+1 move on; one page less to go
         pe = Atom([f"s_mov_b32 s{S_PGCUR}, s{S_PGNEXT}", f"s_add_u32 s{S_T}, s{S_PGNEXT}, 1",
                    f"s_cmp_eq_u32 s{S_T}, s{S_P}", f"s_cselect_b32 s{S_PGNEXT}, 0, s{S_T}",
-                   f"s_sub_u32 s{S_NLEFT}, s{S_NLEFT}, 1"], 0, 40, [rag], 1, hard=59)
+                   f"s_sub_u32 s{S_NLEFT}, s{S_NLEFT}, 1"], 0, 40, [rag], 1, hard=55)
         atoms.append(pe)
 
     fixed = [split_cost(head[i] + tail[i]) for i in range(SLOTS)]
     placed = schedule16(fixed, atoms, CAP)
-    for i in range(65, SLOTS):
+    for i in range(62, SLOTS):
         for a in placed[i]:
             assert not any(l.split()[0].startswith(("s_add", "s_sub", "s_cmp", "s_and", "s_mul")) for l in a.lines), a.lines
     slots = []
@@ -328,12 +323,10 @@ def emit_cold(E, s_cur, s_next, p_cur, cold, back, valid_sreg):
         regs = row_regs(s_cur, qt)
         c += row_max_lines(m, regs)
         c += across_lanes_lines(m, V(RT[3]))
-        c.append(f"v_add_f32 {m}, {HEADROOM}, {m}")
         c.append(f"v_max_f32 {delta}, 0, {delta}")                  # the reference never moves down
         c.append(f"v_exp_f32_e64 {alpha}, -{delta}")
         c.append("s_nop 3")                              # a trans result is not forwarded to the next VALU op
-        c += [f"v_accvgpr_read_b32 {V(RT[8])}, {A(LSUM + 4 * qt)}", f"v_mul_f32 {V(RT[8])}, {V(RT[8])}, {alpha}",
-              f"v_accvgpr_write_b32 {A(LSUM + 4 * qt)}, {V(RT[8])}"]
+        c.append(f"v_mul_f32 {V(LACC + qt)}, {V(LACC + qt)}, {alpha}")
         for dt in range(8):
             for i in range(4):
                 acc = A(o_reg(dt, qt, i))
@@ -347,6 +340,9 @@ def emit_cold(E, s_cur, s_next, p_cur, cold, back, valid_sreg):
         for e in es:
             c.append(f"v_exp_f32 {V(PX + e)}, {V(s_cur + e)}")
         c.append("s_nop 3")
+        c.append(f"v_add_f32 {V(TS[qt])}, {V(PX + es[0])}, {V(PX + es[1])}")
+        for e in es[2:]:
+            c.append(f"v_add_f32 {V(TS[qt])}, {V(TS[qt])}, {V(PX + e)}")
         for j in es[1::2]:
             c.append(f"v_cvt_pk_bf16_f32 {V(p_word(p_cur, j))}, {V(PX + j - 1)}, {V(PX + j)}")
         for i in range(4):                               # -m_ref operand and the tile just produced
@@ -366,6 +362,8 @@ def emit_cold(E, s_cur, s_next, p_cur, cold, back, valid_sreg):
 
 def emit_drain(E, par_last):
     """PV of the final step: V page (parity par_last), keys 96..127, P tile B."""
+    for qt in range(QT):                                  # row sums of the final step
+        E.e(f"v_add_f32 {V(LACC + qt)}, {V(LACC + qt)}, {V(TS[qt])}")
     for dt in range(8):
         E.e(f"ds_read_b128 {V(FR + 4 * dt, 4)}, {V(XOV + 3)} offset:{par_last * PAGE + dt * 4096}")
     E.e("s_waitcnt lgkmcnt(0)")
@@ -401,8 +399,6 @@ def emit_operand_setup(E):
     E.e(f"v_mov_b32 {V(KIDX)}, %[kidx]")
     E.e(f"v_mov_b32 {V(XL16)}, %[xl16]")
     E.e(f"v_mov_b32 {V(XL32)}, %[xl32]")
-    for r in range(4):
-        E.e(f"v_mov_b32 {V(ONES + r)}, %[ones]")
     for j in range(4):
         E.e(f"v_xor_b32 {V(XOK + j)}, {j << 6}, %[xk0]")
         E.e(f"v_add_u32 {V(XOK + j)}, s{S_LDS0}, {V(XOK + j)}")
@@ -412,8 +408,10 @@ def emit_operand_setup(E):
 
 
 def emit_clear(E):
+    for qt in range(QT):
+        E.e(f"v_mov_b32 {V(LACC + qt)}, 0")
+        E.e(f"v_mov_b32 {V(TS[qt])}, 0")
     for r in range(4 * QT):
-        E.e(f"v_accvgpr_write_b32 {A(LSUM + r)}, 0")
         E.e(f"v_mov_b32 {V(NT[0] + r)}, 0")               # m_ref = 0 until tile 0 has been seen
 
 
@@ -438,10 +436,7 @@ def emit_first_reads(E):
     E.e(f"s_waitcnt lgkmcnt({WAITS[SLOTS - 1]})")
 
 
-def emit_results(E):
-    base.emit_results(E)
-    for qt in range(QT):
-        E.e(f"v_accvgpr_read_b32 {V(LOUT + qt)}, {A(LSUM + 4 * qt)}")
+emit_results = base.emit_results
 
 
 def generate():
@@ -451,7 +446,7 @@ def generate():
 def main(out_path):
     # registers the block uses beyond its operands (v148..v151 and NT are outputs)
     clob = [f"v{i}" for i in range(128, 256) if not 148 <= i <= 151 and i not in NT]
-    clob += [f"a{i}" for i in range(0, 128)] + [f"a{i}" for i in range(LSUM, LSUM + 4 * QT)] + [f"s{i}" for i in range(36, 96)]
+    clob += [f"a{i}" for i in range(0, 128)] + [f"s{i}" for i in range(36, 96)]
     base.write_include(out_path, generate(), clob, "CA_CORE16_CLOBBERS")
 
 

@@ -162,3 +162,39 @@ def test_capture_of_other_sizes_than_the_eager_call():
         for x, w, y in xs:
             assert torch.equal(linear(x, w), y)
         assert torch.equal(large.forward_rope(q, [2], BI), o)
+
+
+# Row sums are those of the probabilities before their rounding to bf16, in both main loops.  One key of weight 0.9 outside a walk's
+# first tile, its V zero, the others' 1 +- 0.3: a rounded weight in the row sum scales the whole row by up to 0.9 x 2^-8.  The reference
+# takes the kernel's own operands (Q scaled and rounded, K as its pages hold it), so that a row's mean ratio to it keeps, of relative
+# variance E2 each, the rounding of 128 results and of the light keys' weights: bars at 8 sigma a row, 2 sigma over the rows.
+@pytest.mark.parametrize("heads", [2, 181])
+def test_bf16_row_sums_with_one_heavy_key(heads):
+    w = W.small_variant(W.CONFIGS["c5_wan1p3b_rollout"], heads=heads, grid_h=10, grid_w=15, frames_per_block=1, n_cached=4, n_inflight=1,
+                        sink_blocks=0, window_blocks=16)
+    L, blocks, heavy = w.block_tokens, 5, 2 * w.block_tokens + 37
+    rng = np.random.default_rng(12)
+    _, k, v = W.draw_config(w, seed=9)
+    u = np.sign(rng.standard_normal(128))
+    q = W.f32_to_bf16_bits((u + 0.1 * rng.standard_normal((L, heads, 128))).astype(np.float32))
+    at = orc.token_positions(2, w.frames_per_block, w.grid_h, w.grid_w)[37:38]
+    flip = np.tile([1.0, -1.0], 64)                                  # the rotation by the opposite angle
+    k[heavy] = W.f32_to_bf16_bits((orc.rope3d((0.8 * u * flip)[None, None], at, w.rope_dims, w.rope_theta)[0, 0] * flip).astype(np.float32))
+    v[:] = W.f32_to_bf16_bits((1 + 0.3 * rng.standard_normal(v.shape)).astype(np.float32))
+    v[heavy] = 0
+    pool = Hn.gpu_setup(w, k, v, [0, 1, 2, 3], [4])
+    print(f"one heavy key, {heads} heads", flush=True)
+    out = Hn.from_torch(pool.forward(Hn.to_torch(q, "bf16"), [4], BI), "bf16")
+    raw = pool.pool.cpu().numpy()
+    c = np.float32(1.4426950408889634) / np.sqrt(np.float32(128))
+    for h in (0, heads - 1):
+        kp = np.concatenate([W.to_f64(np.concatenate([Hn.decode_bf16_pages(raw, pool.ctx.kv_cache_page_index(g, pg, h))[0]
+                                                      for pg in range(2)])[:L]) for g in range(blocks)])
+        p = np.exp2(W.to_f64(W.f32_to_bf16_bits(W.bf16_bits_to_f32(q[:, h]) * c)) @ kp.T)
+        p /= p.sum(axis=1, keepdims=True)
+        assert 0.8 < p[:, heavy].min()
+        err = (out[:, h] / (p @ W.to_f64(v[:, h])) - 1).mean(axis=1)
+        light = np.delete(p, heavy, axis=1)
+        sigma = np.sqrt(Hn.E2_BF16 * (1 / 128 + (light ** 2).sum(axis=1) / light.sum(axis=1) ** 2))
+        print(f"[row sums] {heads} heads, head {h}: rms {np.sqrt((err ** 2).mean()):.2e} max {np.abs(err).max():.2e} sigma {sigma.mean():.2e}", flush=True)
+        assert (np.abs(err) <= 8 * sigma).all() and np.sqrt((err ** 2).mean()) <= 2 * sigma.mean()
