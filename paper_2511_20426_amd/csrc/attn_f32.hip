@@ -188,6 +188,12 @@ __global__ __launch_bounds__(64 * kMaxWaves) void attn_f32_kernel(F32Args a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) w[i] = softmax_exp(s[i] - m);
     l += (w[0] + w[1]) + (w[2] + w[3]);
+    if (__builtin_expect(valid < kTileKeys, 0)) {             // keys that do not exist: 0 x a re-read inf would be NaN
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int c = 0; c < D / 16; ++c) v[i][c / T::kW][c % T::kW] = 4 * g + i < valid ? v[i][c / T::kW][c % T::kW] : 0.f;
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll

@@ -30,6 +30,25 @@ def test_f32_key_tiles(head_dim, fpb, gh, gw, page, nc, ni):
         Hn.assert_close(out, ref, "f32", f"f32 tiles D={head_dim} L={w.block_tokens} page={page} mode={mode}")
 
 
+# fp32 attention, an infinite V in a block's last row: its dimension is infinite, all else finite.  (The tile that row is in is
+# filled up with keys that do not exist.)
+@pytest.mark.parametrize("head_dim", [32, 64, 128])
+@pytest.mark.parametrize("fpb,gh,gw,page,nc", [(1, 1, 17, 48, 0), (1, 3, 11, 5, 1), (2, 5, 5, 16, 1)])
+def test_f32_infinite_value_in_the_last_row(head_dim, fpb, gh, gw, page, nc):
+    w = W.small_variant(W.CONFIGS["c1_tiny_f32"], heads=2, grid_h=gh, grid_w=gw, frames_per_block=fpb, head_dim=head_dim,
+                        rope_dims=DIMS[head_dim], page_tokens=page, n_cached=nc, n_inflight=1)
+    q, k, v = W.draw_config(w, seed=5)
+    v[w.block_tokens - 1, 1, 3] = np.inf
+    pool = Hn.gpu_setup(w, k, v, list(range(nc)), [nc])
+    out = Hn.gpu_forward(w, pool, q, [nc], BI)
+    assert (out[:, 1, 3] == np.inf).all()
+    v[w.block_tokens - 1, 1, 3] = 0
+    out[:, 1, 3] = 0
+    ref = np.concatenate(Hn.oracle_forward(w, q, k, v, list(range(nc)), [nc], BI))
+    ref[:, 1, 3] = 0
+    Hn.assert_close(out, ref, "f32", f"infinite V D={head_dim} L={w.block_tokens} page={page}")
+
+
 # bf16 attention of launches that leave CUs idle: every KV walk cut into page ranges.  One item in as many
 # ranges as it has pages (the last one ragged), items absent on some XCDs, walks of different lengths
 # (block-causal) in ranges that begin and end inside blocks.
