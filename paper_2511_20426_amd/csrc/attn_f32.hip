@@ -27,6 +27,8 @@
 // (cached blocks visible to all) and Sec. 3.4 / 4.2 (bidirectional or block-causal cascade).
 #include <hip/hip_runtime.h>
 
+#include <cfloat>
+
 #include "ca_internal.hpp"
 
 namespace ca {
@@ -120,7 +122,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) void attn_f32_kernel(F32Args a) {
   f32x4 o[D / 16];
 #pragma unroll
   for (int c = 0; c < D / 16; ++c) o[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m = -INFINITY, l = 0.f;                               // l: of this lane's keys 4g .. 4g+3 only
+  // l: of this lane's keys 4g .. 4g+3 only; m is finite from the start, so that a tile of scores that are all -inf has weights of 0
+  float m = -FLT_MAX, l = 0.f;
 
   const int block_tiles = (L + kTileKeys - 1) / kTileKeys;
   const int tiles = p.n_vis[qb] * block_tiles;
@@ -172,10 +175,10 @@ __global__ __launch_bounds__(64 * kMaxWaves) void attn_f32_kernel(F32Args a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) s[i] = 4 * g + i < valid ? (s0[i] + s1[i]) * scale : -INFINITY;
     float tm = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
-    if (__builtin_expect(__any(tm > m + kSlack), 0)) {        // always on the first tile (m = -inf)
+    if (__builtin_expect(__any(tm > m + kSlack), 0)) {        // on the first tile, whatever its scores unless they are all -inf
       tm = fmaxf(tm, __shfl_xor(tm, 16));
       tm = fmaxf(tm, __shfl_xor(tm, 32));
-      const float m_new = fmaxf(m, tm);                       // a tile has at least one key: finite
+      const float m_new = fmaxf(m, tm);
       const float alpha = expf(m - m_new);                    // 0 on the first tile
       l *= alpha;
       m = m_new;
@@ -217,7 +220,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void attn_f32_kernel(F32Args a) {
     if (wave < half) {
       const float (*from)[64] = stage[wave];
       const float mb = from[D / 4][lane], mm = fmaxf(m, mb);
-      const float wa = m == -INFINITY ? 0.f : expf(m - mm), wb = mb == -INFINITY ? 0.f : expf(mb - mm);
+      const float wa = expf(m - mm), wb = expf(mb - mm);
       l = l * wa + from[D / 4 + 1][lane] * wb;
       m = mm;
 #pragma unroll

@@ -49,6 +49,30 @@ def test_f32_infinite_value_in_the_last_row(head_dim, fpb, gh, gw, page, nc):
     Hn.assert_close(out, ref, "f32", f"infinite V D={head_dim} L={w.block_tokens} page={page}")
 
 
+def _minus_infinity_scores(w, seed, low, high):
+    """q, k, v whose scores are minus infinity in fp32 for the keys low <= n < high of block 0 and ordinary for all others: block 0 is at
+    frame 0, where pairs of the frame axis are not rotated, and the slowest of them hardly turns at frame 1."""
+    q, k, v = (W.to_f64(x).astype(np.float32) for x in W.draw_config(w, seed=seed))
+    j = w.rope_dims[0] - 2
+    q[:, :, j:j + 2] = k[:, :, j:j + 2] = 0
+    q[:, :, j] = 1e10
+    k[low:high, :, j] = -3e38
+    return tuple(W.store(x, w.dtype) for x in (q, k, v))
+
+
+# fp32 attention, scores of minus infinity (a product out of range) over the whole first tile of some of a workgroup's waves: weight 0
+@pytest.mark.parametrize("head_dim", [32, 64, 128])
+@pytest.mark.parametrize("low,high", [(5, 300), (16, 17), (16, 100), (0, 300)])
+def test_f32_scores_of_minus_infinity(head_dim, low, high):
+    w = W.small_variant(W.CONFIGS["c1_tiny_f32"], heads=2, grid_h=15, grid_w=20, frames_per_block=1, head_dim=head_dim,
+                        rope_dims=DIMS[head_dim], page_tokens=48, n_cached=1, n_inflight=1)
+    q, k, v = _minus_infinity_scores(w, 5, low, high)
+    pool = Hn.gpu_setup(w, k, v, [0], [1])
+    out = Hn.gpu_forward(w, pool, q, [1], BI)
+    ref = np.concatenate(Hn.oracle_forward(w, q, k, v, [0], [1], BI))
+    Hn.assert_close(out, ref, "f32", f"-inf scores D={head_dim} keys {low}..{high}")
+
+
 # bf16 attention of launches that leave CUs idle: every KV walk cut into page ranges.  One item in as many
 # ranges as it has pages (the last one ragged), items absent on some XCDs, walks of different lengths
 # (block-causal) in ranges that begin and end inside blocks.
