@@ -222,6 +222,15 @@ def emit_mask(E, s_base, valid_sreg):
             E.e(f"v_cndmask_b32 {r}, {V(RT[0])}, {r}, vcc")
 
 
+NO_SCORE = "0xc4800000"   # -1024: first reference of a row whose first tile has only scores of -inf
+
+
+def finite_reference_lines(m, tmp):
+    """m = NO_SCORE where it is -inf (the difference to it would be NaN): such keys get weight 0, and the first score above moves
+    the reference as any other does."""
+    return [f"v_mov_b32 {tmp}, {NO_SCORE}", f"v_cmp_gt_f32 vcc, 0xff7fffff, {m}", f"v_cndmask_b32 {m}, {m}, {tmp}, vcc"]
+
+
 def emit_first_reference(E, s_base):
     """The exponent reference of a row starts as the maximum of its first tile (at s_base, its
     per-lane maxima in MX): the tile and the -m_ref operand move by it.  Nothing has been
@@ -232,6 +241,8 @@ def emit_first_reference(E, s_base):
         E.e(f"ds_bpermute_b32 {other}, {V(XLANE)}, {t}")             # the partner lane's (lane ^ 32) maximum
         E.e("s_waitcnt lgkmcnt(0)")
         E.e(f"v_max_f32 {delta}, {t}, {other}")
+        for ln in finite_reference_lines(delta, other):
+            E.e(ln)
         for i in range(16):
             E.e(f"v_sub_f32 {V(NT[nt] + i)}, {V(NT[nt] + i)}, {delta}")
             E.e(f"v_sub_f32 {V(s_base + 16 * nt + i)}, {V(s_base + 16 * nt + i)}, {delta}")

@@ -166,7 +166,7 @@ def emit_first_reference(E, s_base):
     E.e("s_nop 15\ns_nop 15\ns_nop 15")                   # every MFMA issued so far has written back
     for qt in range(QT):
         m = V(MX[qt])
-        for ln in across_lanes_lines(m, V(RT[3])):
+        for ln in across_lanes_lines(m, V(RT[3])) + base.finite_reference_lines(m, V(RT[3])):
             E.e(ln)
         for i in range(4):
             E.e(f"v_sub_f32 {V(NT[qt] + i)}, {V(NT[qt] + i)}, {m}")

@@ -241,3 +241,19 @@ def test_bf16_row_sums_with_one_heavy_key(heads):
         sigma = np.sqrt(Hn.E2_BF16 * (1 / 128 + (light ** 2).sum(axis=1) / light.sum(axis=1) ** 2))
         print(f"[row sums] {heads} heads, head {h}: rms {np.sqrt((err ** 2).mean()):.2e} max {np.abs(err).max():.2e} sigma {sigma.mean():.2e}", flush=True)
         assert (np.abs(err) <= 8 * sigma).all() and np.sqrt((err ** 2).mean()) <= 2 * sigma.mean()
+
+
+# Scores of minus infinity over the whole first tile of a range of a cut walk (one head: every page a range), and of a walk: weight 0
+# (181 heads: one range an item, the 16x16x32 loop).
+@pytest.mark.parametrize("heads", [1, 181])
+@pytest.mark.parametrize("low,high", [(5, 600), (32, 257), (0, 600), (0, 32)])
+def test_bf16_scores_of_minus_infinity(heads, low, high):
+    w = W.small_variant(W.CONFIGS["c5_wan1p3b_rollout"], heads=heads, grid_h=20, grid_w=30, frames_per_block=1, n_cached=1, n_inflight=1,
+                        sink_blocks=0, window_blocks=16)
+    q, k, v = _minus_infinity_scores(w, 5, low, high)
+    print(f"-inf scores {heads} heads keys {low}..{high}", flush=True)
+    pool = Hn.gpu_setup(w, k, v, [0], [1])
+    check = sorted({0, heads - 1})
+    got = Hn.gpu_forward(w, pool, q, [1], BI)[:, check]
+    ref = np.concatenate(Hn.oracle_forward(w, q, k, v, [0], [1], BI, heads=check))
+    Hn.assert_close(got, ref, "bf16", f"-inf scores {heads} heads keys {low}..{high}")
