@@ -224,3 +224,235 @@ def test_gemm_stage_invariants():
         for kk in range(2):
             accs = [re.match(r"v_mfma\S+ (a\[\d+:\d+\])", m_).group(1) for m_, _ in slots[64 * kk:64 * kk + 64]]
             assert len(set(accs)) == 64
+
+
+# ---- the loop on 16x16x32 matrix instructions, and what both attention loops share
+
+def test_schedule16_respects_ready_order_gaps_and_room():
+    rng = np.random.default_rng(11)
+    kinds = ["v_add_f32 v0, v0, v0", "v_exp_f32 v1, v2", "s_add_u32 s0, s0, 1", "ds_read_b128 v[0:3], v4 offset:0"]
+    for trial in range(20):
+        n, atoms = 160, []
+        for k in range(60):
+            after = [atoms[j] for j in rng.choice(len(atoms), size=min(len(atoms), int(rng.integers(0, 3))), replace=False)] if atoms else []
+            ready = int(rng.integers(0, 40))
+            atoms.append(sched.Atom([kinds[int(rng.integers(0, 4))] for _ in range(int(rng.integers(1, 3)))], ready, int(rng.integers(ready, n)),
+                                    after, int(rng.integers(0, 3)), hard=n - 1))
+        fixed = [(1.0, 0.0) if i % 4 == 0 else (0.0, 0.0) for i in range(n)]
+        placed = sched.schedule16(fixed, atoms, 4.0)
+        assert sorted(id(a) for s in placed for a in s) == sorted(id(a) for a in atoms)
+        pos = {id(a): (i, k) for i, s in enumerate(placed) for k, a in enumerate(s)}
+        for a in atoms:
+            assert a.slot == pos[id(a)][0] and a.slot >= a.ready
+            for dep, gap in a.after:
+                assert a.slot >= dep.slot + gap and pos[id(a)] > pos[id(dep)]
+        for i, s in enumerate(placed):
+            other, vector = sched.split_cost([ln for a in s for ln in a.lines])
+            assert sched.slot_end(other + fixed[i][0], vector + fixed[i][1]) <= 4.0 or len(s) == 1 or any(a.hard <= i for a in s)
+    late = sched.Atom(["v_exp_f32 v1, v2"], 0, 9, hard=1)
+    placed = sched.schedule16([(0.0, 0.0)] * 4, [sched.Atom(["v_exp_f32 v3, v4"], 0, 0, hard=3) for _ in range(3)] + [late], 4.0)
+    assert late.slot == 1                                   # due last, but its hard limit has come
+    # a matrix instruction takes one quantum of four and keeps vector work out for two
+    assert sched.slot_end(0, 0) == 1 and sched.slot_end(0, 2) == 4 and sched.slot_end(1, 2) == 4 and sched.slot_end(2, 2) == 5
+
+
+def _regs(text, kind="v"):
+    """register numbers named in a piece of an instruction"""
+    out = set()
+    for a, b in re.findall(rf"\b{kind}\[(\d+):(\d+)\]", text):
+        out |= set(range(int(a), int(b) + 1))
+    return out | {int(x) for x in re.findall(rf"\b{kind}(\d+)\b", text)}
+
+
+def test_attention16_step_invariants():
+    exp_re = re.compile(r"v_exp_f32 (v\d+), (v\d+)")
+    for par in range(2):
+        for R in range(4):
+            slots, cold = attn16.build_step(R, par)
+            s_cur, s_next, p_cur = cold[:3]
+            assert len(slots) == 64 and all(m.startswith("v_mfma_f32_16x16x32_bf16") for m, _ in slots)
+            flat = [(i, ln) for i, (m, lines) in enumerate(slots) for ln in [m] + lines]
+            text = [ln for _, ln in flat]
+            # 32 exponentials of the present tile; every one packed once and summed once, in fp32, at least two slots later
+            exps = {m.group(1): i for i, ln in flat for m in [exp_re.match(ln)] if m}
+            assert len(exps) == 32
+            assert set().union(*(_regs(exp_re.match(ln).group(2)) for _, ln in flat if exp_re.match(ln))) == set(range(s_cur, s_cur + 32))
+            used = []
+            for i, ln in flat:
+                if ln.startswith(("v_cvt_pk_bf16_f32", "v_add_f32")):
+                    for reg in re.findall(r"v\d+", ln.split(",", 1)[1]):
+                        if reg in exps:
+                            assert i >= exps[reg] + 2, (R, ln)
+                            used.append((ln.split()[0], reg))
+            assert sorted(r for op, r in used if op == "v_cvt_pk_bf16_f32") == sorted(exps)
+            assert sorted(r for op, r in used if op == "v_add_f32") == sorted(exps)
+            # the pairs of a query tile land in its P words and its sum
+            for i, ln in flat:
+                if ln.startswith("v_cvt_pk_bf16_f32"):
+                    dst, a, b = (int(x) for x in re.findall(r"v(\d+)", ln.split(None, 1)[1]))
+                    e = a - attn16.PX
+                    assert b == a + 1 and e % 2 == 0 and dst == p_cur + 4 * ((e % 16) // 4) + 2 * (e // 16) + (e % 4) // 2
+                if ln.startswith("v_add_f32") and not ln.startswith(f"v_add_f32 v{attn16.LACC}") and exps.keys() & set(re.findall(r"v\d+", ln)):
+                    dst, *src = (int(x) for x in re.findall(r"v(\d+)", ln.split(None, 1)[1]))
+                    assert all(attn16.TS[((x - attn16.PX) % 16) // 4] == dst for x in src if x >= attn16.PX)
+            # the running sums take the step before's before its registers start afresh
+            for qt in range(4):
+                ts, acc = attn16.TS[qt], attn16.LACC + qt
+                k_acc = text.index(f"v_add_f32 v{acc}, v{acc}, v{ts}")
+                assert k_acc < min(k for k, ln in enumerate(text) if ln.startswith(f"v_add_f32 v{ts},"))
+            # QK writes the other tile, PV reads the other P; nothing of the vector work touches either
+            for i, (m, _) in enumerate(slots):
+                d, a, b, c = (x.strip() for x in re.split(r",(?![^\[]*\])", m.split(None, 1)[1]))
+                if i < 32:
+                    assert _regs(d) <= set(range(s_next, s_next + 32)) and (c == d or _regs(c) <= set(range(184, 200)))
+                else:
+                    assert d == c and not _regs(b) & set(range(p_cur, p_cur + 16))
+            assert len({m.split()[1] for m, _ in slots[:32]}) == 8 and len({m.split()[1] for m, _ in slots[32:]}) == 32
+            # what decides about the out-of-line block: sums -> vcc -> scc -> the branch that ends the step
+            k_cmp, k_or = (max(k for k, ln in enumerate(text) if ln.startswith(x)) for x in ("v_cmp_lt_f32 vcc", "s_or_b64"))
+            k_br = max(k for k, ln in enumerate(text) if ln.startswith("s_cbranch_scc1"))
+            assert k_cmp > max(k for k, ln in enumerate(text) if ln.startswith(tuple(f"v_add_f32 v{t}," for t in attn16.TS)))
+            assert flat[k_or][0] >= flat[k_cmp][0] + 1 and k_br > k_or + 1
+            assert not any(ln.split()[0].startswith(SCC_WRITERS) for ln in text[k_or + 1:k_br])
+            assert sum("vcc" in ln for ln in text) == 2
+            for k, ln in enumerate(text):
+                if ln.split()[0] in ("s_cselect_b32", "s_cselect_b64", "s_addc_u32"):
+                    back = k - 1
+                    while text[back].split()[0] in ("s_cselect_b32", "s_cselect_b64"):
+                        back -= 1
+                    assert text[back].split()[0].startswith(("s_cmp", "s_add_u32", "s_addc_u32")), (R, text[back], ln)
+            assert len(_m0_writes(text)) == [0, 8, attn16.N_KLOADS_R2, 8 - attn16.N_KLOADS_R2][R]
+
+
+def _loop_text(core):
+    """the main loop in program order, one trip (two pages), without the out-of-line blocks"""
+    text = [p for ln in attn.generate(core) for p in ln.split("\n")]
+    start = next(k for k, ln in enumerate(text) if ln.startswith("LOOP_"))
+    return text, text[start + 1:next(k for k, ln in enumerate(text) if ln.startswith("s_branch LOOP_"))]
+
+
+@pytest.mark.parametrize("core", [attn.CORE, attn16], ids=["32x32x16", "16x16x32"])
+def test_attention_operand_fragments_have_arrived(core):
+    """Two trips of the loop: every matrix instruction finds the operand fragment it is meant to have in its registers, and a
+    wait has covered the read (LDS answers a wave's reads in order)."""
+    _, loop = _loop_text(core)
+    want = []                                               # (address register, offset) per matrix instruction
+    for par in range(2):
+        for R in range(4):
+            if core is attn16:
+                # K of the next 32-key step of the walk, V of the one before
+                kp, vp = (par if R < 3 else 1 - par) * attn.PAGE, (par if R > 0 else 1 - par) * attn.PAGE
+                want += [(attn16.XOK + (ks ^ (2 * kt)), kp + ((R + 1) % 4) * 8192 + kt * 2048) for kt in range(2) for qt in range(4) for ks in range(4)]
+                want += [(attn16.XOV + (R - 1) % 4, vp + dt * 4096) for dt in range(8) for qt in range(4)]
+            else:
+                want += [attn.frag_source(R, par, i >> 1) for i in range(32)]
+    held, flying, n = {}, [], 0
+    for trip in range(2):
+        for ln in loop:
+            if ln.startswith("ds_read_b128"):
+                m = re.match(r"ds_read_b128 v\[(\d+):\d+\], v(\d+) offset:(\d+)", ln)
+                reg, src = int(m.group(1)), (int(m.group(2)), int(m.group(3)))
+                held[reg] = src
+                flying.append(reg)
+            elif ln.startswith("s_waitcnt") and "lgkmcnt" in ln:
+                left = int(re.search(r"lgkmcnt\((\d+)\)", ln).group(1))
+                flying = flying[len(flying) - left:] if left < len(flying) else flying
+                if left == 0:
+                    flying = []
+            elif ln.startswith("v_mfma"):
+                reg = int(re.findall(r"v\[(\d+):\d+\]", ln)[1 if ln.split()[1].startswith("v") else 0])
+                if reg in held or trip:                     # (the very first operands were read ahead of the loop)
+                    assert held[reg] == want[n % len(want)] and reg not in flying, (n, ln)
+                n += 1
+            elif ln == "s_barrier":
+                assert not [r for r in flying if r not in held]
+    assert n == 2 * len(want)
+
+
+@pytest.mark.parametrize("core", [attn.CORE, attn16], ids=["32x32x16", "16x16x32"])
+def test_attention_pages_are_there_when_read(core):
+    """The page loop's loads, waits and barriers over eight pages: a read finds the page it is meant to have, published by a
+    barrier behind a wait that covers the page's last load, and no load goes to a slot that a wave may still read."""
+    _, loop = _loop_text(core)
+    # K(0), V(0), K(1) requested ahead of the loop in this order, the first two published
+    queue, published = [("K", 1)] * 8, {("K", 0), ("V", 0)}
+    slot_of = {"K": {0: 0, 1: 1}, "V": {0: 0, 1: None}}      # page held (or on its way) per ring slot
+    last_reads, n_load, m0 = {}, {"K": 16, "V": 8}, None
+    barriers = 0
+    for trip in range(4):
+        step = mfma = 0
+        for ln in loop:
+            if " m0," in ln:
+                m0 = int(ln.split()[-1])
+            elif ln.startswith("global_load_lds"):
+                which = "V" if f"s[{attn.S_ADDRV}:" in ln else "K"
+                pg = n_load[which] // 8
+                slot = (m0 - (attn.VRING if which == "V" else 0)) // attn.PAGE
+                assert slot == pg % 2 and (m0 % attn.PAGE) // 4096 == n_load[which] % 8
+                old = slot_of[which][slot]
+                if old is not None and old != pg:           # the page that leaves: its last read lies before the last barrier
+                    assert last_reads.get((which, old), -1) < barriers, (which, old, pg)
+                slot_of[which][slot] = pg
+                published.discard((which, old))
+                queue.append((which, pg))
+                n_load[which] += 1
+            elif ln.startswith("s_waitcnt vmcnt"):
+                left = int(re.search(r"vmcnt\((\d+)\)", ln).group(1))
+                queue = queue[len(queue) - left:] if left < len(queue) else queue
+            elif ln == "s_barrier":
+                barriers += 1
+                for which in "KV":
+                    for slot, pg in slot_of[which].items():
+                        if pg is not None and (which, pg) not in queue and n_load[which] >= 8 * (pg + 1):
+                            published.add((which, pg))
+            elif ln.startswith("ds_read_b128"):
+                reg, imm = (int(x) for x in re.match(r"ds_read_b128 \S+ v(\d+) offset:(\d+)", ln).groups())
+                is_v = reg >= core.XOV if core is attn16 else reg >= attn.XOV
+                which, slot = ("V" if is_v else "K"), (imm // attn.PAGE) % 2
+                pg = slot_of[which][slot]
+                if which == "V" and pg is None:             # the all-zero P of the first step
+                    assert trip == 0 and step == 0
+                    continue
+                assert (which, pg) in published, (which, pg, trip, step)
+                last_reads[(which, pg)] = barriers
+            elif ln.startswith("v_mfma"):
+                mfma += 1
+                step = mfma // core.SLOTS
+    assert barriers == 16
+
+
+def test_attention16_idle_waves_move_the_same_pages():
+    """A wave without query rows: the same loads to the same places, waits for them and barriers, in the same order, and nothing else
+    that another wave could see."""
+    text, loop = _loop_text(attn16)
+    start = next(k for k, ln in enumerate(text) if re.match(r"IDLE_\d+_%=:", ln))
+    idle = text[start + 1:next(k for k, ln in enumerate(text) if ln.startswith("s_branch IDLE_"))]
+
+    def traffic(lines):
+        return [ln for ln in lines if ln.startswith(("global_load", "s_waitcnt vmcnt", "s_barrier", "v_readlane", "s_mul", "s_add", "s_sub",
+                                                     "s_mov", "s_cmp", "s_cselect"))]
+    assert traffic(idle) == traffic(loop)
+    assert not any(ln.startswith(("ds_", "v_mfma", "global_store")) for ln in idle)
+    assert len(_m0_writes(idle)) == 32
+    assert sum(ln.startswith("s_cbranch_scc1 DONE_") for ln in idle) == 2       # it leaves after the same page
+    for k, ln in enumerate(idle):
+        if ln.startswith("s_cbranch"):
+            assert idle[k - 2] == f"s_cmp_eq_u32 s{attn.S_NLEFT}, 0" and idle[k - 1] == "s_nop 0"
+
+
+def test_attention16_cold_blocks_have_no_barrier_and_return():
+    text, _ = _loop_text(attn16)
+    assert sum(1 for ln in text if ln == "s_barrier") == 1 + 2 * 2 + 2 * 2       # prologue, the loop, the loop of idle waves
+    colds = [k for k, ln in enumerate(text) if ln.startswith("COLD_")]
+    assert len(colds) == 8
+    for k in colds:
+        j = k
+        while not text[j].startswith("s_branch BACK_"):
+            assert text[j] != "s_barrier" and not text[j].startswith(("global_load", "ds_read"))
+            j += 1
+        block = text[k:j]
+        # the step's sums start again from the probabilities formed anew, the running ones are scaled
+        for qt in range(4):
+            ts = attn16.TS[qt]
+            assert sum(ln.startswith(f"v_add_f32 v{ts},") for ln in block) == 7
+            assert sum(ln.startswith(f"v_mul_f32 v{attn16.LACC + qt},") for ln in block) == 1
