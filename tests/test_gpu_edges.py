@@ -30,6 +30,21 @@ def test_f32_key_tiles(head_dim, fpb, gh, gw, page, nc, ni):
         Hn.assert_close(out, ref, "f32", f"f32 tiles D={head_dim} L={w.block_tokens} page={page} mode={mode}")
 
 
+# ... and shared out over four waves instead of eight, at head_dim 128 from more work items (heads x row tiles x blocks) than CUs on:
+# 288 and 258 items, and 256, where it is eight still.
+@pytest.mark.parametrize("heads,fpb,gh,gw,ni", [(4, 2, 5, 37, 3), (3, 1, 19, 36, 2), (4, 1, 10, 25, 4)])
+def test_f32_waves_per_row_tile(heads, fpb, gh, gw, ni):
+    w = W.small_variant(W.CONFIGS["c1_tiny_f32"], heads=heads, grid_h=gh, grid_w=gw, frames_per_block=fpb, head_dim=128, rope_dims=DIMS[128],
+                        page_tokens=100, n_cached=1, n_inflight=ni, max_inflight=4)
+    infl = list(range(1, 1 + ni))
+    q, k, v = W.draw_config(w, seed=15, scale=1.5)
+    pool = Hn.gpu_setup(w, k, v, [0], infl)
+    for mode in (BI, CA):
+        out = Hn.gpu_forward(w, pool, q, infl, mode)
+        ref = np.concatenate(Hn.oracle_forward(w, q, k, v, [0], infl, mode))
+        Hn.assert_close(out, ref, "f32", f"f32 waves heads={heads} L={w.block_tokens} blocks={ni} mode={mode}")
+
+
 # fp32 attention, an infinite V in a block's last row: its dimension is infinite, all else finite.  (The tile that row is in is
 # filled up with keys that do not exist.)
 @pytest.mark.parametrize("head_dim", [32, 64, 128])
@@ -87,6 +102,24 @@ def test_bf16_split_small_launch(heads, gh, gw, nc, ni):
         out = Hn.gpu_forward(w, pool, q, infl, mode)
         ref, bound = (np.concatenate(x) for x in Hn.oracle_forward_bounded(w, q, k, v, cached, infl, mode))
         Hn.assert_close(out, ref, "bf16", f"split heads={heads} grid={gh}x{gw} nc={nc} ni={ni} mode={mode}", bound=bound)
+
+
+# The same with enough ranges of ten pages or more for the 16x16x32 loop (208 to 234 workgroups on 256 CUs): 26 items of 96 pages in
+# eight ranges each, 52 of 63 and 66 pages in four, 39 of 66 in six.  Queries rotated before and by the kernel.
+@pytest.mark.parametrize("nc,ni,mode", [(31, 1, BI), (20, 2, CA), (20, 2, BI)])
+def test_bf16_split_launch_that_fills_the_chip(nc, ni, mode):
+    w = W.small_variant(W.CONFIGS["c5_wan1p3b_rollout"], heads=13, grid_h=6, grid_w=43, frames_per_block=1, n_cached=nc, n_inflight=ni,
+                        sink_blocks=0, window_blocks=nc, max_inflight=ni)
+    cached, infl = list(range(nc)), list(range(nc, nc + ni))
+    q, k, v = W.draw_config(w, seed=16)
+    pool = Hn.gpu_setup(w, k, v, cached, infl)
+    heads = [0, 7, 12]
+    ref, bound = (np.concatenate(x) for x in Hn.oracle_forward_bounded(w, q, k, v, cached, infl, mode, heads=heads))
+    for form in (Hn.gpu_forward, Hn.gpu_forward_rope):
+        pool.pool[pool.pool.numel() - (256 * 256 * 132 * 4):].fill_(0xFF)       # partial results start as NaN
+        out = form(w, pool, q, infl, mode)
+        assert np.isfinite(out).all()
+        Hn.assert_close(out[:, heads], ref, "bf16", f"cut launch on many workgroups nc={nc} ni={ni} mode={mode} {form.__name__}", bound=bound)
 
 
 # Every tile of the linear map: one row, a tile and one row, column counts that end inside a tile, the shortest and
