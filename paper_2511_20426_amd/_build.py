@@ -13,7 +13,7 @@ LIB = os.environ.get("CASCADE_ATTN_LIB") or os.path.join(PKG, "libcascade_attn.s
 
 SOURCES = ["ca_meta.cpp", "ca_api.cpp", "ca_sched.cpp", "rope_cache.hip", "attn_f32.hip", "attn_bf16.hip", "mfma_peak.hip", "gemm_bf16.hip"]
 
-# packed fp32 instructions are kept off for all device code on the test machines
+# packed fp32 instructions are kept off for all device code
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 

@@ -50,7 +50,6 @@ typedef __attribute__((ext_vector_type(2))) float f32x2;
 constexpr int kPageBytes = 128 * 128 * 2;       // one K or V page
 constexpr int kPairBytes = 2 * kPageBytes;      // K page followed by V page
 constexpr int kRowsPerWg = 256;
-constexpr int kMaxSeg = kMaxInflight;
 
 // Everything a launch needs, in the order the kernel reads it.  A workgroup starts with nothing but
 // this block's address, which the first reads of a launch fetch over the bus: the scalars of the

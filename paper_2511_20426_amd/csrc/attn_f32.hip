@@ -270,11 +270,13 @@ int32_t launch_attn_f32(const AttnPlan& p, const void* q, void* out, const void*
   constexpr int kMaxX = 1 << 16;                              // workgroups in x per XCD; a launch may have 2^32 threads in x
   const int gx = per_xcd < kMaxX ? per_xcd : kMaxX;
   const dim3 grid(unsigned(gx) * 8, unsigned((per_xcd + gx - 1) / gx));
-  // Eight waves share a tile's keys.  At head_dim 128 a wave needs 159 registers, so a CU holds one
-  // workgroup of eight waves but three of four: four once every CU has a workgroup anyway.  Measured, a
-  // whole step: 432 tiles 153 us with four, 162 with eight; 162 tiles 75 with four, 73 with eight; at
-  // head_dim 64 (96 registers, 432 tiles) 101 with four, 98 with eight.
-  const int waves = p.head_dim == 128 && items > 256 ? 4 : kMaxWaves;
+  // Eight waves share out the key tiles of a row tile.  At head_dim 128 a wave needs 160 registers, so a CU holds one
+  // workgroup of eight waves but three of four: four once every CU has a workgroup anyway.  Measured on 256 CUs, a
+  // whole step: 432 row tiles 153 us with four, 162 with eight; 162 tiles 75 with four, 73 with eight; at
+  // head_dim 64 (98 registers, 432 tiles) 101 with four, 98 with eight.
+  int n_cu = 0;
+  if (const int32_t rc = device_cu_count(&n_cu); rc != CA_OK) return rc;
+  const int waves = p.head_dim == 128 && items > n_cu ? 4 : kMaxWaves;
   hipStream_t s = static_cast<hipStream_t>(stream);
   switch (p.head_dim) {
     case 32: enqueue_attn_f32<32>(a, grid, waves, s); break;

@@ -323,11 +323,13 @@ int32_t launch_cache_write(const RopeGeom& g, int dtype, int32_t n_blocks, const
     a.pool = static_cast<uint8_t*>(pool);
     a.tok_stride = tok_stride; a.head_stride = head_stride;
     a.block_tokens = block_tokens; a.pages_per_block = pages_per_block;
-    // A CU holds two of these workgroups (250 registers).  Heads are shared out so that one round of 512 takes
-    // all of up to 2048 pages, and twice as many workgroups beyond.  Measured: 1480 pages in 370 workgroups 37.4 us, in 740 43;
+    // A CU holds two of these workgroups (250 registers).  Heads are shared out so that one round takes all of up to eight
+    // pages a CU, and twice as many workgroups beyond.  Measured on 256 CUs: 1480 pages in 370 workgroups 37.4 us, in 740 43;
     // 600 in 600 22.1, in 300 23.0; 7400 in 925 or more 196, in 555 217.
+    int n_cu = 0;
+    if (const int32_t rc = device_cu_count(&n_cu); rc != CA_OK) return rc;
     const int64_t all_pages = int64_t(pages_per_block) * n_blocks * g.heads;
-    const int target = all_pages > 1024 && all_pages <= 2048 ? 512 : 1024;
+    const int64_t target = all_pages > 4 * n_cu && all_pages <= 8 * n_cu ? 2 * n_cu : 4 * n_cu;
     const int64_t per_group = (all_pages + target - 1) / target;
     a.heads_per_group = int32_t(per_group < g.heads ? per_group : g.heads);
     const dim3 grid((unsigned)pages_per_block,
