@@ -198,7 +198,7 @@ def p_word(p_base, j):
 
 
 CAP = 4.0            # issue quanta per MFMA slot the scheduler may fill
-E_SPREAD = 54        # the 32 exponentials of a step are due by this slot
+E_SPREAD = 48        # the 32 exponentials of a step are due by this slot
 E_HARD = 56          # ... and issue by this one
 THRESH = "0x47800000"     # 2^16: a step's sum of 8 probabilities above this moves the reference
 K_BARRIER_SLOT = 32  # step 2: K(q+1) visible, slot of K(q) free
