@@ -446,7 +446,7 @@ def main() -> int:
                            % (C, "cascade_attn_forward_rope (Q rotated inside the attention kernel)" if fused_q else
                               "rope3d_apply(Q) + " + ("cascade_attn_forward" if args.share is None
                                                       else "cascade_attn_forward_share"))},
-        "roofline": {"bound": "mfma", "kernel": "attn_bf16_kernel<true>" if fused_q else "attn_bf16_kernel<false>", "achieved": achieved,
+        "roofline": {"bound": "mfma", "kernel": "attn_bf16_kernel<%s, true>" % ("true" if fused_q else "false"), "achieved": achieved,
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_TFLOPS,
                      "avg_launch_ms": attn_ms,
                      "traffic": ATTN_TRAFFIC_BYTES_C4 if (w.name == "c4_wan14b_cascade5" and
@@ -479,12 +479,14 @@ def main() -> int:
     # assumes 2.4 GHz; under a full MFMA load with toggling operands the chip clocks lower)
     probe = torch.empty(1 << 16, dtype=torch.uint8, device=dev)
     stream = torch.cuda.current_stream(dev).cuda_stream
-    rnd = B.mfma_microbench(1, 100000, probe.data_ptr(), probe.numel(), stream)
-    zer = B.mfma_microbench(0, 100000, probe.data_ptr(), probe.numel(), stream)
-    result["roofline"]["mfma_only_microbench"] = {
-        "random_operands": {"TFLOP/s": rnd[0], "clock_GHz": rnd[1]},
-        "zero_operands": {"TFLOP/s": zer[0], "clock_GHz": zer[1]},
-        "achieved_over_random_operands": achieved / rnd[0]}
+    # in both shapes the attention kernel's loops use; launches that fill the chip take 16x16x32
+    micro = {}
+    for shape, kind in (("16x16x32", 16), ("32x32x16", 0)):
+        rnd, zer = (B.mfma_microbench(kind + k, 100000, probe.data_ptr(), probe.numel(), stream) for k in (1, 0))
+        micro[shape] = {"random_operands": {"TFLOP/s": rnd[0], "clock_GHz": rnd[1]},
+                        "zero_operands": {"TFLOP/s": zer[0], "clock_GHz": zer[1]},
+                        "achieved_over_random_operands": achieved / rnd[0]}
+    result["roofline"]["mfma_only_microbench"] = micro
     # The other shapes and modes of the method, attention launch alone (events, a few launches
     # each): the headline workload in block-causal mode (Sec. 4.2) and as one device's share under
     # the paper's temporal parallelism (Sec. 3.3), the Wan-1.3B cascade in both modes, and the

@@ -304,7 +304,7 @@ int32_t layer_linear_bf16(const void* x_dev, const void* w_dev, void* y_dev, int
 
 int32_t ca_mfma_microbench(int32_t data_kind, int32_t trips, void* scratch_dev, size_t scratch_bytes,
                            void* hip_stream, double* tflops, double* clock_ghz) {
-  if ((data_kind != 0 && data_kind != 1) || trips < 1 || trips > (1 << 24) || !scratch_dev) return CA_EINVAL;
+  if ((data_kind & ~17) != 0 || trips < 1 || trips > (1 << 24) || !scratch_dev) return CA_EINVAL;
   return ca::run_mfma_microbench(data_kind, trips, scratch_dev, scratch_bytes, hip_stream, tflops, clock_ghz);
 }
 

@@ -290,3 +290,17 @@ def test_bf16_scores_of_minus_infinity(heads, low, high):
     got = Hn.gpu_forward(w, pool, q, [1], BI)[:, check]
     ref = np.concatenate(Hn.oracle_forward(w, q, k, v, [0], [1], BI, heads=check))
     Hn.assert_close(got, ref, "bf16", f"-inf scores {heads} heads keys {low}..{high}")
+
+
+def test_mfma_microbench_on_the_smaller_instruction():
+    """16x16x32: below the nominal peak and above half of it; zero operands are not slower than random ones."""
+    import torch
+    from paper_2511_20426_amd import binding as B
+    probe = torch.empty(1 << 16, dtype=torch.uint8, device="cuda:0")
+    rnd, zer = (B.mfma_microbench(16 + k, 20000, probe.data_ptr(), probe.numel(), torch.cuda.current_stream().cuda_stream) for k in (1, 0))
+    print(f"mfma only, 16x16x32: random {rnd[0]:.0f} TFLOP/s at {rnd[1]:.2f} GHz, zeros {zer[0]:.0f} TFLOP/s at {zer[1]:.2f} GHz", flush=True)
+    for t, c in (rnd, zer):
+        assert 1000.0 < t < 2600.0 and 1.0 < c < 2.6
+    assert zer[0] > 0.95 * rnd[0]
+    with pytest.raises(B.CascadeAttnError):
+        B.mfma_microbench(18, 10, probe.data_ptr(), probe.numel(), 0)
