@@ -45,8 +45,9 @@
  *          16*(c/2) + perm[8*(c%2) + e], perm = {0,1,2,3,8,9,10,11,4,5,6,7,12,13,14,15}
  *          (the order in which the matrix accumulators hand P to the next MFMA).
  *   Rows/tokens past the end of a block's last page are stored as zeros.
- * For bf16 the pool ends with a fixed scratch area (about 35 MB) that cascade_attn_forward uses
- * for partial results; forwards on one context must therefore not overlap on the GPU.
+ * For bf16 the pool ends with a fixed scratch area (about 35 MB) that forwards of any size may use
+ * for partial results (small ones too: their KV walks are cut so that they fill the chip); forwards on one
+ * context must therefore not overlap on the GPU, whatever their size.
  */
 #ifndef CASCADE_ATTN_H
 #define CASCADE_ATTN_H
@@ -209,7 +210,7 @@ int32_t cascade_attn_forward_rope(ca_ctx* ctx, const void* q_dev, int64_t q_tok_
  * and sets no memory: it enqueues the same kernel launches.  Nothing in the area has to start at
  * zero (every partial tile is written in full before it is read), and it keeps the last call's
  * contents.  All contexts of a process share one area per GPU: static-scratch forwards that overlap
- * on one GPU (different streams, or different contexts) race and must be ordered by the caller.
+ * on one GPU (different streams, or different contexts), of any size, race and must be ordered by the caller.
  * A forward whose split would need more than 256 partial tiles (possible only on a device with
  * more than 32 CUs per XCD) is refused with CA_ETOOBIG and nothing is enqueued.  The first call on
  * a device (or ca_create with a pool while that device is current) looks up the area's address

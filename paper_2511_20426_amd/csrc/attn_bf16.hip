@@ -57,7 +57,7 @@ constexpr int kRowsPerWg = 256;
 // dword per lane of `lanes` (a lane's entry is picked with v_readlane later), the rotation factors
 // as two vectors per lane.  Divisions by launch constants are a multiplication and a correction.
 struct AttnArgs {
-  const uint16_t* q;                   // [row, head, dim] with the strides below; unrotated for attn_bf16_kernel<true>
+  const uint16_t* q;                   // [row, head, dim] with the strides below; unrotated for attn_bf16_kernel<true, ..>
   uint16_t* o;
   const uint8_t* pool;
   float* partials;                     // [xcd][split item][chunk][kPartialFloats]
@@ -77,7 +77,7 @@ struct AttnArgs {
   float c;                             // log2(e) / sqrt(head_dim)
   float inv_cols, inv_tiles, inv_pages, inv_split, inv_split_items;
   int64_t q_tok_stride, q_head_stride;
-  // Rotary embedding of the queries (attn_bf16_kernel<true> only).  Angles are formed in revolutions:
+  // Rotary embedding of the queries (attn_bf16_kernel<true, ..> only).  Angles are formed in revolutions:
   // pair j turns by pos * freq[j] / 2pi; that factor is split into a 12-bit head and a tail so that
   // pos * head is exact in fp32 for pos < 4096 and only its fractional part meets the hardware
   // sin / cos (measured: cos and sin within 4.2e-7 of fp64 for every pos < 4096 and every pair).
@@ -522,8 +522,8 @@ int split_of_small_launch(int items_per_xcd, int cus_per_xcd, int items, int min
 
 // The loop on the 16x16x32 instruction draws less power a flop, the one on 32x32x16 needs fewer cycles: where most CUs
 // work at once and long enough, power decides.  Whole forwards, us, 32x32x16 / 16x16x32, by workgroups of a round x
-// pages of a walk: 171 x 259 563 / 536, 228 x 259 685 / 634, 200 x 14 50.4 / 49.3, 200 x 10 37.3 / 36.6; 152 x 259 515 / 520, 160 x 14
-// 46.6 / 47.1, 240 x 7 44.6 / 45.5, 240 x 5 36.1 / 36.7, 8 x 14 20.2 / 21.6.
+// pages of a walk: 171 x 259 545 / 528, 228 x 259 658 / 610, 228 x 43 135 / 129, 250 x 14 54.4 / 51.7, 200 x 10 41.1 / 40.6; 152 x 259 515 / 526,
+// 160 x 14 46.7 / 47.1, 240 x 5 35.9 / 36.4, 14 x 1 19.5 / 21.5.  Along the line a few go the other way by little: 200 x 14 48.3 / 49.1, 152 x 74 168 / 159.
 bool takes_core16(const AttnArgs& a, int max_pages, int n_cu) {
   const bool alone = a.full_items == 0;                        // all items cut
   const int64_t workgroups = int64_t(a.total_cols) * a.n_seg * (alone ? a.split : 1);

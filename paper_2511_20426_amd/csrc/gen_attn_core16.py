@@ -3,12 +3,12 @@
 fill the chip.  Walk, page traffic, barriers and scalar registers are that generator's.
 
 Why 16x16x32 and not 32x32x16: a launch that fills the chip is limited by power, and per flop the smaller
-shape moves half as many accumulator registers.  An MFMA-only loop over random operands reaches 1943 TFLOP/s with
-it against 1715 with 32x32x16 in one session, 2060 if four consecutive MFMAs share their accumulator (as QK does below).  The
+shape moves half as many accumulator registers.  An MFMA-only loop over random operands (mfma_peak.hip) reaches 2118..2203
+TFLOP/s with it, four consecutive MFMAs on one accumulator as QK has them below, against 1784..1876 with 32x32x16 in the same sessions.  The
 price is issue room (64 MFMAs a step for 32): a slot is dealt out by its own model (schedule16), and by it a step takes 1096
 cycles, 1024 of them of the matrix pipe: what is left over is vector work that finds no room.  14B step of five blocks 16.45 ->
 15.6 ms, 1.3B one block 688 -> 643 us, one device's share 2.91 -> 2.8 ms.  (Row sums taken by the matrix pipe, ones x P, would
-be 1 % faster, but of probabilities already rounded to bf16: a row with one heavy key was then off by up to 2.5e-3 as a whole.)
+be 1 to 1.5 % faster, but of probabilities already rounded to bf16: a row with one heavy key was then off by up to 2.5e-3 as a whole.)
 
 Pipeline (a "step" is 32 keys, a page is 4 steps; t counts steps):
     QK(t+1): 32 MFMAs  S_next = K_frag x Q                      (K fragments from LDS)
@@ -20,7 +20,7 @@ Keys in the accumulators.  A 16x16 accumulator tile gives lane group g (of 16 la
 step has two such tiles; their 16 rows are keys 0..7 and 16..23 (second tile: 8..15 and 24..31), so that what a
 lane group holds in both, keys 16 (g/2) + 4 (g%2) + {0..3, 8..11}, is one 16-byte chunk of a V row and P goes from accumulator
 to operand without movement.  The K rows a read touches then meet in pairs in an LDS bank; LDS has the room
-(31 % busy).
+(33 % busy, a third of that for these conflicts).
 
 The exponent reference m_ref of a row is lazy: it starts as the maximum of the row's first tile
 and moves only when it has to.  No maximum is taken in the loop; instead the 8 probabilities of a row that a
