@@ -227,7 +227,8 @@ NO_SCORE = "0xc4800000"   # -1024: first reference of a row whose first tile has
 
 def finite_reference_lines(m, tmp):
     """m = NO_SCORE where it is -inf (the difference to it would be NaN): such keys get weight 0, and the first score above moves
-    the reference as any other does."""
+    the reference as any other does.  (A score 126 or more below NO_SCORE, in log2 units, would then count for nothing: at that size
+    the bf16 operands alone leave it several units off.)"""
     return [f"v_mov_b32 {tmp}, {NO_SCORE}", f"v_cmp_gt_f32 vcc, 0xff7fffff, {m}", f"v_cndmask_b32 {m}, {m}, {tmp}, vcc"]
 
 
