@@ -45,6 +45,21 @@ def test_f32_waves_per_row_tile(heads, fpb, gh, gw, ni):
         Hn.assert_close(out, ref, "f32", f"f32 waves heads={heads} L={w.block_tokens} blocks={ni} mode={mode}")
 
 
+# ... and whose rows lie in line or not: pages just longer than a tile (every tile crosses into the next page), a little shorter than
+# two, whole tiles with a ragged last one; 480 items, whose second round is taken in reverse order.
+@pytest.mark.parametrize("head_dim", [32, 64, 128])
+@pytest.mark.parametrize("heads,fpb,gh,gw,page,nc,ni", [(2, 1, 7, 11, 17, 2, 1), (2, 1, 9, 13, 31, 1, 2), (1, 2, 8, 9, 64, 1, 2), (4, 2, 16, 20, 100, 1, 3)])
+def test_f32_tiles_across_pages(head_dim, heads, fpb, gh, gw, page, nc, ni):
+    w = W.small_variant(W.CONFIGS["c1_tiny_f32"], heads=heads, grid_h=gh, grid_w=gw, frames_per_block=fpb, head_dim=head_dim,
+                        rope_dims=DIMS[head_dim], page_tokens=page, n_cached=nc, n_inflight=ni, max_inflight=3)
+    cached, infl = list(range(nc)), list(range(nc, nc + ni))
+    q, k, v = W.draw_config(w, seed=25, scale=1.5)
+    pool = Hn.gpu_setup(w, k, v, cached, infl)
+    out = Hn.gpu_forward(w, pool, q, infl, CA)
+    ref = np.concatenate(Hn.oracle_forward(w, q, k, v, cached, infl, CA))
+    Hn.assert_close(out, ref, "f32", f"f32 across pages D={head_dim} L={w.block_tokens} page={page}")
+
+
 # fp32 attention, an infinite V in a block's last row: its dimension is infinite, all else finite.  (The tile that row is in is
 # filled up with keys that do not exist.)
 @pytest.mark.parametrize("head_dim", [32, 64, 128])
