@@ -168,9 +168,10 @@ constexpr int kAttnLds = 4 * kPageBytes + kRowsPerWg * 16;
 // cycles, the largest part left).  Whole steps: 15 workgroups with 20 pages each 72 -> 67 us, 300 with
 // 70..110 pages 383 -> 366 us; nothing at the 14B shape, where an item walks 407 pages.
 //
+// kTails: the loop that walks half of a short last page (gen_attn_core.py), picked by has_tails.
 // kCore16: which of the two main loops.  Both walk the same pages the same way; they differ in the matrix instruction, and
 // so in where a lane's part of Q, of the accumulators and of a row sum is.
-template <bool kRopeQ, bool kCore16>
+template <bool kRopeQ, bool kCore16, bool kTails>
 __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -339,32 +340,46 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
     const uint32_t xv0 = l15 * 256 + ((grp ^ l15) << 4);
     const uint32_t kidx = 16 * (grp >> 1) + 4 * (grp & 1);
     const uint32_t xl16 = 4 * (lane ^ 16), xl32 = 4 * (lane ^ 32);
-    asm volatile(
+#define CA_CORE16_OPERANDS \
+    : "=&{v[0:15]}"(o0), "=&{v[16:31]}"(o1), "=&{v[32:47]}"(o2), "=&{v[48:63]}"(o3), "=&{v[64:79]}"(o4), \
+    "=&{v[80:95]}"(o5), "={v[96:111]}"(o6), "={v[112:127]}"(o7), "=&{v148}"(l0), "=&{v149}"(l1), \
+    "=&{v150}"(l2), "=&{v151}"(l3), "=&{v184}"(negm0), "=&{v188}"(negm1), "=&{v192}"(negm2), "=&{v196}"(negm3) \
+    : "{a[128:143]}"(qt[0]), "{a[144:159]}"(qt[1]), "{a[160:175]}"(qt[2]), "{a[176:191]}"(qt[3]), \
+    [xk0] "v"(xk0), [xv0] "v"(xv0), [lane_off] "v"(lane_off), [tbl_lo] "v"(tbl_lo), [tbl_hi] "v"(tbl_hi), \
+    [kidx] "v"(kidx), [xl16] "v"(xl16), [xl32] "v"(xl32), \
+    [n_pages] "s"(n_pages), [n_kvb] "s"(n_kvb), [kb0] "s"(kb0), [pg0] "s"(pg0), \
+    [ppb] "s"(a.pages_per_block), [stride] "s"(stride), [last_valid] "s"(a.last_valid), \
+    [wave] "s"(wave), [lds0] "s"(lds0), [idle] "s"(uniform(row0 + wave * 64 - rows_end)) \
+    : "memory", "vcc", "scc", "m0", CA_CORE16_CLOBBERS
+    if constexpr (kTails)
+      asm volatile(
+#include "attn_core16_tails_gfx950.inc"
+          CA_CORE16_OPERANDS);
+    else
+      asm volatile(
 #include "attn_core16_gfx950.inc"
-      : "=&{v[0:15]}"(o0), "=&{v[16:31]}"(o1), "=&{v[32:47]}"(o2), "=&{v[48:63]}"(o3), "=&{v[64:79]}"(o4),
-        "=&{v[80:95]}"(o5), "={v[96:111]}"(o6), "={v[112:127]}"(o7), "=&{v148}"(l0), "=&{v149}"(l1),
-        "=&{v150}"(l2), "=&{v151}"(l3), "=&{v184}"(negm0), "=&{v188}"(negm1), "=&{v192}"(negm2), "=&{v196}"(negm3)
-      : "{a[128:143]}"(qt[0]), "{a[144:159]}"(qt[1]), "{a[160:175]}"(qt[2]), "{a[176:191]}"(qt[3]),
-        [xk0] "v"(xk0), [xv0] "v"(xv0), [lane_off] "v"(lane_off), [tbl_lo] "v"(tbl_lo), [tbl_hi] "v"(tbl_hi),
-        [kidx] "v"(kidx), [xl16] "v"(xl16), [xl32] "v"(xl32),
-        [n_pages] "s"(n_pages), [n_kvb] "s"(n_kvb), [kb0] "s"(kb0), [pg0] "s"(pg0),
-        [ppb] "s"(a.pages_per_block), [stride] "s"(stride), [last_valid] "s"(a.last_valid),
-        [wave] "s"(wave), [lds0] "s"(lds0), [idle] "s"(uniform(row0 + wave * 64 - rows_end))
-      : "memory", "vcc", "scc", "m0", CA_CORE16_CLOBBERS);
+          CA_CORE16_OPERANDS);
   } else {
     const uint32_t xo0 = l31 * 256 + ((hi ^ l15) << 4);    // row offset + swizzled chunk 0 (or 1 for hi)
     const uint32_t kidx = 4 * hi, xlane = 4 * (lane ^ 32);
-    asm volatile(
+#define CA_CORE_OPERANDS \
+    : "=&{v[0:15]}"(o0), "=&{v[16:31]}"(o1), "=&{v[32:47]}"(o2), "=&{v[48:63]}"(o3), "=&{v[64:79]}"(o4), \
+    "=&{v[80:95]}"(o5), "={v[96:111]}"(o6), "={v[112:127]}"(o7), "=&{v148}"(l0), "=&{v149}"(l1), \
+    "=&{v150}"(l2), "=&{v151}"(l3), "=&{v184}"(negm0), "=&{v200}"(negm1) \
+    : "{a[128:143]}"(qt[0]), "{a[144:159]}"(qt[1]), "{a[160:175]}"(qt[2]), "{a[176:191]}"(qt[3]), \
+    [xo0] "v"(xo0), [lane_off] "v"(lane_off), [tbl_lo] "v"(tbl_lo), [tbl_hi] "v"(tbl_hi), \
+    [kidx] "v"(kidx), [xlane] "v"(xlane), [n_pages] "s"(n_pages), [n_kvb] "s"(n_kvb), [kb0] "s"(kb0), [pg0] "s"(pg0), \
+    [ppb] "s"(a.pages_per_block), [stride] "s"(stride), [last_valid] "s"(a.last_valid), \
+    [wave] "s"(wave), [lds0] "s"(lds0) \
+    : "memory", "vcc", "scc", "m0", CA_CORE_CLOBBERS
+    if constexpr (kTails)
+      asm volatile(
+#include "attn_core_tails_gfx950.inc"
+          CA_CORE_OPERANDS);
+    else
+      asm volatile(
 #include "attn_core_gfx950.inc"
-      : "=&{v[0:15]}"(o0), "=&{v[16:31]}"(o1), "=&{v[32:47]}"(o2), "=&{v[48:63]}"(o3), "=&{v[64:79]}"(o4),
-        "=&{v[80:95]}"(o5), "={v[96:111]}"(o6), "={v[112:127]}"(o7), "=&{v148}"(l0), "=&{v149}"(l1),
-        "=&{v150}"(l2), "=&{v151}"(l3), "=&{v184}"(negm0), "=&{v200}"(negm1)
-      : "{a[128:143]}"(qt[0]), "{a[144:159]}"(qt[1]), "{a[160:175]}"(qt[2]), "{a[176:191]}"(qt[3]),
-        [xo0] "v"(xo0), [lane_off] "v"(lane_off), [tbl_lo] "v"(tbl_lo), [tbl_hi] "v"(tbl_hi),
-        [kidx] "v"(kidx), [xlane] "v"(xlane), [n_pages] "s"(n_pages), [n_kvb] "s"(n_kvb), [kb0] "s"(kb0), [pg0] "s"(pg0),
-        [ppb] "s"(a.pages_per_block), [stride] "s"(stride), [last_valid] "s"(a.last_valid),
-        [wave] "s"(wave), [lds0] "s"(lds0)
-      : "memory", "vcc", "scc", "m0", CA_CORE_CLOBBERS);
+          CA_CORE_OPERANDS);
   }
 
   asm volatile("" : "+s"(ap));
@@ -530,6 +545,12 @@ bool takes_core16(const AttnArgs& a, int max_pages, int n_cu) {
   return 3 * workgroups >= 2 * int64_t(n_cu) && max_pages / (alone ? a.split : 1) >= 10;
 }
 
+// Which launches take the loops with short pages: two steps instead of four are walked of a block's last page, and masked tiles find their code in
+// fewer places.  Whole forwards, us, without / with: 12 heads, five blocks of 1170 tokens (18 in the last page) 345 / 328, 40 heads of 180 (52)
+// 73 / 53.5, 40 of 390 (6) 64.5 / 56, 16 of 1683 (19) 148.8 / 143.3.  With more than 64 tokens in the last page both
+// loops walk the same steps and take the same time (55.0 / 55.3, 669 / 673).
+bool has_tails(const AttnArgs& a) { return a.last_valid <= 64; }
+
 // Fills the kernel arguments for one forward.  Splitting: `capacity` partial results fit in
 // the scratch area; with adapt the split is reduced until the partials fit, without it the split
 // the device's CU count asks for is kept and *partials_needed tells the caller how many it takes.
@@ -616,10 +637,10 @@ int32_t plan_attn_bf16(const AttnPlan& p, int variant, const void* q, void* out,
   return CA_OK;
 }
 
-template <bool kRopeQ, bool kCore16>
+template <bool kRopeQ, bool kCore16, bool kTails>
 int32_t enqueue_attn_bf16(const AttnArgs& a, void* stream) {
   const dim3 grid((unsigned)((a.full_items + a.split_items * a.split) * 8));
-  const auto kernel = attn_bf16_kernel<kRopeQ, kCore16>;
+  const auto kernel = attn_bf16_kernel<kRopeQ, kCore16, kTails>;
   hipLaunchKernelGGL(kernel, grid, dim3(256), kAttnLds, static_cast<hipStream_t>(stream), a);
   if (a.split > 1)
     hipLaunchKernelGGL(merge_partials_kernel<kCore16>, dim3((unsigned)(8 * a.split_items), kRowsPerWg / 32), dim3(256), 0,
@@ -629,10 +650,13 @@ int32_t enqueue_attn_bf16(const AttnArgs& a, void* stream) {
 
 template <bool kRopeQ>
 int32_t enqueue_attn_bf16(const AttnArgs& a, bool core16, void* stream) {
-  const KernelLds kernels[] = {{reinterpret_cast<const void*>(attn_bf16_kernel<kRopeQ, false>), kAttnLds},
-                               {reinterpret_cast<const void*>(attn_bf16_kernel<kRopeQ, true>), kAttnLds}};
-  if (const int32_t rc = ensure_dynamic_lds(kernels, 2, kRopeQ ? kLdsAttnRope : kLdsAttn); rc != CA_OK) return rc;
-  return core16 ? enqueue_attn_bf16<kRopeQ, true>(a, stream) : enqueue_attn_bf16<kRopeQ, false>(a, stream);
+  const KernelLds kernels[] = {{reinterpret_cast<const void*>(attn_bf16_kernel<kRopeQ, false, false>), kAttnLds},
+                               {reinterpret_cast<const void*>(attn_bf16_kernel<kRopeQ, false, true>), kAttnLds},
+                               {reinterpret_cast<const void*>(attn_bf16_kernel<kRopeQ, true, false>), kAttnLds},
+                               {reinterpret_cast<const void*>(attn_bf16_kernel<kRopeQ, true, true>), kAttnLds}};
+  if (const int32_t rc = ensure_dynamic_lds(kernels, 4, kRopeQ ? kLdsAttnRope : kLdsAttn); rc != CA_OK) return rc;
+  if (has_tails(a)) return core16 ? enqueue_attn_bf16<kRopeQ, true, true>(a, stream) : enqueue_attn_bf16<kRopeQ, false, true>(a, stream);
+  return core16 ? enqueue_attn_bf16<kRopeQ, true, false>(a, stream) : enqueue_attn_bf16<kRopeQ, false, false>(a, stream);
 }
 
 }  // namespace

@@ -94,20 +94,26 @@ S_LDS0 = 74
 S_ADDRV = 76         # 76,77
 S_RG = 78            # 78,79: nonzero if the tile just produced needs its tail masked
 S_VLP = 80           # 80..87: per 32-key step of a page, (-1 if a block's last page is ragged there, 0)
+# with short pages
+S_RET, S_VALID = 88, 90        # 88,89: where the shared out-of-line code returns to; keys of the tile to mask that exist
+S_SPECIAL, S_SHORT = 91, 92    # the walk ends or the next page is short; page of a block that is short, -1 without
+XOVL = 144           # v144, v145: LDS address of V chunk pairs of the last step walked
 
 
 class Emitter:
-    def __init__(self):
+    def __init__(self, parent=None):
         self.lines = []
         self.cold = []       # out-of-line blocks, appended after the loop
+        self.shared = parent.shared if parent else {}      # out-of-line code of a loop with short pages, per tile parity
+        self.root = parent.root if parent else self
         self.uid = 0
 
     def e(self, s):
         self.lines.append(s)
 
     def label(self, stem):
-        self.uid += 1
-        return f"{stem}_{self.uid}_%="
+        self.root.uid += 1
+        return f"{stem}_{self.root.uid}_%="
 
 
 # ---------------------------------------------------------------------------- building blocks
@@ -122,7 +128,7 @@ def mfma_pv(mt, nt, frag, p_base, kk):
     return f"v_mfma_f32_32x32x16_bf16 {o}, {V(FR + 4 * (frag % 8), 4)}, {V(p_base + 4 * (2 * nt + kk), 4)}, {o}"
 
 
-def frag_source(R, par, f):
+def frag_source(R, par, f, tails=False, short=False):
     """(address register, immediate) of operand fragment f of step (R, par)."""
     if f < 8:                                   # K fragment of step t+1
         if R < 3:
@@ -130,6 +136,10 @@ def frag_source(R, par, f):
         return XOK + f, (1 - par) * PAGE        # first step of page q+1
     g = f - 8
     mt, kk = g & 3, g >> 2                      # an accumulator tile is revisited 8 MFMAs later
+    if R == 0 and tails:                        # V of the last step of page q-1, whichever that was
+        return XOVL + kk, (1 - par) * PAGE + mt * 8192
+    if short:                                   # the step after a short page's first
+        return XOV + kk, par * PAGE + mt * 8192
     if R == 0:                                  # V of the last step of page q-1
         return XOV + 6 + kk, (1 - par) * PAGE + mt * 8192
     return XOV + 2 * (R - 1) + kk, par * PAGE + mt * 8192
@@ -192,13 +202,14 @@ def page_load_lines(i, lds_slot_off, which):
             f"global_load_lds_dwordx4 {V(DMAOFF + i)}, s[{a}:{a + 1}]"]
 
 
-def page_load_atoms(loads, ready, hard):
+def page_load_atoms(loads, ready, hard, tight=False):
     """loads: (page_load_lines, slot due by) of a step in issue order.  M0 is written in an earlier slot than its load, so that an
-    MFMA stands between, and behind the load before."""
+    MFMA stands between, and behind the load before.  tight: so many that each has to leave a slot for every one behind it."""
     atoms, prev = [], None
-    for (m0, load), due in loads:
-        at = Atom([m0], max(ready - 1, 0), due - 1, [prev] if prev else [], 0, hard=hard - 1)
-        prev = Atom([load], ready, due, [at], 1, tag="load", hard=hard)
+    for k, ((m0, load), due) in enumerate(loads):
+        last = hard - (len(loads) - 1 - k) if tight else hard
+        at = Atom([m0], max(ready - 1, 0), due - 1, [prev] if prev else [], 0, hard=last - 1)
+        prev = Atom([load], ready, due, [at], 1, tag="load", hard=last)
         atoms += [at, prev]
     return atoms
 
@@ -283,13 +294,37 @@ K_BARRIER_SLOT = 16  # step 2: K(q+1) visible, slot of K(q) free
 N_KLOADS_R2 = 2      # of the 8 loads of K(q+2), how many issue in step 2 (the rest in step 3)
 
 
-def build_step(R, par):
-    """One 32-key step as a list of 32 slots: (MFMA line, [lines issued after it])."""
+def barriers(R, short, tail, k_barrier_slot):
+    """Waits and barriers of a step, into its slots' tails."""
+    if R == 0 and short:                                   # V(q) and K(q+1), the only ones on their way, visible, K(q)'s slot free; V(q-1)'s
+        tail[k_barrier_slot - 1] += ["s_waitcnt vmcnt(0)", "s_barrier"]
+        tail[-1] += ["s_barrier"]
+    elif R == 0:                                           # before step 1: V(q) visible, V(q-1)'s slot free
+        tail[-1] += ["s_waitcnt vmcnt(@VMCNT_V@)", "s_barrier"]
+    if R == 2:
+        tail[k_barrier_slot - 1] += ["s_waitcnt vmcnt(@VMCNT_K@)", "s_barrier"]
+
+
+def last_step_atoms(core, pe, last_sub, hard):
+    """What the last step of a page leaves for a loop with short pages: where its V rows are, and whether the branch at the end of the page
+    has to look closer."""
+    moves = [f"v_mov_b32 {V(core.XOVL + k)}, {V(core.XOV + core.XOV_STRIDE * last_sub + k)}" for k in range(core.XOV_STRIDE)]
+    look = Atom([f"s_cmp_eq_u32 s{S_PGCUR}, s{S_SHORT}", f"s_cselect_b32 s{S_SPECIAL}, 1, 0",
+                 f"s_cmp_eq_u32 s{S_NLEFT}, 0", f"s_cselect_b32 s{S_SPECIAL}, 1, s{S_SPECIAL}"], 0, hard - 2, [pe], 0, hard=hard)
+    return [Atom([m], 0, hard - 4, hard=hard) for m in moves] + [look]
+
+
+def build_step(R, par, tails=False, short=False):
+    """One 32-key step as a list of 32 slots: (MFMA line, [lines issued after it]).  short: steps 0 and 3 of a short page."""
     cur, nxt = ("A", "B") if R % 2 == 0 else ("B", "A")
     s_cur, s_next = S_TILE[cur], S_TILE[nxt]
     p_prev, p_cur = (P_TILE["B"], P_TILE["A"]) if R % 2 == 0 else (P_TILE["A"], P_TILE["B"])
     nR, npar = ((R + 1) & 3, par if R < 3 else 1 - par)
-    cold, back = f"COLD_{R}_{par}_%=", f"BACK_{R}_{par}_%="
+    if short and R == 0:
+        nR = 3
+        npar = par
+    of = "S" if short else ""
+    cold, back = f"COLD{of}_{R}_{par}_%=", f"BACK{of}_{R}_{par}_%="
 
     mfma, head, tail = [None] * 32, [[] for _ in range(32)], [[] for _ in range(32)]
     for i in range(32):
@@ -301,15 +336,12 @@ def build_step(R, par):
             mfma[i] = mfma_pv(g & 3, nt, f, p_prev, g >> 2)
         if nt == 0:                                        # operand prefetch, D_AHEAD pairs ahead
             fa = f + D_AHEAD
-            src = frag_source(R, par, fa) if fa < 16 else frag_source(nR, npar, fa - 16)
+            src = frag_source(R, par, fa, tails, short and R == 3) if fa < 16 else frag_source(nR, npar, fa - 16, tails)
             head[i].append(ds_read_frag(fa % 16, src))
         # what must precede the next MFMA: every other pair waits for its two fragments
         if (i + 1) % 4 == 0:
             tail[i].append(f"s_waitcnt lgkmcnt({D_AHEAD - 2})")
-    if R == 0:                                             # before step 1: V(q) visible, V(q-1)'s slot free
-        tail[31] += ["s_waitcnt vmcnt(@VMCNT_V@)", "s_barrier"]
-    if R == 2:
-        tail[K_BARRIER_SLOT - 1] += ["s_waitcnt vmcnt(@VMCNT_K@)", "s_barrier"]
+    barriers(R, short, tail, K_BARRIER_SLOT)
 
     atoms = []
     # row sums of the previous step join the running sums; this step's start afresh
@@ -358,12 +390,18 @@ def build_step(R, par):
                                   for i in range(N_KLOADS_R2)], K_BARRIER_SLOT, 29)
     if R == 3:
         n = 8 - N_KLOADS_R2
-        atoms += page_load_atoms([(page_load_lines(N_KLOADS_R2 + i, par * PAGE, 0), 2 + (i * 26) // n) for i in range(n)], 0, 29)
+        if short:                                          # V(q+1), then K(q+2)
+            atoms += page_load_atoms([(page_load_lines(i % 8, par * PAGE if i >= 8 else VRING + (1 - par) * PAGE, i < 8), 2 + (i * 26) // 16)
+                                      for i in range(16)], 0, 29, tight=True)
+        else:
+            atoms += page_load_atoms([(page_load_lines(N_KLOADS_R2 + i, par * PAGE, 0), 2 + (i * 26) // n) for i in range(n)], 0, 29)
         # page-in-block counters of pages q and q+1 move on; one page less to go
         pe = Atom([f"s_mov_b32 s{S_PGCUR}, s{S_PGNEXT}", f"s_add_u32 s{S_T}, s{S_PGNEXT}, 1",
                    f"s_cmp_eq_u32 s{S_T}, s{S_P}", f"s_cselect_b32 s{S_PGNEXT}, 0, s{S_T}",
                    f"s_sub_u32 s{S_NLEFT}, s{S_NLEFT}, 1"], 0, 20, [rag], 1, hard=29)
         atoms.append(pe)
+        if tails:
+            atoms += last_step_atoms(CORE, pe, 1 if short else 3, 29)
 
     fixed = [2.0 + sum(quanta(l) for l in head[i] + tail[i]) for i in range(32)]
     placed = schedule(fixed, atoms, CAP)
@@ -380,20 +418,13 @@ def build_step(R, par):
     return slots, (s_cur, s_next, p_cur, cold, back, (S_VLAST + (R + 1 if R < 3 else 0)))
 
 
-def emit_cold(E, s_cur, s_next, p_cur, cold, back, valid_sreg):
-    """Out-of-line end of a step, entered when some lane's row sum of the step crossed THRESH
-    (vcc) or the tile just produced needs its ragged tail masked (s[S_RG]).
-
-    Moving the reference: the probabilities of the step were formed against a reference that
+def rescale_lines(s_cur, s_next, p_cur):
+    """Moving the reference: the probabilities of the step were formed against a reference that
     turned out too low (they may even have overflowed), so they are formed again from the S tile,
     which is still in registers: the row maximum relative to the old reference gives the shift
     delta >= 0; row sums and accumulators (all from earlier steps) are scaled by 2^-delta, the
     tile just produced and the -m_ref operand move by delta."""
-    c = E.cold
-    skip_ovf, done = E.label("NOOVF"), E.label("CDONE")
-    c.append(f"{cold}:")
-    c.append("s_nop 15\ns_nop 15\ns_nop 15")            # every MFMA issued so far has written back
-    c.append(f"s_cbranch_vccz {skip_ovf}")
+    c = []
     for nt in range(2):
         b = s_cur + 16 * nt
         m, other, delta, alpha = V(MX[nt]), V(RT[3]), V(RT[4]), V(RT[6])
@@ -428,25 +459,87 @@ def emit_cold(E, s_cur, s_next, p_cur, cold, back, valid_sreg):
         for i in range(16):                              # -m_ref operand and the tile just produced
             c.append(f"v_sub_f32 {V(NT[nt] + i)}, {V(NT[nt] + i)}, {delta}")
             c.append(f"v_sub_f32 {V(s_next + 16 * nt + i)}, {V(s_next + 16 * nt + i)}, {delta}")
+    return c
+
+
+def emit_cold(E, s_cur, s_next, p_cur, cold, back, valid_sreg, core=None):
+    """Out-of-line end of a step, entered when some lane's row sum of the step crossed THRESH
+    (vcc) or the tile just produced needs its ragged tail masked (s[S_RG]; its products came early in the step and
+    have been written back)."""
+    core = core or CORE
+    c = E.cold
+    skip_ovf, done = E.label("NOOVF"), E.label("CDONE")
+    c.append(f"{cold}:")
+    c.append(f"s_cbranch_vccz {skip_ovf}")
+    c.append("s_nop 15\ns_nop 15\ns_nop 15")            # every MFMA issued so far has written back
+    c.extend(core.rescale_lines(s_cur, s_next, p_cur))
     c.append(f"{skip_ovf}:")
     c.append(f"s_cmp_eq_u32 s{S_RG}, 0")
     c.append(f"s_cbranch_scc1 {done}")
     sub_e = Emitter()
-    emit_mask(sub_e, s_next, valid_sreg)
+    core.emit_mask(sub_e, s_next, valid_sreg)
     c.extend(sub_e.lines)
     c.append(f"{done}:")
     c.append("s_nop 7")
     c.append(f"s_branch {back}")
 
 
-def emit_step(E, R, par, vmcnt, core):
-    slots, cold_args = core.build_step(R, par)
-    E.e(f"; ---- step R={R} parity={par}")
+def emit_cold_shared(E, s_cur, s_next, p_cur, cold, back, valid_sreg, core):
+    """The same for a loop with short pages: a few lines per step that lead to one copy of the code per tile parity (eight to twelve copies
+    were each fetched anew by a short walk: 1500 cycles a masked tile)."""
+    mask, over, pc = f"MASK_{s_cur}_%=", f"OVER_{s_cur}_%=", E.label("PC")
+    E.cold += [f"{cold}:", f"s_getpc_b64 s[{S_RET}:{S_RET + 1}]", f"{pc}:", f"s_sub_u32 s{S_RET}, s{S_RET}, {pc}-{back}",
+               f"s_subb_u32 s{S_RET + 1}, s{S_RET + 1}, 0", f"s_mov_b32 s{S_VALID}, s{valid_sreg}",
+               f"s_cbranch_vccnz {over}", f"s_branch {mask}"]
+    if s_cur in E.shared:
+        return
+    sub_e = Emitter()
+    core.emit_mask(sub_e, s_next, S_VALID)
+    E.shared[s_cur] = ([f"{over}:", "s_nop 15\ns_nop 15\ns_nop 15"] + core.rescale_lines(s_cur, s_next, p_cur) +
+                       [f"s_cmp_eq_u32 s{S_RG}, 0", "s_nop 7", f"s_cbranch_scc0 {mask}", f"s_setpc_b64 s[{S_RET}:{S_RET + 1}]",
+                        f"{mask}:"] + sub_e.lines + [f"s_setpc_b64 s[{S_RET}:{S_RET + 1}]"])
+
+
+def emit_step(E, R, par, vmcnt, core, tails=False, short=False):
+    slots, cold_args = core.build_step(R, par, tails, short)
+    E.e(f"; ---- step R={R} parity={par}{' of a short page' if short else ''}")
     for m, lines in slots:
         E.e(m)
         for ln in lines:
             E.e(ln.replace("@VMCNT_V@", str(vmcnt[0])).replace("@VMCNT_K@", str(vmcnt[1])))
-    core.emit_cold(E, *cold_args)
+    (emit_cold_shared if tails else emit_cold)(E, *cold_args, core)
+
+
+def emit_pages_with_tails(E, stem, body, exits):
+    """The page loop with short pages: body(E, par, short) emits a page.  A page whose end has to be looked at closer (the walk is over or the next
+    page is short) leads out of line."""
+    top, spec, short = ([f"{stem}{x}{par}_%=" for par in range(2)] for x in ("TOP", "SPEC", "SHORT"))
+
+    def page_end(F, par):
+        F.e(f"s_cmp_lg_u32 s{S_SPECIAL}, 0")
+        F.e("s_nop 0")
+        F.e(f"s_cbranch_scc1 {spec[par]}")
+
+    E.e(f"s_cmp_eq_u32 s{S_PGCUR}, s{S_SHORT}")
+    E.e("s_nop 0")
+    E.e(f"s_cbranch_scc1 {short[0]}")
+    for par in range(2):
+        E.e(f"{top[par]}:")
+        body(E, par, False)
+        page_end(E, par)
+    E.e(f"s_branch {top[0]}")
+    for par in range(2):
+        F = Emitter(E)
+        F.e(f"{spec[par]}:")
+        F.e(f"s_cmp_eq_u32 s{S_NLEFT}, 0")
+        F.e("s_nop 0")
+        F.e(f"s_cbranch_scc1 {exits[par]}")
+        F.e(f"s_branch {short[1 - par]}")
+        F.e(f"{short[par]}:")
+        body(F, par, True)
+        page_end(F, par)
+        F.e(f"s_branch {top[1 - par]}")
+        E.cold += F.lines + F.cold
 
 
 def wait_counts(core=None):
@@ -473,13 +566,13 @@ def wait_counts(core=None):
     return vm_v, vm_k
 
 
-def emit_drain(E, par_last):
-    """PV of the final step: V page (parity par_last), keys 96..127, P tile B."""
+def emit_drain(E, par_last, tails=False):
+    """PV of the final step: V page (parity par_last), keys 96..127 (or of the last step walked), P tile B."""
     for nt in range(2):                                   # row sums of the final step
         E.e(f"v_add_f32 {V(LACC + 2 * nt)}, {V(LACC + 2 * nt)}, {V(TS[nt])}")
     for g in range(8):
         mt, kk = g & 3, g >> 2
-        E.e(f"ds_read_b128 {V(FR + 4 * g, 4)}, {V(XOV + 6 + kk)} offset:{par_last * PAGE + mt * 8192}")
+        E.e(f"ds_read_b128 {V(FR + 4 * g, 4)}, {V((XOVL if tails else XOV + 6) + kk)} offset:{par_last * PAGE + mt * 8192}")
     E.e("s_waitcnt lgkmcnt(0)")
     for g in range(8):
         for nt in range(2):
@@ -532,13 +625,17 @@ def emit_results(E):
         E.e(f"v_accvgpr_read_b32 {V(r)}, {A(r)}")
 
 
-CORE = SimpleNamespace(SLOTS=32, K_BARRIER_SLOT=K_BARRIER_SLOT, build_step=build_step, emit_cold=emit_cold, emit_drain=emit_drain,
+CORE = SimpleNamespace(XOV=XOV, XOVL=XOVL, XOV_STRIDE=2, rescale_lines=rescale_lines, emit_mask=emit_mask, SLOTS=32, K_BARRIER_SLOT=K_BARRIER_SLOT, build_step=build_step, emit_cold=emit_cold, emit_drain=emit_drain,
                        emit_operand_setup=emit_operand_setup, emit_clear=emit_clear, emit_first_tile=emit_first_tile,
                        emit_first_reads=emit_first_reads, emit_results=emit_results)
 
 
-def generate(core=None):
-    """The whole block; what depends on the shape of the matrix instruction comes from `core`."""
+def generate(core=None, tails=False):
+    """The whole block; what depends on the shape of the matrix instruction comes from `core`.  tails: the loop with short pages, for
+    launches whose blocks end in a page of 64 tokens or less: of that page two steps are walked instead of four, and one copy of
+    the out-of-line code serves all steps of a parity.  A short page has its two steps (0 and 3 of the page loop, the second with the V rows of
+    the first) out of line: V(q), K(q+1) are awaited together in the middle of the first, all loads of a page pair
+    issue in the second."""
     core = core or CORE
     E = Emitter()
     # ---- set-up: inputs to fixed registers
@@ -571,6 +668,9 @@ def generate(core=None):
     E.e(f"s_cselect_b32 s{S_PGNEXT}, 0, s{S_T}")
     E.e(f"s_mov_b32 s{S_KKB}, %[kb0]")
     E.e(f"s_mov_b32 s{S_KPG}, %[pg0]")
+    if tails:
+        E.e(f"s_cmp_le_u32 s{S_LASTV}, 64")
+        E.e(f"s_cselect_b32 s{S_SHORT}, s{S_PM1}, -1")
     # ---- K(0) and V(0) are in flight already (requested by the code around this block, oldest first);
     # K(1) joins them, the accumulators are cleared meanwhile; wait for the first two, publish
     for grp in page_advance_lines():
@@ -587,30 +687,39 @@ def generate(core=None):
     done = E.label("DONE")
     vmcnt = wait_counts(core)
     if hasattr(core, "emit_idle"):
-        core.emit_idle(E, done, vmcnt)
+        core.emit_idle(E, done, vmcnt, tails)
     core.emit_first_tile(E)
     core.emit_first_reads(E)
 
     # ---- main loop, two pages per trip (ring parity is compile-time)
     loop, exit_even, exit_odd = E.label("LOOP"), E.label("EXIT_EVEN"), E.label("EXIT_ODD")
-    E.e(f"{loop}:")
-    for par in range(2):
-        for R in range(4):
-            emit_step(E, R, par, vmcnt, core)
-        E.e(f"s_cmp_eq_u32 s{S_NLEFT}, 0")
-        E.e("s_nop 0")
-        E.e(f"s_cbranch_scc1 {exit_even if par == 0 else exit_odd}")
-    E.e(f"s_branch {loop}")
+    if tails:
+        for k in range(core.XOV_STRIDE):                   # (the first step multiplies P = 0)
+            E.e(f"v_mov_b32 {V(core.XOVL + k)}, {V(core.XOV + 3 * core.XOV_STRIDE + k)}")
+
+        def page(F, par, short):
+            for R in (0, 3) if short else range(4):
+                emit_step(F, R, par, vmcnt, core, True, short)
+        emit_pages_with_tails(E, "L", page, (exit_even, exit_odd))
+    else:
+        E.e(f"{loop}:")
+        for par in range(2):
+            for R in range(4):
+                emit_step(E, R, par, vmcnt, core)
+            E.e(f"s_cmp_eq_u32 s{S_NLEFT}, 0")
+            E.e("s_nop 0")
+            E.e(f"s_cbranch_scc1 {exit_even if par == 0 else exit_odd}")
+        E.e(f"s_branch {loop}")
     E.e(f"{exit_even}:")
     E.e("s_waitcnt lgkmcnt(0)")
-    core.emit_drain(E, 0)
+    core.emit_drain(E, 0, tails)
     E.e(f"s_branch {done}")
     E.e(f"{exit_odd}:")
     E.e("s_waitcnt lgkmcnt(0)")
-    core.emit_drain(E, 1)
+    core.emit_drain(E, 1, tails)
     E.e(f"s_branch {done}")
     # ---- out-of-line blocks
-    for ln in E.cold:
+    for ln in E.cold + [x for block in E.shared.values() for x in block]:
         E.e(ln)
     E.e(f"{done}:")
     E.e("s_waitcnt vmcnt(0)")                              # trailing (unused) page loads have landed
@@ -619,7 +728,7 @@ def generate(core=None):
     return E.lines
 
 
-def write_include(out_path, lines, clob, macro):
+def write_lines(out_path, lines):
     text = []
     for ln in lines:
         for part in ln.split("\n"):
@@ -629,18 +738,24 @@ def write_include(out_path, lines, clob, macro):
         f.write(by)
         for t in text:
             f.write('"' + t.replace("\\", "\\\\").replace('"', '\\"') + '\\n"\n')
+    print(f"{out_path}: {len(text)} lines")
+    return by
+
+
+def write_include(out_path, lines, clob, macro):
+    by = write_lines(out_path, lines)
     with open(out_path.replace("_gfx950.inc", "_clobbers.inc"), "w") as f:
         f.write(f"{by}#define {macro} \\\n")
         for i in range(0, len(clob), 12):
             chunk = ", ".join(f'"{c}"' for c in clob[i:i + 12])
             f.write("  " + chunk + (", \\\n" if i + 12 < len(clob) else "\n"))
-    print(f"{out_path}: {len(text)} lines")
 
 
 def main(out_path):
     # registers the block uses beyond its operands (v148..v151 are outputs)
     clob = [f"v{i}" for i in range(128, 256) if not 148 <= i <= 151 and i not in (184, 200)] + [f"a{i}" for i in range(0, 128)] + [f"s{i}" for i in range(36, 96)]
     write_include(out_path, generate(), clob, "CA_CORE_CLOBBERS")
+    write_lines(out_path.replace("_gfx950", "_tails_gfx950"), generate(tails=True))
 
 
 if __name__ == "__main__":

@@ -56,13 +56,15 @@ import sys
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 import gen_attn_core as base  # noqa: E402
 from gen_attn_core import (A, FR, P_TILE, PAGE, S_LDS0, S_NLEFT, S_P, S_PGCUR, S_PGNEXT, S_PM1, S_RG, S_T, S_TILE,  # noqa: E402
-                           S_VLAST, S_VLP, V, VRING, Emitter, page_advance_lines, page_load_atoms, page_load_lines, v_address_lines)
+                           S_VLAST, S_VLP, V, VRING, Emitter, page_advance_lines, page_load_atoms, page_load_lines, v_address_lines,
+                           barriers, emit_pages_with_tails, last_step_atoms)
 from issue_sched import Atom, is_vector, schedule16, split_cost  # noqa: E402
 
 QT = 4               # query tiles of 16 per wave
 SLOTS = 64           # MFMAs of a step: 32 QK, 32 PV
 
 XOK, XOV = 128, 132
+XOVL, XOV_STRIDE = 136, 1      # with short pages: LDS address in the V ring for the last step walked; registers of a step's
 LACC = 148           # 148..151: running row sums per query tile
 TS = [152, 153, 154, 155]      # row sums of the current step
 NT = [184 + 4 * qt for qt in range(QT)]      # -m_ref of the tile's query, four times: C operand of a tile's first MFMA
@@ -106,11 +108,15 @@ def k_source(page_sub, par, f):
     return XOK + (ks ^ (2 * kt)), par * PAGE + page_sub * 8192 + kt * 2048
 
 
-def frag_source(R, par, f):
+def frag_source(R, par, f, tails=False, short=False):
     """(address register, immediate) of operand fragment f of step (R, par): 0..7 K, 8..15 V."""
     if f < 8:                                   # K fragment of step t+1
         return k_source(R + 1, par, f) if R < 3 else k_source(0, 1 - par, f)   # (first step of page q+1)
     dt = f - 8
+    if R == 0 and tails:                        # V of the last step of page q-1, whichever that was
+        return XOVL, (1 - par) * PAGE + dt * 4096
+    if short:                                   # the step after a short page's first
+        return XOV, par * PAGE + dt * 4096
     if R == 0:                                  # V of the last step of page q-1
         return XOV + 3, (1 - par) * PAGE + dt * 4096
     return XOV + R - 1, par * PAGE + dt * 4096
@@ -213,27 +219,27 @@ K_READS = {0: 38, 1: 41, 2: 45, 3: 48, 4: 53, 5: 56, 6: 60}
 WAITS = {15: 0, 31: 0, 47: 3, 63: 3}
 
 
-def build_step(R, par):
-    """One 32-key step as a list of SLOTS slots: (MFMA line, [lines issued after it])."""
+def build_step(R, par, tails=False, short=False):
+    """One 32-key step as a list of SLOTS slots: (MFMA line, [lines issued after it]).  short: steps 0 and 3 of a short page."""
     cur, nxt = ("A", "B") if R % 2 == 0 else ("B", "A")
     s_cur, s_next = S_TILE[cur], S_TILE[nxt]
     p_prev, p_cur = (P_TILE["B"], P_TILE["A"]) if R % 2 == 0 else (P_TILE["A"], P_TILE["B"])
     nR, npar = ((R + 1) & 3, par if R < 3 else 1 - par)
-    cold, back = f"COLD_{R}_{par}_%=", f"BACK_{R}_{par}_%="
+    if short and R == 0:
+        nR, npar = 3, par
+    of = "S" if short else ""
+    cold, back = f"COLD{of}_{R}_{par}_%=", f"BACK{of}_{R}_{par}_%="
 
     head, tail = [[] for _ in range(SLOTS)], [[] for _ in range(SLOTS)]
     mfma = [mfma_qk(s_next, *x) for x in qk_order()] + pv_order(p_prev)
     head[1].append(ds_read_frag(7, frag_source(R, par, 7)))
     for f, at in V_READS.items():
-        head[at].append(ds_read_frag(f, frag_source(R, par, f)))
+        head[at].append(ds_read_frag(f, frag_source(R, par, f, tails, short and R == 3)))
     for f, at in K_READS.items():
         head[at].append(ds_read_frag(f, frag_source(nR, npar, f)))
     for at, n in WAITS.items():
         tail[at].append(f"s_waitcnt lgkmcnt({n})")
-    if R == 0:                                             # before step 1: V(q) visible, V(q-1)'s slot free
-        tail[SLOTS - 1] += ["s_waitcnt vmcnt(@VMCNT_V@)", "s_barrier"]
-    if R == 2:
-        tail[K_BARRIER_SLOT - 1] += ["s_waitcnt vmcnt(@VMCNT_K@)", "s_barrier"]
+    barriers(R, short, tail, K_BARRIER_SLOT)
 
     atoms = []
     # row sums of the previous step join the running sums; this step's start afresh
@@ -280,12 +286,18 @@ def build_step(R, par):
                                   for i in range(N_KLOADS_R2)], K_BARRIER_SLOT, 55)
     if R == 3:
         n = 8 - N_KLOADS_R2
-        atoms += page_load_atoms([(page_load_lines(N_KLOADS_R2 + i, par * PAGE, 0), 4 + (i * 52) // n) for i in range(n)], 0, 55)
+        if short:                                          # V(q+1), then K(q+2)
+            atoms += page_load_atoms([(page_load_lines(i % 8, par * PAGE if i >= 8 else VRING + (1 - par) * PAGE, i < 8), 4 + (i * 50) // 16)
+                                      for i in range(16)], 0, 55, tight=True)
+        else:
+            atoms += page_load_atoms([(page_load_lines(N_KLOADS_R2 + i, par * PAGE, 0), 4 + (i * 52) // n) for i in range(n)], 0, 55)
         # page-in-block counters of pages q and q+1 move on; one page less to go
         pe = Atom([f"s_mov_b32 s{S_PGCUR}, s{S_PGNEXT}", f"s_add_u32 s{S_T}, s{S_PGNEXT}, 1",
                    f"s_cmp_eq_u32 s{S_T}, s{S_P}", f"s_cselect_b32 s{S_PGNEXT}, 0, s{S_T}",
                    f"s_sub_u32 s{S_NLEFT}, s{S_NLEFT}, 1"], 0, 40, [rag], 1, hard=55)
         atoms.append(pe)
+        if tails:
+            atoms += last_step_atoms(sys.modules[__name__], pe, 1 if short else 3, 55)
 
     fixed = [split_cost(head[i] + tail[i]) for i in range(SLOTS)]
     placed = schedule16(fixed, atoms, CAP)
@@ -304,20 +316,9 @@ def build_step(R, par):
     return slots, (s_cur, s_next, p_cur, cold, back, (S_VLAST + (R + 1 if R < 3 else 0)))
 
 
-def emit_cold(E, s_cur, s_next, p_cur, cold, back, valid_sreg):
-    """Out-of-line end of a step, entered when some lane's row sum of the step crossed THRESH
-    (vcc) or the tile just produced needs its ragged tail masked (s[S_RG]).
-
-    Moving the reference: the probabilities of the step were formed against a reference that
-    turned out too low (they may even have overflowed), so they are formed again from the S tile,
-    which is still in registers: the row maximum relative to the old reference gives the shift
-    delta >= 0; row sums and accumulators (all from earlier steps) are scaled by 2^-delta, the
-    tile just produced and the -m_ref operand move by delta."""
-    c = E.cold
-    skip_ovf, done = E.label("NOOVF"), E.label("CDONE")
-    c.append(f"{cold}:")
-    c.append("s_nop 15\ns_nop 15\ns_nop 15")            # every MFMA issued so far has written back
-    c.append(f"s_cbranch_vccz {skip_ovf}")
+def rescale_lines(s_cur, s_next, p_cur):
+    """As gen_attn_core's: the reference moves, the step's probabilities are formed again, what earlier steps left is scaled."""
+    c = []
     for qt in range(QT):
         m, delta, alpha = V(MX[qt]), V(MX[qt]), V(RT[6])
         regs = row_regs(s_cur, qt)
@@ -349,29 +350,21 @@ def emit_cold(E, s_cur, s_next, p_cur, cold, back, valid_sreg):
             c.append(f"v_sub_f32 {V(NT[qt] + i)}, {V(NT[qt] + i)}, {delta}")
         for r in row_regs(s_next, qt):
             c.append(f"v_sub_f32 {V(r)}, {V(r)}, {delta}")
-    c.append(f"{skip_ovf}:")
-    c.append(f"s_cmp_eq_u32 s{S_RG}, 0")
-    c.append(f"s_cbranch_scc1 {done}")
-    sub_e = Emitter()
-    emit_mask(sub_e, s_next, valid_sreg)
-    c.extend(sub_e.lines)
-    c.append(f"{done}:")
-    c.append("s_nop 7")
-    c.append(f"s_branch {back}")
+    return c
 
 
-def emit_drain(E, par_last):
-    """PV of the final step: V page (parity par_last), keys 96..127, P tile B."""
+def emit_drain(E, par_last, tails=False):
+    """PV of the final step: V page (parity par_last), keys 96..127 (or of the last step walked), P tile B."""
     for qt in range(QT):                                  # row sums of the final step
         E.e(f"v_add_f32 {V(LACC + qt)}, {V(LACC + qt)}, {V(TS[qt])}")
     for dt in range(8):
-        E.e(f"ds_read_b128 {V(FR + 4 * dt, 4)}, {V(XOV + 3)} offset:{par_last * PAGE + dt * 4096}")
+        E.e(f"ds_read_b128 {V(FR + 4 * dt, 4)}, {V(XOVL if tails else XOV + 3)} offset:{par_last * PAGE + dt * 4096}")
     E.e("s_waitcnt lgkmcnt(0)")
     for ln in pv_order(P_TILE["B"]):
         E.e(ln)
 
 
-def emit_idle(E, done, vmcnt):
+def emit_idle(E, done, vmcnt, tails=False):
     """A wave without a single query row (the last tile of a segment has up to three) only takes its part in
     moving pages: the lines of a step that do so, and the barriers, in a loop of their own.  Its matrix
     work would cost power that the others can use (half-size 1.3B grid, five blocks: one wave in twenty)."""
@@ -379,20 +372,29 @@ def emit_idle(E, done, vmcnt):
     E.e("s_cmp_ge_i32 %[idle], 0")
     E.e("s_nop 0")
     E.e(f"s_cbranch_scc1 {idle}")
-    c = E.cold
-    c.append(f"{idle}:")
-    for par in range(2):
-        for R in range(4):
-            for _, lines in build_step(R, par)[0]:
+
+    def page(F, par, short):
+        c = F.lines
+        for R in (0, 3) if short else range(4):
+            for _, lines in build_step(R, par, tails, short)[0]:
                 for ln in lines:
                     if ln.startswith(("global_load", "v_readlane", "s_")) and not ln.startswith(("s_cbranch", "s_or", "s_waitcnt lgkmcnt")):
                         if ln.startswith("global_load") and " m0," in c[-1]:
                             c.append("s_nop 0")           # (what stands between in a working wave is left out here)
                         c.append(ln.replace("@VMCNT_V@", str(vmcnt[0])).replace("@VMCNT_K@", str(vmcnt[1])))
-        c.append(f"s_cmp_eq_u32 s{S_NLEFT}, 0")
-        c.append("s_nop 0")
-        c.append(f"s_cbranch_scc1 {done}")
-    c.append(f"s_branch {idle}")
+
+    F = Emitter(E)
+    F.e(f"{idle}:")
+    if tails:
+        emit_pages_with_tails(F, "I", page, (done, done))
+    else:
+        for par in range(2):
+            page(F, par, False)
+            F.e(f"s_cmp_eq_u32 s{S_NLEFT}, 0")
+            F.e("s_nop 0")
+            F.e(f"s_cbranch_scc1 {done}")
+        F.e(f"s_branch {idle}")
+    E.cold += F.lines + F.cold
 
 
 def emit_operand_setup(E):
@@ -439,8 +441,8 @@ def emit_first_reads(E):
 emit_results = base.emit_results
 
 
-def generate():
-    return base.generate(sys.modules[__name__])
+def generate(tails=False):
+    return base.generate(sys.modules[__name__], tails)
 
 
 def main(out_path):
@@ -448,6 +450,7 @@ def main(out_path):
     clob = [f"v{i}" for i in range(128, 256) if not 148 <= i <= 151 and i not in NT]
     clob += [f"a{i}" for i in range(0, 128)] + [f"s{i}" for i in range(36, 96)]
     base.write_include(out_path, generate(), clob, "CA_CORE16_CLOBBERS")
+    base.write_lines(out_path.replace("_gfx950", "_tails_gfx950"), generate(tails=True))
 
 
 if __name__ == "__main__":

@@ -456,3 +456,202 @@ def test_attention16_cold_blocks_have_no_barrier_and_return():
             ts = attn16.TS[qt]
             assert sum(ln.startswith(f"v_add_f32 v{ts},") for ln in block) == 7
             assert sum(ln.startswith(f"v_mul_f32 v{attn16.LACC + qt},") for ln in block) == 1
+
+
+class _Walk:
+    """Runs a generated attention loop for one wave on the CPU as far as control, page traffic and operands go: scalar instructions are
+    interpreted, memory to LDS loads, barriers, waits and operand reads are followed with the page they concern, no row sum ever
+    exceeds its limit.  Leaves the 32-key steps multiplied (K side and V side), the tiles masked, and the barriers met."""
+    BLOCK = 1 << 20                                          # bytes from one KV block's first page to the next one's
+
+    def __init__(self, core, text, n_pages, ppb, last_valid, n_kvb, kb0, pg0, idle=False):
+        self.core, self.text = core, text
+        self.stride = 2 * attn.PAGE
+        self.label = {ln[:-1]: k for k, ln in enumerate(text) if ln.endswith(":")}
+        self.s = {}
+        self.arg = {"n_pages": n_pages, "ppb": ppb, "stride": self.stride, "n_kvb": n_kvb, "kb0": kb0, "pg0": pg0, "last_valid": last_valid,
+                    "wave": 0, "lds0": 0, "idle": 0 if idle else -1}
+        self.scc = 0
+        self.moved = {}                                      # v_mov_b32 of one LDS address register to another
+        self.queue, self.slot, self.ready, self.read_at = [], {}, set(), {}
+        self.held, self.flying = {}, []
+        self.barriers, self.k_tiles, self.v_steps, self.masked, self.n_mfma = 0, [], [], {}, {"K": 0, "V": 0}
+        self.traffic = []
+        for which in "KV":                                   # requested ahead of the block, oldest first
+            self.slot[which, 0] = [(kb0, pg0), 8]
+            self.queue += [(which, 0)] * 8
+        self.run()
+
+    def val(self, x):
+        x = x.strip()
+        if x.startswith("%["):
+            return self.arg[x[2:-1]]
+        if x == "vcc":
+            return 0
+        if x.startswith("s["):
+            a = int(x[2:].split(":")[0])
+            return self.s.get(a, 0) | self.s.get(a + 1, 0) << 32
+        if re.fullmatch(r"s\d+", x):
+            return self.s.get(int(x[1:]), 0)
+        if x == "m0":
+            return self.m0
+        if "-" in x[1:]:                                     # a difference of labels
+            a, b = x.split("-", 1)
+            return self.label[a] - self.label[b]
+        return int(x, 0) & 0xffffffff
+
+    def put(self, d, v):
+        d = d.strip()
+        if d == "m0":
+            self.m0 = v & 0xffffffff
+        elif d.startswith("s["):
+            a = int(d[2:].split(":")[0])
+            self.s[a], self.s[a + 1] = v & 0xffffffff, (v >> 32) & 0xffffffff
+        else:
+            self.s[int(d[1:])] = v & 0xffffffff
+
+    def page_at(self, addr):
+        return addr // self.BLOCK, addr % self.BLOCK // self.stride, "V" if addr % self.stride >= attn.PAGE else "K"
+
+    def run(self):
+        signed = lambda v: v - (1 << 32) if v & 0x80000000 else v
+        k, steps = 0, 0
+        while k < len(self.text):
+            ln = self.text[k]
+            k, steps = k + 1, steps + 1
+            assert steps < 400000
+            if ln.endswith(":") or ln.startswith(";"):
+                continue
+            op, _, rest = ln.partition(" ")
+            a = [x.strip() for x in re.split(r",(?![^\[]*\])", rest)]
+            if op in ("s_mov_b32", "s_mul_i32", "s_mul_hi_u32", "s_lshl_b32", "s_add_u32", "s_addc_u32", "s_sub_u32", "s_subb_u32", "s_sub_i32",
+                      "s_max_i32", "s_min_i32", "s_cselect_b32", "s_cselect_b64", "s_or_b64"):
+                x, y = (self.val(v) for v in (a[1:3] if len(a) > 2 else (a[1], a[1])))
+                if op == "s_mov_b32":
+                    self.put(a[0], x)
+                elif op == "s_mul_i32":
+                    self.put(a[0], x * y)
+                elif op == "s_mul_hi_u32":
+                    self.put(a[0], (x * y) >> 32)
+                elif op == "s_lshl_b32":
+                    self.put(a[0], x << y)
+                elif op in ("s_add_u32", "s_addc_u32"):
+                    v = x + y + (self.scc if op == "s_addc_u32" else 0)
+                    self.put(a[0], v)
+                    self.scc = v >> 32
+                elif op in ("s_sub_u32", "s_subb_u32"):
+                    v = x - y - (self.scc if op == "s_subb_u32" else 0)
+                    self.put(a[0], v)
+                    self.scc = int(v < 0)
+                elif op == "s_sub_i32":
+                    self.put(a[0], x - y)
+                elif op in ("s_max_i32", "s_min_i32"):
+                    self.put(a[0], (max if op == "s_max_i32" else min)(signed(x), signed(y)))
+                elif op == "s_or_b64":
+                    self.put(a[0], x | y)
+                    self.scc = int(x | y != 0)
+                else:
+                    self.put(a[0], x if self.scc else y)
+            elif op.startswith("s_cmp_"):
+                x, y = self.val(a[0]), self.val(a[1])
+                if op.endswith("i32"):
+                    x, y = signed(x), signed(y)
+                self.scc = int({"eq": x == y, "lg": x != y, "lt": x < y, "le": x <= y, "ge": x >= y}[op.split("_")[2]])
+            elif op == "s_getpc_b64":
+                self.put(a[0], k)
+            elif op == "s_setpc_b64":
+                k = self.val(a[0])
+                assert self.text[k].startswith("BACK")
+            elif op == "s_branch" or (op == "s_cbranch_scc1" and self.scc) or (op == "s_cbranch_scc0" and not self.scc) or op == "s_cbranch_vccz":
+                k = self.label[a[0]]
+            elif op == "v_readlane_b32":
+                kb = self.val(a[2])
+                assert kb < self.arg["n_kvb"]
+                self.put(a[0], kb * self.BLOCK if a[1] == f"v{attn.TBLLO}" else 0)
+            elif op == "global_load_lds_dwordx4":
+                kb, pg, which = self.page_at(self.val(a[1]))
+                assert pg < self.arg["ppb"] and which == ("V" if a[1].startswith(f"s[{attn.S_ADDRV}:") else "K")
+                key = (which, self.m0 % attn.VRING // attn.PAGE)
+                assert (self.m0 >= attn.VRING) == (which == "V") and self.m0 % attn.PAGE == 4096 * (int(a[0][1:]) - attn.DMAOFF)
+                old = self.slot.get(key)
+                if old is None or old[1] == 8:               # the page that was there: its last read lies before the last barrier
+                    assert self.read_at.get(key, -1) < self.barriers
+                    self.ready.discard(key)
+                    old = self.slot[key] = [(kb, pg), 0]
+                assert old[0] == (kb, pg)
+                old[1] += 1
+                self.queue.append(key)
+                self.traffic.append((which, kb, pg, self.m0))
+            elif op == "s_waitcnt":
+                m = re.search(r"vmcnt\((\d+)\)", ln)
+                if m:
+                    self.queue = self.queue[len(self.queue) - int(m.group(1)):] if int(m.group(1)) else []
+                    self.traffic.append(ln)
+                m = re.search(r"lgkmcnt\((\d+)\)", ln)
+                if m:
+                    self.flying = self.flying[len(self.flying) - int(m.group(1)):] if int(m.group(1)) else []
+            elif op == "s_barrier":
+                self.barriers += 1
+                self.traffic.append(ln)
+                self.ready |= {key for key, (_, n) in self.slot.items() if n == 8 and key not in self.queue}
+            elif op == "v_mov_b32" and self.core.XOVL <= int(a[0][1:] if a[0][1:].isdigit() else -1) < self.core.XOVL + self.core.XOV_STRIDE:
+                self.moved[int(a[0][1:])] = int(a[1][1:])
+            elif op == "ds_read_b128":
+                src, imm = (int(x) for x in re.match(r"v(\d+) offset:(\d+)", a[1]).groups())
+                src = self.moved.get(src, src)
+                xok, xov = (self.core.XOK, self.core.XOV) if self.core is attn16 else (attn.XOK, attn.XOV)
+                which = "V" if src >= xov else "K"
+                key = (which, imm // attn.PAGE)
+                sub = (src - xov) // self.core.XOV_STRIDE if which == "V" else imm % attn.PAGE // 8192
+                reg = int(re.match(r"v\[(\d+)", a[0]).group(1))
+                if key in self.slot and not (which == "V" and not self.v_steps and not self.k_tiles[1:]):
+                    assert key in self.ready, (ln, key, steps)
+                    self.read_at[key] = self.barriers
+                    self.held[reg] = (which, *self.slot[key][0], sub, (src, imm % attn.PAGE))
+                else:                                        # the all-zero P of the first step
+                    self.held[reg] = (which, None, None, None, (src, imm % attn.PAGE))
+                self.flying.append(reg)
+            elif op.startswith("v_mfma"):
+                frag = int(re.match(r"v\[(\d+)", a[1]).group(1))
+                assert frag not in self.flying
+                which, kb, pg, sub, _ = self.held[frag]
+                per = 16 if self.core is attn.CORE else 32
+                out = self.k_tiles if a[0].startswith("v") else self.v_steps
+                assert which == ("K" if a[0].startswith("v") else "V")
+                if self.n_mfma[which] % per == 0:
+                    out.append((kb, pg, sub))
+                assert out[-1] == (kb, pg, sub), (ln, out[-1], self.held[frag])
+                self.n_mfma[which] += 1
+            elif op == "v_cmp_lt_i32":                       # a tile is masked: what it compares key 0's offset with
+                tile = len(self.k_tiles) - 1
+                valid = signed(self.val(a[2]))
+                self.masked[tile] = max(self.masked.get(tile, -1 << 20), valid)
+            else:
+                assert op.startswith(("v_", "ds_bpermute", "s_nop")) or op in ("s_cbranch_scc0", "s_cbranch_scc1", "s_cbranch_vccnz"), ln
+
+
+@pytest.mark.parametrize("tails", [False, True])
+@pytest.mark.parametrize("core", [attn.CORE, attn16], ids=["32x32x16", "16x16x32"])
+def test_attention_walks_every_step_of_its_pages(core, tails):
+    """The steps multiplied are those of the pages of the walk, in order, on both sides, the ones with absent keys masked, and a wave
+    without rows moves the same pages.  With short pages two steps are walked of a block's last page of up to 64 tokens."""
+    text = [p for ln in attn.generate(None if core is attn.CORE else core, tails) for p in ln.split("\n")]
+    core_ = attn.CORE if core is attn.CORE else attn16
+    for ppb, n_kvb, last in ((1, 4, 64), (1, 1, 7), (2, 3, 1), (3, 3, 33), (4, 3, 128), (3, 2, 65), (5, 2, 64)):
+        pages = [(kb, pg) for kb in range(n_kvb) for pg in range(ppb)]
+        for lo, hi in ((0, len(pages)), (0, 1), (len(pages) - 1, len(pages)), (len(pages) // 2, len(pages)), (1 % len(pages), len(pages))):
+            w = _Walk(core_, text, hi - lo, ppb, last, n_kvb, *pages[lo])
+            want, valid = [], []
+            for kb, pg in pages[lo:hi]:
+                n = min(max(last - 0, 0), 128) if pg == ppb - 1 else 128
+                for sub in range(2 if tails and n <= 64 else 4):
+                    want.append((kb, pg, sub))
+                    valid.append(min(max(n - 32 * sub, 0), 32))
+            # one tile more is formed at the end (of a page that is there again, or the last one), and one of P = 0 at the start
+            assert w.k_tiles[:-1] == want and len(w.k_tiles) == len(want) + 1, (ppb, n_kvb, last, lo, hi)
+            assert w.v_steps[1:] == want, (ppb, n_kvb, last, lo, hi, w.v_steps)
+            for i, n in enumerate(valid):
+                assert (i in w.masked) == (n < 32) and (n == 32 or w.masked[i] == n), (i, n, w.masked.get(i))
+            if core is attn16:
+                idle = _Walk(core_, text, hi - lo, ppb, last, n_kvb, *pages[lo], idle=True)
+                assert idle.traffic == w.traffic and not idle.k_tiles and not idle.v_steps

@@ -200,6 +200,23 @@ def test_bf16_many_workgroups(gh, gw, nc):
     Hn.assert_close(Hn.gpu_forward(w, pool, q, infl, BI)[:, heads], ref, "bf16", f"many workgroups L={w.block_tokens}", bound=bound)
 
 
+# ... and on few workgroups: last pages of 1 .. 64 tokens, of which half the steps are walked, and one token more; blocks of one
+# such page only; walks cut in front of, behind and between them; the reference moving beside a masked tile.
+@pytest.mark.parametrize("heads,gh,gw,nc,ni,scale", [(1, 8, 8, 4, 1, 1), (2, 3, 11, 2, 3, 1), (1, 3, 43, 3, 1, 1), (3, 10, 16, 2, 2, 1), (2, 7, 23, 3, 1, 4),
+                                                     (1, 12, 16, 4, 2, 1), (2, 5, 13, 3, 2, 1), (1, 1, 1, 5, 1, 1)])
+def test_bf16_short_last_pages(heads, gh, gw, nc, ni, scale):
+    w = W.small_variant(W.CONFIGS["c3_wan1p3b_cascade5"], heads=heads, grid_h=gh, grid_w=gw, frames_per_block=1, n_cached=nc, n_inflight=ni,
+                        window_blocks=6)
+    cached, infl = list(range(nc)), list(range(nc, nc + ni))
+    q, k, v = W.draw_config(w, seed=18, scale=0.5 * scale)
+    pool = Hn.gpu_setup(w, k, v, cached, infl)
+    for mode in (BI, CA):
+        ref, bound = (np.concatenate(x) for x in Hn.oracle_forward_bounded(w, q, k, v, cached, infl, mode))
+        print(f"short pages L={w.block_tokens} mode={mode}", flush=True)
+        Hn.assert_close(Hn.gpu_forward(w, pool, q, infl, mode), ref, "bf16", f"short last pages L={w.block_tokens} mode={mode}", bound=bound,
+                        **({} if scale == 1 else {"max_abs": 0.12, "rel": 1.2e-2}))
+
+
 # ... and its moving exponent reference: rising, falling, past the fp32 exponent range, from one key to the next.  The bars are
 # those of the same ramps on few workgroups (the bf16 rounding of K moves logits of 25 by 5e-2, of 400 by 0.8).
 @pytest.mark.parametrize("ramp,bar", [((1.0, 24.0), 2e-2), ((24.0, 1.0), 2e-2), ((1.0, 400.0), 8e-2), ((1.0, 400.0, "step"), 8e-2)])
