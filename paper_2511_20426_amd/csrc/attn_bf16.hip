@@ -82,8 +82,12 @@ struct AttnArgs {
   // pos * head is exact in fp32 for pos < 4096 and only its fractional part meets the hardware
   // sin / cos (measured: cos and sin within 4.2e-7 of fp64 for every pos < 4096 and every pair).
   int32_t pairs_t, pairs_h;            // pairs [0, pairs_t): frame axis, then pairs_h: row axis, rest: column axis
-  int32_t block_tokens, plane, grid_w; // plane = grid_h * grid_w
-  float inv_block, inv_plane, inv_grid_w;
+  int32_t block_tokens, plane, grid_h, grid_w;   // plane = grid_h * grid_w
+  int32_t frames_per_block;
+  float inv_block, inv_plane, inv_grid_w, inv_frames;
+  // cos and sin per axis value present in a tile, in LDS: tab_f frames x pairs_t, then tab_y rows x pairs_h, then grid_w columns x
+  // the rest; tab_y == 0: a geometry too large for it, every lane evaluates its own
+  int32_t tab_f, tab_y;
   int32_t lanes[64];                   // kLane*: first row, rows, visible blocks per segment; first frame per query block; KV slots
   float rev_hi[kMaxPairs], rev_lo[kMaxPairs];
 };
@@ -152,21 +156,25 @@ __device__ __forceinline__ void wave_lds_fence() {
 #include "attn_core_clobbers.inc"
 #include "attn_core16_clobbers.inc"
 
-// LDS map: K ring (2 pages), V ring (2 pages), token positions of the tile's rows; the main loop lives
+// LDS map: K ring (2 pages), V ring (2 pages), token positions of the tile's rows, cos / sin table; the main loop lives
 // in attn_core_gfx950.inc (generated by gen_attn_core.py, which also documents the pipeline and the
 // register map).  Before the loop the second slots of the two rings hold the tile's Q rows.
 constexpr uint32_t kVRing = 2 * kPageBytes;
 constexpr uint32_t kPosArea = 4 * kPageBytes;
-constexpr int kAttnLds = 4 * kPageBytes + kRowsPerWg * 16;
+constexpr uint32_t kTrigArea = kPosArea + kRowsPerWg * 16;
+constexpr int kAttnLds = 160 * 1024;
+constexpr int kTrigEntries = (kAttnLds - int(kTrigArea)) / 8;
 
 // What a workgroup spends outside the loop is paid once per item, and one workgroup per CU means that
 // nothing overlaps it: 31 000 cycles (timestamps of a probe build; 7 pages of walk) when a thread rotated a
-// whole row, scalars were fetched one by one and results left in 8-byte pieces, 23 000 now.  So the
-// first K and V page are requested as soon as the item is known, Q is read and the results are
-// written as whole 256-byte rows (through LDS; the matrix layouts hold 16-byte pieces of 32 rows), and
-// the rotation is shared out so that a thread needs the factors of four pairs only (8 700 -> 5 500
-// cycles, the largest part left).  Whole steps: 15 workgroups with 20 pages each 72 -> 67 us, 300 with
-// 70..110 pages 383 -> 366 us; nothing at the 14B shape, where an item walks 407 pages.
+// whole row, scalars were fetched one by one and results left in 8-byte pieces, 23 000 when Q was read and the results written
+// as whole 256-byte rows (through LDS; the matrix layouts hold 16-byte pieces of 32 rows) and the rotation was shared out so
+// that a thread needs the factors of four pairs only, 21 500 with cos and sin from a table in LDS: a tile of 256 rows meets few
+// values per axis (1262 entries at 30 x 52 for 16 384 pairs), filled while Q is on its way, and a pair's rotation
+// is 12 vector instructions instead of 18 with two of quarter rate (8200 -> 5300 cycles).  The first K and V page are requested when
+// Q has landed, behind loads that the compiler counts: requested before, they cost 0.5 us, the waits for Q then
+// include them.  Whole steps: 3 heads x 1170 rows 32.0 -> 31.3 us, 8 x 2160 58.0 -> 57.0; nothing at the 14B shape, where an item
+// walks 407 pages.
 //
 // kTails: the loop that walks half of a short last page (gen_attn_core.py), picked by has_tails.
 // kCore16: which of the two main loops.  Both walk the same pages the same way; they differ in the matrix instruction, and
@@ -179,11 +187,7 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
   const int lane_tab = a.lanes[lane];
   const int my_slot = a.lanes[kLaneSlot + (lane & 31)];
   const int c16 = lane & 15, r4 = lane >> 4;               // 16-byte chunk and row (mod 4) of Q / O this lane moves
-  float rev_hi[4], rev_lo[4];
-  if (kRopeQ) {
-    *reinterpret_cast<float4*>(rev_hi) = *reinterpret_cast<const float4*>(a.rev_hi + 4 * c16);
-    *reinterpret_cast<float4*>(rev_lo) = *reinterpret_cast<const float4*>(a.rev_lo + 4 * c16);
-  }
+  const float pair_hi = kRopeQ ? a.rev_hi[lane] : 0.f, pair_lo = kRopeQ ? a.rev_lo[lane] : 0.f;   // of pair `lane`
 
   // ---- which (head, row tile, page range): XCD x takes its own work_per_xcd items; inside an XCD
   // the full items come first, then the split ones, all their first page ranges, then the second ...
@@ -217,6 +221,57 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
       v[i] = *reinterpret_cast<const u32x4*>(qp + int64_t(r) * a.q_tok_stride);
     }
   }
+  uint8_t* const parked = lds + kPageBytes + (wave >> 1) * kPageBytes + wave * 64 * 256;
+  int4* const pos = reinterpret_cast<int4*>(lds + kPosArea) + wave * 64;
+  if (kRopeQ) {
+    // ---- while Q is on its way: the rows' positions (without a table) or places in it, and the table, of which a lane fills its
+    // pair's entries, a wave every fourth value
+    int in_plane, x, in_block, x0;
+    const int r = min(row0 + tid, rows_end - 1);
+    const int frame = div_by(r, a.plane, a.inv_plane, &in_plane);        // counted through all query blocks
+    const int y = div_by(in_plane, a.grid_w, a.inv_grid_w, &x);
+    if (a.tab_y > 0) {
+      const int frame0 = uniform(div_by(row0, a.plane, a.inv_plane, &in_plane));
+      const int y0 = uniform(div_by(in_plane, a.grid_w, a.inv_grid_w, &x0));
+      const int last_frame = uniform(div_by(rows_end - 1, a.plane, a.inv_plane, &in_plane));
+      const int pairs_w = 64 - a.pairs_t - a.pairs_h;
+      const int in_y = a.tab_f * a.pairs_t, in_x = in_y + a.tab_y * a.pairs_h;
+      // entry of a pair: pos + 8 * pair
+      pos[lane] = make_int4(8 * (frame - frame0) * a.pairs_t,
+                            8 * (in_y + (y - y0 + (y < y0 ? a.grid_h : 0)) * a.pairs_h - a.pairs_t),
+                            8 * (in_x + x * pairs_w - a.pairs_t - a.pairs_h), 0);
+      auto cos_sin = [&](float at, float hi_part, float lo_part) {
+        const float rev = __builtin_amdgcn_fractf(at * hi_part) + at * lo_part;
+        return make_float2(__builtin_amdgcn_cosf(rev) * a.c, __builtin_amdgcn_sinf(rev) * a.c);
+      };
+      float2* const trig = reinterpret_cast<float2*>(lds + kTrigArea);
+      // frames and rows: a lane its own pair, a wave every fourth value
+      const bool on_t = lane < a.pairs_t;
+      const int n_ty = on_t ? a.tab_f : (lane < a.pairs_t + a.pairs_h ? a.tab_y : 0);
+      for (int v = wave; v < max(a.tab_f, a.tab_y); v += 4) {
+        const int fr = min(frame0 + v, last_frame), blk = uniform(div_by(fr, a.frames_per_block, a.inv_frames, &in_block));
+        const int t_pos = __builtin_amdgcn_readlane(lane_tab, kLaneFrame + blk) + uniform(in_block);
+        const int y_pos = y0 + v - (y0 + v >= a.grid_h ? a.grid_h : 0);
+        const float2 e = cos_sin(float(on_t ? t_pos : y_pos), pair_hi, pair_lo);
+        if (v < n_ty) trig[on_t ? v * a.pairs_t + lane : in_y + v * a.pairs_h + lane - a.pairs_t] = e;
+      }
+      // columns: the lanes share out as many as fit, a wave every fourth such group
+      if (pairs_w > 0) {
+        const int group = 64 / pairs_w, of = lane / pairs_w, k = lane - of * pairs_w;
+        const float k_hi = __shfl(pair_hi, 64 - pairs_w + k), k_lo = __shfl(pair_lo, 64 - pairs_w + k);
+        for (int v = wave * group + of; v < a.grid_w + of; v += 4 * group) {        // (uniform: a wave's lanes go on together)
+          const float2 e = cos_sin(float(v), k_hi, k_lo);
+          if (v < a.grid_w && of < group) trig[in_x + v * pairs_w + k] = e;
+        }
+      }
+    } else {
+      const int blk = div_by(frame, a.frames_per_block, a.inv_frames, &in_block);
+      pos[lane] = make_int4(__shfl(lane_tab, kLaneFrame + blk) + in_block, y, x, 0);
+    }
+  }
+  // Q has landed (and is taken note of as such before other loads are on their way, which the compiler does not count)
+#pragma unroll
+  for (int i = 0; i < 16; ++i) asm volatile("" : "+v"(v[i]));
   // ---- the first K and V page on their way into the first slots of their rings
   const uint32_t lane_off = wave * 1024 + lane * 16;   // this lane's 16 bytes inside each 4 KB slice of a page
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
@@ -233,40 +288,65 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
   }
   // ---- rotate, scale by c (scores then leave the matrix pipe in log2 units), round once, park the rows
   // in the second ring slots (rows 0..127 in K's, the others in V's), chunks swizzled as in a page
-  uint8_t* const parked = lds + kPageBytes + (wave >> 1) * kPageBytes + wave * 64 * 256;
   if (kRopeQ) {
-    float4* const pos = reinterpret_cast<float4*>(lds + kPosArea) + wave * 64;
-    {
-      int n, in_plane, x;
-      const int r = min(row0 + tid, rows_end - 1);
-      const int blk = div_by(r, a.block_tokens, a.inv_block, &n);
-      const int fr = div_by(n, a.plane, a.inv_plane, &in_plane);
-      const int y = div_by(in_plane, a.grid_w, a.inv_grid_w, &x);
-      pos[lane] = make_float4(float(__shfl(lane_tab, kLaneFrame + blk) + fr), float(y), float(x), 0.f);
-    }
-    wave_lds_fence();
     bool on_t[4], on_y[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       on_t[j] = 4 * c16 + j < a.pairs_t;
       on_y[j] = 4 * c16 + j < a.pairs_t + a.pairs_h;
     }
+    if (a.tab_y > 0) {
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");       // the table is there (page loads stay in flight)
+      const uint8_t* const entry = lds + kTrigArea + 32 * c16;
+      // eight rows at a time, so that their reads wait together
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int r = r4 + 4 * i;
-      const float4 p = pos[r];
-      u32x4 out;
+      for (int i0 = 0; i0 < 16; i0 += 8) {
+        float2 e[8][4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float at = on_t[j] ? p.x : (on_y[j] ? p.y : p.z);
-        const float rev = __builtin_amdgcn_fractf(at * rev_hi[j]) + at * rev_lo[j];
-        const float cs = __builtin_amdgcn_cosf(rev), sn = __builtin_amdgcn_sinf(rev);
-        const uint32_t x = v[i][j];
-        const float u = __uint_as_float(x << 16), w = __uint_as_float(x & 0xffff0000u);
-        out[j] = pack2((u * cs - w * sn) * a.c, (u * sn + w * cs) * a.c);
+        for (int i = 0; i < 8; ++i) {
+          const int4 p = pos[r4 + 4 * (i0 + i)];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) e[i][j].x = __int_as_float(on_t[j] ? p.x : (on_y[j] ? p.y : p.z));
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) e[i][j] = *reinterpret_cast<const float2*>(entry + __float_as_int(e[i][j].x) + 8 * j);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int r = r4 + 4 * (i0 + i);
+          u32x4 out;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const uint32_t x = v[i0 + i][j];
+            const float u = __uint_as_float(x << 16), w = __uint_as_float(x & 0xffff0000u);
+            out[j] = pack2(u * e[i][j].x - w * e[i][j].y, u * e[i][j].y + w * e[i][j].x);
+          }
+          if (row0 + wave * 64 + r >= rows_end) out = u32x4{0, 0, 0, 0};
+          *reinterpret_cast<u32x4*>(parked + r * 256 + ((c16 ^ (r & 15)) << 4)) = out;
+        }
       }
-      if (row0 + wave * 64 + r >= rows_end) out = u32x4{0, 0, 0, 0};
-      *reinterpret_cast<u32x4*>(parked + r * 256 + ((c16 ^ (r & 15)) << 4)) = out;
+    } else {
+      const float4 hi4 = *reinterpret_cast<const float4*>(a.rev_hi + 4 * c16), lo4 = *reinterpret_cast<const float4*>(a.rev_lo + 4 * c16);
+      const float rev_hi[4] = {hi4.x, hi4.y, hi4.z, hi4.w}, rev_lo[4] = {lo4.x, lo4.y, lo4.z, lo4.w};
+      wave_lds_fence();
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int r = r4 + 4 * i;
+        const int4 p = pos[r];
+        u32x4 out;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float at = float(on_t[j] ? p.x : (on_y[j] ? p.y : p.z));
+          const float rev = __builtin_amdgcn_fractf(at * rev_hi[j]) + at * rev_lo[j];
+          const float cs = __builtin_amdgcn_cosf(rev) * a.c, sn = __builtin_amdgcn_sinf(rev) * a.c;
+          const uint32_t x = v[i][j];
+          const float u = __uint_as_float(x << 16), w = __uint_as_float(x & 0xffff0000u);
+          out[j] = pack2(u * cs - w * sn, u * sn + w * cs);
+        }
+        if (row0 + wave * 64 + r >= rows_end) out = u32x4{0, 0, 0, 0};
+        *reinterpret_cast<u32x4*>(parked + r * 256 + ((c16 ^ (r & 15)) << 4)) = out;
+      }
     }
   } else {
 #pragma unroll
@@ -691,12 +771,20 @@ int32_t launch_attn_bf16_rope(const AttnPlan& p, const QRopePlan& rp, int varian
   }
   a.pairs_t = rp.geom.pairs_t;
   a.pairs_h = rp.geom.pairs_h;
+  a.grid_h = rp.geom.grid_h;
   a.grid_w = rp.geom.grid_w;
   a.plane = rp.geom.grid_h * rp.geom.grid_w;
   a.block_tokens = p.block_tokens;
   a.inv_block = 1.0f / float(a.block_tokens);
   a.inv_plane = 1.0f / float(a.plane);
   a.inv_grid_w = 1.0f / float(a.grid_w);
+  a.frames_per_block = a.block_tokens / a.plane;
+  a.inv_frames = 1.0f / float(a.frames_per_block);
+  // what the 256 consecutive rows of a tile can meet: that many frames, rows (from the first one's on, round the end), all columns
+  a.tab_f = kRowsPerWg / a.plane + 2;
+  a.tab_y = kRowsPerWg / a.grid_w + 2 < a.grid_h ? kRowsPerWg / a.grid_w + 2 : a.grid_h;
+  const int64_t entries = int64_t(a.tab_f) * a.pairs_t + int64_t(a.tab_y) * a.pairs_h + int64_t(a.grid_w) * (64 - a.pairs_t - a.pairs_h);
+  if (entries > kTrigEntries) a.tab_y = 0;
   for (int i = 0; i < p.n_q_blocks; ++i) {
     // positions must stay below 4096 for the exact head product (frames are the only axis that grows)
     if (rp.first_frame[i] < 0 || rp.first_frame[i] + p.block_tokens / a.plane >= 4096) return CA_EUNSUPPORTED;

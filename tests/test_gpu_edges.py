@@ -184,6 +184,30 @@ def test_publish_tiles(heads, fpb, gh, gw, ids, k_in):
     assert torch.equal(one.pool[:pages], two.pool[:pages])
 
 
+# Queries rotated by the attention kernel: cos and sin from a table in LDS per tile.  Many frames and rows to a tile, one row or column, a
+# tile that begins in the middle of a frame and goes round its end, the widest grid whose table fits (171 columns do not
+# always: their lanes evaluate their own), axes without pairs, query blocks that are not consecutive.
+@pytest.mark.parametrize("fpb,gh,gw,dims,infl", [(40, 1, 7, (44, 42, 42), (2, 3)), (3, 29, 3, (44, 42, 42), (2, 5)), (2, 9, 31, (44, 42, 42), (2, 3)),
+                                                 (1, 2, 140, (44, 42, 42), (2, 3)), (1, 2, 171, (44, 42, 42), (2, 4)), (300, 1, 1, (44, 42, 42), (2,)),
+                                                 (2, 11, 13, (0, 64, 64), (2, 3)), (2, 11, 13, (64, 64, 0), (2, 3)), (2, 11, 13, (126, 0, 2), (2, 3))])
+def test_bf16_rotation_table(fpb, gh, gw, dims, infl):
+    w = W.small_variant(W.CONFIGS["c3_wan1p3b_cascade5"], heads=2, grid_h=gh, grid_w=gw, frames_per_block=fpb, rope_dims=dims, n_cached=2,
+                        n_inflight=len(infl), window_blocks=6)
+    rng = np.random.default_rng(4)
+    L, H, D = w.block_tokens, w.heads, w.head_dim
+    q, k, v = (W.store(rng.standard_normal((n, H, D), dtype=np.float32), "bf16") for n in (len(infl) * L, (2 + len(infl)) * L, (2 + len(infl)) * L))
+    print(f"rotation table {fpb} x {gh} x {gw} {dims}", flush=True)
+    pool = Hn.gpu_setup(w, k, v, [0, 1], list(infl))
+    import torch
+    for mode in (BI, CA):
+        got = Hn.gpu_forward_rope(w, pool, q, list(infl), mode)
+        # the same rows through rope3d_apply, block by block, and the forward on rotated queries: two roundings of Q for one
+        qt = Hn.to_torch(q, "bf16")
+        rot = torch.cat([pool.rope(qt[i * L:(i + 1) * L], fpb * g) for i, g in enumerate(infl)])
+        ref = Hn.from_torch(pool.forward(rot, list(infl), mode), "bf16")
+        assert np.isfinite(got).all() and Hn.rel_l2(got, ref) < 8e-3, (fpb, gh, gw, dims, mode, Hn.rel_l2(got, ref))
+
+
 # bf16 attention on the 16x16x32 instruction (launches of many workgroups and ten pages or more): every class of ragged
 # last page, blocks that begin inside a step, rows past the last query; two heads checked whole.
 @pytest.mark.parametrize("gh,gw,nc", [(3, 43, 4), (3, 53, 4), (10, 16, 4), (7, 23, 4), (12, 16, 4), (223, 1, 4), (14, 16, 4), (15, 15, 4),
