@@ -1,14 +1,14 @@
 // Y[M,N] = X[M,K] . W[N,K]^T in bf16 with fp32 accumulation: the linear maps either side of the
 // attention inside a DiT layer (QKV projection before it, output projection after it).
 //
-//   gemm_bf16_kernel, for products that fill the chip with 256 x 256 tiles (pick_gemm_tile; the others: gemm_tile_kernel).
-//   Workgroup = 4 waves = a 256 x 256 tile of Y, one wave per SIMD; the main loop (K in stages of
+//   gemm_bf16_kernel, for products that fill the chip with tiles of 256 columns (pick_gemm_tile; the others: gemm_tile_kernel).
+//   Workgroup = 4 waves = a tile of 256, 192 or 128 x 256 of Y, one wave per SIMD; the main loop (K in stages of
 //   64, both operands through rings in LDS that together fill its 160 KB) is the assembly
 //   emitted by gen_gemm_core.py, which documents the pipeline and the register map.  This file
 //   holds the set-up, the epilogue (tile transposed through LDS so that rows of Y are written as
 //   256-byte runs) and the launch.
 //   Workgroups are numbered so that the 32 running together on one XCD form an 8 x 4 block of
-//   tiles: they share 8 row slabs of X and 4 row slabs of W in that XCD's L2.
+//   tiles (tile_of_workgroup).
 //
 //   A second instantiation is the QKV projection of the blocks in flight with the publication of
 //   their K/V fused into its epilogue (Sec. 3.3: every block's K/V go to the shared pool at every
@@ -32,7 +32,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int kTile = 256;
-constexpr int kSbRows = 8, kSbCols = 4;           // tiles of one XCD's block
+constexpr int kBandRows = 8;                      // row tiles of a band
 constexpr int kEpiRow = 272;                      // bytes per row of a wave's 128 x 128 bf16 tile in LDS
 constexpr int kEpiRowV = 260;                     // the same for a V sub-tile of the publishing epilogue, which is read
                                                   // back two bytes at a time down its columns: 65 dwords per row spread
@@ -57,7 +57,7 @@ struct GemmArgs {
   uint16_t* y;                                    // publishing: the packed queries [M][heads * 128]
   int32_t M, N, K;
   int64_t ldx, ldw, ldy;                          // row strides in elements
-  int32_t tiles_m, tiles_n, sb_cols, n_sb;        // gemm_tile_kernel: n_sb = tiles of an XCD
+  int32_t tiles_m, tiles_n;
   // Row tiles are counted inside row blocks of block_rows rows, tiles_per_block each (the last
   // one ragged): one block spanning all of M for the plain product, one per in-flight block when
   // publishing.
@@ -151,33 +151,57 @@ __device__ __forceinline__ void publish_tile(const GemmArgs& a, const uint8_t* t
   }
 }
 
-template <bool kPublish>
+// Which tile a workgroup takes, if any.  Tiles are numbered down bands of eight row tiles and dealt to the XCDs (workgroup b runs on b % 8) 32
+// at a time, so that the workgroups that run together on one share 8 row slabs of X and 4 of W in its L2, and those of all
+// XCDs lie close together; what is left over for the last round is dealt evenly.  Blocks of 8 x 4 tiles counted in a grid of
+// such blocks left some XCDs with twice the tiles of others (4680 x 1536 x 1536 in 222 tiles 39 us, now 23); one contiguous range per
+// XCD keeps them apart (23400 x 15360 x 5120 2740 us, now 2440).
+__device__ __forceinline__ bool tile_of_workgroup(const GemmArgs& a, int* tm, int* tn) {
+  const int xcd = int(blockIdx.x & 7), j = int(blockIdx.x >> 3), total = a.tiles_m * a.tiles_n;
+  const int full = total >> 8, left = total & 255, share = (left + 7) >> 3;
+  int nth;
+  if (j < full * 32) {
+    nth = ((j & ~31) << 3) + xcd * 32 + (j & 31);
+  } else {
+    const int in_round = xcd * share + (j - full * 32);
+    if (in_round >= left) return false;
+    nth = full * 256 + in_round;
+  }
+  const int band = nth / (kBandRows * a.tiles_n), in_band = nth - band * kBandRows * a.tiles_n;
+  const int height = min(kBandRows, a.tiles_m - band * kBandRows);
+  *tn = in_band / height;
+  *tm = band * kBandRows + in_band - *tn * height;
+  return true;
+}
+
+// kMt: 16-row sub-tiles of X to a wave; a tile of Y has 32 kMt rows (256, 192 or 128) and 256 columns.
+template <bool kPublish, int kMt>
 __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(GemmArgs a) {
+  constexpr int kTileRows = 32 * kMt, kWaveRows = 16 * kMt;
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l15 = lane & 15, grp = lane >> 4;
-  const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
-  const int sb = (j >> 5) * 8 + xcd, within = j & 31;
-  if (sb >= a.n_sb) return;
-  const int tm = (sb / a.sb_cols) * kSbRows + (within & 7);
-  const int tn = (sb % a.sb_cols) * kSbCols + (within >> 3);
-  if (tm >= a.tiles_m || tn >= a.tiles_n) return;
+  int tm, tn;
+  if (!tile_of_workgroup(a, &tm, &tn)) return;
   const int blk = tm / a.tiles_per_block, tile_in_blk = tm - blk * a.tiles_per_block;
-  const int m0 = blk * a.block_rows + tile_in_blk * kTile, n0 = tn * kTile;
+  const int m0 = blk * a.block_rows + tile_in_blk * kTileRows, n0 = tn * kTile;
   const int m_end = min((blk + 1) * a.block_rows, a.M);           // first row past this tile's row block
   const int wm = wave & 1, wn = wave >> 1;
 
   // load i of this wave brings rows (8 wave + i) 8 .. +7 of a part (128-byte rows: whole cache
   // lines); lane L brings what is stored at position L & 7 of row L >> 3: chunk (L & 7) ^ ((row >> 1) & 7)
-  uint32_t offw[8], offx[8];
+  uint32_t offw[8], offx[kMt];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const int row = (wave * 8 + i) * 8 + (lane >> 3);
-    const int c = (lane & 7) ^ ((row >> 1) & 7);
     const int nrow = min(n0 + row, a.N - 1) - n0;                // rows of w past n_out re-read its last row
-    offw[i] = uint32_t(int64_t(nrow) * a.ldw * 2 + c * 16);
+    offw[i] = uint32_t(int64_t(nrow) * a.ldw * 2 + ((lane & 7) ^ ((row >> 1) & 7)) * 16);
+  }
+#pragma unroll
+  for (int i = 0; i < kMt; ++i) {
+    const int row = (wave * kMt + i) * 8 + (lane >> 3);
     const int mrow = min(m0 + row, m_end - 1) - m0;              // rows past the block's end re-read its last row
-    offx[i] = uint32_t(int64_t(mrow) * a.ldx * 2 + c * 16);
+    offx[i] = uint32_t(int64_t(mrow) * a.ldx * 2 + ((lane & 7) ^ ((row >> 1) & 7)) * 16);
   }
   const uint64_t base_w = reinterpret_cast<uint64_t>(a.w + int64_t(n0) * a.ldw);
   const uint64_t base_x = reinterpret_cast<uint64_t>(a.x + int64_t(m0) * a.ldx);
@@ -185,34 +209,51 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(GemmArgs a) {
   // grp): chunk grp of k-step 0 of the lane's row in the wave's 128 rows
   const uint32_t swz = (l15 >> 1) & 7;
   const uint32_t aw0 = uint32_t((wn * 128 + l15) * 128) + ((uint32_t(grp) ^ swz) << 4);
-  const uint32_t ax0 = uint32_t((wm * 128 + l15) * 128) + ((uint32_t(grp) ^ swz) << 4);
+  const uint32_t ax0 = uint32_t((wm * kWaveRows + l15) * 128) + ((uint32_t(grp) ^ swz) << 4);
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   const int n_stages = a.K / 64;
 
-  u32x16 o0, o1, o2, o3, o4, o5, o6, o7;
-  asm volatile(
+  u32x16 o[kMt];
+#define CA_GEMM_OPERANDS                                                                                              \
+  [base_w] "s"(base_w), [base_x] "s"(base_x), [n_stages] "s"(n_stages), [wave] "s"(wave_s), [lds0] "s"(lds0),         \
+      [offw0] "v"(offw[0]), [offw1] "v"(offw[1]), [offw2] "v"(offw[2]), [offw3] "v"(offw[3]), [offw4] "v"(offw[4]),   \
+      [offw5] "v"(offw[5]), [offw6] "v"(offw[6]), [offw7] "v"(offw[7]), [offx0] "v"(offx[0]), [offx1] "v"(offx[1]),   \
+      [offx2] "v"(offx[2]), [offx3] "v"(offx[3]), [aw0] "v"(aw0), [ax0] "v"(ax0)
+  if constexpr (kMt == 8) {
+    asm volatile(
 #include "gemm_core_gfx950.inc"
-      : "=&{v[0:15]}"(o0), "=&{v[16:31]}"(o1), "=&{v[32:47]}"(o2), "=&{v[48:63]}"(o3), "=&{v[64:79]}"(o4),
-        "=&{v[80:95]}"(o5), "=&{v[96:111]}"(o6), "=&{v[112:127]}"(o7)
-      : [base_w] "s"(base_w), [base_x] "s"(base_x), [n_stages] "s"(n_stages), [wave] "s"(wave_s),
-        [lds0] "s"(lds0), [offw0] "v"(offw[0]), [offw1] "v"(offw[1]), [offw2] "v"(offw[2]), [offw3] "v"(offw[3]),
-        [offw4] "v"(offw[4]), [offw5] "v"(offw[5]), [offw6] "v"(offw[6]), [offw7] "v"(offw[7]),
-        [offx0] "v"(offx[0]), [offx1] "v"(offx[1]), [offx2] "v"(offx[2]), [offx3] "v"(offx[3]),
-        [offx4] "v"(offx[4]), [offx5] "v"(offx[5]), [offx6] "v"(offx[6]), [offx7] "v"(offx[7]),
-        [aw0] "v"(aw0), [ax0] "v"(ax0)
-      : "memory", "scc", "m0", CA_GEMM_CLOBBERS);
+        : "=&{v[0:15]}"(o[0]), "=&{v[16:31]}"(o[1]), "=&{v[32:47]}"(o[2]), "=&{v[48:63]}"(o[3]), "=&{v[64:79]}"(o[4]),
+          "=&{v[80:95]}"(o[5]), "=&{v[96:111]}"(o[6]), "=&{v[112:127]}"(o[7])
+        : CA_GEMM_OPERANDS, [offx4] "v"(offx[4]), [offx5] "v"(offx[5]), [offx6] "v"(offx[6]), [offx7] "v"(offx[7])
+        : "memory", "scc", "m0", CA_GEMM_CLOBBERS);
+  } else if constexpr (kMt == 6) {
+    asm volatile(
+#include "gemm_core192_gfx950.inc"
+        : "=&{v[0:15]}"(o[0]), "=&{v[16:31]}"(o[1]), "=&{v[32:47]}"(o[2]), "=&{v[48:63]}"(o[3]), "=&{v[64:79]}"(o[4]),
+          "=&{v[80:95]}"(o[5])
+        : CA_GEMM_OPERANDS, [offx4] "v"(offx[4]), [offx5] "v"(offx[5])
+        : "memory", "scc", "m0", CA_GEMM_CLOBBERS192);
+  } else {
+    asm volatile(
+#include "gemm_core128_gfx950.inc"
+        : "=&{v[0:15]}"(o[0]), "=&{v[16:31]}"(o[1]), "=&{v[32:47]}"(o[2]), "=&{v[48:63]}"(o[3])
+        : CA_GEMM_OPERANDS
+        : "memory", "scc", "m0", CA_GEMM_CLOBBERS128);
+  }
 
-  // ---- epilogue: the wave's 128 (m) x 128 (n) tile goes through LDS to come out row by row.
-  // Pair p of MFMA tile T = 8 ti + tj: n = 16 ti + 4 grp + 2 p, m = 16 tj + l15.
+  // ---- epilogue: the wave's tile of kWaveRows (m) x 128 (n) goes through LDS to come out row by row.
+  // Pair p of MFMA tile T = kMt ti + tj: n = 16 ti + 4 grp + 2 p, m = 16 tj + l15.
   __syncthreads();                                    // every wave is done with the stage buffers
-  uint8_t* mine = lds + wave * kEpiWave;
   const int v_section = kPublish && (n0 + wn * 128) / (a.pub.heads * 128) == 2;
   const int pitch = v_section ? kEpiRowV : kEpiRow;
-  const u32x16 o[8] = {o0, o1, o2, o3, o4, o5, o6, o7};
+  // publishing with 128 rows: the two waves of a page share its 128 x 128 tile
+  constexpr bool kShared = kPublish && kMt == 4;
+  static_assert(!kPublish || kMt == 8 || kMt == 4, "a wave's rows are a page or half of one");
+  uint8_t* mine = kShared ? lds + wn * kEpiWave + wm * kWaveRows * pitch : lds + wave * kEpiWave;
 #pragma unroll
-  for (int T = 0; T < 64; ++T) {
-    const int ti = T >> 3, tj = T & 7;
+  for (int T = 0; T < 8 * kMt; ++T) {
+    const int ti = T / kMt, tj = T % kMt;
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
       const int n = 16 * ti + 4 * grp + 2 * p;
@@ -221,22 +262,24 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(GemmArgs a) {
     }
   }
   __syncthreads();
-  if (!kPublish) {
+  if constexpr (!kPublish) {
 #pragma unroll 4
-    for (int it = 0; it < 32; ++it) {
+    for (int it = 0; it < kWaveRows / 4; ++it) {
       const int row = it * 4 + (lane >> 4), c = lane & 15;
       const u32x4 v = *reinterpret_cast<const u32x4*>(mine + row * kEpiRow + c * 16);
-      const int gm = m0 + wm * 128 + row;
+      const int gm = m0 + wm * kWaveRows + row;
       // the result passes through once: keep it from displacing the operand tiles in the caches
       if (gm < m_end && n0 + wn * 128 + c * 8 < a.N)            // n_out is a multiple of 8: a chunk is inside or outside
         __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(a.y + int64_t(gm) * a.ldy + n0 + wn * 128 + c * 8));
     }
-    return;
+  } else if constexpr (kShared) {
+    publish_tile<128>(a, lds + wn * kEpiWave, n0 + wn * 128, blk, tile_in_blk, m0, reinterpret_cast<float2*>(lds + 2 * kEpiWave),
+                      wm * 64 + lane, tid, 256);
+  } else {
+    // the wave's sub-tile is one head of q, k or v for one page of a block
+    float2* trig = reinterpret_cast<float2*>(lds + 4 * kEpiWave + wm * kTrigBytes);
+    publish_tile<64>(a, mine, n0 + wn * 128, blk, 2 * tile_in_blk + wm, m0 + wm * 128, trig, lane, wn * 64 + lane, 128);
   }
-  // ---- publishing epilogue: the wave's sub-tile is one head of q, k or v for one page of a block
-  const int page = 2 * tile_in_blk + wm;
-  float2* trig = reinterpret_cast<float2*>(lds + 4 * kEpiWave + wm * kTrigBytes);
-  publish_tile<64>(a, mine, n0 + wn * 128, blk, page, m0 + wm * 128, trig, lane, wn * 64 + lane, 128);
 }
 
 
@@ -258,7 +301,6 @@ struct TileShape {
   static_assert(kLoadsW * 8 * kWaves == BN && kLoadsX * 8 * kWaves == BM && kLds <= kGemmLds, "shape");
 };
 
-using Tile256x128 = TileShape<256, 128, 4, 2, 3>;
 using Tile128 = TileShape<128, 128, 2, 4, 4>;
 using Tile64 = TileShape<64, 64, 2, 2, 4>;
 using Tile64Wide = TileShape<64, 64, 2, 4, 6>;
@@ -270,13 +312,8 @@ __global__ __launch_bounds__(T::kThreads) void gemm_tile_kernel(GemmArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l15 = lane & 15, grp = lane >> 4;
   const int wm = wave % kWavesM, wn = wave / kWavesM;
-  // XCD x takes a contiguous range of the tiles, which are numbered down bands of eight row tiles: its workgroups
-  // share a few row slabs of X and of W in that XCD's L2
-  const int nth = int(blockIdx.x & 7) * a.n_sb + int(blockIdx.x >> 3);
-  if (nth >= a.tiles_m * a.tiles_n) return;
-  const int band = nth / (kSbRows * a.tiles_n), in_band = nth - band * kSbRows * a.tiles_n;
-  const int height = min(kSbRows, a.tiles_m - band * kSbRows);
-  const int tn = in_band / height, tm = band * kSbRows + in_band - tn * height;
+  int tm, tn;
+  if (!tile_of_workgroup(a, &tm, &tn)) return;
   const int blk = tm / a.tiles_per_block, tile_in_blk = tm - blk * a.tiles_per_block;
   const int m0 = blk * a.block_rows + tile_in_blk * BM, n0 = tn * BN;
   const int m_end = min((blk + 1) * a.block_rows, a.M);
@@ -402,16 +439,20 @@ int32_t check_gemm_shape(int64_t M, int32_t N, int32_t K, int64_t ldx, int64_t l
   return CA_OK;
 }
 
-template <bool kPublish>
+// workgroups for tile_of_workgroup: whole rounds of 256, then eight times an XCD's share of the rest
+unsigned tile_workgroups(const GemmArgs& a) {
+  const unsigned total = unsigned(a.tiles_m) * unsigned(a.tiles_n);
+  return (total & ~255u) + ((total & 255u) + 7) / 8 * 8;
+}
+
+template <bool kPublish, int kMt>
 int32_t enqueue_gemm(GemmArgs& a, void* stream) {
-  a.tiles_per_block = (a.block_rows + kTile - 1) / kTile;
+  constexpr int kTileRows = 32 * kMt;
+  a.tiles_per_block = (a.block_rows + kTileRows - 1) / kTileRows;
   a.tiles_m = (a.M / a.block_rows) * a.tiles_per_block;
   a.tiles_n = (a.N + kTile - 1) / kTile;
-  a.sb_cols = (a.tiles_n + kSbCols - 1) / kSbCols;
-  a.n_sb = ((a.tiles_m + kSbRows - 1) / kSbRows) * a.sb_cols;
-  const unsigned rounds = unsigned((a.n_sb + 7) / 8);
-  hipLaunchKernelGGL(gemm_bf16_kernel<kPublish>, dim3(rounds * 8 * 32), dim3(256), kGemmLds,
-                     static_cast<hipStream_t>(stream), a);
+  const auto kernel = gemm_bf16_kernel<kPublish, kMt>;
+  hipLaunchKernelGGL(kernel, dim3(tile_workgroups(a)), dim3(256), kGemmLds, static_cast<hipStream_t>(stream), a);
   return finish_launch("gemm_bf16.hip");
 }
 
@@ -421,36 +462,41 @@ int32_t enqueue_gemm_tiles(GemmArgs& a, void* stream) {
   a.tiles_per_block = (a.block_rows + BM - 1) / BM;
   a.tiles_m = (a.M / a.block_rows) * a.tiles_per_block;
   a.tiles_n = (a.N + BN - 1) / BN;
-  a.n_sb = (a.tiles_m * a.tiles_n + 7) / 8;                  // tiles of an XCD
-  hipLaunchKernelGGL((gemm_tile_kernel<T, kPublish>), dim3(unsigned(a.n_sb) * 8), dim3(T::kThreads), T::kLds, static_cast<hipStream_t>(stream), a);
+  hipLaunchKernelGGL((gemm_tile_kernel<T, kPublish>), dim3(tile_workgroups(a)), dim3(T::kThreads), T::kLds, static_cast<hipStream_t>(stream), a);
   return finish_launch("gemm_bf16.hip");
 }
 
 // Which tile a product takes.  Outputs are the same to the last bit with every one of them (each is one chain of the
 // same matrix instruction over k in steps of 32), so the choice is the cheapest by a model of what was measured: rounds
-// of workgroups over the CUs times (stages of 64 k x time of a stage + set-up and epilogue), in microseconds:
-//   256 x 256 (asm loop)   stage 1.25, fixed 8      128 x 128   stage 0.43, fixed 5
-//   256 x 128              stage 0.85, fixed 6       64 x 64 two a CU 0.31, 4; one a CU 0.165, 4
+// of workgroups over the CUs times (stages of 64 k x time of a stage + set-up and epilogue).  A stage takes longer when most CUs work
+// (`full`, from half of them on in proportion).  Microseconds:
+//   256 x 256 (asm loops)   stage 1.0 .. 1.19, fixed 8      128 x 128   stage 0.43, fixed 5
+//   192 x 256               0.82 .. 0.95, 7.5               64 x 64     two a CU 0.31, 4; one a CU 0.165, 4
+//   128 x 256               0.58 .. 0.66, 7
 // Whole calls, us, 256 x 256 first and then what is taken: 257 x 768 x 1024 (6 tiles of 256 x 256) 22.7 -> 8.1, 64 x 128 x 5120
-// 80 -> 17, 1200 x 1400 x 1152 27.7 -> 10.1, 4680 x 1536 x 1536 36.7 -> 25.1 (256 x 128; 28.8 with 128 x 128, 39 with 64 x 64),
-// 23400 x 128 x 5120 93 -> 41 (128 x 128); 256 x 256 stays where its tiles fill the chip: 23400 x 5120 x 5120 901 against 1120.
-// The publishing epilogue needs whole pages and heads: 128 columns, 128 or 256 rows.
-enum GemmTile { kTile256, kTile256x128, kTile128, kTile64, kTile64Wide };
+// 80 -> 17, 1200 x 1400 x 1152 27.7 -> 10.1, 23400 x 128 x 5120 86 -> 39 (128 x 128), 4680 x 1536 x 1536 32.7 -> 22.8 (128 x 256; a
+// 256 x 128 tile of compiled code, since gone, took 26.5), 4680 x 4608 x 1536 69.8 -> 58.7 (192), 3000 x 3000 x 2944 56.2 -> 47.3 (192),
+// 1170 x 15360 x 5120 191 -> 157 (192); 256 x 256 stays where its tiles fill the chip: 23400 x 15360 x 5120 2440 against 2540, 8192^3 670 against 750.
+// The publishing epilogue needs whole pages and heads: 128 or 256 rows.
+enum GemmTile { kTile256, kTile192, kTile128x256, kTile128, kTile64, kTile64Wide };
 
 int32_t pick_gemm_tile(const GemmArgs& a, bool publish, GemmTile* tile) {
-  static constexpr struct { int bm, bn, per_cu, threads, stage, fixed; } kModel[] = {
-      {256, 256, 1, 256, 1250, 8000}, {256, 128, 1, 512, 850, 6000}, {128, 128, 1, 512, 430, 5000},
-      {64, 64, 2, 256, 310, 4000}, {64, 64, 1, 512, 165, 4000}};
+  static constexpr struct { int bm, bn, per_cu, threads, stage, full, fixed; bool publishes; } kModel[] = {
+      {256, 256, 1, 256, 1000, 1190, 8000, true}, {192, 256, 1, 256, 820, 950, 7500, false}, {128, 256, 1, 256, 580, 660, 7000, true},
+      {128, 128, 1, 512, 430, 430, 5000, true},   {64, 64, 2, 256, 310, 310, 4000, false},   {64, 64, 1, 512, 165, 165, 4000, false}};
   int n_cu = 0;
   if (const int32_t rc = device_cu_count(&n_cu); rc != CA_OK) return rc;
   const int64_t blocks = a.M / a.block_rows, stages = a.K / 64;
   int64_t best = 0;
-  for (int i = 0; i < (publish ? 3 : 5); ++i) {
+  for (int i = 0; i < int(sizeof(kModel) / sizeof(kModel[0])); ++i) {
     const auto& m = kModel[i];
+    if (publish && !m.publishes) continue;
     const int64_t tiles = blocks * ((a.block_rows + m.bm - 1) / m.bm) * ((a.N + m.bn - 1) / m.bn);
     if (i > 0 && tiles * m.threads >= (int64_t(1) << 31)) continue;      // a launch may have 2^32 threads
     const int64_t slots = int64_t(n_cu) * m.per_cu;
-    const int64_t cost = (tiles + slots - 1) / slots * (stages * m.stage + m.fixed);
+    const int64_t busy = tiles < slots ? tiles : slots;
+    const int64_t stage = m.stage + (2 * busy > slots ? (m.full - m.stage) * (2 * busy - slots) / slots : 0);
+    const int64_t cost = (tiles + slots - 1) / slots * (stages * stage + m.fixed);
     if (i == 0 || cost < best) {
       best = cost;
       *tile = GemmTile(i);
@@ -463,19 +509,21 @@ template <bool kPublish>
 int32_t dispatch_gemm(GemmArgs& a, void* stream) {
   GemmTile tile = kTile256;
   if (const int32_t rc = pick_gemm_tile(a, kPublish, &tile); rc != CA_OK) return rc;
-  const KernelLds kernels[] = {{reinterpret_cast<const void*>(gemm_bf16_kernel<kPublish>), kGemmLds},
-                               {reinterpret_cast<const void*>(gemm_tile_kernel<Tile256x128, kPublish>), Tile256x128::kLds},
+  const KernelLds kernels[] = {{reinterpret_cast<const void*>(gemm_bf16_kernel<kPublish, 8>), kGemmLds},
+                               {reinterpret_cast<const void*>(gemm_bf16_kernel<kPublish, 4>), kGemmLds},
                                {reinterpret_cast<const void*>(gemm_tile_kernel<Tile128, kPublish>), Tile128::kLds},
+                               {reinterpret_cast<const void*>(gemm_bf16_kernel<false, 6>), kGemmLds},
                                {reinterpret_cast<const void*>(gemm_tile_kernel<Tile64, false>), Tile64::kLds},
                                {reinterpret_cast<const void*>(gemm_tile_kernel<Tile64Wide, false>), Tile64Wide::kLds}};
-  if (const int32_t rc = ensure_dynamic_lds(kernels, kPublish ? 3 : 5, kPublish ? kLdsGemmPublish : kLdsGemm); rc != CA_OK) return rc;
+  if (const int32_t rc = ensure_dynamic_lds(kernels, kPublish ? 3 : 6, kPublish ? kLdsGemmPublish : kLdsGemm); rc != CA_OK) return rc;
   if constexpr (!kPublish) {
+    if (tile == kTile192) return enqueue_gemm<false, 6>(a, stream);
     if (tile == kTile64) return enqueue_gemm_tiles<Tile64, false>(a, stream);
     if (tile == kTile64Wide) return enqueue_gemm_tiles<Tile64Wide, false>(a, stream);
   }
+  if (tile == kTile128x256) return enqueue_gemm<kPublish, 4>(a, stream);
   if (tile == kTile128) return enqueue_gemm_tiles<Tile128, kPublish>(a, stream);
-  if (tile == kTile256x128) return enqueue_gemm_tiles<Tile256x128, kPublish>(a, stream);
-  return enqueue_gemm<kPublish>(a, stream);
+  return enqueue_gemm<kPublish, 8>(a, stream);
 }
 
 }  // namespace

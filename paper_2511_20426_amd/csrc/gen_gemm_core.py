@@ -2,6 +2,9 @@
 """Emits gemm_core_gfx950.inc: the main loop of the bf16 GEMM  Y[M,N] = X[M,K] . W[N,K]^T  used
 for the projections either side of the attention (fp32 accumulation in AGPRs).
 
+Three loops, for tiles of 256, 192 and 128 rows of X by 256 rows of W (MT = 8, 6, 4 sub-tiles of 16 rows to a wave); what follows
+describes the first, in the others a wave's part of X, and with it the products of a stage, is MT / 8 of that.
+
 Workgroup = 4 waves = a 256 x 256 tile of Y; wave (wm, wn) owns 128 x 128 of it as 8 x 8 MFMA
 tiles of 16 x 16 (v_mfma_f32_16x16x32_bf16, A = rows of W, B = rows of X, so that a lane ends up
 with 4 consecutive n of one m: pairs pack into bf16 words of a row of Y).  All 256 accumulator
@@ -27,12 +30,12 @@ double-buffered in VGPRs and read one k-step ahead.  Instructions are dealt to t
 of a stage by the list scheduler of issue_sched.py.
 
 Register map:
-  a[0:255]   accumulators, tile (ti over n, tj over m) at a[4*(8*ti+tj) ..]
+  a[0:32 MT - 1]   accumulators, tile (ti over n, tj over m) at a[4*(MT*ti+tj) ..]
   v[0:127]   operand fragments: buffer b, operand (0 = W, 1 = X), sub-tile t at v[64b + 32op + 4t ..]
   v192..v197 LDS read addresses of W: v[192 + 2*ring slot + kk];  v198..v201 of X: v[198 + 2*ring slot + kk]
   v202..v209, v210..v217  lane's byte offset from the stage's global base for W / X loads 0..7
-  v220..v222 temporaries of the set-up and the epilogue
-On exit v[0:127] hold the wave's tile as packed bf16 pairs: tile T = 8*ti+tj, pair p (n = 16 ti +
+  v218..v223 temporaries of the set-up and the epilogue
+On exit v[0:16 MT - 1] hold the wave's tile as packed bf16 pairs: tile T = MT*ti+tj, pair p (n = 16 ti +
 4 (lane/16) + 2 p, +1; m = 16 tj + lane%16) in v[2T + p].
 """
 from __future__ import annotations
@@ -55,7 +58,7 @@ OFFW, OFFX = 202, 210    # +i
 TMP = 220
 
 S_BW, S_BX = 36, 38      # global bases of the W / X stage being loaded (64-bit each)
-S_TRIPS, S_ISS, S_NST, S_M0B, S_INC, S_XISS = 40, 41, 42, 43, 44, 45
+S_TRIPS, S_ISS, S_NST, S_M0B, S_INC, S_XISS, S_M0X = 40, 41, 42, 43, 44, 45, 46
 
 
 def V(n, w=1):
@@ -70,8 +73,8 @@ def frag(b, op, t):
     return 64 * b + 32 * op + 4 * t
 
 
-def mfma(b, ti, tj):
-    acc = A(4 * (8 * ti + tj), 4)
+def mfma(b, ti, tj, mt=8):
+    acc = A(4 * (mt * ti + tj), 4)
     return f"v_mfma_f32_16x16x32_bf16 {acc}, {V(frag(b, 0, ti), 4)}, {V(frag(b, 1, tj), 4)}, {acc}"
 
 
@@ -80,13 +83,13 @@ def read_frag(b, op, t, stage, kk):
     return f"ds_read_b128 {V(frag(b, op, t), 4)}, {V(addr)} offset:{2048 * t}"
 
 
-def load_lines(op, stage, i):
-    """Load i (0..7) of this wave's share of a stage of W (op 0) or X (op 1): 8 rows x 128 bytes
+def load_lines(op, stage, i, mt=8):
+    """Load i of this wave's share of a stage of W (op 0; eight of them) or X (op 1; mt): 8 rows x 128 bytes
     -> 1 KB of LDS.  The two lines may not follow each other directly: a load to LDS takes M0 one wait state
     after a scalar instruction wrote it."""
-    ring = (stage % NW) * PART if op == 0 else XBASE + (stage % NX) * PART
-    base, off = (S_BW, OFFW) if op == 0 else (S_BX, OFFX)
-    return [f"s_add_u32 m0, s{S_M0B}, {ring + 1024 * i}",
+    ring = (stage % NW) * PART if op == 0 else XBASE + (stage % NX) * PART * mt // 8
+    base, off, m0b = (S_BW, OFFW, S_M0B) if op == 0 else (S_BX, OFFX, S_M0X)
+    return [f"s_add_u32 m0, s{m0b}, {ring + 1024 * i}",
             f"global_load_lds_dwordx4 {V(off + i)}, s[{base}:{base + 1}]"]
 
 
@@ -98,18 +101,25 @@ def advance_lines(base, counter):
 
 
 # fragments in the order the MFMAs (ti outer, tj inner) first need them
-READ_ORDER = [(0, 0)] + [(1, t) for t in range(8)] + [(0, t) for t in range(1, 8)]
+def read_order(mt=8):
+    return [(0, 0)] + [(1, t) for t in range(mt)] + [(0, t) for t in range(1, 8)]
+
+
+READ_ORDER = read_order()
 X_BY = 40               # the 8 X loads of a stage issue within this many slots behind the barrier
 
 
-def build_stage(P):
-    """Stage P (mod PERIOD) of the steady state: SLOTS slots of (MFMA, lines issued after it)."""
+def build_stage(P, mt=8):
+    """Stage P (mod PERIOD) of the steady state: 16 mt slots of (MFMA, lines issued after it)."""
+    SLOTS, READ_ORDER, X_BY = 16 * mt, read_order(mt), 5 * mt
     half = SLOTS // 2
+    read_gap = (half - 8) / len(READ_ORDER) if mt < 8 else 3
+    w_gap = (half - 12) / 8 if mt < 8 else 7
     mf, tail = [], [[] for _ in range(SLOTS)]
     for kk in range(2):
         for ti in range(8):
-            for tj in range(8):
-                mf.append(mfma(kk, ti, tj))
+            for tj in range(mt):
+                mf.append(mfma(kk, ti, tj, mt))
     # before the last k-step: this stage's last fragments are in registers; everything but the
     # W loads issued last has landed; behind the barrier this stage's buffers are free
     tail[half - 1] += ["s_waitcnt vmcnt(@VM@) lgkmcnt(0)", "s_barrier"]
@@ -119,7 +129,7 @@ def build_stage(P):
         nstage, nkk = (P, 1) if kk == 0 else (P + 1, 0)
         prev = None
         for k, (op, t) in enumerate(READ_ORDER):
-            at = half * kk + 1 + 3 * k
+            at = half * kk + 1 + int(read_gap * k)
             prev = Atom([read_frag(1 - kk, op, t, nstage, nkk)], at, at, [prev] if prev else [], 0,
                         hard=half * kk + half - 6)
             atoms.append(prev)
@@ -130,9 +140,9 @@ def build_stage(P):
         atoms.append(prev)
     # (M0 is written in an earlier slot than its load, so that an MFMA stands between, and behind the load before)
     last = prev
-    for op, stage, i, at, hard in ([(1, P + 2, i, half + 4 + (i * X_BY) // 8, half + X_BY + 6) for i in range(8)] +
-                                   [(0, P + 3, i, half + 6 + 7 * i, SLOTS - 3) for i in range(8)]):
-        m0, load = load_lines(op, stage, i)
+    for op, stage, i, at, hard in ([(1, P + 2, i, half + 4 + (i * X_BY) // mt, min(half + X_BY + 6, SLOTS - 12)) for i in range(mt)] +
+                                   [(0, P + 3, i, half + 6 + int(w_gap * i), SLOTS - 3 - (7 - i if mt < 8 else 0)) for i in range(8)]):
+        m0, load = load_lines(op, stage, i, mt)
         write = Atom([m0], at - 1, at - 1, [last], 0, hard=hard - 1)
         last = Atom([load], at, at, [write], 1, hard=hard)
         atoms += [write, last]
@@ -152,7 +162,7 @@ def build_stage(P):
     return out
 
 
-def generate():
+def generate(mt=8):
     L = []
     e = L.append
     e(f"s_mov_b64 s[{S_BW}:{S_BW + 1}], %[base_w]")
@@ -163,45 +173,44 @@ def generate():
     e(f"s_mov_b32 s{S_XISS}, 1")
     e(f"s_lshl_b32 s{S_M0B}, %[wave], 13")
     e(f"s_add_u32 s{S_M0B}, s{S_M0B}, %[lds0]")
+    e(f"s_mul_i32 s{S_M0X}, %[wave], {1024 * mt}")
+    e(f"s_add_u32 s{S_M0X}, s{S_M0X}, %[lds0]")
     dst = {f"offw{i}": OFFW + i for i in range(8)}
-    dst.update({f"offx{i}": OFFX + i for i in range(8)})
+    dst.update({f"offx{i}": OFFX + i for i in range(mt)})
     dst.update({"aw0": TMP, "ax0": TMP + 1})
     for n, r in dst.items():
         e(f"v_mov_b32 {V(r)}, %[{n}]")
-    for name, areg, depth, ring0 in (("aw0", ADDRW, NW, 0), ("ax0", ADDRX, NX, XBASE)):
+
+    # stage 0 first, then what the steady state would have requested, in its order: X of stage 1, W of 1 and 2
+    def request(op, st):
+        if st:
+            for grp in advance_lines(*((S_BW, S_ISS) if op == 0 else (S_BX, S_XISS))):
+                L.extend(grp)
+        for i in range(mt if op else 8):
+            m0, load = load_lines(op, st, i, mt)
+            L.extend([m0, "s_nop 0", load])
+    for op, st in ((0, 0), (1, 0), (1, 1), (0, 1), (0, 2)):
+        request(op, st)
+    # (meanwhile: read addresses, accumulators)
+    for name, areg, depth, ring0, part in (("aw0", ADDRW, NW, 0, PART), ("ax0", ADDRX, NX, XBASE, PART * mt // 8)):
         for slot in range(depth):
             for kk in range(2):                           # chunk index of k-step 1 = that of 0, xor 4
                 r = areg + 2 * slot + kk
                 e(f"v_xor_b32 {V(r)}, {kk << 6}, {V(dst[name])}")
                 e(f"v_add_u32 {V(r)}, %[lds0], {V(r)}")
-                e(f"v_add_u32 {V(r)}, {ring0 + slot * PART}, {V(r)}")
-    for r in range(256):
+                e(f"v_add_u32 {V(r)}, {ring0 + slot * part}, {V(r)}")
+    for r in range(32 * mt):
         e(f"v_accvgpr_write_b32 {A(r)}, 0")
-    # W stages 0, 1, 2 and X stages 0, 1 on their way; everything lands; first fragments
-    for st in range(NW):
-        if st:
-            for grp in advance_lines(S_BW, S_ISS):
-                L.extend(grp)
-        for i in range(8):
-            m0, load = load_lines(0, st, i)
-            L.extend([m0, "s_nop 0", load])
-    for st in range(NX):
-        if st:
-            for grp in advance_lines(S_BX, S_XISS):
-                L.extend(grp)
-        for i in range(8):
-            m0, load = load_lines(1, st, i)
-            L.extend([m0, "s_nop 0", load])
-    e("s_waitcnt vmcnt(0)")
+    e(f"s_waitcnt vmcnt({mt + 16})")                      # stage 0 has landed
     e("s_barrier")
-    for op, t in READ_ORDER:
+    for op, t in read_order(mt):
         e(read_frag(0, op, t, 0, 0))
     e("s_waitcnt lgkmcnt(0)")
     # the trip count is checked every two stages; a loop trip is PERIOD stages
     e("LOOP_%=:")
     for P in range(PERIOD):
         e(f"; ---- stage {P}")
-        for m, lines in build_stage(P):
+        for m, lines in build_stage(P, mt):
             e(m)
             L.extend(lines)
         if P % 2 == 1:
@@ -213,29 +222,32 @@ def generate():
     e("s_waitcnt vmcnt(0)")                                # surplus loads have landed
     e("s_nop 15")
     e("s_nop 15")                                          # the last MFMAs have written back
-    for T in range(64):
+    for T in range(8 * mt):
+        for k in range(4):
+            e(f"v_accvgpr_read_b32 {V(218 + k)}, {A(4 * T + k)}")
         for p in range(2):
-            e(f"v_accvgpr_read_b32 {V(TMP)}, {A(4 * T + 2 * p)}")
-            e(f"v_accvgpr_read_b32 {V(TMP + 1)}, {A(4 * T + 2 * p + 1)}")
-            e(f"v_cvt_pk_bf16_f32 {V(2 * T + p)}, {V(TMP)}, {V(TMP + 1)}")
+            e(f"v_cvt_pk_bf16_f32 {V(2 * T + p)}, {V(218 + 2 * p)}, {V(219 + 2 * p)}")
     return L
 
 
 def main(out_path):
-    text = []
-    for ln in generate():
-        text.extend(ln.split("\n"))
-    with open(out_path, "w") as f:
-        f.write("// Generated by gen_gemm_core.py -- do not edit.\n")
-        for t in text:
-            f.write('"' + t + '\\n"\n')
-    clob = [f"v{i}" for i in range(128, 224)] + [f"a{i}" for i in range(256)] + [f"s{i}" for i in range(36, 48)]
-    with open(out_path.replace("gemm_core_gfx950.inc", "gemm_core_clobbers.inc"), "w") as f:
-        f.write("// Generated by gen_gemm_core.py -- do not edit.\n#define CA_GEMM_CLOBBERS \\\n")
+    by = "// Generated by gen_gemm_core.py -- do not edit.\n"
+    clobbers = by
+    for mt in (8, 6, 4):
+        text = [ln for part in generate(mt) for ln in part.split("\n")]
+        path = out_path if mt == 8 else out_path.replace("_gfx950", f"{32 * mt}_gfx950")
+        with open(path, "w") as f:
+            f.write(by)
+            for t in text:
+                f.write('"' + t + '\\n"\n')
+        print(f"{path}: {len(text)} lines")
+        clob = [f"v{i}" for i in list(range(16 * mt, 128)) + list(range(128, 224))] + [f"a{i}" for i in range(32 * mt)] + [f"s{i}" for i in range(36, 48)]
+        clobbers += f"#define CA_GEMM_CLOBBERS{'' if mt == 8 else 32 * mt} \\\n"
         for i in range(0, len(clob), 12):
             chunk = ", ".join(f'"{c}"' for c in clob[i:i + 12])
-            f.write("  " + chunk + (", \\\n" if i + 12 < len(clob) else "\n"))
-    print(f"{out_path}: {len(text)} lines")
+            clobbers += "  " + chunk + (", \\\n" if i + 12 < len(clob) else "\n")
+    with open(out_path.replace("gemm_core_gfx950.inc", "gemm_core_clobbers.inc"), "w") as f:
+        f.write(clobbers)
 
 
 if __name__ == "__main__":

@@ -655,3 +655,70 @@ def test_attention_walks_every_step_of_its_pages(core, tails):
             if core is attn16:
                 idle = _Walk(core_, text, hi - lo, ppb, last, n_kvb, *pages[lo], idle=True)
                 assert idle.traffic == w.traffic and not idle.k_tiles and not idle.v_steps
+
+
+@pytest.mark.parametrize("mt", [8, 6, 4])
+@pytest.mark.parametrize("n_stages", [2, 4, 6, 14])
+def test_gemm_loops_multiply_every_stage(mt, n_stages):
+    """The whole program of a tile, followed on the CPU: every product takes the fragments of its stage and k-step, read from a ring slot whose
+    loads have landed and been published, behind a wait for the read; no load goes to a slot before the barrier behind its last
+    read; every accumulator gets every k-step once, in order."""
+    text = [p for ln in gemm.generate(mt) for p in ln.split("\n")]
+    label = {ln[:-1]: k for k, ln in enumerate(text) if ln.endswith(":")}
+    trips, scc, m0 = n_stages // 2, 0, None
+    queue, slot, ready, last_read, barriers = [], {}, set(), {}, 0
+    count = {"w": 0, "x": 0}                                 # loads issued
+    per = {"w": 8, "x": mt}
+    part = {"w": gemm.PART, "x": gemm.PART * mt // 8}
+    depth = {"w": gemm.NW, "x": gemm.NX}
+    held, flying, steps = {}, [], {}
+    k = 0
+    while k < len(text):
+        ln = text[k]
+        k += 1
+        if ln.startswith("s_sub_u32") and f"s{gemm.S_TRIPS}," in ln:
+            trips -= 1
+            scc = int(trips != 0)
+        elif ln.startswith("s_cbranch_scc1") and scc or ln.startswith("s_cbranch_scc0") and not scc and "DONE" in ln:
+            k = label[ln.split()[1]]
+        elif " m0," in ln:
+            base, off = re.match(r"s_add_u32 m0, s(\d+), (\d+)", ln).groups()
+            m0 = (int(base), int(off))
+        elif ln.startswith("global_load_lds"):
+            op = "x" if f"s[{gemm.S_BX}:" in ln else "w"
+            assert m0[0] == (gemm.S_M0X if op == "x" else gemm.S_M0B)
+            st, i = divmod(count[op], per[op])
+            key = (op, st % depth[op])
+            assert m0[1] == (gemm.XBASE if op == "x" else 0) + key[1] * part[op] + 1024 * i
+            assert int(re.search(r" v(\d+),", ln).group(1)) == (gemm.OFFX if op == "x" else gemm.OFFW) + i
+            if i == 0:
+                assert last_read.get(key, -1) < barriers, (op, st)
+                ready.discard(key)
+                slot[key] = st
+            count[op] += 1
+            queue.append(key)
+        elif ln.startswith("s_waitcnt"):
+            m = re.search(r"vmcnt\((\d+)\)", ln)
+            if m:
+                queue = queue[len(queue) - int(m.group(1)):] if int(m.group(1)) else []
+            if "lgkmcnt(0)" in ln:
+                flying = []
+        elif ln == "s_barrier":
+            barriers += 1
+            ready |= {key for key, st in slot.items() if key not in queue and count[key[0]] >= per[key[0]] * (st + 1)}
+        elif ln.startswith("ds_read_b128"):
+            reg, addr, off = (int(x) for x in re.match(r"ds_read_b128 v\[(\d+):\d+\], v(\d+) offset:(\d+)", ln).groups())
+            op = "x" if addr >= gemm.ADDRX else "w"
+            s, kk = divmod(addr - (gemm.ADDRX if op == "x" else gemm.ADDRW), 2)
+            assert (op, s) in ready
+            last_read[op, s] = barriers
+            held[reg] = (op, slot[op, s], kk, off // 2048)
+            flying.append(reg)
+        elif ln.startswith("v_mfma"):
+            acc, a, b = (int(x) for x in re.match(r"v_mfma_f32_16x16x32_bf16 a\[(\d+):\d+\], v\[(\d+):\d+\], v\[(\d+):\d+\]", ln).groups())
+            assert a not in flying and b not in flying
+            ti, tj = divmod(acc // 4, mt)
+            n = steps.get(acc, 0)
+            assert held[a] == ("w", n // 2, n % 2, ti) and held[b] == ("x", n // 2, n % 2, tj), (ln, n, held[a], held[b])
+            steps[acc] = n + 1
+    assert len(steps) == 8 * mt and set(steps.values()) == {2 * n_stages} and not queue

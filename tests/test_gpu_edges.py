@@ -184,6 +184,17 @@ def test_publish_tiles(heads, fpb, gh, gw, ids, k_in):
     assert torch.equal(one.pool[:pages], two.pool[:pages])
 
 
+# ... of 128 and 192 rows by 256 columns, plain (last row and column tiles of one row and of a few columns) and publishing (pages of one token).
+@pytest.mark.parametrize("M,N,K", [(1921, 2200, 256), (2881, 2824, 128), (2900, 2896, 384)])
+def test_linear_tall_tiles(M, N, K):
+    test_linear_tiles(M, N, K)
+
+
+@pytest.mark.parametrize("heads,gh,gw,k_in", [(4, 19, 27, 128), (6, 13, 20, 384)])
+def test_publish_tall_tiles(heads, gh, gw, k_in):
+    test_publish_tiles(heads, 1, gh, gw, (1, 2, 3, 4, 5), k_in)
+
+
 # Queries rotated by the attention kernel: cos and sin from a table in LDS per tile.  Many frames and rows to a tile, one row or column, a
 # tile that begins in the middle of a frame and goes round its end, the widest grid whose table fits (171 columns do not
 # always: their lanes evaluate their own), axes without pairs, query blocks that are not consecutive.
