@@ -94,7 +94,7 @@ __global__ __launch_bounds__(256) void rope_generic_kernel(RopeGeom g, GenericAr
 }
 
 // ----------------------------------------------------------------------------- bf16 paged write
-// head_dim 128, 128-token pages.  One workgroup writes one page for a group of heads.
+// head_dim 128, 128-token pages.  One workgroup writes one page, or kTokens tokens of one, for a group of heads.
 // K page: row = token, sixteen 16-byte chunks, chunk c kept at position c ^ (row & 15).
 // V page: row = dim, chunk c = eight tokens in MFMA hand-over order, same swizzle.
 // V goes through LDS to be transposed; rows of 65 dwords keep the column reads conflict-free.
@@ -128,7 +128,10 @@ struct PagedArgs {             // what the kernel body works with: the batch's e
   TrigTable tab;
 };
 
+template <int kTokens>
 __global__ __launch_bounds__(256) void cache_write_bf16_kernel(RopeGeom g, PagedBatch batch) {
+  constexpr int kParts = kPage / kTokens, kRows = kTokens / 16;   // workgroups of a page; rows (K) and chunks (V) of a thread
+  constexpr int kChunks = kTokens / 8, kDims = 256 / kChunks;     // V chunks a workgroup writes of a dim; dims a step covers
   PagedArgs a;
   {
     const PagedBlock& blk = batch.b[blockIdx.z];
@@ -137,22 +140,22 @@ __global__ __launch_bounds__(256) void cache_write_bf16_kernel(RopeGeom g, Paged
     a.block_tokens = batch.block_tokens; a.pages_per_block = batch.pages_per_block;
     a.heads_per_group = batch.heads_per_group; a.tab = batch.tab;
   }
-  __shared__ uint32_t vt[kPage * kVRowWords];
+  __shared__ uint32_t vt[kTokens * kVRowWords];
   extern __shared__ float2 trig[];   // [n_f][pairs_t] then [n_y][pairs_h] then [n_x][pairs_w]
   const int t = threadIdx.x;
-  const int page = blockIdx.x;
-  const int c = t & 15;              // chunk owned by this thread (K: dims 8c..8c+7; V: 8 tokens)
-  const int r0 = t >> 4;             // first row; rows r0, r0+16, ..., r0+112
-  const int tok0 = page * kPage;
+  const int page = blockIdx.x / kParts, part = blockIdx.x % kParts;
+  const int c = t & 15;              // chunk owned by this thread (K: dims 8c..8c+7)
+  const int r0 = t >> 4;             // first row; rows r0, r0+16, ...
+  const int tok0 = page * kPage + part * kTokens;
 
   // K and V of the first head are on their way while the angles are evaluated, those of the next head while
   // this one's V is transposed; rows past the block's end re-read its last one and are stored as zeros
   const int h0 = blockIdx.y * a.heads_per_group;
   const int h1 = min(h0 + a.heads_per_group, g.heads);
-  U4 kin[8], vin[8];
+  U4 kin[kRows], vin[kRows];
   auto request = [&](int h) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < kRows; ++i) {
       const int64_t src = int64_t(min(tok0 + r0 + 16 * i, a.block_tokens - 1)) * a.tok_stride + int64_t(h) * a.head_stride + c * 8;
       kin[i] = load_once(a.k + src);
       vin[i] = load_once(a.v + src);
@@ -160,21 +163,21 @@ __global__ __launch_bounds__(256) void cache_write_bf16_kernel(RopeGeom g, Paged
   };
   request(h0);
 
-  // cos/sin of this thread's 4 pairs at its 8 tokens
-  float cs[8][4], sn[8][4];
+  // cos/sin of this thread's 4 pairs at its tokens
+  float cs[kRows][4], sn[kRows][4];
   if (a.tab.n_f > 0) {
     const TrigLayout lay = trig_layout(g, a.tab, tok0, a.block_tokens, a.first_frame);
     trig_fill(g, lay, trig, t, 256);
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < kRows; ++i) {
       const int n = tok0 + r0 + 16 * i;
       const TokenPos p = token_pos(min(n, a.block_tokens - 1), a.first_frame, g.grid_h, g.grid_w);
       trig_pick(g, lay, trig, p, c, cs[i], sn[i]);
     }
   } else {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < kRows; ++i) {
       const int n = tok0 + r0 + 16 * i;
       const TokenPos p = token_pos(min(n, a.block_tokens - 1), a.first_frame, g.grid_h, g.grid_w);
 #pragma unroll
@@ -184,11 +187,11 @@ __global__ __launch_bounds__(256) void cache_write_bf16_kernel(RopeGeom g, Paged
 
   for (int h = h0; h < h1; ++h) {
     const int64_t pair = (int64_t(a.slot) * a.pages_per_block + page) * g.heads + h;
-    uint8_t* kpage = a.pool + pair * (2 * kPage * 128 * 2);
-    uint8_t* vpage = kpage + kPage * 128 * 2;
+    uint8_t* kpage = a.pool + pair * (2 * kPage * 128 * 2) + part * kTokens * 256;
+    uint8_t* vpage = a.pool + pair * (2 * kPage * 128 * 2) + kPage * 128 * 2;
     // ---- K: rotate and store swizzled; V: stage into LDS
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < kRows; ++i) {
       const int r = r0 + 16 * i;
       const bool pad = tok0 + r >= a.block_tokens;
       const U4 raw = kin[i];
@@ -205,11 +208,12 @@ __global__ __launch_bounds__(256) void cache_write_bf16_kernel(RopeGeom g, Paged
     }
     if (h + 1 < h1) request(h + 1);
     __syncthreads();
-    // ---- V: thread builds chunk c of dim rows r0 + 16 i: tokens 16*(c/2) + perm[8*(c%2) + e]
+    // ---- V: thread builds chunk vc of dim rows t / kChunks + kDims i: tokens 16*(vc/2) + perm[8*(vc%2) + e]
+    const int vc = t % kChunks;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int d = r0 + 16 * i;
-      const int tb = 16 * (c >> 1) + 4 * (c & 1);     // tokens tb..tb+3 and tb+8..tb+11
+    for (int i = 0; i < kRows; ++i) {
+      const int d = t / kChunks + kDims * i;
+      const int tb = 16 * (vc >> 1) + 4 * (vc & 1);   // tokens tb..tb+3 and tb+8..tb+11
       uint32_t e[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
@@ -220,7 +224,7 @@ __global__ __launch_bounds__(256) void cache_write_bf16_kernel(RopeGeom g, Paged
       U4 o;
       o.x = e[0] | (e[1] << 16); o.y = e[2] | (e[3] << 16);
       o.z = e[4] | (e[5] << 16); o.w = e[6] | (e[7] << 16);
-      *reinterpret_cast<U4*>(vpage + d * 256 + ((c ^ (d & 15)) << 4)) = o;
+      *reinterpret_cast<U4*>(vpage + d * 256 + (((part * kChunks + vc) ^ (d & 15)) << 4)) = o;
     }
     __syncthreads();
   }
@@ -332,12 +336,17 @@ int32_t launch_cache_write(const RopeGeom& g, int dtype, int32_t n_blocks, const
     const int64_t target = all_pages > 4 * n_cu && all_pages <= 8 * n_cu ? 2 * n_cu : 4 * n_cu;
     const int64_t per_group = (all_pages + target - 1) / target;
     a.heads_per_group = int32_t(per_group < g.heads ? per_group : g.heads);
-    const dim3 grid((unsigned)pages_per_block,
+    // A workgroup's chain (angles, positions, transposition) is as long as its tokens are many: small launches take a half or a quarter of a
+    // page each, and so do those that would leave a second round of two workgroups a CU half empty.  Microseconds per launch (replayed from
+    // a graph) with 128 / 64 / 32 tokens, by pages: 3 6.5 / 4.6 / 3.8, 36 6.9 / 4.9 / 4.2, 144 8.0 / 6.9 / 6.6, 240 9.0 / 8.0 / 8.1, 280 11.3 / 9.2 / 8.8,
+    // 400 12.8 / 14.1 / 14.0, 444 14.3 / 15.9 / 15.2, 560 20.4 / 16.4 / 17.7, 720 21.4 / 19.8 / 21.6, 1000 28.2 / 27.7 / 28.6, 7400 195 / 198 / 241.
+    const int tokens = 4 * all_pages <= 3 * n_cu ? 32 : (4 * all_pages <= 5 * n_cu || (all_pages > 2 * n_cu && all_pages <= 4 * n_cu) ? 64 : kPage);
+    const dim3 grid((unsigned)(pages_per_block * (kPage / tokens)),
                     (unsigned)((g.heads + a.heads_per_group - 1) / a.heads_per_group), (unsigned)n_blocks);
     size_t tab_bytes = 0;
-    const TrigTable tab = trig_table_for(g, kPage, 16384, &tab_bytes);
-    a.tab = tab;
-    hipLaunchKernelGGL(cache_write_bf16_kernel, grid, dim3(256), tab_bytes, s, g, a);
+    a.tab = trig_table_for(g, tokens, 16384, &tab_bytes);
+    const auto kernel = tokens == 32 ? cache_write_bf16_kernel<32> : (tokens == 64 ? cache_write_bf16_kernel<64> : cache_write_bf16_kernel<kPage>);
+    hipLaunchKernelGGL(kernel, grid, dim3(256), tab_bytes, s, g, a);
   } else {
     GenericArgs a{};
     for (int i = 0; i < n_blocks; ++i) {

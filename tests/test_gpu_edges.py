@@ -195,6 +195,25 @@ def test_publish_tall_tiles(heads, gh, gw, k_in):
     test_publish_tiles(heads, 1, gh, gw, (1, 2, 3, 4, 5), k_in)
 
 
+# The cache write in workgroups of a page, half a page or a quarter of one (by pages x heads of the launch): all blocks in one launch and one
+# by one, which take different ones (40 and 10, 260 and 65, 480 and 120, 600 and 150 pages), write the same bytes, padding and
+# swizzle included; the smallest is compared with the oracle elsewhere.
+@pytest.mark.parametrize("heads,gh,gw", [(5, 11, 23), (13, 21, 27), (20, 21, 31), (30, 20, 32)])
+def test_cache_write_workgroup_sizes(heads, gh, gw):
+    import torch
+    from paper_2511_20426_amd.runner import CascadePool
+    w = W.small_variant(W.CONFIGS["c3_wan1p3b_cascade5"], heads=heads, frames_per_block=1, grid_h=gh, grid_w=gw)
+    gen = torch.Generator(device="cuda:0").manual_seed(6)
+    ks, vs = ([torch.randn((w.block_tokens, heads, 128), generator=gen, device="cuda:0").to(torch.bfloat16) for _ in range(4)] for _ in range(2))
+    two, one = CascadePool.for_workload(w), CascadePool.for_workload(w)
+    two.pool.fill_(0xAB); one.pool.fill_(0xAB)
+    two.append_batch([1, 2, 3, 4], [250] * 4, 0, ks, vs)
+    for i in range(4):
+        one.append(1 + i, 250, 0, ks[i], vs[i])
+    pages = two.pool.numel() - (256 * 256 * 132 * 4)
+    assert torch.equal(one.pool[:pages], two.pool[:pages])
+
+
 # Queries rotated by the attention kernel: cos and sin from a table in LDS per tile.  Many frames and rows to a tile, one row or column, a
 # tile that begins in the middle of a frame and goes round its end, the widest grid whose table fits (171 columns do not
 # always: their lanes evaluate their own), axes without pairs, query blocks that are not consecutive.
