@@ -206,9 +206,8 @@ class Context:
     def kv_cache_append(self, block_id: int, timestep: int, prompt_epoch: int, k_ptr: int, v_ptr: int,
                         tok_stride: int, head_stride: int, stream: int = 0) -> int:
         slot = C.c_int32(-1)
-        _check(lib.kv_cache_append(self._h, block_id, timestep, prompt_epoch, C.c_void_p(k_ptr or None),
-                                   C.c_void_p(v_ptr or None), tok_stride, head_stride,
-                                   C.c_void_p(stream or None), C.byref(slot)), "kv_cache_append")
+        _check(lib.kv_cache_append(self._h, block_id, timestep, prompt_epoch, k_ptr, v_ptr, tok_stride,
+                                   head_stride, stream, C.byref(slot)), "kv_cache_append")
         return slot.value
 
     def kv_cache_append_batch(self, block_ids: Sequence[int], timesteps: Sequence[int], prompt_epoch: int,
@@ -222,7 +221,7 @@ class Context:
         vp = (C.c_void_p * n)(*[p or None for p in v_ptrs])
         slots = (C.c_int32 * max(n, 1))()
         _check(lib.kv_cache_append_batch(self._h, n, ids, ts, prompt_epoch, kp, vp, tok_stride, head_stride,
-                                         C.c_void_p(stream or None), slots), "kv_cache_append_batch")
+                                         stream, slots), "kv_cache_append_batch")
         return [int(slots[i]) for i in range(n)]
 
     def layer_qkv_publish(self, block_ids: Sequence[int], timesteps: Sequence[int], prompt_epoch: int, x_ptr: int,
@@ -232,9 +231,8 @@ class Context:
         ids = (C.c_int64 * n)(*block_ids)
         ts = (C.c_int32 * n)(*timesteps)
         slots = (C.c_int32 * max(n, 1))()
-        _check(lib.layer_qkv_publish(self._h, n, ids, ts, prompt_epoch, C.c_void_p(x_ptr or None), ldx,
-                                     C.c_void_p(w_ptr or None), ldw, k_in, C.c_void_p(q_out_ptr or None),
-                                     C.c_void_p(stream or None), slots), "layer_qkv_publish")
+        _check(lib.layer_qkv_publish(self._h, n, ids, ts, prompt_epoch, x_ptr, ldx, w_ptr, ldw, k_in,
+                                     q_out_ptr, stream, slots), "layer_qkv_publish")
         return [int(slots[i]) for i in range(n)]
 
     def kv_cache_promote(self, block_id: int) -> None:
@@ -261,44 +259,40 @@ class Context:
     # device work
     def rope3d_apply(self, x_ptr: int, y_ptr: int, n_tokens: int, first_frame: int, tok_stride: int,
                      head_stride: int, stream: int = 0) -> None:
-        _check(lib.rope3d_apply(self._h, C.c_void_p(x_ptr or None), C.c_void_p(y_ptr or None), n_tokens,
-                                first_frame, tok_stride, head_stride, C.c_void_p(stream or None)),
+        _check(lib.rope3d_apply(self._h, x_ptr, y_ptr, n_tokens, first_frame, tok_stride, head_stride, stream),
                "rope3d_apply")
 
     def rope3d_apply_strided(self, x_ptr: int, x_tok_stride: int, x_head_stride: int, y_ptr: int,
                              y_tok_stride: int, y_head_stride: int, n_tokens: int, first_frame: int,
                              stream: int = 0) -> None:
-        _check(lib.rope3d_apply_strided(self._h, C.c_void_p(x_ptr or None), x_tok_stride, x_head_stride,
-                                        C.c_void_p(y_ptr or None), y_tok_stride, y_head_stride, n_tokens,
-                                        first_frame, C.c_void_p(stream or None)), "rope3d_apply_strided")
+        _check(lib.rope3d_apply_strided(self._h, x_ptr, x_tok_stride, x_head_stride, y_ptr, y_tok_stride,
+                                        y_head_stride, n_tokens, first_frame, stream), "rope3d_apply_strided")
 
     def cascade_attn_forward(self, q_ptr: int, inflight_block_ids: Sequence[int], mode: int, out_ptr: int,
                              stream: int = 0) -> None:
         ids = (C.c_int64 * len(inflight_block_ids))(*inflight_block_ids)
-        _check(lib.cascade_attn_forward(self._h, C.c_void_p(q_ptr or None), ids, len(inflight_block_ids),
-                                        mode, C.c_void_p(out_ptr or None), C.c_void_p(stream or None)),
+        _check(lib.cascade_attn_forward(self._h, q_ptr, ids, len(inflight_block_ids), mode, out_ptr, stream),
                "cascade_attn_forward")
 
     def cascade_attn_forward_static(self, q_ptr: int, inflight_block_ids: Sequence[int], mode: int, out_ptr: int,
                                     stream: int = 0) -> None:
         ids = (C.c_int64 * len(inflight_block_ids))(*inflight_block_ids)
-        _check(lib.cascade_attn_forward_static(self._h, C.c_void_p(q_ptr or None), ids, len(inflight_block_ids),
-                                               mode, C.c_void_p(out_ptr or None), C.c_void_p(stream or None)),
+        _check(lib.cascade_attn_forward_static(self._h, q_ptr, ids, len(inflight_block_ids), mode, out_ptr, stream),
                "cascade_attn_forward_static")
 
     def cascade_attn_forward_rope(self, q_ptr: int, q_tok_stride: int, q_head_stride: int,
                                   inflight_block_ids: Sequence[int], mode: int, out_ptr: int, stream: int = 0) -> None:
         ids = (C.c_int64 * len(inflight_block_ids))(*inflight_block_ids)
-        _check(lib.cascade_attn_forward_rope(self._h, C.c_void_p(q_ptr or None), q_tok_stride, q_head_stride, ids,
-                                             len(inflight_block_ids), mode, C.c_void_p(out_ptr or None),
-                                             C.c_void_p(stream or None)), "cascade_attn_forward_rope")
+        _check(lib.cascade_attn_forward_rope(self._h, q_ptr, q_tok_stride, q_head_stride, ids,
+                                             len(inflight_block_ids), mode, out_ptr, stream),
+               "cascade_attn_forward_rope")
 
     def cascade_attn_forward_share(self, q_ptr: int, inflight_block_ids: Sequence[int], first: int, count: int,
                                    mode: int, out_ptr: int, stream: int = 0) -> None:
         ids = (C.c_int64 * len(inflight_block_ids))(*inflight_block_ids)
-        _check(lib.cascade_attn_forward_share(self._h, C.c_void_p(q_ptr or None), ids, len(inflight_block_ids),
-                                              first, count, mode, C.c_void_p(out_ptr or None),
-                                              C.c_void_p(stream or None)), "cascade_attn_forward_share")
+        _check(lib.cascade_attn_forward_share(self._h, q_ptr, ids, len(inflight_block_ids),
+                                              first, count, mode, out_ptr, stream),
+               "cascade_attn_forward_share")
 
     def debug_visibility(self, inflight_block_ids: Sequence[int], mode: int):
         """(vis [n_inflight][n_kv] as nested lists, kv_block_ids)."""
