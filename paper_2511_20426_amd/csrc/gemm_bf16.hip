@@ -57,7 +57,7 @@ struct GemmArgs {
   uint16_t* y;                                    // publishing: the packed queries [M][heads * 128]
   int32_t M, N, K;
   int64_t ldx, ldw, ldy;                          // row strides in elements
-  int32_t tiles_m, tiles_n;
+  int32_t tiles_m, tiles_n, xcd_tiles;            // xcd_tiles: gemm_tile_kernel's tiles of an XCD
   // Row tiles are counted inside row blocks of block_rows rows, tiles_per_block each (the last
   // one ragged): one block spanning all of M for the plain product, one per in-flight block when
   // publishing.
@@ -151,7 +151,15 @@ __device__ __forceinline__ void publish_tile(const GemmArgs& a, const uint8_t* t
   }
 }
 
-// Which tile a workgroup takes, if any.  Tiles are numbered down bands of eight row tiles and dealt to the XCDs (workgroup b runs on b % 8) 32
+// Tiles are numbered down bands of eight row tiles.
+__device__ __forceinline__ void tile_at(const GemmArgs& a, int nth, int* tm, int* tn) {
+  const int band = nth / (kBandRows * a.tiles_n), in_band = nth - band * kBandRows * a.tiles_n;
+  const int height = min(kBandRows, a.tiles_m - band * kBandRows);
+  *tn = in_band / height;
+  *tm = band * kBandRows + in_band - *tn * height;
+}
+
+// Which tile a workgroup of gemm_bf16_kernel takes, if any.  Tiles are numbered down bands of eight row tiles and dealt to the XCDs (workgroup b runs on b % 8) 32
 // at a time, so that the workgroups that run together on one share 8 row slabs of X and 4 of W in its L2, and those of all
 // XCDs lie close together; what is left over for the last round is dealt evenly.  Blocks of 8 x 4 tiles counted in a grid of
 // such blocks left some XCDs with twice the tiles of others (4680 x 1536 x 1536 in 222 tiles 39 us, now 23); one contiguous range per
@@ -167,10 +175,7 @@ __device__ __forceinline__ bool tile_of_workgroup(const GemmArgs& a, int* tm, in
     if (in_round >= left) return false;
     nth = full * 256 + in_round;
   }
-  const int band = nth / (kBandRows * a.tiles_n), in_band = nth - band * kBandRows * a.tiles_n;
-  const int height = min(kBandRows, a.tiles_m - band * kBandRows);
-  *tn = in_band / height;
-  *tm = band * kBandRows + in_band - *tn * height;
+  tile_at(a, nth, tm, tn);
   return true;
 }
 
@@ -312,8 +317,12 @@ __global__ __launch_bounds__(T::kThreads) void gemm_tile_kernel(GemmArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l15 = lane & 15, grp = lane >> 4;
   const int wm = wave % kWavesM, wn = wave / kWavesM;
+  // XCD x takes a contiguous range of the tiles.  Dealing them as gemm_bf16_kernel does costs a short kernel its longer
+  // set-up: 220 x 2696 x 3072 12.0 us, 12.7 dealt; 2868 x 992 x 512 7.5, 7.6.
+  const int nth = int(blockIdx.x & 7) * a.xcd_tiles + int(blockIdx.x >> 3);
+  if (nth >= a.tiles_m * a.tiles_n) return;
   int tm, tn;
-  if (!tile_of_workgroup(a, &tm, &tn)) return;
+  tile_at(a, nth, &tm, &tn);
   const int blk = tm / a.tiles_per_block, tile_in_blk = tm - blk * a.tiles_per_block;
   const int m0 = blk * a.block_rows + tile_in_blk * BM, n0 = tn * BN;
   const int m_end = min((blk + 1) * a.block_rows, a.M);
@@ -462,7 +471,8 @@ int32_t enqueue_gemm_tiles(GemmArgs& a, void* stream) {
   a.tiles_per_block = (a.block_rows + BM - 1) / BM;
   a.tiles_m = (a.M / a.block_rows) * a.tiles_per_block;
   a.tiles_n = (a.N + BN - 1) / BN;
-  hipLaunchKernelGGL((gemm_tile_kernel<T, kPublish>), dim3(tile_workgroups(a)), dim3(T::kThreads), T::kLds, static_cast<hipStream_t>(stream), a);
+  a.xcd_tiles = (a.tiles_m * a.tiles_n + 7) / 8;
+  hipLaunchKernelGGL((gemm_tile_kernel<T, kPublish>), dim3(unsigned(a.xcd_tiles) * 8), dim3(T::kThreads), T::kLds, static_cast<hipStream_t>(stream), a);
   return finish_launch("gemm_bf16.hip");
 }
 
