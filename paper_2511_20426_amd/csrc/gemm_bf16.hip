@@ -159,14 +159,19 @@ __device__ __forceinline__ void tile_at(const GemmArgs& a, int nth, int* tm, int
   *tm = band * kBandRows + in_band - *tn * height;
 }
 
+// Tiles that an XCD takes in the last round of `left`.  Up to 64 go 16 to an XCD, for with a few each the tiles of an XCD have hardly a slab
+// in common and the round takes longer: 23400 x 5120 x 5120 (48 left) 875 us, 906 dealt evenly; 1560 x 1536 x 1536 14.5 / 15.0.  More
+// go evenly: 18720 x 3072 x 3072 (120 left) 255 us, 267 with 32 to an XCD.
+__host__ __device__ constexpr int last_round_share(int left) { return left > 0 && left <= 64 ? 16 : (left + 7) >> 3; }
+
 // Which tile a workgroup of gemm_bf16_kernel takes, if any.  Tiles are numbered down bands of eight row tiles and dealt to the XCDs (workgroup b runs on b % 8) 32
 // at a time, so that the workgroups that run together on one share 8 row slabs of X and 4 of W in its L2, and those of all
-// XCDs lie close together; what is left over for the last round is dealt evenly.  Blocks of 8 x 4 tiles counted in a grid of
+// XCDs lie close together; what is left over for the last round goes by last_round_share.  Blocks of 8 x 4 tiles counted in a grid of
 // such blocks left some XCDs with twice the tiles of others (4680 x 1536 x 1536 in 222 tiles 39 us, now 23); one contiguous range per
 // XCD keeps them apart (23400 x 15360 x 5120 2740 us, now 2440).
 __device__ __forceinline__ bool tile_of_workgroup(const GemmArgs& a, int* tm, int* tn) {
   const int xcd = int(blockIdx.x & 7), j = int(blockIdx.x >> 3), total = a.tiles_m * a.tiles_n;
-  const int full = total >> 8, left = total & 255, share = (left + 7) >> 3;
+  const int full = total >> 8, left = total & 255, share = last_round_share(left);
   int nth;
   if (j < full * 32) {
     nth = ((j & ~31) << 3) + xcd * 32 + (j & 31);
@@ -451,7 +456,7 @@ int32_t check_gemm_shape(int64_t M, int32_t N, int32_t K, int64_t ldx, int64_t l
 // workgroups for tile_of_workgroup: whole rounds of 256, then eight times an XCD's share of the rest
 unsigned tile_workgroups(const GemmArgs& a) {
   const unsigned total = unsigned(a.tiles_m) * unsigned(a.tiles_n);
-  return (total & ~255u) + ((total & 255u) + 7) / 8 * 8;
+  return (total & ~255u) + 8 * unsigned(last_round_share(int(total & 255u)));
 }
 
 template <bool kPublish, int kMt>
