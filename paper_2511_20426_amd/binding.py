@@ -3,7 +3,9 @@
 Argument marshalling only: every step of the path (rotary embedding, cache write,
 attention) runs in the library's HIP kernels.  Device buffers are passed as raw
 addresses (e.g. torch.Tensor.data_ptr()), the stream as a raw hipStream_t
-(torch.cuda.current_stream().cuda_stream).  There is no CPU fallback: if the
+(torch.cuda.current_stream().cuda_stream): integers, or None for null.  They go through
+`index`, which refuses everything else, since ctypes takes bytes, str and its own objects for a
+pointer too and a kernel would be given host memory.  There is no CPU fallback: if the
 library has not been built, importing this module raises.
 """
 from __future__ import annotations
@@ -11,6 +13,7 @@ from __future__ import annotations
 import ctypes as C
 import os
 from dataclasses import dataclass
+from operator import index
 from typing import List, Optional, Sequence, Tuple
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
@@ -206,8 +209,8 @@ class Context:
     def kv_cache_append(self, block_id: int, timestep: int, prompt_epoch: int, k_ptr: int, v_ptr: int,
                         tok_stride: int, head_stride: int, stream: int = 0) -> int:
         slot = C.c_int32(-1)
-        _check(lib.kv_cache_append(self._h, block_id, timestep, prompt_epoch, k_ptr, v_ptr, tok_stride,
-                                   head_stride, stream, C.byref(slot)), "kv_cache_append")
+        _check(lib.kv_cache_append(self._h, block_id, timestep, prompt_epoch, index(k_ptr or 0), index(v_ptr or 0),
+                                   tok_stride, head_stride, index(stream or 0), C.byref(slot)), "kv_cache_append")
         return slot.value
 
     def kv_cache_append_batch(self, block_ids: Sequence[int], timesteps: Sequence[int], prompt_epoch: int,
@@ -221,7 +224,7 @@ class Context:
         vp = (C.c_void_p * n)(*[p or None for p in v_ptrs])
         slots = (C.c_int32 * max(n, 1))()
         _check(lib.kv_cache_append_batch(self._h, n, ids, ts, prompt_epoch, kp, vp, tok_stride, head_stride,
-                                         stream, slots), "kv_cache_append_batch")
+                                         index(stream or 0), slots), "kv_cache_append_batch")
         return [int(slots[i]) for i in range(n)]
 
     def layer_qkv_publish(self, block_ids: Sequence[int], timesteps: Sequence[int], prompt_epoch: int, x_ptr: int,
@@ -231,8 +234,8 @@ class Context:
         ids = (C.c_int64 * n)(*block_ids)
         ts = (C.c_int32 * n)(*timesteps)
         slots = (C.c_int32 * max(n, 1))()
-        _check(lib.layer_qkv_publish(self._h, n, ids, ts, prompt_epoch, x_ptr, ldx, w_ptr, ldw, k_in,
-                                     q_out_ptr, stream, slots), "layer_qkv_publish")
+        _check(lib.layer_qkv_publish(self._h, n, ids, ts, prompt_epoch, index(x_ptr or 0), ldx, index(w_ptr or 0), ldw,
+                                     k_in, index(q_out_ptr or 0), index(stream or 0), slots), "layer_qkv_publish")
         return [int(slots[i]) for i in range(n)]
 
     def kv_cache_promote(self, block_id: int) -> None:
@@ -259,39 +262,40 @@ class Context:
     # device work
     def rope3d_apply(self, x_ptr: int, y_ptr: int, n_tokens: int, first_frame: int, tok_stride: int,
                      head_stride: int, stream: int = 0) -> None:
-        _check(lib.rope3d_apply(self._h, x_ptr, y_ptr, n_tokens, first_frame, tok_stride, head_stride, stream),
-               "rope3d_apply")
+        _check(lib.rope3d_apply(self._h, index(x_ptr or 0), index(y_ptr or 0), n_tokens, first_frame,
+                                tok_stride, head_stride, index(stream or 0)), "rope3d_apply")
 
     def rope3d_apply_strided(self, x_ptr: int, x_tok_stride: int, x_head_stride: int, y_ptr: int,
                              y_tok_stride: int, y_head_stride: int, n_tokens: int, first_frame: int,
                              stream: int = 0) -> None:
-        _check(lib.rope3d_apply_strided(self._h, x_ptr, x_tok_stride, x_head_stride, y_ptr, y_tok_stride,
-                                        y_head_stride, n_tokens, first_frame, stream), "rope3d_apply_strided")
+        _check(lib.rope3d_apply_strided(self._h, index(x_ptr or 0), x_tok_stride, x_head_stride, index(y_ptr or 0),
+                                        y_tok_stride, y_head_stride, n_tokens, first_frame, index(stream or 0)),
+               "rope3d_apply_strided")
 
     def cascade_attn_forward(self, q_ptr: int, inflight_block_ids: Sequence[int], mode: int, out_ptr: int,
                              stream: int = 0) -> None:
         ids = (C.c_int64 * len(inflight_block_ids))(*inflight_block_ids)
-        _check(lib.cascade_attn_forward(self._h, q_ptr, ids, len(inflight_block_ids), mode, out_ptr, stream),
-               "cascade_attn_forward")
+        _check(lib.cascade_attn_forward(self._h, index(q_ptr or 0), ids, len(inflight_block_ids), mode,
+                                        index(out_ptr or 0), index(stream or 0)), "cascade_attn_forward")
 
     def cascade_attn_forward_static(self, q_ptr: int, inflight_block_ids: Sequence[int], mode: int, out_ptr: int,
                                     stream: int = 0) -> None:
         ids = (C.c_int64 * len(inflight_block_ids))(*inflight_block_ids)
-        _check(lib.cascade_attn_forward_static(self._h, q_ptr, ids, len(inflight_block_ids), mode, out_ptr, stream),
-               "cascade_attn_forward_static")
+        _check(lib.cascade_attn_forward_static(self._h, index(q_ptr or 0), ids, len(inflight_block_ids), mode,
+                                               index(out_ptr or 0), index(stream or 0)), "cascade_attn_forward_static")
 
     def cascade_attn_forward_rope(self, q_ptr: int, q_tok_stride: int, q_head_stride: int,
                                   inflight_block_ids: Sequence[int], mode: int, out_ptr: int, stream: int = 0) -> None:
         ids = (C.c_int64 * len(inflight_block_ids))(*inflight_block_ids)
-        _check(lib.cascade_attn_forward_rope(self._h, q_ptr, q_tok_stride, q_head_stride, ids,
-                                             len(inflight_block_ids), mode, out_ptr, stream),
+        _check(lib.cascade_attn_forward_rope(self._h, index(q_ptr or 0), q_tok_stride, q_head_stride, ids,
+                                             len(inflight_block_ids), mode, index(out_ptr or 0), index(stream or 0)),
                "cascade_attn_forward_rope")
 
     def cascade_attn_forward_share(self, q_ptr: int, inflight_block_ids: Sequence[int], first: int, count: int,
                                    mode: int, out_ptr: int, stream: int = 0) -> None:
         ids = (C.c_int64 * len(inflight_block_ids))(*inflight_block_ids)
-        _check(lib.cascade_attn_forward_share(self._h, q_ptr, ids, len(inflight_block_ids),
-                                              first, count, mode, out_ptr, stream),
+        _check(lib.cascade_attn_forward_share(self._h, index(q_ptr or 0), ids, len(inflight_block_ids),
+                                              first, count, mode, index(out_ptr or 0), index(stream or 0)),
                "cascade_attn_forward_share")
 
     def debug_visibility(self, inflight_block_ids: Sequence[int], mode: int):
@@ -313,7 +317,8 @@ class Context:
 
 def layer_linear_bf16(x_ptr: int, w_ptr: int, y_ptr: int, m_rows: int, n_out: int, k_in: int,
                       ldx: int, ldw: int, ldy: int, stream: int = 0) -> None:
-    _check(lib.layer_linear_bf16(x_ptr, w_ptr, y_ptr, m_rows, n_out, k_in, ldx, ldw, ldy, stream), "layer_linear_bf16")
+    _check(lib.layer_linear_bf16(index(x_ptr or 0), index(w_ptr or 0), index(y_ptr or 0), m_rows, n_out, k_in,
+                                 ldx, ldw, ldy, index(stream or 0)), "layer_linear_bf16")
 
 
 def mfma_microbench(data_kind: int, trips: int, scratch_ptr: int, scratch_bytes: int, stream: int = 0):
