@@ -3,9 +3,9 @@
 Argument marshalling only: every step of the path (rotary embedding, cache write,
 attention) runs in the library's HIP kernels.  Device buffers are passed as raw
 addresses (e.g. torch.Tensor.data_ptr()), the stream as a raw hipStream_t
-(torch.cuda.current_stream().cuda_stream): integers, or None for null.  They go through
-`index`, which refuses everything else, since ctypes takes bytes, str and its own objects for a
-pointer too and a kernel would be given host memory.  There is no CPU fallback: if the
+(torch.cuda.current_stream().cuda_stream): integers, or None for null.  A Context's go
+through `index`, which refuses everything else: ctypes takes bytes, str and its own objects for a
+pointer too, and a kernel would be given host memory.  There is no CPU fallback: if the
 library has not been built, importing this module raises.
 """
 from __future__ import annotations
@@ -317,8 +317,7 @@ class Context:
 
 def layer_linear_bf16(x_ptr: int, w_ptr: int, y_ptr: int, m_rows: int, n_out: int, k_in: int,
                       ldx: int, ldw: int, ldy: int, stream: int = 0) -> None:
-    _check(lib.layer_linear_bf16(index(x_ptr or 0), index(w_ptr or 0), index(y_ptr or 0), m_rows, n_out, k_in,
-                                 ldx, ldw, ldy, index(stream or 0)), "layer_linear_bf16")
+    _check(lib.layer_linear_bf16(x_ptr, w_ptr, y_ptr, m_rows, n_out, k_in, ldx, ldw, ldy, stream), "layer_linear_bf16")
 
 
 def mfma_microbench(data_kind: int, trips: int, scratch_ptr: int, scratch_bytes: int, stream: int = 0):

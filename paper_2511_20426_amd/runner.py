@@ -13,8 +13,7 @@ from . import binding as B
 
 
 # Small calls are bound by the host (a launch alone takes 3.5 - 4 us): checks read a tensor's shape and strides once,
-# as tuples, and addresses go to the library as plain integers, for each look or object costs 0.1 - 0.2 us (a linear
-# map of 257 x 768 x 1024 6.5 -> 6.1 us, an fp32 step of three launches 20.2 -> 18.5).
+# as tuples, and no ctypes object is made for an address, for each look or object costs 0.1 us.
 _BF16 = torch.bfloat16
 
 
