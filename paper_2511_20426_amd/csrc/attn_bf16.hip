@@ -169,14 +169,16 @@ constexpr int kTrigEntries = (kAttnLds - int(kTrigArea)) / 8;
 
 // What a workgroup spends outside the loop is paid once per item, and one workgroup per CU means that
 // nothing overlaps it: 31 000 cycles (timestamps of a probe build; 7 pages of walk) when a thread rotated a
-// whole row, scalars were fetched one by one and results left in 8-byte pieces, 23 000 when Q was read and the results written
-// as whole 256-byte rows (through LDS; the matrix layouts hold 16-byte pieces of 32 rows) and the rotation was shared out so
-// that a thread needs the factors of four pairs only, 21 500 with cos and sin from a table in LDS: a tile of 256 rows meets few
-// values per axis (1262 entries at 30 x 52 for 16 384 pairs), filled while Q is on its way, and a pair's rotation
-// is 12 vector instructions instead of 18 with two of quarter rate (8200 -> 5300 cycles).  The first K and V page are requested when
-// Q has landed, behind loads that the compiler counts: requested before, they cost 0.5 us, the waits for Q then
-// include them.  Whole steps: 3 heads x 1170 rows 32.0 -> 31.3 us, 8 x 2160 58.0 -> 57.0; nothing at the 14B shape, where an item
-// walks 407 pages.
+// whole row, scalars were fetched one by one and results left in 8-byte pieces, 23 000 when Q was read and the
+// results written as whole 256-byte rows (through LDS; the matrix layouts hold 16-byte pieces of 32 rows) and the
+// rotation was shared out so that a thread needs the factors of four pairs only, about 22 000 with cos and sin from a
+// table in LDS: a tile of 256 rows meets few values per axis (1262 entries at 30 x 52 for 16 384 pairs), filled while Q
+// is on its way, and a pair's rotation is 14 vector instructions instead of 18 with two of quarter rate (8200 cycles
+// before; 5300 with the scale c multiplied into the table, which is two instructions less and 0.27 us of the smallest
+// step, 26.73 / 27.00, but rounds otherwise and keeps finite what rope3d_apply takes out of range: c comes behind
+// the rotation).  The first K and V page are requested when Q has landed, behind loads that the compiler counts:
+// requested before, they cost 0.5 us, the waits for Q then include them.  Nothing of this shows at the 14B shape, where
+// an item walks 407 pages.
 //
 // kTails: the loop that walks half of a short last page (gen_attn_core.py), picked by has_tails.
 // kCore16: which of the two main loops.  Both walk the same pages the same way; they differ in the matrix instruction, and
@@ -244,7 +246,7 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
                             8 * (in_x + x * pairs_w - a.pairs_t - a.pairs_h), 0);
       auto cos_sin = [&](float at, float hi_part, float lo_part) {
         const float rev = __builtin_amdgcn_fractf(at * hi_part) + at * lo_part;
-        return make_float2(__builtin_amdgcn_cosf(rev) * a.c, __builtin_amdgcn_sinf(rev) * a.c);
+        return make_float2(__builtin_amdgcn_cosf(rev), __builtin_amdgcn_sinf(rev));
       };
       float2* const trig = reinterpret_cast<float2*>(lds + kTrigArea);
       // frames and rows: a lane its own pair, a wave every fourth value
@@ -322,7 +324,7 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
           for (int j = 0; j < 4; ++j) {
             const uint32_t x = v[i0 + i][j];
             const float u = __uint_as_float(x << 16), w = __uint_as_float(x & 0xffff0000u);
-            out[j] = pack2(u * e[i][j].x - w * e[i][j].y, u * e[i][j].y + w * e[i][j].x);
+            out[j] = pack2((u * e[i][j].x - w * e[i][j].y) * a.c, (u * e[i][j].y + w * e[i][j].x) * a.c);
           }
           if (row0 + wave * 64 + r >= rows_end) out = u32x4{0, 0, 0, 0};
           *reinterpret_cast<u32x4*>(parked + r * 256 + ((c16 ^ (r & 15)) << 4)) = out;
@@ -341,10 +343,10 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
         for (int j = 0; j < 4; ++j) {
           const float at = float(on_t[j] ? p.x : (on_y[j] ? p.y : p.z));
           const float rev = __builtin_amdgcn_fractf(at * rev_hi[j]) + at * rev_lo[j];
-          const float cs = __builtin_amdgcn_cosf(rev) * a.c, sn = __builtin_amdgcn_sinf(rev) * a.c;
+          const float cs = __builtin_amdgcn_cosf(rev), sn = __builtin_amdgcn_sinf(rev);
           const uint32_t x = v[i][j];
           const float u = __uint_as_float(x << 16), w = __uint_as_float(x & 0xffff0000u);
-          out[j] = pack2(u * cs - w * sn, u * sn + w * cs);
+          out[j] = pack2((u * cs - w * sn) * a.c, (u * sn + w * cs) * a.c);
         }
         if (row0 + wave * 64 + r >= rows_end) out = u32x4{0, 0, 0, 0};
         *reinterpret_cast<u32x4*>(parked + r * 256 + ((c16 ^ (r & 15)) << 4)) = out;

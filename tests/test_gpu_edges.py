@@ -238,6 +238,23 @@ def test_bf16_rotation_table(fpb, gh, gw, dims, infl):
         assert np.isfinite(got).all() and Hn.rel_l2(got, ref) < 8e-3, (fpb, gh, gw, dims, mode, Hn.rel_l2(got, ref))
 
 
+# Queries rotated by the attention kernel are scaled by log2(e) / sqrt(D) behind the rotation: a pair that the rotation takes out of fp32's
+# range is infinite there as it is in rope3d_apply, and its row NaN, since K is zero in that pair.  With the table of angles and without.
+@pytest.mark.parametrize("gh,gw", [(3, 5), (1, 200)])
+def test_bf16_rotation_out_of_range(gh, gw):
+    w = W.small_variant(W.CONFIGS["c3_wan1p3b_cascade5"], heads=2, grid_h=gh, grid_w=gw, frames_per_block=1, n_cached=1, n_inflight=1)
+    q, k, v = (W.to_f64(x).astype(np.float32) for x in W.draw_config(w, seed=8))
+    k[:, :, :2] = 0
+    q[3, 1, :2] = q[11, 0, :2] = 3e38                        # pair 0 turns by 1 rad at frame 1: 3e38 (sin 1 + cos 1) = 4.1e38
+    q, k, v = (W.store(x, "bf16") for x in (q, k, v))
+    pool = Hn.gpu_setup(w, k, v, [0], [1])
+    two, one = Hn.gpu_forward(w, pool, q, [1], BI), Hn.gpu_forward_rope(w, pool, q, [1], BI)
+    want = np.ones(two.shape, bool)
+    want[3, 1] = want[11, 0] = False
+    assert (np.isfinite(two) == want).all() and (np.isfinite(one) == want).all()
+    assert Hn.rel_l2(one[want], two[want]) < 8e-3
+
+
 # bf16 attention on the 16x16x32 instruction (launches of many workgroups and ten pages or more): every class of ragged
 # last page, blocks that begin inside a step, rows past the last query; two heads checked whole.
 @pytest.mark.parametrize("gh,gw,nc", [(3, 43, 4), (3, 53, 4), (10, 16, 4), (7, 23, 4), (12, 16, 4), (223, 1, 4), (14, 16, 4), (15, 15, 4),
