@@ -5,7 +5,7 @@ attention) runs in the library's HIP kernels.  Device buffers are passed as raw
 addresses (e.g. torch.Tensor.data_ptr()), the stream as a raw hipStream_t
 (torch.cuda.current_stream().cuda_stream): integers, or None for null.  A Context's go
 through `index`, which refuses everything else: ctypes takes bytes, str and its own objects for a
-pointer too, and a kernel would be given host memory.  There is no CPU fallback: if the
+pointer too, and a kernel would be given host memory (numpy's integers and tensors are refused as c_void_p refuses them).  There is no CPU fallback: if the
 library has not been built, importing this module raises.
 """
 from __future__ import annotations
@@ -13,8 +13,9 @@ from __future__ import annotations
 import ctypes as C
 import os
 from dataclasses import dataclass
-from operator import index
 from typing import List, Optional, Sequence, Tuple
+
+index = int.__index__          # TypeError for what is not an int; operator.index would ask any object for its __index__
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("CASCADE_ATTN_LIB") or os.path.join(_PKG, "libcascade_attn.so")

@@ -8,6 +8,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 import workloads as W
 from oracle import cascade_oracle as orc
@@ -352,8 +353,10 @@ def test_append_batch_is_the_sequence_of_appends_or_nothing():
     fails(B.CA_ESTATE, [live[-1], 0])                            # the sink block is finished
     fails(B.CA_EINVAL, [live[0], -3])
 
+
 def _pointer_calls():
-    """(name, argument, call) of every call of a context that takes device addresses: the call with that address replaced."""
+    """(name, argument, call) of every call of a context that takes device addresses: the call with that address replaced.
+    (The context has no pool: nothing is launched.)"""
     w = W.small_variant(W.CONFIGS["c3_wan1p3b_cascade5"], heads=2, grid_h=4, grid_w=4)
     ctx = B.Context(_cfg(w))
     ctx.kv_cache_append(0, 0, 0, 0, 0, 256, 128)
@@ -372,14 +375,15 @@ def _pointer_calls():
             for i in range(n)]
 
 
-@pytest.mark.parametrize("host", [b"bytes of the host", "a string", (ctypes.c_char * 64)(), ctypes.c_void_p(16), 16.0],
-                         ids=["bytes", "str", "array", "c_void_p", "float"])
+@pytest.mark.parametrize("host", [b"bytes of the host", "a string", (ctypes.c_char * 64)(), ctypes.c_void_p(16), 16.0,
+                                  np.int64(16), torch.tensor(16)],
+                         ids=["bytes", "str", "array", "c_void_p", "float", "numpy", "tensor"])
 def test_addresses_are_integers(host):
     """Host memory never passes for a device address, at any pointer of a context's calls; integers and None (a null pointer) do."""
     for name, i, call in _pointer_calls():
+        print(f"{name}: argument {i}")
         with pytest.raises(TypeError):
             call(host)
-            print(f"{name}: argument {i} took {host!r}")
         for null in (0, None):
             try:
                 call(null)
