@@ -389,3 +389,24 @@ def test_addresses_are_integers(host):
                 call(null)
             except B.CascadeAttnError:
                 pass
+
+
+def test_linear_map_kernels_do_not_spill(tmp_path):
+    """The assembly loops leave few vector registers: what lives across them has to fit, a spilled value is fetched from memory in the
+    epilogue of every tile.  (The kernels are compiled here; nothing is run.)"""
+    import importlib.util
+    import subprocess
+    import sys
+    spec = importlib.util.spec_from_file_location("_flags", os.path.join(ROOT, "paper_2511_20426_amd", "_build.py"))
+    build = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(build)
+    subprocess.run([sys.executable, os.path.join(build.CSRC, "gen_gemm_core.py"), str(tmp_path / "gemm_core_gfx950.inc")], check=True,
+                   capture_output=True)
+    out = tmp_path / "gemm.s"
+    subprocess.run([build.hipcc(), "-x", "hip", "-S", "--offload-device-only", os.path.join(build.CSRC, "gemm_bf16.hip"), "-o", str(out), "-O3",
+                    "-std=c++17", "--offload-arch=gfx950", "-I", os.path.join(ROOT, "include"), "-I", build.CSRC, "-I", str(tmp_path)] +
+                   build.DEVICE_FLAGS, check=True, capture_output=True)
+    text = out.read_text()
+    kernels = re.findall(r"\.name:\s*(\S*gemm_\S*)", text)
+    spilled = [int(n) for n in re.findall(r"\.vgpr_spill_count:\s*(\d+)", text)]
+    assert len(kernels) == len(spilled) >= 8 and not any(spilled), list(zip(kernels, spilled))
