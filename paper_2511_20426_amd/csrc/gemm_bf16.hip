@@ -317,6 +317,7 @@ struct TileShape {
   static_assert(kLoadsW * 8 * kWaves == BN && kLoadsX * 8 * kWaves == BM && kLds <= kGemmLds, "shape");
 };
 
+using Tile256x128 = TileShape<256, 128, 4, 2, 3>;
 using Tile128 = TileShape<128, 128, 2, 4, 4>;
 using Tile64 = TileShape<64, 64, 2, 2, 4>;
 using Tile64Wide = TileShape<64, 64, 2, 4, 6>;
@@ -489,35 +490,43 @@ int32_t enqueue_gemm_tiles(GemmArgs& a, void* stream) {
 
 // Which tile a product takes.  Outputs are the same to the last bit with every one of them (each is one chain of the
 // same matrix instruction over k in steps of 32), so the choice is the cheapest by a model of what was measured: rounds
-// of workgroups over the CUs times (stages of 64 k x time of a stage + set-up and epilogue).  A stage takes longer when most CUs work
-// (`full`, from half of them on in proportion).  Microseconds:
-//   256 x 256 (asm loops)   stage 1.0 .. 1.19, fixed 8      128 x 128   stage 0.43, fixed 5
-//   192 x 256               0.82 .. 0.95, 7.5               64 x 64     two a CU 0.31, 4; one a CU 0.165, 4
-//   128 x 256               0.58 .. 0.66, 7
-// Whole calls, us, 256 x 256 first and then what is taken: 257 x 768 x 1024 (6 tiles of 256 x 256) 22.7 -> 8.1, 64 x 128 x 5120
-// 80 -> 17, 1200 x 1400 x 1152 27.7 -> 10.1, 23400 x 128 x 5120 86 -> 39 (128 x 128), 4680 x 1536 x 1536 32.7 -> 22.8 (128 x 256; a
-// 256 x 128 tile of compiled code, since gone, took 26.5), 4680 x 4608 x 1536 69.8 -> 58.7 (192), 3000 x 3000 x 2944 56.2 -> 47.3 (192),
-// 1170 x 15360 x 5120 191 -> 157 (192); 256 x 256 stays where its tiles fill the chip: 23400 x 15360 x 5120 2440 against 2540, 8192^3 670 against 750.
-// The publishing epilogue needs whole pages and heads: 128 or 256 rows.
-enum GemmTile { kTile256, kTile192, kTile128x256, kTile128, kTile64, kTile64Wide };
+// of workgroups over the CUs times (stages of 64 k x time of a stage + set-up and epilogue).  A stage takes longer when
+// most CUs work (`full`, from half of them on in proportion: the last round has its own).  Microseconds (fixed: plain, publishing):
+//   256 x 256 (asm loops)   stage 1.0 .. 1.19, fixed 8, 12.5      256 x 128   stage 0.85 .. 0.87, fixed 5.8, 6.25
+//   192 x 256               0.82 .. 0.95, 7.5                     128 x 128   0.43, 5, 4.5
+//   128 x 256               0.58 .. 0.66, 7, 9.25                 64 x 64     two a CU 0.31, 4; one a CU 0.165, 4
+// Over 226 products the pick is 0.4 % slower than the fastest tile in the geometric mean, 16 % at the worst (16568 x 1408 x 128).  Whole
+// calls, us, 256 x 256 first and then what is taken: 257 x 768 x 1024 (6 tiles of 256 x 256) 22.7 -> 8.1, 64 x 128 x 5120
+// 80 -> 17, 1200 x 1400 x 1152 27.7 -> 10.1, 23400 x 128 x 5120 86 -> 39 (128 x 128), 4680 x 1536 x 1536 32.7 -> 22.2
+// (128 x 256), 4680 x 4608 x 1536 69.8 -> 58.7 (192), 3000 x 3000 x 2944 56.2 -> 47.3 (192), 1170 x 15360 x 5120 191 -> 157
+// (192); 256 x 256 stays where its tiles fill the chip: 23400 x 15360 x 5120 2440 against 2540, 8192^3 670 against 750.
+// 256 x 128, of compiled code, is for column counts that 256 does not divide well (an odd number of heads): 14040 x 1152 x
+// 384 19.6 against 23.0 with 192, 23400 x 640 x 640 25.8 / 29.7, 17961 x 328 x 2432 36.1 / 38.8.
+// The publishing epilogue needs whole pages and heads: 128 or 256 rows.  It writes pages instead of rows, which the
+// largest tiles pay for most: of 23400 x 768 x 256, 34.0 us with 256 x 256, 33.5 with 128 x 256, 26.6 with 256 x 128, 29.4
+// with 128 x 128; 23400 x 3072 x 1024 163 / 176 / 182 / 206; 7920 x 2304 x 768 52 / 45 / 49 / 46.
+enum GemmTile { kTile256, kTile192, kTile256x128, kTile128x256, kTile128, kTile64, kTile64Wide };
 
 int32_t pick_gemm_tile(const GemmArgs& a, bool publish, GemmTile* tile) {
-  static constexpr struct { int bm, bn, per_cu, threads, stage, full, fixed; bool publishes; } kModel[] = {
-      {256, 256, 1, 256, 1000, 1190, 8000, true}, {192, 256, 1, 256, 820, 950, 7500, false}, {128, 256, 1, 256, 580, 660, 7000, true},
-      {128, 128, 1, 512, 430, 430, 5000, true},   {64, 64, 2, 256, 310, 310, 4000, false},   {64, 64, 1, 512, 165, 165, 4000, false}};
+  // fixed_publish: 0 where the tile does not publish
+  static constexpr struct { int bm, bn, per_cu, threads, stage, full, fixed, fixed_publish; } kModel[] = {
+      {256, 256, 1, 256, 1000, 1190, 8000, 12500}, {192, 256, 1, 256, 820, 950, 7500, 0},
+      {256, 128, 1, 512, 850, 870, 5800, 6250},    {128, 256, 1, 256, 580, 660, 7000, 9250},
+      {128, 128, 1, 512, 430, 430, 5000, 4500},    {64, 64, 2, 256, 310, 310, 4000, 0},
+      {64, 64, 1, 512, 165, 165, 4000, 0}};
   int n_cu = 0;
   if (const int32_t rc = device_cu_count(&n_cu); rc != CA_OK) return rc;
   const int64_t blocks = a.M / a.block_rows, stages = a.K / 64;
   int64_t best = 0;
   for (int i = 0; i < int(sizeof(kModel) / sizeof(kModel[0])); ++i) {
     const auto& m = kModel[i];
-    if (publish && !m.publishes) continue;
+    if (publish && m.fixed_publish == 0) continue;
     const int64_t tiles = blocks * ((a.block_rows + m.bm - 1) / m.bm) * ((a.N + m.bn - 1) / m.bn);
     if (i > 0 && tiles * m.threads >= (int64_t(1) << 31)) continue;      // a launch may have 2^32 threads
     const int64_t slots = int64_t(n_cu) * m.per_cu;
-    const int64_t busy = tiles < slots ? tiles : slots;
-    const int64_t stage = m.stage + (2 * busy > slots ? (m.full - m.stage) * (2 * busy - slots) / slots : 0);
-    const int64_t cost = (tiles + slots - 1) / slots * (stages * stage + m.fixed);
+    const int64_t left = tiles % slots, fixed = publish ? m.fixed_publish : m.fixed;        // left: tiles of a last round
+    const int64_t stage = m.stage + (2 * left > slots ? (m.full - m.stage) * (2 * left - slots) / slots : 0);
+    const int64_t cost = tiles / slots * (stages * m.full + fixed) + (left > 0 ? stages * stage + fixed : 0);
     if (i == 0 || cost < best) {
       best = cost;
       *tile = GemmTile(i);
@@ -532,17 +541,19 @@ int32_t dispatch_gemm(GemmArgs& a, void* stream) {
   if (const int32_t rc = pick_gemm_tile(a, kPublish, &tile); rc != CA_OK) return rc;
   const KernelLds kernels[] = {{reinterpret_cast<const void*>(gemm_bf16_kernel<kPublish, 8>), kGemmLds},
                                {reinterpret_cast<const void*>(gemm_bf16_kernel<kPublish, 4>), kGemmLds},
+                               {reinterpret_cast<const void*>(gemm_tile_kernel<Tile256x128, kPublish>), Tile256x128::kLds},
                                {reinterpret_cast<const void*>(gemm_tile_kernel<Tile128, kPublish>), Tile128::kLds},
                                {reinterpret_cast<const void*>(gemm_bf16_kernel<false, 6>), kGemmLds},
                                {reinterpret_cast<const void*>(gemm_tile_kernel<Tile64, false>), Tile64::kLds},
                                {reinterpret_cast<const void*>(gemm_tile_kernel<Tile64Wide, false>), Tile64Wide::kLds}};
-  if (const int32_t rc = ensure_dynamic_lds(kernels, kPublish ? 3 : 6, kPublish ? kLdsGemmPublish : kLdsGemm); rc != CA_OK) return rc;
+  if (const int32_t rc = ensure_dynamic_lds(kernels, kPublish ? 4 : 7, kPublish ? kLdsGemmPublish : kLdsGemm); rc != CA_OK) return rc;
   if constexpr (!kPublish) {
     if (tile == kTile192) return enqueue_gemm<false, 6>(a, stream);
     if (tile == kTile64) return enqueue_gemm_tiles<Tile64, false>(a, stream);
     if (tile == kTile64Wide) return enqueue_gemm_tiles<Tile64Wide, false>(a, stream);
   }
   if (tile == kTile128x256) return enqueue_gemm<kPublish, 4>(a, stream);
+  if (tile == kTile256x128) return enqueue_gemm_tiles<Tile256x128, kPublish>(a, stream);
   if (tile == kTile128) return enqueue_gemm_tiles<Tile128, kPublish>(a, stream);
   return enqueue_gemm<kPublish, 8>(a, stream);
 }

@@ -5,6 +5,9 @@ imports the other.
 """
 from __future__ import annotations
 
+import os
+import re
+
 import numpy as np
 
 import workloads as W
@@ -82,6 +85,31 @@ def attention_element_bound(o, p, q_rot, k_rot, v, logit_roundings: int = 3):
     v2 = v * v
     var_o = ps @ v2 - 2.0 * o * (ps @ v) + o * o * ps.sum(axis=1, keepdims=True) + E2_BF16 * (p2 @ v2)
     return 1.01 * 2.0 ** -8 * np.abs(o) + N_SIGMA * np.sqrt(np.maximum(var_o, 0.0)) + 1e-30
+
+
+# --------------------------------------------------------------------------- tile of a linear map
+
+def gemm_tile(M: int, N: int, K: int, block_rows: int | None = None, publish: bool = False) -> str:
+    """The tile that pick_gemm_tile takes for a product on 256 CUs, from the cost model as gemm_bf16.hip holds it."""
+    source = open(os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2511_20426_amd", "csrc",
+                               "gemm_bf16.hip")).read()
+    table = re.search(r"kModel\[\] = \{(.*?)\};", source, re.S).group(1)
+    names = re.search(r"enum GemmTile \{(.*?)\};", source).group(1).split(",")
+    rows = [[int(x) for x in r.split(",")] for r in re.findall(r"\{([\d, ]+)\}", table)]
+    assert len(rows) == len(names)
+    block_rows, best = block_rows or M, None
+    for name, (bm, bn, per_cu, _threads, stage, full, fixed, fixed_publish) in zip(names, rows):
+        if publish and fixed_publish == 0:
+            continue
+        tiles, slots = M // block_rows * -(-block_rows // bm) * -(-N // bn), 256 * per_cu
+        whole, left = divmod(tiles, slots)
+        fixed = fixed_publish if publish else fixed
+        if 2 * left > slots:
+            stage += (full - stage) * (2 * left - slots) // slots
+        cost = whole * (K // 64 * full + fixed) + (K // 64 * stage + fixed if left else 0)
+        if best is None or cost < best[0]:
+            best = (cost, name.strip())
+    return best[1]
 
 
 # --------------------------------------------------------------------------- oracle side

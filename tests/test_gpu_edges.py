@@ -195,6 +195,31 @@ def test_publish_tall_tiles(heads, gh, gw, k_in):
     test_publish_tiles(heads, 1, gh, gw, (1, 2, 3, 4, 5), k_in)
 
 
+# Every tile by name (the cost model may send the products above elsewhere): last row and column tiles of one row and eight columns,
+# the shortest walk and a longer one; 256 x 256 also with a short last round of 4 and of 24 tiles behind three whole ones.
+LINEAR_TILES = [("kTile256", 769, 13064, 128), ("kTile256", 4097, 3592, 768), ("kTile256", 49153, 776, 128), ("kTile256", 50561, 904, 256),
+                ("kTile192", 1537, 4872, 128), ("kTile192", 2881, 2824, 384), ("kTile128x256", 513, 11016, 128),
+                ("kTile256x128", 1025, 3720, 128), ("kTile256x128", 4680, 1544, 384), ("kTile128", 2050, 1160, 128),
+                ("kTile64", 1100, 1400, 256), ("kTile64Wide", 129, 200, 768)]
+
+
+@pytest.mark.parametrize("tile,M,N,K", LINEAR_TILES)
+def test_linear_tile_by_name(tile, M, N, K):
+    assert Hn.gemm_tile(M, N, K) == tile
+    test_linear_tiles(M, N, K)
+
+
+# ... and publishing: blocks whose last page has one to four tokens, an odd number of pages.
+PUBLISH_TILES = [("kTile256", 18, 10, 13, 5, 128), ("kTile128x256", 16, 13, 20, 3, 128), ("kTile256x128", 4, 19, 27, 5, 128),
+                 ("kTile128", 2, 13, 51, 3, 256)]
+
+
+@pytest.mark.parametrize("tile,heads,gh,gw,blocks,k_in", PUBLISH_TILES)
+def test_publish_tile_by_name(tile, heads, gh, gw, blocks, k_in):
+    assert Hn.gemm_tile(blocks * gh * gw, 3 * heads * 128, k_in, gh * gw, publish=True) == tile
+    test_publish_tiles(heads, 1, gh, gw, tuple(range(1, 1 + blocks)), k_in)
+
+
 # The cache write in workgroups of a page, half a page or a quarter of one (by pages x heads of the launch): all blocks in one launch and one
 # by one, which take different ones (40 and 10, 260 and 65, 480 and 120, 600 and 150 pages), write the same bytes, padding and
 # swizzle included; the smallest is compared with the oracle elsewhere.
