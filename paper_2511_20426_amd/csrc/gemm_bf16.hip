@@ -159,16 +159,21 @@ __device__ __forceinline__ void tile_at(const GemmArgs& a, int nth, int* tm, int
   *tm = band * kBandRows + in_band - *tn * height;
 }
 
-// Tiles that an XCD takes in the last round of `left`.  Up to 64 go 16 to an XCD, for with a few each the tiles of an XCD have hardly a slab
-// in common and the round takes longer: 23400 x 5120 x 5120 (48 left) 875 us, 906 dealt evenly; 1560 x 1536 x 1536 14.5 / 15.0.  More
-// go evenly: 18720 x 3072 x 3072 (120 left) 255 us, 267 with 32 to an XCD.
+// Tiles that an XCD takes in the last round of `left`.  Up to 64 go 16 to an XCD: with a few each, the tiles of an XCD
+// have hardly a slab in common.  Us dealt evenly / 16 to an XCD, 256 x 256 tiles of x 5120 x 5120 by whole rounds and
+// tiles left: 7 + 8 882 / 857, 7 + 28 891 / 874, 7 + 48 908 / 883, 4 + 16 513 / 508, 3 + 12 407 / 406, 6 + 44 724 / 724, 6 + 24 the
+// other way 731 / 743; with K 1536 4 + 2 179.3 / 177.1, 5 + 16 217.0 / 214.5.  More than 64 go evenly: 16 to an XCD gives little and
+// not always, 6 + 84 750 / 750, 7 + 68 900 / 894, 7 + 108 923 / 913, 3 + 72 407 / 407, 32 to an XCD 3 + 72 425, 5 + 80 622 / 635.
 __host__ __device__ constexpr int last_round_share(int left) { return left > 0 && left <= 64 ? 16 : (left + 7) >> 3; }
 
-// Which tile a workgroup of gemm_bf16_kernel takes, if any.  Tiles are numbered down bands of eight row tiles and dealt to the XCDs (workgroup b runs on b % 8) 32
-// at a time, so that the workgroups that run together on one share 8 row slabs of X and 4 of W in its L2, and those of all
-// XCDs lie close together; what is left over for the last round goes by last_round_share.  Blocks of 8 x 4 tiles counted in a grid of
-// such blocks left some XCDs with twice the tiles of others (4680 x 1536 x 1536 in 222 tiles 39 us, now 23); one contiguous range per
-// XCD keeps them apart (23400 x 15360 x 5120 2740 us, now 2440).
+// Which tile a workgroup of gemm_bf16_kernel takes, if any.  Tiles are numbered down bands of eight row tiles and dealt
+// to the XCDs (workgroup b runs on b % 8) 32 at a time, so that the workgroups that run together on one share 8 row slabs
+// of X and 4 of W in its L2, and those of all XCDs lie close together; what is left over for the last round goes by
+// last_round_share.  Blocks of 8 x 4 tiles counted in a grid of such blocks, as they were dealt before, leave some XCDs with
+// twice the tiles of others where the grid's edge cuts blocks: 4680 x 1536 x 1536 in 222 tiles 39 us, now 23; 9360 x 5120 x
+// 5120 404 / 332, 14040 x 15360 x 5120 1500 / 1465.  Where it does not they are up to 1 % ahead, within the noise: 23400 x
+// 15360 x 5120 2454 / 2471, 18720 x 15360 x 5120 1983 / 2001, 23400 x 5120 x 5120 881 / 879, 16128 x 15360 x 5120 1688 / 1685.
+// One contiguous range per XCD keeps the XCDs apart (23400 x 15360 x 5120 2740).
 __device__ __forceinline__ bool tile_of_workgroup(const GemmArgs& a, int* tm, int* tn) {
   const int xcd = int(blockIdx.x & 7), j = int(blockIdx.x >> 3), total = a.tiles_m * a.tiles_n;
   const int full = total >> 8, left = total & 255, share = last_round_share(left);
