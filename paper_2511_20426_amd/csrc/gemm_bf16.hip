@@ -58,6 +58,7 @@ struct GemmArgs {
   int32_t M, N, K;
   int64_t ldx, ldw, ldy;                          // row strides in elements
   int32_t tiles_m, tiles_n, xcd_tiles;            // xcd_tiles: gemm_tile_kernel's tiles of an XCD
+  int32_t block_cols;                             // columns of 8 x 4 blocks where tiles go by blocks (publishing), or 0
   // Row tiles are counted inside row blocks of block_rows rows, tiles_per_block each (the last
   // one ragged): one block spanning all of M for the plain product, one per in-flight block when
   // publishing.
@@ -174,8 +175,15 @@ __host__ __device__ constexpr int last_round_share(int left) { return left > 0 &
 // 5120 404 / 332, 14040 x 15360 x 5120 1500 / 1465.  Where it does not they are up to 1 % ahead, within the noise: 23400 x
 // 15360 x 5120 2454 / 2471, 18720 x 15360 x 5120 1983 / 2001, 23400 x 5120 x 5120 881 / 879, 16128 x 15360 x 5120 1688 / 1685.
 // One contiguous range per XCD keeps the XCDs apart (23400 x 15360 x 5120 2740).
+template <bool kPublish>
 __device__ __forceinline__ bool tile_of_workgroup(const GemmArgs& a, int* tm, int* tn) {
   const int xcd = int(blockIdx.x & 7), j = int(blockIdx.x >> 3), total = a.tiles_m * a.tiles_n;
+  if (kPublish && a.block_cols > 0) {
+    const int block = (j >> 5) * 8 + xcd, band = block / a.block_cols;
+    *tm = band * kBandRows + (j & 7);
+    *tn = (block - band * a.block_cols) * 4 + ((j >> 3) & 3);
+    return *tm < a.tiles_m;
+  }
   const int full = total >> 8, left = total & 255, share = last_round_share(left);
   int nth;
   if (j < full * 32) {
@@ -197,7 +205,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(GemmArgs a) {
   int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, grp = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int tm, tn;
-  if (!tile_of_workgroup(a, &tm, &tn)) return;
+  if (!tile_of_workgroup<kPublish>(a, &tm, &tn)) return;
   const int blk = tm / a.tiles_per_block, tile_in_blk = tm - blk * a.tiles_per_block;
   const int m0 = blk * a.block_rows + tile_in_blk * kTileRows, n0 = tn * kTile;
   const int m_end = min((blk + 1) * a.block_rows, a.M);           // first row past this tile's row block
@@ -465,9 +473,21 @@ int32_t check_gemm_shape(int64_t M, int32_t N, int32_t K, int64_t ldx, int64_t l
   return CA_OK;
 }
 
+// Whether a publishing product's tiles go by blocks of 8 x 4 in the last round too (before it the two ways are one).  A
+// tile of v takes several us longer in the epilogue than one of q: by blocks an XCD takes q, k and v in turn, dealt evenly
+// some get v, k and v again.  It pays where blocks are whole, no XCD has a round more for them and the last round is not a
+// short one.  Us dealt / by blocks: 14040 x 3072 x 1024 98 / 93, x 512 71 / 64, 23400 x 3072 x 1024 162 / 154, 23400 x 9216 x
+// 3072 999 / 987, 14040 x 6144 x 2048 312 / 313, 18720 x 3072 x 1024 131.6 / 132.5; with a short last round 3510 x 9216 x 3072 194 / 202,
+// 13200 x 6144 x 2048 304 / 311; with an XCD a round longer 14040 x 15360 x 5120 1653 / 1708, 23400 x 4608 x 1536 299 / 322.
+int publish_block_cols(const GemmArgs& a) {
+  const int total = a.tiles_m * a.tiles_n, cols = a.tiles_n / 4, blocks = (a.tiles_m + kBandRows - 1) / kBandRows * cols;
+  return a.tiles_n % 4 == 0 && total > 256 && (total & 255) > 64 && (blocks + 7) / 8 == (total + 255) / 256 ? cols : 0;
+}
+
 // workgroups for tile_of_workgroup: whole rounds of 256, then eight times an XCD's share of the rest
 unsigned tile_workgroups(const GemmArgs& a) {
   const unsigned total = unsigned(a.tiles_m) * unsigned(a.tiles_n);
+  if (a.block_cols > 0) return (total + 255u) & ~255u;
   return (total & ~255u) + 8 * unsigned(last_round_share(int(total & 255u)));
 }
 
@@ -477,6 +497,7 @@ int32_t enqueue_gemm(GemmArgs& a, void* stream) {
   a.tiles_per_block = (a.block_rows + kTileRows - 1) / kTileRows;
   a.tiles_m = (a.M / a.block_rows) * a.tiles_per_block;
   a.tiles_n = (a.N + kTile - 1) / kTile;
+  a.block_cols = kPublish && kMt == 8 ? publish_block_cols(a) : 0;
   const auto kernel = gemm_bf16_kernel<kPublish, kMt>;
   hipLaunchKernelGGL(kernel, dim3(tile_workgroups(a)), dim3(256), kGemmLds, static_cast<hipStream_t>(stream), a);
   return finish_launch("gemm_bf16.hip");

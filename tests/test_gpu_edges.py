@@ -209,8 +209,9 @@ def test_linear_tile_by_name(tile, M, N, K):
     test_linear_tiles(M, N, K)
 
 
-# ... and publishing: blocks whose last page has one to four tokens, an odd number of pages.
-PUBLISH_TILES = [("kTile256", 18, 10, 13, 5, 128), ("kTile128x256", 16, 13, 20, 3, 128), ("kTile256x128", 4, 19, 27, 5, 128),
+# ... and publishing: blocks whose last page has one to four tokens, an odd number of pages; 256 x 256 dealt evenly and (8 heads, 420
+# tiles) by blocks.
+PUBLISH_TILES = [("kTile256", 18, 10, 13, 5, 128), ("kTile256", 8, 57, 27, 5, 128), ("kTile128x256", 16, 13, 20, 3, 128), ("kTile256x128", 4, 19, 27, 5, 128),
                  ("kTile128", 2, 13, 51, 3, 256)]
 
 
