@@ -336,11 +336,14 @@ int32_t launch_cache_write(const RopeGeom& g, int dtype, int32_t n_blocks, const
     const int64_t target = all_pages > 4 * n_cu && all_pages <= 8 * n_cu ? 2 * n_cu : 4 * n_cu;
     const int64_t per_group = (all_pages + target - 1) / target;
     a.heads_per_group = int32_t(per_group < g.heads ? per_group : g.heads);
-    // A workgroup's chain (angles, positions, transposition) is as long as its tokens are many: small launches take a half or a quarter of a
-    // page each, and so do those that would leave a second round of two workgroups a CU half empty.  Microseconds per launch (replayed from
-    // a graph) with 128 / 64 / 32 tokens, by pages: 3 6.5 / 4.6 / 3.8, 36 6.9 / 4.9 / 4.2, 144 8.0 / 6.9 / 6.6, 240 9.0 / 8.0 / 8.1, 280 11.3 / 9.2 / 8.8,
-    // 400 12.8 / 14.1 / 14.0, 444 14.3 / 15.9 / 15.2, 560 20.4 / 16.4 / 17.7, 720 21.4 / 19.8 / 21.6, 1000 28.2 / 27.7 / 28.6, 7400 195 / 198 / 241.
-    const int tokens = 4 * all_pages <= 3 * n_cu ? 32 : (4 * all_pages <= 5 * n_cu || (all_pages > 2 * n_cu && all_pages <= 4 * n_cu) ? 64 : kPage);
+    // A workgroup's chain (angles, positions, transposition) is as long as its tokens are many: small launches take a half
+    // or a quarter of a page each, and so do those that would leave a second round of two workgroups a CU half empty.
+    // Microseconds per launch (replayed from a graph) with 128 / 64 / 32 tokens, by pages: 3 6.5 / 4.6 / 3.8, 36 6.9 / 4.9 / 4.2,
+    // 144 8.0 / 6.9 / 6.6, 240 9.0 / 8.0 / 8.1, 280 11.3 / 9.2 / 8.8, 400 12.8 / 14.1 / 14.0, 444 14.3 / 15.9 / 15.2, 560 20.4 / 16.4 / 17.7,
+    // 720 21.4 / 19.8 / 21.6, 7400 195 / 198 / 241; one launch after the other on inputs that are not in the caches: 504 15.3 / 16.9 / 18.1,
+    // 600 21.3 / 18.0 / 20.0, 800 24.8 / 23.0 / 22.6, 864 25.1 / 24.8 / 25.9, 888 26.8 / 27.9 / 26.9, 960 27.7 / 28.3 / 28.4, 1008 27.5 / 28.8 / 29.3.
+    const int tokens = 4 * all_pages <= 3 * n_cu ? 32 :
+                       4 * all_pages <= 5 * n_cu || (all_pages > 2 * n_cu && 8 * all_pages <= 27 * n_cu) ? 64 : kPage;
     const dim3 grid((unsigned)(pages_per_block * (kPage / tokens)),
                     (unsigned)((g.heads + a.heads_per_group - 1) / a.heads_per_group), (unsigned)n_blocks);
     size_t tab_bytes = 0;

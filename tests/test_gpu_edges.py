@@ -222,9 +222,10 @@ def test_publish_tile_by_name(tile, heads, gh, gw, blocks, k_in):
 
 
 # The cache write in workgroups of a page, half a page or a quarter of one (by pages x heads of the launch): all blocks in one launch and one
-# by one, which take different ones (40 and 10, 260 and 65, 480 and 120, 600 and 150 pages), write the same bytes, padding and
-# swizzle included; the smallest is compared with the oracle elsewhere.
-@pytest.mark.parametrize("heads,gh,gw", [(5, 11, 23), (13, 21, 27), (20, 21, 31), (30, 20, 32)])
+# by one, which take different ones but for the first (40 and 10 pages a quarter; 400 a page and 100 a quarter, 260 a half and 65 a
+# quarter, 480 a page and 120 a quarter, 600 a half and 150 a quarter, 880 a page and 220 a half), write the same bytes, padding
+# and swizzle included; the smallest is compared with the oracle elsewhere.
+@pytest.mark.parametrize("heads,gh,gw", [(5, 11, 23), (50, 11, 23), (13, 21, 27), (20, 21, 31), (30, 20, 32), (44, 20, 32)])
 def test_cache_write_workgroup_sizes(heads, gh, gw):
     import torch
     from paper_2511_20426_amd.runner import CascadePool
