@@ -82,9 +82,8 @@ struct AttnArgs {
   // pos * head is exact in fp32 for pos < 4096 and only its fractional part meets the hardware
   // sin / cos (measured: cos and sin within 4.2e-7 of fp64 for every pos < 4096 and every pair).
   int32_t pairs_t, pairs_h;            // pairs [0, pairs_t): frame axis, then pairs_h: row axis, rest: column axis
-  int32_t block_tokens, plane, grid_h, grid_w;   // plane = grid_h * grid_w
-  int32_t frames_per_block;
-  float inv_block, inv_plane, inv_grid_w, inv_frames;
+  int32_t plane, grid_h, grid_w, frames_per_block;   // plane = grid_h * grid_w
+  float inv_plane, inv_grid_w, inv_frames;
   // cos and sin per axis value present in a tile, in LDS: tab_f frames x pairs_t, then tab_y rows x pairs_h, then grid_w columns x
   // the rest; tab_y == 0: a geometry too large for it, every lane evaluates its own
   int32_t tab_f, tab_y;
@@ -803,11 +802,9 @@ int32_t launch_attn_bf16_rope(const AttnPlan& p, const QRopePlan& rp, int varian
   a.grid_h = rp.geom.grid_h;
   a.grid_w = rp.geom.grid_w;
   a.plane = rp.geom.grid_h * rp.geom.grid_w;
-  a.block_tokens = p.block_tokens;
-  a.inv_block = 1.0f / float(a.block_tokens);
   a.inv_plane = 1.0f / float(a.plane);
   a.inv_grid_w = 1.0f / float(a.grid_w);
-  a.frames_per_block = a.block_tokens / a.plane;
+  a.frames_per_block = p.block_tokens / a.plane;
   a.inv_frames = 1.0f / float(a.frames_per_block);
   // what the 256 consecutive rows of a tile can meet: that many frames, rows (from the first one's on, round the end), all columns
   a.tab_f = kRowsPerWg / a.plane + 2;

@@ -51,7 +51,6 @@ PART = 32768             # bytes of one operand's rows of one stage
 NW, NX = 3, 2            # ring depths; LDS = [W ring][X ring] = 160 KB
 XBASE = NW * PART
 PERIOD = 6               # stages after which both rings are back where they were
-SLOTS = 128              # MFMAs per stage and wave: 2 k-steps x 8 x 8 tiles
 
 ADDRW, ADDRX = 192, 198  # + 2*ring slot + kk
 OFFW, OFFX = 202, 210    # +i
@@ -105,17 +104,13 @@ def read_order(mt=8):
     return [(0, 0)] + [(1, t) for t in range(mt)] + [(0, t) for t in range(1, 8)]
 
 
-READ_ORDER = read_order()
-X_BY = 40               # the 8 X loads of a stage issue within this many slots behind the barrier
-
-
 def build_stage(P, mt=8):
     """Stage P (mod PERIOD) of the steady state: 16 mt slots of (MFMA, lines issued after it)."""
-    SLOTS, READ_ORDER, X_BY = 16 * mt, read_order(mt), 5 * mt
-    half = SLOTS // 2
-    read_gap = (half - 8) / len(READ_ORDER) if mt < 8 else 3
+    slots, order, x_by = 16 * mt, read_order(mt), 5 * mt    # x_by: X loads issue within this many slots behind the barrier
+    half = slots // 2
+    read_gap = (half - 8) / len(order) if mt < 8 else 3
     w_gap = (half - 12) / 8 if mt < 8 else 7
-    mf, tail = [], [[] for _ in range(SLOTS)]
+    mf, tail = [], [[] for _ in range(slots)]
     for kk in range(2):
         for ti in range(8):
             for tj in range(mt):
@@ -123,12 +118,12 @@ def build_stage(P, mt=8):
     # before the last k-step: this stage's last fragments are in registers; everything but the
     # W loads issued last has landed; behind the barrier this stage's buffers are free
     tail[half - 1] += ["s_waitcnt vmcnt(@VM@) lgkmcnt(0)", "s_barrier"]
-    tail[SLOTS - 1] += ["s_waitcnt lgkmcnt(0)"]
+    tail[slots - 1] += ["s_waitcnt lgkmcnt(0)"]
     atoms = []
     for kk in range(2):
         nstage, nkk = (P, 1) if kk == 0 else (P + 1, 0)
         prev = None
-        for k, (op, t) in enumerate(READ_ORDER):
+        for k, (op, t) in enumerate(order):
             at = half * kk + 1 + int(read_gap * k)
             prev = Atom([read_frag(1 - kk, op, t, nstage, nkk)], at, at, [prev] if prev else [], 0,
                         hard=half * kk + half - 6)
@@ -140,16 +135,16 @@ def build_stage(P, mt=8):
         atoms.append(prev)
     # (M0 is written in an earlier slot than its load, so that an MFMA stands between, and behind the load before)
     last = prev
-    for op, stage, i, at, hard in ([(1, P + 2, i, half + 4 + (i * X_BY) // mt, min(half + X_BY + 6, SLOTS - 12)) for i in range(mt)] +
-                                   [(0, P + 3, i, half + 6 + int(w_gap * i), SLOTS - 3 - (7 - i if mt < 8 else 0)) for i in range(8)]):
+    for op, stage, i, at, hard in ([(1, P + 2, i, half + 4 + (i * x_by) // mt, min(half + x_by + 6, slots - 12)) for i in range(mt)] +
+                                   [(0, P + 3, i, half + 6 + int(w_gap * i), slots - 3 - (7 - i if mt < 8 else 0)) for i in range(8)]):
         m0, load = load_lines(op, stage, i, mt)
         write = Atom([m0], at - 1, at - 1, [last], 0, hard=hard - 1)
         last = Atom([load], at, at, [write], 1, hard=hard)
         atoms += [write, last]
-    fixed = [2.0 + sum(quanta(l) for l in tail[i]) for i in range(SLOTS)]
+    fixed = [2.0 + sum(quanta(l) for l in tail[i]) for i in range(slots)]
     placed = schedule(fixed, atoms, CAP)
     out = []
-    for i in range(SLOTS):
+    for i in range(slots):
         lines = []
         for a in placed[i]:
             lines += a.lines
