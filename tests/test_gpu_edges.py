@@ -318,8 +318,9 @@ def test_bf16_short_last_pages(heads, gh, gw, nc, ni, scale):
 # ... and its moving exponent reference: rising, falling, past the fp32 exponent range, from one key to the next.  The bars are
 # those of the same ramps on few workgroups (the bf16 rounding of K moves logits of 25 by 5e-2, of 400 by 0.8).
 @pytest.mark.parametrize("ramp,bar", [((1.0, 24.0), 2e-2), ((24.0, 1.0), 2e-2), ((1.0, 400.0), 8e-2), ((1.0, 400.0, "step"), 8e-2)])
-def test_bf16_many_workgroups_moving_maximum(ramp, bar):
-    w = W.small_variant(W.CONFIGS["c3_wan1p3b_cascade5"], heads=90, grid_h=10, grid_w=13, n_cached=2, n_inflight=1)
+@pytest.mark.parametrize("gw", [13, 15])                     # with short last pages and without
+def test_bf16_many_workgroups_moving_maximum(ramp, bar, gw):
+    w = W.small_variant(W.CONFIGS["c3_wan1p3b_cascade5"], heads=90, grid_h=10, grid_w=gw, n_cached=2, n_inflight=1)
     q, k, v = W.draw_config(w, seed=31, k_ramp=ramp)
     pool = Hn.gpu_setup(w, k, v, [0, 1], [2])
     heads = [0, 89]

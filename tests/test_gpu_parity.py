@@ -283,7 +283,8 @@ def test_forward_on_unrotated_queries_rejects_what_it_does_not_cover():
 @pytest.mark.parametrize("mode", [BI, CA])
 @pytest.mark.parametrize("ramp,bar", [((1.0, 24.0), 2e-2), ((24.0, 1.0), 2e-2), ((1.0, 400.0), 8e-2),
                                       ((1.0, 400.0, "step"), 8e-2)])
-def test_bf16_moving_row_maximum(mode, ramp, bar):
+@pytest.mark.parametrize("gw", [13, 15])                     # last pages of 6 and of 66 tokens: the loop with short pages and the other
+def test_bf16_moving_row_maximum(mode, ramp, bar, gw):
     """The running exponent reference has to move: K grows (or shrinks) geometrically along the
     KV sequence, so the largest logit of a row rises by tens of log2 units over the pages (first
     case), never rises after the first page (second), or jumps by more than the fp32 exponent
@@ -294,8 +295,8 @@ def test_bf16_moving_row_maximum(mode, ramp, bar):
     size on the dominant weights: the bars (relative L2 2e-2 and 8e-2, measured 6e-3 and 3e-2)
     follow from that; what the test guards is the rescaling logic, whose failures are gross (inf,
     NaN, rows off by factors)."""
-    w = W.small_variant(W.CONFIGS["c3_wan1p3b_cascade5"], heads=2, grid_h=10, grid_w=13, n_cached=2, n_inflight=2)
-    _say(f"bf16 moving row maximum ramp={ramp} mode={mode}")
+    w = W.small_variant(W.CONFIGS["c3_wan1p3b_cascade5"], heads=2, grid_h=10, grid_w=gw, n_cached=2, n_inflight=2)
+    _say(f"bf16 moving row maximum ramp={ramp} mode={mode} gw={gw}")
     outs, ref, bound = _one_shot(w, mode, seed=31, k_ramp=ramp, bounded=True)
     got, want, bound = _cat(outs), _cat(ref), _cat(bound)
     assert np.isfinite(got).all()
