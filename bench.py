@@ -446,7 +446,10 @@ def main() -> int:
                            % (C, "cascade_attn_forward_rope (Q rotated inside the attention kernel)" if fused_q else
                               "rope3d_apply(Q) + " + ("cascade_attn_forward" if args.share is None
                                                       else "cascade_attn_forward_share"))},
-        "roofline": {"bound": "mfma", "kernel": "attn_bf16_kernel<%s, true>" % ("true" if fused_q else "false"), "achieved": achieved,
+        # (rotates Q, 16x16x32 loop, loop with short last pages)
+        "roofline": {"bound": "mfma", "kernel": "attn_bf16_kernel<%s, true, %s>" % ("true" if fused_q else "false",
+                                                                                    "true" if 0 < L % 128 <= 64 else "false"),
+                     "achieved": achieved,
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_TFLOPS,
                      "avg_launch_ms": attn_ms,
                      "traffic": ATTN_TRAFFIC_BYTES_C4 if (w.name == "c4_wan14b_cascade5" and
