@@ -84,8 +84,8 @@ struct AttnArgs {
   int32_t pairs_t, pairs_h;            // pairs [0, pairs_t): frame axis, then pairs_h: row axis, rest: column axis
   int32_t plane, grid_h, grid_w, frames_per_block;   // plane = grid_h * grid_w
   float inv_plane, inv_grid_w, inv_frames;
-  // cos and sin per axis value present in a tile, in LDS: tab_f frames x pairs_t, then tab_y rows x pairs_h, then grid_w columns x
-  // the rest; tab_y == 0: a geometry too large for it, every lane evaluates its own
+  // cos and sin per axis value present in a tile, in LDS: tab_f frames x pairs_t, then tab_y rows x pairs_h, then
+  // grid_w columns x the rest; tab_y == 0: a geometry too large for it, every lane evaluates its own
   int32_t tab_f, tab_y;
   int32_t lanes[64];                   // kLane*: first row, rows, visible blocks per segment; first frame per query block; KV slots
   float rev_hi[kMaxPairs], rev_lo[kMaxPairs];
@@ -180,8 +180,8 @@ constexpr int kTrigEntries = (kAttnLds - int(kTrigArea)) / 8;
 // an item walks 407 pages.
 //
 // kTails: the loop that walks half of a short last page (gen_attn_core.py), picked by has_tails.
-// kCore16: which of the two main loops.  Both walk the same pages the same way; they differ in the matrix instruction, and
-// so in where a lane's part of Q, of the accumulators and of a row sum is.
+// kCore16: which of the two main loops.  Both walk the same pages the same way; they differ in the matrix
+// instruction, and so in where a lane's part of Q, of the accumulators and of a row sum is.
 template <bool kRopeQ, bool kCore16, bool kTails>
 __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
@@ -643,20 +643,22 @@ int split_of_small_launch(int items_per_xcd, int cus_per_xcd, int items, int min
   return best;
 }
 
-// The loop on the 16x16x32 instruction draws less power a flop, the one on 32x32x16 needs fewer cycles: where most CUs
-// work at once and long enough, power decides.  Whole forwards, us, 32x32x16 / 16x16x32, by workgroups of a round x
-// pages of a walk: 171 x 259 545 / 528, 228 x 259 658 / 610, 228 x 43 135 / 129, 250 x 14 54.4 / 51.7, 200 x 10 41.1 / 40.6; 152 x 259 515 / 526,
-// 160 x 14 46.7 / 47.1, 240 x 5 35.9 / 36.4, 14 x 1 19.5 / 21.5.  Along the line a few go the other way by little: 200 x 14 48.3 / 49.1, 152 x 74 168 / 159.
+// The loop on the 16x16x32 instruction draws less power a flop, the one on 32x32x16 needs fewer cycles: where most
+// CUs work at once and long enough, power decides.  Whole forwards, us, 32x32x16 / 16x16x32, by workgroups of a round
+// x pages of a walk: 171 x 259 545 / 528, 228 x 259 658 / 610, 228 x 43 135 / 129, 250 x 14 54.4 / 51.7, 200 x 10
+// 41.1 / 40.6; 152 x 259 515 / 526, 160 x 14 46.7 / 47.1, 240 x 5 35.9 / 36.4, 14 x 1 19.5 / 21.5.  Along the line a
+// few go the other way by little: 200 x 14 48.3 / 49.1, 152 x 74 168 / 159.
 bool takes_core16(const AttnArgs& a, int max_pages, int n_cu) {
   const bool alone = a.full_items == 0;                        // all items cut
   const int64_t workgroups = int64_t(a.total_cols) * a.n_seg * (alone ? a.split : 1);
   return 3 * workgroups >= 2 * int64_t(n_cu) && max_pages / (alone ? a.split : 1) >= 10;
 }
 
-// Which launches take the loops with short pages: two steps instead of four are walked of a block's last page, and masked tiles find their code in
-// fewer places.  Whole forwards, us, without / with: 12 heads, five blocks of 1170 tokens (18 in the last page) 345 / 328, 40 heads of 180 (52)
-// 73 / 53.5, 40 of 390 (6) 64.5 / 56, 16 of 1683 (19) 148.8 / 143.3.  With more than 64 tokens in the last page both
-// loops walk the same steps and take the same time (55.0 / 55.3, 669 / 673).
+// Which launches take the loops with short pages: two steps instead of four are walked of a block's last page, and
+// masked tiles find their code in fewer places.  Whole forwards, us, without / with: 12 heads, five blocks of 1170
+// tokens (18 in the last page) 345 / 328, 40 heads of 180 (52) 73 / 53.5, 40 of 390 (6) 64.5 / 56, 16 of 1683 (19)
+// 148.8 / 143.3.  With more than 64 tokens in the last page both loops walk the same steps and take the same time
+// (55.0 / 55.3, 669 / 673).
 bool has_tails(const AttnArgs& a) { return a.last_valid <= 64; }
 
 // Fills the kernel arguments for one forward.  Splitting: `capacity` partial results fit in
@@ -806,7 +808,8 @@ int32_t launch_attn_bf16_rope(const AttnPlan& p, const QRopePlan& rp, int varian
   a.inv_grid_w = 1.0f / float(a.grid_w);
   a.frames_per_block = p.block_tokens / a.plane;
   a.inv_frames = 1.0f / float(a.frames_per_block);
-  // what the 256 consecutive rows of a tile can meet: that many frames, rows (from the first one's on, round the end), all columns
+  // what the 256 consecutive rows of a tile can meet: that many frames, rows (from the first one's on, round the
+  // end), all columns
   a.tab_f = kRowsPerWg / a.plane + 2;
   a.tab_y = kRowsPerWg / a.grid_w + 2 < a.grid_h ? kRowsPerWg / a.grid_w + 2 : a.grid_h;
   const int64_t entries = int64_t(a.tab_f) * a.pairs_t + int64_t(a.tab_y) * a.pairs_h + int64_t(a.grid_w) * (64 - a.pairs_t - a.pairs_h);

@@ -11,25 +11,26 @@
 // instructions, which is what the code below is written to keep down.
 //
 // Per tile, S^T = K Q^T and O^T += V^T P^T.  The order of the contraction index is free: for QK lane (g, r) = (lane /
-// 16, lane % 16) holds dims 16j + 4g .. +3 of key r, and k-step (j, i) multiplies dims 16j + 4g + i;
-// for PV k-step i multiplies keys 4g + i, which is what the S^T accumulator (keys 4g + i of query r in
-// register i) hands over without any movement; an accumulator tile c of O^T holds dims 4m + c
-// (2m + c at head_dim 32), so that one 16-byte load per key feeds four tiles.  V is loaded that way straight from the
-// pool: 16 lanes to a row.  K would meet 16 rows in an instruction (64 cache accesses for V's 16), so it is
-// loaded as it lies and turned through 16 rows of LDS of the wave's own.  A tile's V is requested before its K is multiplied, K
-// two tiles ahead.  Within a page and a block rows lie one behind the other, and a load needs no address of its own; a tile that
-// crosses into another page or ends its block finds its rows one by one.
+// 16, lane % 16) holds dims 16j + 4g .. +3 of key r, and k-step (j, i) multiplies dims 16j + 4g + i; for PV k-step i
+// multiplies keys 4g + i, which is what the S^T accumulator (keys 4g + i of query r in register i) hands over without
+// any movement; an accumulator tile c of O^T holds dims 4m + c (2m + c at head_dim 32), so that one 16-byte load per
+// key feeds four tiles.  V is loaded that way straight from the pool: 16 lanes to a row.  K would meet 16 rows in an
+// instruction (64 cache accesses for V's 16), so it is loaded as it lies and turned through 16 rows of LDS of the
+// wave's own.  A tile's V is requested before its K is multiplied, K two tiles ahead.  Within a page and a block rows
+// lie one behind the other, and a load needs no address of its own; a tile that crosses into another page or ends its
+// block finds its rows one by one.
 //
 // Weights are exp2(s c + n) with c = log2(e) / sqrt(D) and n = -(reference) c: one fused multiply-add and v_exp_f32
 // (within an ulp).  A row's reference moves only when four of its weights sum to more than kSlack, so that the common
-// tile has no maximum, no cross-lane step and no rescaling.  Errors against fp64 over 18 shapes and scales, six seeds each: 8.49e-8 ..
-// 1.03e-6, where weights of expf of rounded logits had 8.56e-8 .. 1.06e-6.
+// tile has no maximum, no cross-lane step and no rescaling.  Errors against fp64 over 18 shapes and scales, six seeds
+// each: 8.49e-8 .. 1.03e-6, where weights of expf of rounded logits had 8.56e-8 ..  1.06e-6.
 //
-// Measured (4 heads x 3 blocks of 576 rows, 3..5 KV blocks of 576, head_dim 128; whole step with two other launches): 118.8 us when loads
-// stood in a bunch and a tile took 117 vector instructions, 114.7 with 30, 101 with loads dealt out, 93 with the second round of
-// workgroups in reverse order (attention 82 us = 99 TFLOP/s; a loop of nothing but these MFMAs reaches 137 at the 2.1 GHz it
-// holds).  Two waves a SIMD take 2380 cycles a tile of each, one alone 2765, of which 2048 are products.  2 heads x 144
-// rows x 432 keys, head_dim 64: 10.5 us, launch and loads from cold caches.
+// Measured (4 heads x 3 blocks of 576 rows, 3..5 KV blocks of 576, head_dim 128; whole step with two other launches):
+// 118.8 us when loads stood in a bunch and a tile took 117 vector instructions, 114.7 with 30, 101 with loads dealt
+// out, 93 with the second round of workgroups in reverse order (attention 82 us = 99 TFLOP/s; a loop of nothing but
+// these MFMAs reaches 137 at the 2.1 GHz it holds).  Two waves a SIMD take 2380 cycles a tile of each, one alone
+// 2765, of which 2048 are products.  2 heads x 144 rows x 432 keys, head_dim 64: 10.5 us, launch and loads from cold
+// caches.
 //
 // Visibility per block pair follows Sec. 3.1 (a block is bidirectional inside), Sec. 3.3
 // (cached blocks visible to all) and Sec. 3.4 / 4.2 (bidirectional or block-causal cascade).
@@ -80,9 +81,9 @@ struct Geometry {                              // of the pool, in bytes
   float inv_page;                              // 1 / page_tokens
 };
 
-// Row `row` of the tile (keys past the block's end: its last one, `valid` exist), from the tile's first row on, in bytes.
-// kFar: pages of less than 16 tokens, of which a tile may span several, or farther apart than 32 bits of bytes; otherwise a tile
-// crosses into one more page at most.
+// Row `row` of the tile (keys past the block's end: its last one, `valid` exist), from the tile's first row on, in
+// bytes.  kFar: pages of less than 16 tokens, of which a tile may span several, or farther apart than 32 bits of
+// bytes; otherwise a tile crosses into one more page at most.
 template <int D, bool kFar>
 __device__ __forceinline__ auto row_offset(const AttnPlan& p, const Geometry& geo, const Tile& t, int row, int valid) {
   const int r = min(row, valid - 1);
@@ -155,8 +156,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_f32_kernel(F32Args a) {
   f32x4 k[T::kVecs], kin[T::kVecs];
   const int in_row = lane / T::kChunks, in_chunk = lane % T::kChunks;
   float* const mine = stage[wave];
-  // Where a lane's rows of a tile are: the same from tile to tile while rows lie in line, so found again only for a tile where
-  // they do not and for the one behind it
+  // Where a lane's rows of a tile are: the same from tile to tile while rows lie in line, so found again only for a
+  // tile where they do not and for the one behind it
   decltype(row_offset<D, kFar>(p, geo, Tile(), 0, 0)) k_off[T::kVecs], v_off[4];
   bool k_in_line = false, v_in_line = false;
   auto place_k = [&](const Tile& t) {
@@ -206,8 +207,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_f32_kernel(F32Args a) {
   f32x4 o[D / 16];
 #pragma unroll
   for (int c = 0; c < D / 16; ++c) o[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // l: of this lane's keys 4g .. 4g+3 only.  n is finite from the start, so that a tile of scores that are all -inf has weights
-  // of 0; the first other one has infinite ones and moves the reference
+  // l: of this lane's keys 4g .. 4g+3 only.  n is finite from the start, so that a tile of scores that are all -inf
+  // has weights of 0; the first other one has infinite ones and moves the reference
   float n = FLT_MAX, l = 0.f;
 
   if (t_begin < t_end) {
@@ -385,9 +386,9 @@ int32_t launch_attn_f32(const AttnPlan& p, const void* q, void* out, const void*
   int n_cu = 0;
   if (const int32_t rc = device_cu_count(&n_cu); rc != CA_OK) return rc;
   const int cus_per_xcd = n_cu >= 8 ? n_cu / 8 : 1;
-  // Two workgroups share a CU.  Where the launch is between one and two of them a CU, the second round goes the other way, so that the CUs
-  // with the longest walks get the shortest ones as their second: walks of 5 and 4 blocks then meet with 3 and 4 (8 at the
-  // most, 93 us) instead of 4 and 3 (9, 101 us).  Longer launches keep the longest first.
+  // Two workgroups share a CU.  Where the launch is between one and two of them a CU, the second round goes the other
+  // way, so that the CUs with the longest walks get the shortest ones as their second: walks of 5 and 4 blocks then
+  // meet with 3 and 4 (8 at the most, 93 us) instead of 4 and 3 (9, 101 us).  Longer launches keep the longest first.
   const bool fold = per_xcd > cus_per_xcd && per_xcd <= 2 * cus_per_xcd;
   a.fold_from = fold ? cus_per_xcd : INT32_MAX;
   a.fold_sum = cus_per_xcd + per_xcd - 1;

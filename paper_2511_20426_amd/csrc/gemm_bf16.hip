@@ -160,21 +160,23 @@ __device__ __forceinline__ void tile_at(const GemmArgs& a, int nth, int* tm, int
   *tm = band * kBandRows + in_band - *tn * height;
 }
 
-// Tiles that an XCD takes in the last round of `left`.  Up to 64 go 16 to an XCD: with a few each, the tiles of an XCD
-// have hardly a slab in common.  Us dealt evenly / 16 to an XCD, 256 x 256 tiles of x 5120 x 5120 by whole rounds and
-// tiles left: 7 + 8 882 / 857, 7 + 28 891 / 874, 7 + 48 908 / 883, 4 + 16 513 / 508, 3 + 12 407 / 406, 6 + 44 724 / 724, 6 + 24 the
-// other way 731 / 743; with K 1536 4 + 2 179.3 / 177.1, 5 + 16 217.0 / 214.5.  More than 64 go evenly: 16 to an XCD gives little and
-// not always, 6 + 84 750 / 750, 7 + 68 900 / 894, 7 + 108 923 / 913, 3 + 72 407 / 407, 32 to an XCD 3 + 72 425, 5 + 80 622 / 635.
+// Tiles that an XCD takes in the last round of `left`.  Up to 64 go 16 to an XCD: with a few each, the tiles of an
+// XCD have hardly a slab in common.  Us dealt evenly / 16 to an XCD, 256 x 256 tiles of x 5120 x 5120 by whole rounds
+// and tiles left: 7 + 8 882 / 857, 7 + 28 891 / 874, 7 + 48 908 / 883, 4 + 16 513 / 508, 3 + 12 407 / 406, 6 + 44 724
+// / 724, 6 + 24 the other way 731 / 743; with K 1536 4 + 2 179.3 / 177.1, 5 + 16 217.0 / 214.5.  More than 64 go
+// evenly: 16 to an XCD gives little and not always, 6 + 84 750 / 750, 7 + 68 900 / 894, 7 + 108 923 / 913, 3 + 72 407
+// / 407, 32 to an XCD 3 + 72 425, 5 + 80 622 / 635.
 __host__ __device__ constexpr int last_round_share(int left) { return left > 0 && left <= 64 ? 16 : (left + 7) >> 3; }
 
-// Which tile a workgroup of gemm_bf16_kernel takes, if any.  Tiles are numbered down bands of eight row tiles and dealt
-// to the XCDs (workgroup b runs on b % 8) 32 at a time, so that the workgroups that run together on one share 8 row slabs
-// of X and 4 of W in its L2, and those of all XCDs lie close together; what is left over for the last round goes by
-// last_round_share.  Blocks of 8 x 4 tiles counted in a grid of such blocks, as they were dealt before, leave some XCDs with
-// twice the tiles of others where the grid's edge cuts blocks: 4680 x 1536 x 1536 in 222 tiles 39 us, now 23; 9360 x 5120 x
-// 5120 404 / 332, 14040 x 15360 x 5120 1500 / 1465.  Where it does not they are up to 1 % ahead, within the noise: 23400 x
-// 15360 x 5120 2454 / 2471, 18720 x 15360 x 5120 1983 / 2001, 23400 x 5120 x 5120 881 / 879, 16128 x 15360 x 5120 1688 / 1685.
-// One contiguous range per XCD keeps the XCDs apart (23400 x 15360 x 5120 2740).
+// Which tile a workgroup of gemm_bf16_kernel takes, if any.  Tiles are numbered down bands of eight row tiles and
+// dealt to the XCDs (workgroup b runs on b % 8) 32 at a time, so that the workgroups that run together on one share 8
+// row slabs of X and 4 of W in its L2, and those of all XCDs lie close together; what is left over for the last round
+// goes by last_round_share.  Blocks of 8 x 4 tiles counted in a grid of such blocks, as they were dealt before, leave
+// some XCDs with twice the tiles of others where the grid's edge cuts blocks: 4680 x 1536 x 1536 in 222 tiles 39 us,
+// now 23; 9360 x 5120 x 5120 404 / 332, 14040 x 15360 x 5120 1500 / 1465.  Where it does not they are up to 1 %
+// ahead, within the noise: 23400 x 15360 x 5120 2454 / 2471, 18720 x 15360 x 5120 1983 / 2001, 23400 x 5120 x 5120
+// 881 / 879, 16128 x 15360 x 5120 1688 / 1685.  One contiguous range per XCD keeps the XCDs apart (23400 x 15360 x
+// 5120 2740).
 template <bool kPublish>
 __device__ __forceinline__ bool tile_of_workgroup(const GemmArgs& a, int* tm, int* tn) {
   const int xcd = int(blockIdx.x & 7), j = int(blockIdx.x >> 3), total = a.tiles_m * a.tiles_n;
@@ -264,10 +266,10 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(GemmArgs a) {
         : "memory", "scc", "m0", CA_GEMM_CLOBBERS128);
   }
 
-  // The loop leaves 14 vector registers for what lives across it: the lane's places are worked out again from its number, the
-  // wave's are scalars.  Kept in vector registers they were spilled in the publishing form, and each reload in the
-  // epilogue is a memory latency: 23400 x 768 x 256 36.6 -> 33.7 us, 14040 x 3072 x 1024 103.4 -> 98.3, 23400 x 15360 x 5120
-  // 2653 -> 2633.
+  // The loop leaves 14 vector registers for what lives across it: the lane's places are worked out again from its
+  // number, the wave's are scalars.  Kept in vector registers they were spilled in the publishing form, and each
+  // reload in the epilogue is a memory latency: 23400 x 768 x 256 36.6 -> 33.7 us, 14040 x 3072 x 1024 103.4 -> 98.3,
+  // 23400 x 15360 x 5120 2653 -> 2633.
   asm volatile("" : "+v"(tid));
   lane = tid & 63, l15 = lane & 15, grp = lane >> 4;
 
@@ -312,11 +314,11 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(GemmArgs a) {
 }
 
 
-// Smaller tiles, for products whose 256 x 256 tiles would leave CUs idle: K walked in the same stages of 64, through a
-// ring of kStages in LDS filled by global -> LDS loads, kWavesM x kWavesN waves of 16 x 16 tiles, operands read one k-step
-// ahead.  What bounds them: LDS reads and fills (128 x 128 in eight waves: 128 KB a stage = 1024 cycles, 1000 measured, for
-// 512 of the matrix pipe), at 64 x 64 with few workgroups the latency of a stage; that is why the smallest takes eight
-// waves and six stages.
+// Smaller tiles, for products whose 256 x 256 tiles would leave CUs idle: K walked in the same stages of 64, through
+// a ring of kStages in LDS filled by global -> LDS loads, kWavesM x kWavesN waves of 16 x 16 tiles, operands read one
+// k-step ahead.  What bounds them: LDS reads and fills (128 x 128 in eight waves: 128 KB a stage = 1024 cycles, 1000
+// measured, for 512 of the matrix pipe), at 64 x 64 with few workgroups the latency of a stage; that is why the
+// smallest takes eight waves and six stages.
 template <int BM, int BN, int kWavesM, int kWavesN, int kStages>
 struct TileShape {
   static constexpr int kBm = BM, kBn = BN, kWavesAlongM = kWavesM, kRing = kStages;
@@ -473,12 +475,13 @@ int32_t check_gemm_shape(int64_t M, int32_t N, int32_t K, int64_t ldx, int64_t l
   return CA_OK;
 }
 
-// Whether a publishing product's tiles go by blocks of 8 x 4 in the last round too (before it the two ways are one).  A
-// tile of v takes several us longer in the epilogue than one of q: by blocks an XCD takes q, k and v in turn, dealt evenly
-// some get v, k and v again.  It pays where blocks are whole, no XCD has a round more for them and the last round is not a
-// short one.  Us dealt / by blocks: 14040 x 3072 x 1024 98 / 93, x 512 71 / 64, 23400 x 3072 x 1024 162 / 154, 23400 x 9216 x
-// 3072 999 / 987, 14040 x 6144 x 2048 312 / 313, 18720 x 3072 x 1024 131.6 / 132.5; with a short last round 3510 x 9216 x 3072 194 / 202,
-// 13200 x 6144 x 2048 304 / 311; with an XCD a round longer 14040 x 15360 x 5120 1653 / 1708, 23400 x 4608 x 1536 299 / 322.
+// Whether a publishing product's tiles go by blocks of 8 x 4 in the last round too (before it the two ways are one).
+// A tile of v takes several us longer in the epilogue than one of q: by blocks an XCD takes q, k and v in turn, dealt
+// evenly some get v, k and v again.  It pays where blocks are whole, no XCD has a round more for them and the last
+// round is not a short one.  Us dealt / by blocks: 14040 x 3072 x 1024 98 / 93, x 512 71 / 64, 23400 x 3072 x 1024
+// 162 / 154, 23400 x 9216 x 3072 999 / 987, 14040 x 6144 x 2048 312 / 313, 18720 x 3072 x 1024 131.6 / 132.5; with a
+// short last round 3510 x 9216 x 3072 194 / 202, 13200 x 6144 x 2048 304 / 311; with an XCD a round longer 14040 x
+// 15360 x 5120 1653 / 1708, 23400 x 4608 x 1536 299 / 322.
 int publish_block_cols(const GemmArgs& a) {
   const int total = a.tiles_m * a.tiles_n, cols = a.tiles_n / 4, blocks = (a.tiles_m + kBandRows - 1) / kBandRows * cols;
   return a.tiles_n % 4 == 0 && total > 256 && (total & 255) > 64 && (blocks + 7) / 8 == (total + 255) / 256 ? cols : 0;
@@ -515,22 +518,24 @@ int32_t enqueue_gemm_tiles(GemmArgs& a, void* stream) {
 }
 
 // Which tile a product takes.  Outputs are the same to the last bit with every one of them (each is one chain of the
-// same matrix instruction over k in steps of 32), so the choice is the cheapest by a model of what was measured: rounds
-// of workgroups over the CUs times (stages of 64 k x time of a stage + set-up and epilogue).  A stage takes longer when
-// most CUs work (`full`, from half of them on in proportion: the last round has its own).  Microseconds (fixed: plain, publishing):
+// same matrix instruction over k in steps of 32), so the choice is the cheapest by a model of what was measured:
+// rounds of workgroups over the CUs times (stages of 64 k x time of a stage + set-up and epilogue).  A stage takes
+// longer when most CUs work (`full`, from half of them on in proportion: the last round has its own).  Microseconds
+// (fixed: plain, publishing):
 //   256 x 256 (asm loops)   stage 1.0 .. 1.19, fixed 8, 12.5      256 x 128   stage 0.85 .. 0.87, fixed 5.8, 6.25
 //   192 x 256               0.82 .. 0.95, 7.5                     128 x 128   0.43, 5, 4.5
 //   128 x 256               0.58 .. 0.66, 7, 9.25                 64 x 64     two a CU 0.31, 4; one a CU 0.165, 4
-// Over 226 products the pick is 0.4 % slower than the fastest tile in the geometric mean, 16 % at the worst (16568 x 1408 x 128).  Whole
-// calls, us, 256 x 256 first and then what is taken: 257 x 768 x 1024 (6 tiles of 256 x 256) 22.7 -> 8.1, 64 x 128 x 5120
-// 80 -> 17, 1200 x 1400 x 1152 27.7 -> 10.1, 23400 x 128 x 5120 86 -> 39 (128 x 128), 4680 x 1536 x 1536 32.7 -> 22.2
-// (128 x 256), 4680 x 4608 x 1536 69.8 -> 58.7 (192), 3000 x 3000 x 2944 56.2 -> 47.3 (192), 1170 x 15360 x 5120 191 -> 157
-// (192); 256 x 256 stays where its tiles fill the chip: 23400 x 15360 x 5120 2440 against 2540, 8192^3 670 against 750.
-// 256 x 128, of compiled code, is for column counts that 256 does not divide well (an odd number of heads): 14040 x 1152 x
-// 384 19.6 against 23.0 with 192, 23400 x 640 x 640 25.8 / 29.7, 17961 x 328 x 2432 36.1 / 38.8.
-// The publishing epilogue needs whole pages and heads: 128 or 256 rows.  It writes pages instead of rows, which the
-// largest tiles pay for most: of 23400 x 768 x 256, 34.0 us with 256 x 256, 33.5 with 128 x 256, 26.6 with 256 x 128, 29.4
-// with 128 x 128; 23400 x 3072 x 1024 163 / 176 / 182 / 206; 7920 x 2304 x 768 52 / 45 / 49 / 46.
+// Over 226 products the pick is 0.4 % slower than the fastest tile in the geometric mean, 16 % at the worst (16568 x
+// 1408 x 128).  Whole calls, us, 256 x 256 first and then what is taken: 257 x 768 x 1024 (6 tiles of 256 x 256) 22.7
+// -> 8.1, 64 x 128 x 5120 80 -> 17, 1200 x 1400 x 1152 27.7 -> 10.1, 23400 x 128 x 5120 86 -> 39 (128 x 128), 4680 x
+// 1536 x 1536 32.7 -> 22.2 (128 x 256), 4680 x 4608 x 1536 69.8 -> 58.7 (192), 3000 x 3000 x 2944 56.2 -> 47.3 (192),
+// 1170 x 15360 x 5120 191 -> 157 (192); 256 x 256 stays where its tiles fill the chip: 23400 x 15360 x 5120 2440
+// against 2540, 8192^3 670 against 750.  256 x 128, of compiled code, is for column counts that 256 does not divide
+// well (an odd number of heads): 14040 x 1152 x 384 19.6 against 23.0 with 192, 23400 x 640 x 640 25.8 / 29.7, 17961
+// x 328 x 2432 36.1 / 38.8.  The publishing epilogue needs whole pages and heads: 128 or 256 rows.  It writes pages
+// instead of rows, which the largest tiles pay for most: of 23400 x 768 x 256, 34.0 us with 256 x 256, 33.5 with 128
+// x 256, 26.6 with 256 x 128, 29.4 with 128 x 128; 23400 x 3072 x 1024 163 / 176 / 182 / 206; 7920 x 2304 x 768 52 /
+// 45 / 49 / 46.
 enum GemmTile { kTile256, kTile192, kTile256x128, kTile128x256, kTile128, kTile64, kTile64Wide };
 
 int32_t pick_gemm_tile(const GemmArgs& a, bool publish, GemmTile* tile) {

@@ -306,8 +306,8 @@ def barriers(R, short, tail, k_barrier_slot):
 
 
 def last_step_atoms(core, pe, last_sub, hard):
-    """What the last step of a page leaves for a loop with short pages: where its V rows are, and whether the branch at the end of the page
-    has to look closer."""
+    """What the last step of a page leaves for a loop with short pages: where its V rows are, and whether the branch at
+    the end of the page has to look closer."""
     moves = [f"v_mov_b32 {V(core.XOVL + k)}, {V(core.XOV + core.XOV_STRIDE * last_sub + k)}" for k in range(core.XOV_STRIDE)]
     look = Atom([f"s_cmp_eq_u32 s{S_PGCUR}, s{S_SHORT}", f"s_cselect_b32 s{S_SPECIAL}, 1, 0",
                  f"s_cmp_eq_u32 s{S_NLEFT}, 0", f"s_cselect_b32 s{S_SPECIAL}, 1, s{S_SPECIAL}"], 0, hard - 2, [pe], 0, hard=hard)
@@ -485,8 +485,8 @@ def emit_cold(E, s_cur, s_next, p_cur, cold, back, valid_sreg, core=None):
 
 
 def emit_cold_shared(E, s_cur, s_next, p_cur, cold, back, valid_sreg, core):
-    """The same for a loop with short pages: a few lines per step that lead to one copy of the code per tile parity (eight to twelve copies
-    were each fetched anew by a short walk: 1500 cycles a masked tile)."""
+    """The same for a loop with short pages: a few lines per step that lead to one copy of the code per tile parity
+    (eight to twelve copies were each fetched anew by a short walk: 1500 cycles a masked tile)."""
     mask, over, pc = f"MASK_{s_cur}_%=", f"OVER_{s_cur}_%=", E.label("PC")
     E.cold += [f"{cold}:", f"s_getpc_b64 s[{S_RET}:{S_RET + 1}]", f"{pc}:", f"s_sub_u32 s{S_RET}, s{S_RET}, {pc}-{back}",
                f"s_subb_u32 s{S_RET + 1}, s{S_RET + 1}, 0", f"s_mov_b32 s{S_VALID}, s{valid_sreg}",
@@ -511,8 +511,8 @@ def emit_step(E, R, par, vmcnt, core, tails=False, short=False):
 
 
 def emit_pages_with_tails(E, stem, body, exits):
-    """The page loop with short pages: body(E, par, short) emits a page.  A page whose end has to be looked at closer (the walk is over or the next
-    page is short) leads out of line."""
+    """The page loop with short pages: body(E, par, short) emits a page. A page whose end has to be looked at closer
+    (the walk is over or the next page is short) leads out of line."""
     top, spec, short = ([f"{stem}{x}{par}_%=" for par in range(2)] for x in ("TOP", "SPEC", "SHORT"))
 
     def page_end(F, par):
@@ -625,17 +625,18 @@ def emit_results(E):
         E.e(f"v_accvgpr_read_b32 {V(r)}, {A(r)}")
 
 
-CORE = SimpleNamespace(XOV=XOV, XOVL=XOVL, XOV_STRIDE=2, rescale_lines=rescale_lines, emit_mask=emit_mask, SLOTS=32, K_BARRIER_SLOT=K_BARRIER_SLOT, build_step=build_step, emit_cold=emit_cold, emit_drain=emit_drain,
+CORE = SimpleNamespace(XOV=XOV, XOVL=XOVL, XOV_STRIDE=2, rescale_lines=rescale_lines, emit_mask=emit_mask, SLOTS=32,
+                       K_BARRIER_SLOT=K_BARRIER_SLOT, build_step=build_step, emit_cold=emit_cold, emit_drain=emit_drain,
                        emit_operand_setup=emit_operand_setup, emit_clear=emit_clear, emit_first_tile=emit_first_tile,
                        emit_first_reads=emit_first_reads, emit_results=emit_results)
 
 
 def generate(core=None, tails=False):
-    """The whole block; what depends on the shape of the matrix instruction comes from `core`.  tails: the loop with short pages, for
-    launches whose blocks end in a page of 64 tokens or less: of that page two steps are walked instead of four, and one copy of
-    the out-of-line code serves all steps of a parity.  A short page has its two steps (0 and 3 of the page loop, the second with the V rows of
-    the first) out of line: V(q), K(q+1) are awaited together in the middle of the first, all loads of a page pair
-    issue in the second."""
+    """The whole block; what depends on the shape of the matrix instruction comes from `core`. tails: the loop with
+    short pages, for launches whose blocks end in a page of 64 tokens or less: of that page two steps are walked
+    instead of four, and one copy of the out-of-line code serves all steps of a parity. A short page has its two
+    steps (0 and 3 of the page loop, the second with the V rows of the first) out of line: V(q), K(q+1) are awaited
+    together in the middle of the first, all loads of a page pair issue in the second."""
     core = core or CORE
     E = Emitter()
     # ---- set-up: inputs to fixed registers

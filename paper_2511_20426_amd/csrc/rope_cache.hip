@@ -327,21 +327,22 @@ int32_t launch_cache_write(const RopeGeom& g, int dtype, int32_t n_blocks, const
     a.pool = static_cast<uint8_t*>(pool);
     a.tok_stride = tok_stride; a.head_stride = head_stride;
     a.block_tokens = block_tokens; a.pages_per_block = pages_per_block;
-    // A CU holds two of these workgroups (250 registers).  Heads are shared out so that one round takes all of up to eight
-    // pages a CU, and twice as many workgroups beyond.  Measured on 256 CUs: 1480 pages in 370 workgroups 37.4 us, in 740 43;
-    // 600 in 600 22.1, in 300 23.0; 7400 in 925 or more 196, in 555 217.
+    // A CU holds two of these workgroups (250 registers).  Heads are shared out so that one round takes all of up to
+    // eight pages a CU, and twice as many workgroups beyond.  Measured on 256 CUs: 1480 pages in 370 workgroups 37.4
+    // us, in 740 43; 600 in 600 22.1, in 300 23.0; 7400 in 925 or more 196, in 555 217.
     int n_cu = 0;
     if (const int32_t rc = device_cu_count(&n_cu); rc != CA_OK) return rc;
     const int64_t all_pages = int64_t(pages_per_block) * n_blocks * g.heads;
     const int64_t target = all_pages > 4 * n_cu && all_pages <= 8 * n_cu ? 2 * n_cu : 4 * n_cu;
     const int64_t per_group = (all_pages + target - 1) / target;
     a.heads_per_group = int32_t(per_group < g.heads ? per_group : g.heads);
-    // A workgroup's chain (angles, positions, transposition) is as long as its tokens are many: small launches take a half
-    // or a quarter of a page each, and so do those that would leave a second round of two workgroups a CU half empty.
-    // Microseconds per launch (replayed from a graph) with 128 / 64 / 32 tokens, by pages: 3 6.5 / 4.6 / 3.8, 36 6.9 / 4.9 / 4.2,
-    // 144 8.0 / 6.9 / 6.6, 240 9.0 / 8.0 / 8.1, 280 11.3 / 9.2 / 8.8, 400 12.8 / 14.1 / 14.0, 444 14.3 / 15.9 / 15.2, 560 20.4 / 16.4 / 17.7,
-    // 720 21.4 / 19.8 / 21.6, 7400 195 / 198 / 241; one launch after the other on inputs that are not in the caches: 504 15.3 / 16.9 / 18.1,
-    // 600 21.3 / 18.0 / 20.0, 800 24.8 / 23.0 / 22.6, 864 25.1 / 24.8 / 25.9, 888 26.8 / 27.9 / 26.9, 960 27.7 / 28.3 / 28.4, 1008 27.5 / 28.8 / 29.3.
+    // A workgroup's chain (angles, positions, transposition) is as long as its tokens are many: small launches take a
+    // half or a quarter of a page each, and so do those that would leave a second round of two workgroups a CU half
+    // empty.  Microseconds per launch (replayed from a graph) with 128 / 64 / 32 tokens, by pages: 3 6.5 / 4.6 / 3.8,
+    // 36 6.9 / 4.9 / 4.2, 144 8.0 / 6.9 / 6.6, 240 9.0 / 8.0 / 8.1, 280 11.3 / 9.2 / 8.8, 400 12.8 / 14.1 / 14.0, 444
+    // 14.3 / 15.9 / 15.2, 560 20.4 / 16.4 / 17.7, 720 21.4 / 19.8 / 21.6, 7400 195 / 198 / 241; one launch after the
+    // other on inputs that are not in the caches: 504 15.3 / 16.9 / 18.1, 600 21.3 / 18.0 / 20.0, 800 24.8 / 23.0 /
+    // 22.6, 864 25.1 / 24.8 / 25.9, 888 26.8 / 27.9 / 26.9, 960 27.7 / 28.3 / 28.4, 1008 27.5 / 28.8 / 29.3.
     const int tokens = 4 * all_pages <= 3 * n_cu ? 32 :
                        4 * all_pages <= 5 * n_cu || (all_pages > 2 * n_cu && 8 * all_pages <= 27 * n_cu) ? 64 : kPage;
     const dim3 grid((unsigned)(pages_per_block * (kPage / tokens)),

@@ -30,8 +30,8 @@ def test_f32_key_tiles(head_dim, fpb, gh, gw, page, nc, ni):
         Hn.assert_close(out, ref, "f32", f"f32 tiles D={head_dim} L={w.block_tokens} page={page} mode={mode}")
 
 
-# ... and shared out over four waves instead of eight, at head_dim 128 from more work items (heads x row tiles x blocks) than CUs on:
-# 288 and 258 items, and 256, where it is eight still.
+# ... and shared out over four waves instead of eight, at head_dim 128 from more work items (heads x row tiles x
+# blocks) than CUs on: 288 and 258 items, and 256, where it is eight still.
 @pytest.mark.parametrize("heads,fpb,gh,gw,ni", [(4, 2, 5, 37, 3), (3, 1, 19, 36, 2), (4, 1, 10, 25, 4)])
 def test_f32_waves_per_row_tile(heads, fpb, gh, gw, ni):
     w = W.small_variant(W.CONFIGS["c1_tiny_f32"], heads=heads, grid_h=gh, grid_w=gw, frames_per_block=fpb, head_dim=128, rope_dims=DIMS[128],
@@ -45,8 +45,9 @@ def test_f32_waves_per_row_tile(heads, fpb, gh, gw, ni):
         Hn.assert_close(out, ref, "f32", f"f32 waves heads={heads} L={w.block_tokens} blocks={ni} mode={mode}")
 
 
-# ... and whose rows lie in line or not: pages just longer than a tile (every tile crosses into the next page), a little shorter than
-# two, whole tiles with a ragged last one; 480 items, whose second round is taken in reverse order.
+# ... and whose rows lie in line or not: pages just longer than a tile (every tile crosses into the next page), a
+# little shorter than two, whole tiles with a ragged last one; 480 items, whose second round is taken in reverse
+# order.
 @pytest.mark.parametrize("head_dim", [32, 64, 128])
 @pytest.mark.parametrize("heads,fpb,gh,gw,page,nc,ni", [(2, 1, 7, 11, 17, 2, 1), (2, 1, 9, 13, 31, 1, 2), (1, 2, 8, 9, 64, 1, 2), (4, 2, 16, 20, 100, 1, 3)])
 def test_f32_tiles_across_pages(head_dim, heads, fpb, gh, gw, page, nc, ni):
@@ -60,8 +61,8 @@ def test_f32_tiles_across_pages(head_dim, heads, fpb, gh, gw, page, nc, ni):
     Hn.assert_close(out, ref, "f32", f"f32 across pages D={head_dim} L={w.block_tokens} page={page}")
 
 
-# fp32 attention, an infinite V in a block's last row: its dimension is infinite, all else finite.  (The tile that row is in is
-# filled up with keys that do not exist.)
+# fp32 attention, an infinite V in a block's last row: its dimension is infinite, all else finite.  (The tile that row
+# is in is filled up with keys that do not exist.)
 @pytest.mark.parametrize("head_dim", [32, 64, 128])
 @pytest.mark.parametrize("fpb,gh,gw,page,nc", [(1, 1, 17, 48, 0), (1, 3, 11, 5, 1), (2, 5, 5, 16, 1)])
 def test_f32_infinite_value_in_the_last_row(head_dim, fpb, gh, gw, page, nc):
@@ -90,7 +91,8 @@ def _minus_infinity_scores(w, seed, low, high):
     return tuple(W.store(x, w.dtype) for x in (q, k, v))
 
 
-# fp32 attention, scores of minus infinity (a product out of range) over the whole first tile of some of a workgroup's waves: weight 0
+# fp32 attention, scores of minus infinity (a product out of range) over the whole first tile of some of a workgroup's
+# waves: weight 0
 @pytest.mark.parametrize("head_dim", [32, 64, 128])
 @pytest.mark.parametrize("low,high", [(5, 300), (16, 17), (16, 100), (0, 300)])
 def test_f32_scores_of_minus_infinity(head_dim, low, high):
@@ -119,8 +121,9 @@ def test_bf16_split_small_launch(heads, gh, gw, nc, ni):
         Hn.assert_close(out, ref, "bf16", f"split heads={heads} grid={gh}x{gw} nc={nc} ni={ni} mode={mode}", bound=bound)
 
 
-# The same with enough ranges of ten pages or more for the 16x16x32 loop (208 to 234 workgroups on 256 CUs): 26 items of 96 pages in
-# eight ranges each, 52 of 63 and 66 pages in four, 39 of 66 in six.  Queries rotated before and by the kernel.
+# The same with enough ranges of ten pages or more for the 16x16x32 loop (208 to 234 workgroups on 256 CUs): 26 items
+# of 96 pages in eight ranges each, 52 of 63 and 66 pages in four, 39 of 66 in six.  Queries rotated before and by the
+# kernel.
 @pytest.mark.parametrize("nc,ni,mode", [(31, 1, BI), (20, 2, CA), (20, 2, BI)])
 def test_bf16_split_launch_that_fills_the_chip(nc, ni, mode):
     w = W.small_variant(W.CONFIGS["c5_wan1p3b_rollout"], heads=13, grid_h=6, grid_w=43, frames_per_block=1, n_cached=nc, n_inflight=ni,
@@ -137,7 +140,7 @@ def test_bf16_split_launch_that_fills_the_chip(nc, ni, mode):
         Hn.assert_close(out[:, heads], ref, "bf16", f"cut launch on many workgroups nc={nc} ni={ni} mode={mode} {form.__name__}", bound=bound)
 
 
-# Every tile of the linear map: one row, a tile and one row, column counts that end inside a tile, the shortest and
+# Tiles of the linear map: one row, a tile and one row, column counts that end inside a tile, the shortest and
 # longer walks over k, several tiles per band and XCD.  (Two stages are fewer than any ring holds.)
 @pytest.mark.parametrize("M,N,K", [(1, 8, 128), (65, 72, 128), (129, 200, 768), (1100, 1400, 256), (2050, 1160, 128), (1345, 3000, 256),
                                    (1300, 4104, 128), (4680, 1544, 384), (9001, 136, 1024), (4100, 4104, 128)])
@@ -184,7 +187,8 @@ def test_publish_tiles(heads, fpb, gh, gw, ids, k_in):
     assert torch.equal(one.pool[:pages], two.pool[:pages])
 
 
-# ... of 128 and 192 rows by 256 columns, plain (last row and column tiles of one row and of a few columns) and publishing (pages of one token).
+# ... more of them, plain (last row and column tiles of one row and of a few columns) and publishing (pages of one
+# token).
 @pytest.mark.parametrize("M,N,K", [(1921, 2200, 256), (2881, 2824, 128), (2900, 2896, 384)])
 def test_linear_tall_tiles(M, N, K):
     test_linear_tiles(M, N, K)
@@ -195,8 +199,9 @@ def test_publish_tall_tiles(heads, gh, gw, k_in):
     test_publish_tiles(heads, 1, gh, gw, (1, 2, 3, 4, 5), k_in)
 
 
-# Every tile by name (the cost model may send the products above elsewhere): last row and column tiles of one row and eight columns,
-# the shortest walk and a longer one; 256 x 256 also with a short last round of 4 and of 24 tiles behind three whole ones.
+# Every tile by name (the cost model may send the products above elsewhere): last row and column tiles of one row and
+# eight columns, the shortest walk and a longer one; 256 x 256 also with a short last round of 4 and of 24 tiles
+# behind three whole ones.
 LINEAR_TILES = [("kTile256", 769, 13064, 128), ("kTile256", 4097, 3592, 768), ("kTile256", 49153, 776, 128), ("kTile256", 50561, 904, 256),
                 ("kTile192", 1537, 4872, 128), ("kTile192", 2881, 2824, 384), ("kTile128x256", 513, 11016, 128),
                 ("kTile256x128", 1025, 3720, 128), ("kTile256x128", 4680, 1544, 384), ("kTile128", 2050, 1160, 128),
@@ -209,8 +214,8 @@ def test_linear_tile_by_name(tile, M, N, K):
     test_linear_tiles(M, N, K)
 
 
-# ... and publishing: blocks whose last page has one to four tokens, an odd number of pages; 256 x 256 dealt evenly and (8 heads, 420
-# tiles) by blocks.
+# ... and publishing: blocks whose last page has one to four tokens, an odd number of pages; 256 x 256 dealt evenly
+# and (8 heads, 420 tiles) by blocks.
 PUBLISH_TILES = [("kTile256", 18, 10, 13, 5, 128), ("kTile256", 8, 57, 27, 5, 128), ("kTile128x256", 16, 13, 20, 3, 128), ("kTile256x128", 4, 19, 27, 5, 128),
                  ("kTile128", 2, 13, 51, 3, 256)]
 
@@ -221,10 +226,11 @@ def test_publish_tile_by_name(tile, heads, gh, gw, blocks, k_in):
     test_publish_tiles(heads, 1, gh, gw, tuple(range(1, 1 + blocks)), k_in)
 
 
-# The cache write in workgroups of a page, half a page or a quarter of one (by pages x heads of the launch): all blocks in one launch and one
-# by one, which take different ones but for the first (40 and 10 pages a quarter; 400 a page and 100 a quarter, 260 a half and 65 a
-# quarter, 480 a page and 120 a quarter, 600 a half and 150 a quarter, 880 a page and 220 a half), write the same bytes, padding
-# and swizzle included; the smallest is compared with the oracle elsewhere.
+# The cache write in workgroups of a page, half a page or a quarter of one (by pages x heads of the launch): all
+# blocks in one launch and one by one, which take different ones but for the first (40 and 10 pages a quarter; 400 a
+# page and 100 a quarter, 260 a half and 65 a quarter, 480 a page and 120 a quarter, 600 a half and 150 a quarter, 880
+# a page and 220 a half), write the same bytes, padding and swizzle included; the smallest is compared with the oracle
+# elsewhere.
 @pytest.mark.parametrize("heads,gh,gw", [(5, 11, 23), (50, 11, 23), (13, 21, 27), (20, 21, 31), (30, 20, 32), (44, 20, 32)])
 def test_cache_write_workgroup_sizes(heads, gh, gw):
     import torch
@@ -241,9 +247,10 @@ def test_cache_write_workgroup_sizes(heads, gh, gw):
     assert torch.equal(one.pool[:pages], two.pool[:pages])
 
 
-# Queries rotated by the attention kernel: cos and sin from a table in LDS per tile.  Many frames and rows to a tile, one row or column, a
-# tile that begins in the middle of a frame and goes round its end, the widest grid whose table fits (171 columns do not
-# always: their lanes evaluate their own), axes without pairs, query blocks that are not consecutive.
+# Queries rotated by the attention kernel: cos and sin from a table in LDS per tile.  Many frames and rows to a tile,
+# one row or column, a tile that begins in the middle of a frame and goes round its end, the widest grid whose table
+# fits (171 columns do not always: their lanes evaluate their own), axes without pairs, query blocks that are not
+# consecutive.
 @pytest.mark.parametrize("fpb,gh,gw,dims,infl", [(40, 1, 7, (44, 42, 42), (2, 3)), (3, 29, 3, (44, 42, 42), (2, 5)), (2, 9, 31, (44, 42, 42), (2, 3)),
                                                  (1, 2, 140, (44, 42, 42), (2, 3)), (1, 2, 171, (44, 42, 42), (2, 4)), (300, 1, 1, (44, 42, 42), (2,)),
                                                  (2, 11, 13, (0, 64, 64), (2, 3)), (2, 11, 13, (64, 64, 0), (2, 3)), (2, 11, 13, (126, 0, 2), (2, 3))])
@@ -258,15 +265,17 @@ def test_bf16_rotation_table(fpb, gh, gw, dims, infl):
     import torch
     for mode in (BI, CA):
         got = Hn.gpu_forward_rope(w, pool, q, list(infl), mode)
-        # the same rows through rope3d_apply, block by block, and the forward on rotated queries: two roundings of Q for one
+        # the same rows through rope3d_apply, block by block, and the forward on rotated queries: two roundings of Q
+        # for one
         qt = Hn.to_torch(q, "bf16")
         rot = torch.cat([pool.rope(qt[i * L:(i + 1) * L], fpb * g) for i, g in enumerate(infl)])
         ref = Hn.from_torch(pool.forward(rot, list(infl), mode), "bf16")
         assert np.isfinite(got).all() and Hn.rel_l2(got, ref) < 8e-3, (fpb, gh, gw, dims, mode, Hn.rel_l2(got, ref))
 
 
-# Queries rotated by the attention kernel are scaled by log2(e) / sqrt(D) behind the rotation: a pair that the rotation takes out of fp32's
-# range is infinite there as it is in rope3d_apply, and its row NaN, since K is zero in that pair.  With the table of angles and without.
+# Queries rotated by the attention kernel are scaled by log2(e) / sqrt(D) behind the rotation: a pair that the
+# rotation takes out of fp32's range is infinite there as it is in rope3d_apply, and its row NaN, since K is zero in
+# that pair.  With the table of angles and without.
 @pytest.mark.parametrize("gh,gw", [(3, 5), (1, 200)])
 def test_bf16_rotation_out_of_range(gh, gw):
     w = W.small_variant(W.CONFIGS["c3_wan1p3b_cascade5"], heads=2, grid_h=gh, grid_w=gw, frames_per_block=1, n_cached=1, n_inflight=1)
@@ -298,8 +307,9 @@ def test_bf16_many_workgroups(gh, gw, nc):
     Hn.assert_close(Hn.gpu_forward(w, pool, q, infl, BI)[:, heads], ref, "bf16", f"many workgroups L={w.block_tokens}", bound=bound)
 
 
-# ... and on few workgroups: last pages of 1 .. 64 tokens, of which half the steps are walked, and one token more; blocks of one
-# such page only; walks cut in front of, behind and between them; the reference moving beside a masked tile.
+# ... and on few workgroups: last pages of 1 .. 64 tokens, of which half the steps are walked, and one token more;
+# blocks of one such page only; walks cut in front of, behind and between them; the reference moving beside a masked
+# tile.
 @pytest.mark.parametrize("heads,gh,gw,nc,ni,scale", [(1, 8, 8, 4, 1, 1), (2, 3, 11, 2, 3, 1), (1, 3, 43, 3, 1, 1), (3, 10, 16, 2, 2, 1), (2, 7, 23, 3, 1, 4),
                                                      (1, 12, 16, 4, 2, 1), (2, 5, 13, 3, 2, 1), (1, 1, 1, 5, 1, 1)])
 def test_bf16_short_last_pages(heads, gh, gw, nc, ni, scale):
@@ -315,8 +325,9 @@ def test_bf16_short_last_pages(heads, gh, gw, nc, ni, scale):
                         **({} if scale == 1 else {"max_abs": 0.12, "rel": 1.2e-2}))
 
 
-# ... and its moving exponent reference: rising, falling, past the fp32 exponent range, from one key to the next.  The bars are
-# those of the same ramps on few workgroups (the bf16 rounding of K moves logits of 25 by 5e-2, of 400 by 0.8).
+# ... and its moving exponent reference: rising, falling, past the fp32 exponent range, from one key to the next.  The
+# bars are those of the same ramps on few workgroups (the bf16 rounding of K moves logits of 25 by 5e-2, of 400 by
+# 0.8).
 @pytest.mark.parametrize("ramp,bar", [((1.0, 24.0), 2e-2), ((24.0, 1.0), 2e-2), ((1.0, 400.0), 8e-2), ((1.0, 400.0, "step"), 8e-2)])
 @pytest.mark.parametrize("gw", [13, 15])                     # with short last pages and without
 def test_bf16_many_workgroups_moving_maximum(ramp, bar, gw):
@@ -371,10 +382,11 @@ def test_capture_of_other_sizes_than_the_eager_call():
         assert torch.equal(large.forward_rope(q, [2], BI), o)
 
 
-# Row sums are those of the probabilities before their rounding to bf16, in both main loops.  One key of weight 0.9 outside a walk's
-# first tile, its V zero, the others' 1 +- 0.3: a rounded weight in the row sum scales the whole row by up to 0.9 x 2^-8.  The reference
-# takes the kernel's own operands (Q scaled and rounded, K as its pages hold it), so that a row's mean ratio to it keeps, of relative
-# variance E2 each, the rounding of 128 results and of the light keys' weights: bars at 8 sigma a row, 2 sigma over the rows.
+# Row sums are those of the probabilities before their rounding to bf16, in both main loops.  One key of weight 0.9
+# outside a walk's first tile, its V zero, the others' 1 +- 0.3: a rounded weight in the row sum scales the whole row
+# by up to 0.9 x 2^-8.  The reference takes the kernel's own operands (Q scaled and rounded, K as its pages hold it),
+# so that a row's mean ratio to it keeps, of relative variance E2 each, the rounding of 128 results and of the light
+# keys' weights: bars at 8 sigma a row, 2 sigma over the rows.
 @pytest.mark.parametrize("heads", [2, 181])
 def test_bf16_row_sums_with_one_heavy_key(heads):
     w = W.small_variant(W.CONFIGS["c5_wan1p3b_rollout"], heads=heads, grid_h=10, grid_w=15, frames_per_block=1, n_cached=4, n_inflight=1,
@@ -407,8 +419,8 @@ def test_bf16_row_sums_with_one_heavy_key(heads):
         assert (np.abs(err) <= 8 * sigma).all() and np.sqrt((err ** 2).mean()) <= 2 * sigma.mean()
 
 
-# Scores of minus infinity over the whole first tile of a range of a cut walk (one head: every page a range), and of a walk: weight 0
-# (181 heads: one range an item, the 16x16x32 loop).
+# Scores of minus infinity over the whole first tile of a range of a cut walk (one head: every page a range), and of a
+# walk: weight 0 (181 heads: one range an item, the 16x16x32 loop).
 @pytest.mark.parametrize("heads", [1, 181])
 @pytest.mark.parametrize("low,high", [(5, 600), (32, 257), (0, 600), (0, 32)])
 def test_bf16_scores_of_minus_infinity(heads, low, high):
