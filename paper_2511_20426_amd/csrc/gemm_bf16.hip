@@ -522,11 +522,11 @@ int32_t enqueue_gemm_tiles(GemmArgs& a, void* stream) {
 // rounds of workgroups over the CUs times (stages of 64 k x time of a stage + set-up and epilogue).  A stage takes
 // longer when most CUs work (`full`, from half of them on in proportion: the last round has its own).  Microseconds
 // (fixed: plain, publishing):
-//   256 x 256 (asm loops)   stage 1.0 .. 1.19, fixed 8, 12.5      256 x 128   stage 0.85 .. 0.87, fixed 5.8, 6.25
-//   192 x 256               0.82 .. 0.95, 7.5                     128 x 128   0.43, 5, 4.5
+//   256 x 256 (asm loops)   stage 1.0 .. 1.19, fixed 11, 12.5     256 x 128   stage 0.85 .. 0.87, fixed 5.8, 6.25
+//   192 x 256               0.82 .. 0.97, 8.25                    128 x 128   0.43, 5, 4.5
 //   128 x 256               0.58 .. 0.66, 7, 9.25                 64 x 64     two a CU 0.31, 4; one a CU 0.165, 4
-// Over 226 products the pick is 0.4 % slower than the fastest tile in the geometric mean, 16 % at the worst (16568 x
-// 1408 x 128).  Whole calls, us, 256 x 256 first and then what is taken: 257 x 768 x 1024 (6 tiles of 256 x 256) 22.7
+// Over 270 products the pick is 0.4 % slower than the fastest tile in the geometric mean, 9 % at the worst (8987 x 4592
+// x 256).  Whole calls, us, 256 x 256 first and then what is taken: 257 x 768 x 1024 (6 tiles of 256 x 256) 22.7
 // -> 8.1, 64 x 128 x 5120 80 -> 17, 1200 x 1400 x 1152 27.7 -> 10.1, 23400 x 128 x 5120 86 -> 39 (128 x 128), 4680 x
 // 1536 x 1536 32.7 -> 22.2 (128 x 256), 4680 x 4608 x 1536 69.8 -> 58.7 (192), 3000 x 3000 x 2944 56.2 -> 47.3 (192),
 // 1170 x 15360 x 5120 191 -> 157 (192); 256 x 256 stays where its tiles fill the chip: 23400 x 15360 x 5120 2440
@@ -541,7 +541,7 @@ enum GemmTile { kTile256, kTile192, kTile256x128, kTile128x256, kTile128, kTile6
 int32_t pick_gemm_tile(const GemmArgs& a, bool publish, GemmTile* tile) {
   // fixed_publish: 0 where the tile does not publish
   static constexpr struct { int bm, bn, per_cu, threads, stage, full, fixed, fixed_publish; } kModel[] = {
-      {256, 256, 1, 256, 1000, 1190, 8000, 12500}, {192, 256, 1, 256, 820, 950, 7500, 0},
+      {256, 256, 1, 256, 1000, 1190, 11000, 12500}, {192, 256, 1, 256, 820, 970, 8250, 0},
       {256, 128, 1, 512, 850, 870, 5800, 6250},    {128, 256, 1, 256, 580, 660, 7000, 9250},
       {128, 128, 1, 512, 430, 430, 5000, 4500},    {64, 64, 2, 256, 310, 310, 4000, 0},
       {64, 64, 1, 512, 165, 165, 4000, 0}};

@@ -200,9 +200,9 @@ def test_publish_tall_tiles(heads, gh, gw, k_in):
 
 
 # Every tile by name (the cost model may send the products above elsewhere): last row and column tiles of one row and
-# eight columns, the shortest walk and a longer one; 256 x 256 also with a short last round of 4 and of 24 tiles
-# behind three whole ones.
-LINEAR_TILES = [("kTile256", 769, 13064, 128), ("kTile256", 4097, 3592, 768), ("kTile256", 49153, 776, 128), ("kTile256", 50561, 904, 256),
+# eight columns, the shortest walk and a longer one; 256 x 256 also with a short last round of 6 and of 18 tiles
+# behind six whole ones.
+LINEAR_TILES = [("kTile256", 769, 13064, 128), ("kTile256", 4097, 3592, 768), ("kTile256", 65537, 1288, 512), ("kTile256", 66049, 1288, 512),
                 ("kTile192", 1537, 4872, 128), ("kTile192", 2881, 2824, 384), ("kTile128x256", 513, 11016, 128),
                 ("kTile256x128", 1025, 3720, 128), ("kTile256x128", 4680, 1544, 384), ("kTile128", 2050, 1160, 128),
                 ("kTile64", 1100, 1400, 256), ("kTile64Wide", 129, 200, 768)]
