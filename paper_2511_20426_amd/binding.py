@@ -5,8 +5,9 @@ attention) runs in the library's HIP kernels.  Device buffers are passed as raw
 addresses (e.g. torch.Tensor.data_ptr()), the stream as a raw hipStream_t
 (torch.cuda.current_stream().cuda_stream): integers, or None for null.  A Context's go
 through `index`, which refuses everything else: ctypes takes bytes, str and its own objects for a
-pointer too, and a kernel would be given host memory (numpy's integers and tensors are refused as c_void_p refuses them).  There is no CPU fallback: if the
-library has not been built, importing this module raises.
+pointer too, and a kernel would be given host memory; numpy's integers and tensors are refused as
+c_void_p refuses them.  There is no CPU fallback: if the library has not been built, importing
+this module raises.
 """
 from __future__ import annotations
 
