@@ -11,7 +11,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.environ.get("CASCADE_ATTN_LIB") or os.path.join(PKG, "libcascade_attn.so")
 
-SOURCES = ["ca_meta.cpp", "ca_api.cpp", "ca_sched.cpp", "rope_cache.hip", "attn_f32.hip", "attn_bf16.hip", "mfma_peak.hip", "gemm_bf16.hip"]
+SOURCES = ["ca_meta.cpp", "ca_api.cpp", "ca_sched.cpp", "rope_cache.hip", "attn_f32.hip", "attn_bf16.hip", "mfma_peak.hip", "gemm_bf16.hip", "gemm_rows.hip"]
 
 # packed fp32 instructions are kept off for all device code
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
@@ -29,7 +29,7 @@ def build(verbose: bool = False, extra=(), bdir: str | None = None) -> str:
     bdir = bdir or os.path.join(PKG, "_build")
     os.makedirs(bdir, exist_ok=True)
     # the hand-scheduled main loops are emitted as inline-assembly includes
-    for core in ("attn_core", "attn_core16", "gemm_core"):
+    for core in ("attn_core", "attn_core16", "gemm_core", "gemm_rows"):
         subprocess.run([sys.executable, os.path.join(CSRC, f"gen_{core}.py"), os.path.join(bdir, f"{core}_gfx950.inc")],
                        check=True, stdout=None if verbose else subprocess.DEVNULL)
     common = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-I", os.path.join(ROOT, "include"),

@@ -120,6 +120,11 @@ int32_t run_mfma_microbench(int data_kind, int trips, void* scratch, size_t scra
                             double* tflops, double* clock_ghz);
 int32_t launch_gemm_bf16(const void* x, const void* w, void* y, int64_t M, int32_t N, int32_t K,
                          int64_t ldx, int64_t ldw, int64_t ldy, void* stream);
+// The same in tiles of tile_rows (256, 192 or 128) x 256, a workgroup taking several one after the other; gemm_rows_ready
+// readies its kernels for stream capture.
+int32_t launch_gemm_rows(int tile_rows, const void* x, const void* w, void* y, int32_t M, int32_t N, int32_t K,
+                         int64_t ldx, int64_t ldw, int64_t ldy, void* stream);
+int32_t gemm_rows_ready();
 // The QKV projection of n_blocks blocks (x rows: block b at b * block_tokens; w rows: q|k|v, head,
 // dim) with the publication of K/V to the blocks' slots fused into its epilogue; q_out gets the
 // packed, unrotated queries [n_blocks * block_tokens][heads * 128].
@@ -136,7 +141,7 @@ struct KernelLds {
   const void* kernel;
   int bytes;
 };
-enum LdsSlot { kLdsAttn, kLdsAttnRope, kLdsGemm, kLdsGemmPublish, kLdsSlots };
+enum LdsSlot { kLdsAttn, kLdsAttnRope, kLdsGemm, kLdsGemmRows, kLdsGemmPublish, kLdsSlots };
 int32_t ensure_dynamic_lds(const KernelLds* kernels, int n, LdsSlot slot);   // slot: which set of kernels
 int32_t finish_launch(const char* what);   // launchers end with this: CA_OK, or CA_EDEVICE after recording HIP's last error
 int32_t device_failure(const char* what, int hip_error);   // records the text, clears HIP's last error, returns CA_EDEVICE

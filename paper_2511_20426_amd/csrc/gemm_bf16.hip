@@ -1,22 +1,19 @@
 // Y[M,N] = X[M,K] . W[N,K]^T in bf16 with fp32 accumulation: the linear maps either side of the
 // attention inside a DiT layer (QKV projection before it, output projection after it).
 //
-//   gemm_bf16_kernel, for products that fill the chip with tiles of 256 columns (pick_gemm_tile; the others: gemm_tile_kernel).
-//   Workgroup = 4 waves = a tile of 256, 192 or 128 x 256 of Y, one wave per SIMD; the main loop (K in stages of
-//   64, both operands through rings in LDS that together fill its 160 KB) is the assembly
-//   emitted by gen_gemm_core.py, which documents the pipeline and the register map.  This file
-//   holds the set-up, the epilogue (tile transposed through LDS so that rows of Y are written as
-//   256-byte runs) and the launch.
-//   Workgroups are numbered so that the 32 running together on one XCD form an 8 x 4 block of
-//   tiles (tile_of_workgroup).
-//
-//   A second instantiation is the QKV projection of the blocks in flight with the publication of
+//   Plain products that fill the chip with tiles of 256 columns are gemm_rows.hip's; gemm_tile_kernel here takes the others
+//   (dispatch_gemm_plain picks).
+//   gemm_bf16_kernel is the QKV projection of the blocks in flight with the publication of
 //   their K/V fused into its epilogue (Sec. 3.3: every block's K/V go to the shared pool at every
 //   self-attention layer): row tiles are counted per block, so that a wave's 128 x 128 sub-tile is
 //   exactly one page of one head; K sub-tiles are rotated and stored as K pages, V sub-tiles are
 //   stored transposed as V pages, Q sub-tiles go to a packed tensor -- the same bytes the separate
 //   cache-write kernel produces from the projection's output, without that output ever being
 //   written.
+//   Workgroup = 4 waves = a tile of 256 or 128 x 256 of Y, one wave per SIMD; the main loop (K in stages of 64, both operands
+//   through rings in LDS that together fill its 160 KB) is the assembly emitted by gen_gemm_core.py, which documents
+//   the pipeline and the register map.  This file holds the set-up, the epilogue (the tile goes through LDS) and the launch.
+//   Workgroups are numbered so that the 32 running together on one XCD share rows of X and W in its L2 (tile_of_workgroup).
 #include <hip/hip_runtime.h>
 
 #include "ca_internal.hpp"
@@ -25,6 +22,7 @@ namespace ca {
 namespace {
 
 #include "rope_device.hpp"
+#include "gemm_tiles.hpp"
 
 typedef __attribute__((ext_vector_type(16))) uint32_t u32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
@@ -32,7 +30,6 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int kTile = 256;
-constexpr int kBandRows = 8;                      // row tiles of a band
 constexpr int kEpiRow = 272;                      // bytes per row of a wave's 128 x 128 bf16 tile in LDS
 constexpr int kEpiRowV = 260;                     // the same for a V sub-tile of the publishing epilogue, which is read
                                                   // back two bytes at a time down its columns: 65 dwords per row spread
@@ -152,22 +149,6 @@ __device__ __forceinline__ void publish_tile(const GemmArgs& a, const uint8_t* t
   }
 }
 
-// Tiles are numbered down bands of eight row tiles.
-__device__ __forceinline__ void tile_at(const GemmArgs& a, int nth, int* tm, int* tn) {
-  const int band = nth / (kBandRows * a.tiles_n), in_band = nth - band * kBandRows * a.tiles_n;
-  const int height = min(kBandRows, a.tiles_m - band * kBandRows);
-  *tn = in_band / height;
-  *tm = band * kBandRows + in_band - *tn * height;
-}
-
-// Tiles that an XCD takes in the last round of `left`.  Up to 64 go 16 to an XCD: with a few each, the tiles of an
-// XCD have hardly a slab in common.  Us dealt evenly / 16 to an XCD, 256 x 256 tiles of x 5120 x 5120 by whole rounds
-// and tiles left: 7 + 8 882 / 857, 7 + 28 891 / 874, 7 + 48 908 / 883, 4 + 16 513 / 508, 3 + 12 407 / 406, 6 + 44 724
-// / 724, 6 + 24 the other way 731 / 743; with K 1536 4 + 2 179.3 / 177.1, 5 + 16 217.0 / 214.5.  More than 64 go
-// evenly: 16 to an XCD gives little and not always, 6 + 84 750 / 750, 7 + 68 900 / 894, 7 + 108 923 / 913, 3 + 72 407
-// / 407, 32 to an XCD 3 + 72 425, 5 + 80 622 / 635.
-__host__ __device__ constexpr int last_round_share(int left) { return left > 0 && left <= 64 ? 16 : (left + 7) >> 3; }
-
 // Which tile a workgroup of gemm_bf16_kernel takes, if any.  Tiles are numbered down bands of eight row tiles and
 // dealt to the XCDs (workgroup b runs on b % 8) 32 at a time, so that the workgroups that run together on one share 8
 // row slabs of X and 4 of W in its L2, and those of all XCDs lie close together; what is left over for the last round
@@ -177,10 +158,9 @@ __host__ __device__ constexpr int last_round_share(int left) { return left > 0 &
 // ahead, within the noise: 23400 x 15360 x 5120 2454 / 2471, 18720 x 15360 x 5120 1983 / 2001, 23400 x 5120 x 5120
 // 881 / 879, 16128 x 15360 x 5120 1688 / 1685.  One contiguous range per XCD keeps the XCDs apart (23400 x 15360 x
 // 5120 2740).
-template <bool kPublish>
 __device__ __forceinline__ bool tile_of_workgroup(const GemmArgs& a, int* tm, int* tn) {
   const int xcd = int(blockIdx.x & 7), j = int(blockIdx.x >> 3), total = a.tiles_m * a.tiles_n;
-  if (kPublish && a.block_cols > 0) {
+  if (a.block_cols > 0) {
     const int block = (j >> 5) * 8 + xcd, band = block / a.block_cols;
     *tm = band * kBandRows + (j & 7);
     *tn = (block - band * a.block_cols) * 4 + ((j >> 3) & 3);
@@ -195,19 +175,19 @@ __device__ __forceinline__ bool tile_of_workgroup(const GemmArgs& a, int* tm, in
     if (in_round >= left) return false;
     nth = full * 256 + in_round;
   }
-  tile_at(a, nth, tm, tn);
+  tile_at(a.tiles_m, a.tiles_n, nth, tm, tn);
   return true;
 }
 
-// kMt: 16-row sub-tiles of X to a wave; a tile of Y has 32 kMt rows (256, 192 or 128) and 256 columns.
-template <bool kPublish, int kMt>
+// kMt: 16-row sub-tiles of X to a wave; a tile of Y has 32 kMt rows (256 or 128) and 256 columns.
+template <int kMt>
 __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(GemmArgs a) {
   constexpr int kTileRows = 32 * kMt, kWaveRows = 16 * kMt;
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, grp = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int tm, tn;
-  if (!tile_of_workgroup<kPublish>(a, &tm, &tn)) return;
+  if (!tile_of_workgroup(a, &tm, &tn)) return;
   const int blk = tm / a.tiles_per_block, tile_in_blk = tm - blk * a.tiles_per_block;
   const int m0 = blk * a.block_rows + tile_in_blk * kTileRows, n0 = tn * kTile;
   const int m_end = min((blk + 1) * a.block_rows, a.M);           // first row past this tile's row block
@@ -251,13 +231,6 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(GemmArgs a) {
           "=&{v[80:95]}"(o[5]), "=&{v[96:111]}"(o[6]), "=&{v[112:127]}"(o[7])
         : CA_GEMM_OPERANDS, [offx4] "v"(offx[4]), [offx5] "v"(offx[5]), [offx6] "v"(offx[6]), [offx7] "v"(offx[7])
         : "memory", "scc", "m0", CA_GEMM_CLOBBERS);
-  } else if constexpr (kMt == 6) {
-    asm volatile(
-#include "gemm_core192_gfx950.inc"
-        : "=&{v[0:15]}"(o[0]), "=&{v[16:31]}"(o[1]), "=&{v[32:47]}"(o[2]), "=&{v[48:63]}"(o[3]), "=&{v[64:79]}"(o[4]),
-          "=&{v[80:95]}"(o[5])
-        : CA_GEMM_OPERANDS, [offx4] "v"(offx[4]), [offx5] "v"(offx[5])
-        : "memory", "scc", "m0", CA_GEMM_CLOBBERS192);
   } else {
     asm volatile(
 #include "gemm_core128_gfx950.inc"
@@ -276,11 +249,11 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(GemmArgs a) {
   // ---- epilogue: the wave's tile of kWaveRows (m) x 128 (n) goes through LDS to come out row by row.
   // Pair p of MFMA tile T = kMt ti + tj: n = 16 ti + 4 grp + 2 p, m = 16 tj + l15.
   __syncthreads();                                    // every wave is done with the stage buffers
-  const int v_section = kPublish && (n0 + wn * 128) / (a.pub.heads * 128) == 2;
+  const int v_section = (n0 + wn * 128) / (a.pub.heads * 128) == 2;
   const int pitch = v_section ? kEpiRowV : kEpiRow;
-  // publishing with 128 rows: the two waves of a page share its 128 x 128 tile
-  constexpr bool kShared = kPublish && kMt == 4;
-  static_assert(!kPublish || kMt == 8 || kMt == 4, "a wave's rows are a page or half of one");
+  // with 128 rows the two waves of a page share its 128 x 128 tile
+  constexpr bool kShared = kMt == 4;
+  static_assert(kMt == 8 || kMt == 4, "a wave's rows are a page or half of one");
   uint8_t* mine = kShared ? lds + wn * kEpiWave + wm * kWaveRows * pitch : lds + wave * kEpiWave;
 #pragma unroll
   for (int T = 0; T < 8 * kMt; ++T) {
@@ -293,17 +266,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(GemmArgs a) {
     }
   }
   __syncthreads();
-  if constexpr (!kPublish) {
-#pragma unroll 4
-    for (int it = 0; it < kWaveRows / 4; ++it) {
-      const int row = it * 4 + (lane >> 4), c = lane & 15;
-      const u32x4 v = *reinterpret_cast<const u32x4*>(mine + row * kEpiRow + c * 16);
-      const int gm = m0 + wm * kWaveRows + row;
-      // the result passes through once: keep it from displacing the operand tiles in the caches
-      if (gm < m_end && n0 + wn * 128 + c * 8 < a.N)            // n_out is a multiple of 8: a chunk is inside or outside
-        __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(a.y + int64_t(gm) * a.ldy + n0 + wn * 128 + c * 8));
-    }
-  } else if constexpr (kShared) {
+  if constexpr (kShared) {
     publish_tile<128>(a, lds + wn * kEpiWave, n0 + wn * 128, blk, tile_in_blk, m0, reinterpret_cast<float2*>(lds + 2 * kEpiWave),
                       wm * 64 + lane, tid, 256);
   } else {
@@ -349,7 +312,7 @@ __global__ __launch_bounds__(T::kThreads) void gemm_tile_kernel(GemmArgs a) {
   const int nth = int(blockIdx.x & 7) * a.xcd_tiles + int(blockIdx.x >> 3);
   if (nth >= a.tiles_m * a.tiles_n) return;
   int tm, tn;
-  tile_at(a, nth, &tm, &tn);
+  tile_at(a.tiles_m, a.tiles_n, nth, &tm, &tn);
   const int blk = tm / a.tiles_per_block, tile_in_blk = tm - blk * a.tiles_per_block;
   const int m0 = blk * a.block_rows + tile_in_blk * BM, n0 = tn * BN;
   const int m_end = min((blk + 1) * a.block_rows, a.M);
@@ -494,14 +457,14 @@ unsigned tile_workgroups(const GemmArgs& a) {
   return (total & ~255u) + 8 * unsigned(last_round_share(int(total & 255u)));
 }
 
-template <bool kPublish, int kMt>
+template <int kMt>
 int32_t enqueue_gemm(GemmArgs& a, void* stream) {
   constexpr int kTileRows = 32 * kMt;
   a.tiles_per_block = (a.block_rows + kTileRows - 1) / kTileRows;
   a.tiles_m = (a.M / a.block_rows) * a.tiles_per_block;
   a.tiles_n = (a.N + kTile - 1) / kTile;
-  a.block_cols = kPublish && kMt == 8 ? publish_block_cols(a) : 0;
-  const auto kernel = gemm_bf16_kernel<kPublish, kMt>;
+  a.block_cols = kMt == 8 ? publish_block_cols(a) : 0;
+  const auto kernel = gemm_bf16_kernel<kMt>;
   hipLaunchKernelGGL(kernel, dim3(tile_workgroups(a)), dim3(256), kGemmLds, static_cast<hipStream_t>(stream), a);
   return finish_launch("gemm_bf16.hip");
 }
@@ -521,7 +484,8 @@ int32_t enqueue_gemm_tiles(GemmArgs& a, void* stream) {
 // same matrix instruction over k in steps of 32), so the choice is the cheapest by a model of what was measured:
 // rounds of workgroups over the CUs times (stages of 64 k x time of a stage + set-up and epilogue).  A stage takes
 // longer when most CUs work (`full`, from half of them on in proportion: the last round has its own).  Microseconds
-// (fixed: plain, publishing):
+// (fixed: plain, publishing; the plain ones of 256 columns are of a workgroup that ends with its tile: such products go on
+// to rows_tile, which weighs gemm_rows.hip's against the cheapest of the others):
 //   256 x 256 (asm loops)   stage 1.0 .. 1.19, fixed 11, 12.5     256 x 128   stage 0.85 .. 0.87, fixed 5.8, 6.25
 //   192 x 256               0.82 .. 0.97, 8.25                    128 x 128   0.43, 5, 4.5
 //   128 x 256               0.58 .. 0.66, 7, 9.25                 64 x 64     two a CU 0.31, 4; one a CU 0.165, 4
@@ -538,7 +502,8 @@ int32_t enqueue_gemm_tiles(GemmArgs& a, void* stream) {
 // 45 / 49 / 46.
 enum GemmTile { kTile256, kTile192, kTile256x128, kTile128x256, kTile128, kTile64, kTile64Wide };
 
-int32_t pick_gemm_tile(const GemmArgs& a, bool publish, GemmTile* tile) {
+// compiled, compiled_cost: the cheapest of the tiles of compiled code that do not publish, if asked for
+int32_t pick_gemm_tile(const GemmArgs& a, bool publish, GemmTile* tile, GemmTile* compiled, int64_t* compiled_cost) {
   // fixed_publish: 0 where the tile does not publish
   static constexpr struct { int bm, bn, per_cu, threads, stage, full, fixed, fixed_publish; } kModel[] = {
       {256, 256, 1, 256, 1000, 1190, 11000, 12500}, {192, 256, 1, 256, 820, 970, 8250, 0},
@@ -562,31 +527,71 @@ int32_t pick_gemm_tile(const GemmArgs& a, bool publish, GemmTile* tile) {
       best = cost;
       *tile = GemmTile(i);
     }
+    if (compiled && i != kTile256 && i != kTile192 && i != kTile128x256 && cost < *compiled_cost) {
+      *compiled = GemmTile(i);
+      *compiled_cost = cost;
+    }
   }
   return CA_OK;
 }
 
-template <bool kPublish>
-int32_t dispatch_gemm(GemmArgs& a, void* stream) {
+// Tile height of gemm_rows.hip that a plain product takes, or 0 where one of the tiles of compiled code is cheaper.  A
+// workgroup goes on from tile to tile there, so that a round costs its stages and the results' way out, and a launch its
+// set-up once: nanoseconds by stages of 64 k = start + whole rounds x (stages x full + tile) + last round (stages x stage +
+// tile), stage up to full from half of the CUs on.  Fitted to 254 products; the pick is 0.14 % slower than the fastest of
+// them, 7 % at the worst (3737 x 15120 x 384).  Whole calls, us, as pick_gemm_tile has it with a tile to a workgroup / now: 23400 x
+// 5120 x 256 101 / 80, 10709 x 4200 x 256 43.8 / 30.5, 5882 x 8776 x 640 82 / 63, 4680 x 3072 x 512 19.1 / 17.5, 4680 x 4608 x 1536 59 /
+// 55, 23400 x 15360 x 5120 2583 / 2453.  The 256 x 128 tile stays ahead of an equal cost (14040 x 1152 x 384 20.1, 192 x 256 21.5).
+int rows_tile(const GemmArgs& a, int n_cu, int64_t compiled, GemmTile by) {
+  static constexpr struct { int rows, start, stage, full, tile; } kRows[] = {
+      {256, 2260, 960, 1325, 5100}, {192, 2280, 754, 1070, 3900}, {128, 2840, 594, 785, 2410}};
+  const int64_t stages = a.K / 64, limit = by == kTile256x128 ? compiled - compiled / 14 : compiled;
+  int64_t best = limit;
+  int rows = 0;
+  for (const auto& m : kRows) {
+    const int64_t tiles = ((a.M + int64_t(m.rows) - 1) / m.rows) * ((a.N + 255) / 256), left = tiles % n_cu;
+    const int64_t stage = m.stage + (2 * left > n_cu ? (m.full - m.stage) * (2 * left - n_cu) / n_cu : 0);
+    const int64_t cost = m.start + tiles / n_cu * (stages * m.full + m.tile) + (left > 0 ? stages * stage + m.tile : 0);
+    if (cost < best) {
+      best = cost;
+      rows = m.rows;
+    }
+  }
+  return rows;
+}
+
+int32_t dispatch_gemm_publish(GemmArgs& a, void* stream) {
   GemmTile tile = kTile256;
-  if (const int32_t rc = pick_gemm_tile(a, kPublish, &tile); rc != CA_OK) return rc;
-  const KernelLds kernels[] = {{reinterpret_cast<const void*>(gemm_bf16_kernel<kPublish, 8>), kGemmLds},
-                               {reinterpret_cast<const void*>(gemm_bf16_kernel<kPublish, 4>), kGemmLds},
-                               {reinterpret_cast<const void*>(gemm_tile_kernel<Tile256x128, kPublish>), Tile256x128::kLds},
-                               {reinterpret_cast<const void*>(gemm_tile_kernel<Tile128, kPublish>), Tile128::kLds},
-                               {reinterpret_cast<const void*>(gemm_bf16_kernel<false, 6>), kGemmLds},
+  if (const int32_t rc = pick_gemm_tile(a, true, &tile, nullptr, nullptr); rc != CA_OK) return rc;
+  const KernelLds kernels[] = {{reinterpret_cast<const void*>(gemm_bf16_kernel<8>), kGemmLds},
+                               {reinterpret_cast<const void*>(gemm_bf16_kernel<4>), kGemmLds},
+                               {reinterpret_cast<const void*>(gemm_tile_kernel<Tile256x128, true>), Tile256x128::kLds},
+                               {reinterpret_cast<const void*>(gemm_tile_kernel<Tile128, true>), Tile128::kLds}};
+  if (const int32_t rc = ensure_dynamic_lds(kernels, 4, kLdsGemmPublish); rc != CA_OK) return rc;
+  if (tile == kTile128x256) return enqueue_gemm<4>(a, stream);
+  if (tile == kTile256x128) return enqueue_gemm_tiles<Tile256x128, true>(a, stream);
+  if (tile == kTile128) return enqueue_gemm_tiles<Tile128, true>(a, stream);
+  return enqueue_gemm<8>(a, stream);
+}
+
+int32_t dispatch_gemm_plain(GemmArgs& a, void* stream) {
+  GemmTile tile = kTile256, compiled = kTile128;
+  int64_t cost = INT64_MAX;
+  int n_cu = 0;
+  if (const int32_t rc = pick_gemm_tile(a, false, &tile, &compiled, &cost); rc != CA_OK) return rc;
+  if (const int32_t rc = device_cu_count(&n_cu); rc != CA_OK) return rc;
+  const KernelLds kernels[] = {{reinterpret_cast<const void*>(gemm_tile_kernel<Tile256x128, false>), Tile256x128::kLds},
+                               {reinterpret_cast<const void*>(gemm_tile_kernel<Tile128, false>), Tile128::kLds},
                                {reinterpret_cast<const void*>(gemm_tile_kernel<Tile64, false>), Tile64::kLds},
                                {reinterpret_cast<const void*>(gemm_tile_kernel<Tile64Wide, false>), Tile64Wide::kLds}};
-  if (const int32_t rc = ensure_dynamic_lds(kernels, kPublish ? 4 : 7, kPublish ? kLdsGemmPublish : kLdsGemm); rc != CA_OK) return rc;
-  if constexpr (!kPublish) {
-    if (tile == kTile192) return enqueue_gemm<false, 6>(a, stream);
-    if (tile == kTile64) return enqueue_gemm_tiles<Tile64, false>(a, stream);
-    if (tile == kTile64Wide) return enqueue_gemm_tiles<Tile64Wide, false>(a, stream);
-  }
-  if (tile == kTile128x256) return enqueue_gemm<kPublish, 4>(a, stream);
-  if (tile == kTile256x128) return enqueue_gemm_tiles<Tile256x128, kPublish>(a, stream);
-  if (tile == kTile128) return enqueue_gemm_tiles<Tile128, kPublish>(a, stream);
-  return enqueue_gemm<kPublish, 8>(a, stream);
+  if (const int32_t rc = ensure_dynamic_lds(kernels, 4, kLdsGemm); rc != CA_OK) return rc;
+  if (const int32_t rc = gemm_rows_ready(); rc != CA_OK) return rc;
+  if (const int rows = rows_tile(a, n_cu, cost, compiled))
+    return launch_gemm_rows(rows, a.x, a.w, a.y, a.M, a.N, a.K, a.ldx, a.ldw, a.ldy, stream);
+  if (compiled == kTile64) return enqueue_gemm_tiles<Tile64, false>(a, stream);
+  if (compiled == kTile64Wide) return enqueue_gemm_tiles<Tile64Wide, false>(a, stream);
+  if (compiled == kTile256x128) return enqueue_gemm_tiles<Tile256x128, false>(a, stream);
+  return enqueue_gemm_tiles<Tile128, false>(a, stream);
 }
 
 }  // namespace
@@ -603,7 +608,7 @@ int32_t launch_gemm_bf16(const void* x, const void* w, void* y, int64_t M, int32
   a.M = int32_t(M); a.N = N; a.K = K;
   a.ldx = ldx; a.ldw = ldw; a.ldy = ldy;
   a.block_rows = a.M;                             // one row block: tiles run through all of M
-  return dispatch_gemm<false>(a, stream);
+  return dispatch_gemm_plain(a, stream);
 }
 
 int32_t launch_gemm_qkv_publish(const RopeGeom& g, int32_t n_blocks, int32_t block_tokens, int32_t pages_per_block,
@@ -632,7 +637,7 @@ int32_t launch_gemm_qkv_publish(const RopeGeom& g, int32_t n_blocks, int32_t blo
   }
   size_t tab_bytes = 0;
   a.pub.tab = trig_table_for(g, 128, kTrigBytes, &tab_bytes);
-  return dispatch_gemm<true>(a, stream);
+  return dispatch_gemm_publish(a, stream);
 }
 
 }  // namespace ca

@@ -1,0 +1,21 @@
+// How the tiles of a linear map are numbered and dealt to the XCDs, shared by its kernels.
+// (Included inside namespace ca { namespace { ... } }.)
+#pragma once
+
+constexpr int kBandRows = 8;                      // row tiles of a band
+
+// Tiles are numbered down bands of eight row tiles.
+__device__ __forceinline__ void tile_at(int tiles_m, int tiles_n, int nth, int* tm, int* tn) {
+  const int band = nth / (kBandRows * tiles_n), in_band = nth - band * kBandRows * tiles_n;
+  const int height = min(kBandRows, tiles_m - band * kBandRows);
+  *tn = in_band / height;
+  *tm = band * kBandRows + in_band - *tn * height;
+}
+
+// Tiles that an XCD takes in the last round of `left`.  Up to 64 go 16 to an XCD: with a few each, the tiles of an
+// XCD have hardly a slab in common.  Us dealt evenly / 16 to an XCD, 256 x 256 tiles of x 5120 x 5120 by whole rounds
+// and tiles left: 7 + 8 882 / 857, 7 + 28 891 / 874, 7 + 48 908 / 883, 4 + 16 513 / 508, 3 + 12 407 / 406, 6 + 44 724
+// / 724, 6 + 24 the other way 731 / 743; with K 1536 4 + 2 179.3 / 177.1, 5 + 16 217.0 / 214.5.  More than 64 go
+// evenly: 16 to an XCD gives little and not always, 6 + 84 750 / 750, 7 + 68 900 / 894, 7 + 108 923 / 913, 3 + 72 407
+// / 407, 32 to an XCD 3 + 72 425, 5 + 80 622 / 635.
+__host__ __device__ constexpr int last_round_share(int left) { return left > 0 && left <= 64 ? 16 : (left + 7) >> 3; }

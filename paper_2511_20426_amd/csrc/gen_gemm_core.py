@@ -237,7 +237,7 @@ def generate(mt=8):
 def main(out_path):
     by = "// Generated by gen_gemm_core.py -- do not edit.\n"
     clobbers = by
-    for mt in (8, 6, 4):
+    for mt in (8, 4):
         text = [ln for part in generate(mt) for ln in part.split("\n")]
         path = out_path if mt == 8 else out_path.replace("_gfx950", f"{32 * mt}_gfx950")
         with open(path, "w") as f:
