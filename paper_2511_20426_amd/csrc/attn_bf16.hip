@@ -51,12 +51,12 @@ constexpr int kPageBytes = 128 * 128 * 2;       // one K or V page
 constexpr int kPairBytes = 2 * kPageBytes;      // K page followed by V page
 constexpr int kRowsPerWg = 256;
 
-// Everything a launch needs, in the order the kernel reads it.  A workgroup starts with nothing but
-// this block's address, which the first reads of a launch fetch over the bus: the scalars of the
-// first part come in a few wide loads issued together, the per-segment and per-block tables as one
-// dword per lane of `lanes` (a lane's entry is picked with v_readlane later), the rotation factors
-// as two vectors per lane.  Divisions by launch constants are a multiplication and a correction.
-struct AttnArgs {
+// Everything a launch needs.  A workgroup starts with nothing but this block's address: the scalars of the first part come
+// in three loads issued together (load_head: left to the compiler they were fetched one after the other as they were needed,
+// seven trips before the first load of Q), the per-block tables as one dword per lane of
+// `lanes` (a lane's entry is picked with v_readlane later), the rotation factors as two vectors per lane.  What a workgroup
+// works on is found with scalar instructions alone: divisions by launch constants are a multiplication and a correction.
+struct AttnHead {
   const uint16_t* q;                   // [row, head, dim] with the strides below; unrotated for attn_bf16_kernel<true, ..>
   uint16_t* o;
   const uint8_t* pool;
@@ -68,6 +68,7 @@ struct AttnArgs {
   // i / cols_per_xcd of column i % cols_per_xcd.  Workgroups that run together on an XCD then
   // walk KV prefixes of one length, start and finish together, and stay in step on the same pages
   // of the same few heads, which is what keeps those pages in the XCD's L2.
+  // Segment i has rows seg_first - i seg_rows .. and sees the first vis_first - i KV blocks.
   int32_t heads, pages_per_block, last_valid, n_seg;
   int32_t tiles_per_seg, total_cols, cols_per_xcd, work_per_xcd;   // work_per_xcd = cols_per_xcd * n_seg
   // Splitting: the last `split_items` work items of every XCD's range have their KV walk cut
@@ -75,7 +76,7 @@ struct AttnArgs {
   // merge_partials_kernel.
   int32_t split, split_items, full_items;   // per XCD: full_items + split_items == work_per_xcd
   float c;                             // log2(e) / sqrt(head_dim)
-  float inv_cols, inv_tiles, inv_pages, inv_split, inv_split_items;
+  uint32_t per_cols, per_tiles, per_pages, per_split, per_split_items;   // reciprocal() of those
   int64_t q_tok_stride, q_head_stride;
   // Rotary embedding of the queries (attn_bf16_kernel<true, ..> only).  Angles are formed in revolutions:
   // pair j turns by pos * freq[j] / 2pi; that factor is split into a 12-bit head and a tail so that
@@ -83,17 +84,35 @@ struct AttnArgs {
   // sin / cos (measured: cos and sin within 4.2e-7 of fp64 for every pos < 4096 and every pair).
   int32_t pairs_t, pairs_h;            // pairs [0, pairs_t): frame axis, then pairs_h: row axis, rest: column axis
   int32_t plane, grid_h, grid_w, frames_per_block;   // plane = grid_h * grid_w
-  float inv_plane, inv_grid_w, inv_frames;
-  // cos and sin per axis value present in a tile, in LDS: tab_f frames x pairs_t, then tab_y rows x pairs_h, then
-  // grid_w columns x the rest; tab_y == 0: a geometry too large for it, every lane evaluates its own
-  int32_t tab_f, tab_y;
-  int32_t lanes[64];                   // kLane*: first row, rows, visible blocks per segment; first frame per query block; KV slots
+  uint32_t per_plane, per_grid_w;
+  // cos and sin per axis value present in a tile, in LDS, by quads of four pairs as a lane of 16 has them: tab_f frames, then
+  // tab_y rows, then grid_w columns, each with the quads that its axis has a pair in; tab_y == 0: a geometry without a table,
+  // every lane evaluates its own
+  int32_t tab_f, tab_y, tab_quads;     // tab_quads: of the table
+  int32_t seg_first, seg_rows, vis_first;
+  int32_t spare[4];
+};
+static_assert(sizeof(AttnHead) == 192, "three loads of 64 bytes");
+
+struct AttnArgs : AttnHead {
+  int32_t lanes[64];                   // kLane*: first frame per query block; KV slots
   float rev_hi[kMaxPairs], rev_lo[kMaxPairs];
 };
-constexpr int kLaneRow0 = 0, kLaneRows = 8, kLaneNvis = 16, kLaneFrame = 24, kLaneSlot = 32;
+constexpr int kLaneFrame = 0, kLaneSlot = 32;
 static_assert(kMaxInflight == 8 && kMaxKvBlocks == 32, "AttnArgs::lanes");
 
 constexpr int kMaxSplit = 16;          // page ranges of a walk
+
+typedef __attribute__((ext_vector_type(16))) uint32_t u32x16;
+
+// the scalars of the launch (AttnArgs is the kernel's one argument)
+__device__ __forceinline__ AttnHead load_head() {
+  struct Raw { u32x16 x[3]; } raw;
+  const uint64_t at = reinterpret_cast<uint64_t>(__builtin_amdgcn_kernarg_segment_ptr());
+  asm volatile("s_load_dwordx16 %0, %3, 0x0\n\ts_load_dwordx16 %1, %3, 0x40\n\ts_load_dwordx16 %2, %3, 0x80\n\ts_waitcnt lgkmcnt(0)"
+               : "=&s"(raw.x[0]), "=&s"(raw.x[1]), "=&s"(raw.x[2]) : "s"(at));
+  return __builtin_bit_cast(AttnHead, raw);
+}
 
 // one partial result of a 256-row tile, in the order the accumulators leave the registers: O^T
 // contributions [wave][register group][lane] as fp32 x 4 (not normalised), then (exponent
@@ -102,21 +121,17 @@ constexpr int kPartialMl = kRowsPerWg * 128;
 constexpr int kPartialFloats = kRowsPerWg * 132;
 static_assert(size_t(kMaxPartials) * kPartialFloats * 4 == kAttnScratchBytes, "scratch size");
 
-// n / d and n % d for 0 <= n < 2^31, n / d < 2^22, with inv = 1.0f / d: the product is off by less
-// than one, so the quotient needs at most one correction
-__device__ __forceinline__ int div_by(int n, int d, float inv, int* rem) {
-  int q = int(float(n) * inv), r = n - q * d;
-  if (r < 0) {
-    --q;
-    r += d;
-  }
-  if (r >= d) {
-    ++q;
-    r -= d;
-  }
-  *rem = r;
-  return q;
+// n / d and n % d with per = reciprocal(d): floor(n per / 2^32) is the quotient or one less
+__host__ constexpr uint32_t reciprocal(int32_t d) { return d > 1 ? uint32_t((uint64_t(1) << 32) / uint32_t(d)) : 0xffffffffu; }
+__device__ __forceinline__ int div_by(int n, int d, uint32_t per, int* rem) {
+  uint32_t q = __umulhi(uint32_t(n), per), r = uint32_t(n) - q * uint32_t(d);
+  const bool more = r >= uint32_t(d);
+  *rem = int(more ? r - uint32_t(d) : r);
+  return int(more ? q + 1 : q);
 }
+
+// n / d with inv = 1 / d to within an ulp, for n < 2^20: half of 1 / d away from the next whole number, the product cannot round to it
+__device__ __forceinline__ int div_small(int n, float inv) { return int((float(n) + 0.5f) * inv); }
 
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
@@ -124,17 +139,15 @@ struct WorkItem {
   int h, row0, rows_end, n_kvb;     // h < 0: no such item (the last XCD may own fewer columns)
 };
 
-// lane_tab: this lane's entry of AttnArgs::lanes
-__device__ __forceinline__ WorkItem decode_item(const AttnArgs& a, int lane_tab, int xcd, int item) {
+__device__ __forceinline__ WorkItem decode_item(const AttnHead& a, int xcd, int item) {
   WorkItem w;
   int in_seg, t;
-  const int seg = uniform(div_by(item, a.cols_per_xcd, a.inv_cols, &in_seg));
-  const int col = xcd * a.cols_per_xcd + uniform(in_seg);
-  w.h = uniform(div_by(col, a.tiles_per_seg, a.inv_tiles, &t));
-  const int row0 = __builtin_amdgcn_readlane(lane_tab, kLaneRow0 + seg);
-  w.row0 = row0 + uniform(t) * kRowsPerWg;
-  w.rows_end = row0 + __builtin_amdgcn_readlane(lane_tab, kLaneRows + seg);
-  w.n_kvb = __builtin_amdgcn_readlane(lane_tab, kLaneNvis + seg);
+  const int seg = div_by(item, a.cols_per_xcd, a.per_cols, &in_seg), col = xcd * a.cols_per_xcd + in_seg;
+  w.h = div_by(col, a.tiles_per_seg, a.per_tiles, &t);
+  const int row0 = a.seg_first - seg * a.seg_rows;
+  w.row0 = row0 + t * kRowsPerWg;
+  w.rows_end = row0 + a.seg_rows;
+  w.n_kvb = a.vis_first - seg;
   if (col >= a.total_cols) w.h = -1;
   return w;
 }
@@ -164,33 +177,52 @@ constexpr uint32_t kVRing = 2 * kPageBytes;
 constexpr uint32_t kPosArea = 4 * kPageBytes;
 constexpr uint32_t kTrigArea = kPosArea + kRowsPerWg * 16;
 constexpr int kAttnLds = 160 * 1024;
-constexpr int kTrigEntries = (kAttnLds - int(kTrigArea)) / 8;
+constexpr int kTrigQuads = (kAttnLds - int(kTrigArea)) / 32;
 
-// What a workgroup spends outside the loop is paid once per item, and one workgroup per CU means that
-// nothing overlaps it: 31 000 cycles (timestamps of a probe build; 7 pages of walk) when a thread rotated a
-// whole row, scalars were fetched one by one and results left in 8-byte pieces, 23 000 when Q was read and the
-// results written as whole 256-byte rows (through LDS; the matrix layouts hold 16-byte pieces of 32 rows) and the
-// rotation was shared out so that a thread needs the factors of four pairs only, about 22 000 with cos and sin from a
-// table in LDS: a tile of 256 rows meets few values per axis (1262 entries at 30 x 52 for 16 384 pairs), filled while Q
-// is on its way, and a pair's rotation is 14 vector instructions instead of 18 with two of quarter rate (8200 cycles
-// before; 5300 with the scale c multiplied into the table, which is two instructions less and 0.27 us of the smallest
-// step, 26.73 / 27.00, but rounds otherwise and keeps finite what rope3d_apply takes out of range: c comes behind
-// the rotation).  The first K and V page are requested when Q has landed, behind loads that the compiler counts:
-// requested before, they cost 0.5 us, the waits for Q then include them.  Nothing of this shows at the 14B shape, where
-// an item walks 407 pages.
+// rows I0 .. I1 - 1 of a lane's 16 (row i is 4 i rows on, `rows` are left), from `at` on in steps of `step` bytes; rows past the end
+// re-read the last one.  They stay where they stand between other work.
+template <int I0, int I1>
+__device__ __forceinline__ void load_q(u32x4 (&v)[16], uint64_t& at, uint64_t end, uint64_t step, int rows) {
+#pragma unroll
+  for (int i = I0; i < I1; ++i, at += step)
+    v[i] = *reinterpret_cast<const __attribute__((address_space(1))) u32x4*>(4 * i < rows ? at : end);
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// load i of the wave's 16 of a K page and its V page (at `page`) into the first slots of their rings
+__device__ __forceinline__ void load_page_piece(uint32_t lds_wave, uint32_t lane_off, uint64_t page, int i) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :: "s"(lds_wave + (i & 7) * 4096 + (i >> 3) * kVRing), "v"(lane_off + (i & 7) * 4096),
+                  "s"(page + (i >> 3) * uint64_t(kPageBytes)) : "m0");
+}
+
+// What a workgroup spends outside the loop is paid once per item, and one workgroup per CU means that nothing overlaps it.  Cycles
+// (timestamps of a probe build; a page of walk is 4300): 31 000 when a thread rotated a whole row, scalars were fetched one by one
+// and results left in 8-byte pieces; 23 000 with Q read and the results written as whole 256-byte rows and the
+// rotation shared out so that a thread needs the factors of four pairs only; 22 000 with cos and sin from a table in LDS: a
+// tile of 256 rows meets few values per axis (1262 at 30 x 52 for 16 384 pairs), filled while Q is on its way; 18 000 now, the
+// smallest step 26.9 -> 24.9 us.  What that took: the item found with scalar instructions and the arguments in one go (to the
+// first load of Q 2100 -> 1000), the table filled by all threads in turn, Q's loads dealt out between (with positions and Q's loads
+// 5600 -> 2700), the reads of the table ahead of the products and beside the page loads (7000 -> 5300), the accumulators cleared and
+// K(1) requested beside the first tile's products (3600 -> 3000).  The scale c comes behind the rotation: multiplied into
+// the table it would be two instructions less a pair, but rounds otherwise and keeps finite what rope3d_apply takes out of
+// range.  The first K and V page are requested when Q has landed, behind loads that the compiler counts: requested
+// before, they cost 0.5 us, the waits for Q then include them.  Nothing of this shows at the 14B shape, where an item walks
+// 407 pages.
 //
 // kTails: the loop that walks half of a short last page (gen_attn_core.py), picked by has_tails.
 // kCore16: which of the two main loops.  Both walk the same pages the same way; they differ in the matrix
 // instruction, and so in where a lane's part of Q, of the accumulators and of a row sum is.
 template <bool kRopeQ, bool kCore16, bool kTails>
-__global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
+__global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs args) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l31 = lane & 31, hi = lane >> 5, l15 = lane & 15, grp = lane >> 4;
-  const int lane_tab = a.lanes[lane];
-  const int my_slot = a.lanes[kLaneSlot + (lane & 31)];
+  const int lane_tab = args.lanes[lane];
+  const int my_slot = args.lanes[kLaneSlot + (lane & 31)];
   const int c16 = lane & 15, r4 = lane >> 4;               // 16-byte chunk and row (mod 4) of Q / O this lane moves
-  const float pair_hi = kRopeQ ? a.rev_hi[lane] : 0.f, pair_lo = kRopeQ ? a.rev_lo[lane] : 0.f;   // of pair `lane`
+  const float pair_hi = kRopeQ ? args.rev_hi[lane] : 0.f, pair_lo = kRopeQ ? args.rev_lo[lane] : 0.f;   // of pair `lane`
+  const AttnHead a = load_head();
 
   // ---- which (head, row tile, page range): XCD x takes its own work_per_xcd items; inside an XCD
   // the full items come first, then the split ones, all their first page ranges, then the second ...
@@ -198,99 +230,108 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
   int item = nth, chunk = 0, n_chunks = 1;
   if (nth >= a.full_items) {
     int in_chunk;
-    chunk = uniform(div_by(nth - a.full_items, a.split_items, a.inv_split_items, &in_chunk));
-    item = a.full_items + uniform(in_chunk);
+    chunk = div_by(nth - a.full_items, a.split_items, a.per_split_items, &in_chunk);
+    item = a.full_items + in_chunk;
     n_chunks = a.split;
   }
-  const WorkItem wi = decode_item(a, lane_tab, xcd, item);
+  const WorkItem wi = decode_item(a, xcd, item);
   if (wi.h < 0) return;
   const int h = wi.h, row0 = wi.row0, rows_end = wi.rows_end, n_kvb = wi.n_kvb;
   const int all_pages = n_kvb * a.pages_per_block;
   int page_lo = 0, page_hi = all_pages, in_block, rem;
   if (n_chunks > 1) {
-    page_lo = uniform(div_by(all_pages * chunk, n_chunks, a.inv_split, &rem));
-    page_hi = uniform(div_by(all_pages * (chunk + 1), n_chunks, a.inv_split, &rem));
+    page_lo = div_by(all_pages * chunk, n_chunks, a.per_split, &rem);
+    page_hi = div_by(all_pages * (chunk + 1), n_chunks, a.per_split, &rem);
   }
-  const int kb0 = uniform(div_by(page_lo, a.pages_per_block, a.inv_pages, &in_block)), pg0 = uniform(in_block);
+  const int kb0 = div_by(page_lo, a.pages_per_block, a.per_pages, &in_block), pg0 = in_block;
   const int n_pages = page_hi - page_lo;
 
-  // ---- Q rows: a wave takes its own 64, 16 lanes to a row
+  // ---- Q rows: a wave takes its own 64, 16 lanes to a row (one multiplication per lane and one for the last row, which rows past
+  // the end re-read)
   u32x4 v[16];
-  {
-    const uint16_t* qp = a.q + int64_t(h) * a.q_head_stride + c16 * 8;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int r = min(row0 + wave * 64 + r4 + 4 * i, rows_end - 1);
-      v[i] = *reinterpret_cast<const u32x4*>(qp + int64_t(r) * a.q_tok_stride);
-    }
-  }
+  const int first = row0 + wave * 64 + r4;
+  const uint64_t qp = reinterpret_cast<uint64_t>(a.q) + 2 * (int64_t(h) * a.q_head_stride + c16 * 8);
+  const uint64_t q_end = qp + 2 * int64_t(rows_end - 1) * a.q_tok_stride, q_step = 8 * a.q_tok_stride;
+  uint64_t q_at = qp + 2 * int64_t(first) * a.q_tok_stride;
+  // (a load keeps the unit that forms addresses busy for 16 cycles, those of four waves for 64: with a table to fill they are dealt out)
+  load_q<0, kRopeQ ? 4 : 16>(v, q_at, q_end, q_step, rows_end - first);
   uint8_t* const parked = lds + kPageBytes + (wave >> 1) * kPageBytes + wave * 64 * 256;
+  uint8_t* park[4];                                        // of this lane's piece of rows r4 + 4 i, i = 0..3; 16 rows on: 4096 bytes
+#pragma unroll
+  for (int i = 0; i < 4; ++i) park[i] = parked + (r4 + 4 * i) * 256 + ((c16 ^ (r4 + 4 * i)) << 4);
   int4* const pos = reinterpret_cast<int4*>(lds + kPosArea) + wave * 64;
   if (kRopeQ) {
-    // ---- while Q is on its way: the rows' positions (without a table) or places in it, and the table, of which a lane fills its
-    // pair's entries, a wave every fourth value
-    int in_plane, x, in_block, x0;
-    const int r = min(row0 + tid, rows_end - 1);
-    const int frame = div_by(r, a.plane, a.inv_plane, &in_plane);        // counted through all query blocks
-    const int y = div_by(in_plane, a.grid_w, a.inv_grid_w, &x);
-    if (a.tab_y > 0) {
-      const int frame0 = uniform(div_by(row0, a.plane, a.inv_plane, &in_plane));
-      const int y0 = uniform(div_by(in_plane, a.grid_w, a.inv_grid_w, &x0));
-      const int last_frame = uniform(div_by(rows_end - 1, a.plane, a.inv_plane, &in_plane));
-      const int pairs_w = 64 - a.pairs_t - a.pairs_h;
-      const int in_y = a.tab_f * a.pairs_t, in_x = in_y + a.tab_y * a.pairs_h;
-      // entry of a pair: pos + 8 * pair
-      pos[lane] = make_int4(8 * (frame - frame0) * a.pairs_t,
-                            8 * (in_y + (y - y0 + (y < y0 ? a.grid_h : 0)) * a.pairs_h - a.pairs_t),
-                            8 * (in_x + x * pairs_w - a.pairs_t - a.pairs_h), 0);
-      auto cos_sin = [&](float at, float hi_part, float lo_part) {
-        const float rev = __builtin_amdgcn_fractf(at * hi_part) + at * lo_part;
-        return make_float2(__builtin_amdgcn_cosf(rev), __builtin_amdgcn_sinf(rev));
-      };
-      float2* const trig = reinterpret_cast<float2*>(lds + kTrigArea);
-      // frames and rows: a lane its own pair, a wave every fourth value
-      const bool on_t = lane < a.pairs_t;
-      const int n_ty = on_t ? a.tab_f : (lane < a.pairs_t + a.pairs_h ? a.tab_y : 0);
-      for (int v = wave; v < max(a.tab_f, a.tab_y); v += 4) {
-        const int fr = min(frame0 + v, last_frame), blk = uniform(div_by(fr, a.frames_per_block, a.inv_frames, &in_block));
-        const int t_pos = __builtin_amdgcn_readlane(lane_tab, kLaneFrame + blk) + uniform(in_block);
-        const int y_pos = y0 + v - (y0 + v >= a.grid_h ? a.grid_h : 0);
-        const float2 e = cos_sin(float(on_t ? t_pos : y_pos), pair_hi, pair_lo);
-        if (v < n_ty) trig[on_t ? v * a.pairs_t + lane : in_y + v * a.pairs_h + lane - a.pairs_t] = e;
-      }
-      // columns: the lanes share out as many as fit, a wave every fourth such group
-      if (pairs_w > 0) {
-        const int group = 64 / pairs_w, of = lane / pairs_w, k = lane - of * pairs_w;
-        const float k_hi = __shfl(pair_hi, 64 - pairs_w + k), k_lo = __shfl(pair_lo, 64 - pairs_w + k);
-        for (int v = wave * group + of; v < a.grid_w + of; v += 4 * group) {        // (uniform: a wave's lanes go on together)
-          const float2 e = cos_sin(float(v), k_hi, k_lo);
-          if (v < a.grid_w && of < group) trig[in_x + v * pairs_w + k] = e;
-        }
-      }
+    // ---- while Q is on its way: the rows' positions (without a table) or places in it, and the table
+    int in_plane, x0;
+    const int frame0 = div_by(row0, a.plane, a.per_plane, &in_plane);    // counted through all query blocks
+    const int y0 = div_by(in_plane, a.grid_w, a.per_grid_w, &x0);
+    const float inv_w = __builtin_amdgcn_rcpf(float(a.grid_w)), inv_h = __builtin_amdgcn_rcpf(float(a.grid_h));
+    const float inv_frames = __builtin_amdgcn_rcpf(float(a.frames_per_block));
+    // of row tid of the tile: columns and rows counted on from the first row's
+    const int along = x0 + min(tid, rows_end - 1 - row0), down = div_small(along, inv_w), x = along - down * a.grid_w;
+    const int frames = div_small(y0 + down, inv_h), y = y0 + down - frames * a.grid_h;
+    auto frame_pos = [&](int frame) {
+      const int blk = div_small(frame, inv_frames);
+      return __shfl(lane_tab, kLaneFrame + blk) + frame - blk * a.frames_per_block;
+    };
+    if (a.tab_y == 0) {
+      pos[lane] = make_int4(frame_pos(frame0 + frames), y, x, 0);
+      load_q<4, 16>(v, q_at, q_end, q_step, rows_end - first);
     } else {
-      const int blk = div_by(frame, a.frames_per_block, a.inv_frames, &in_block);
-      pos[lane] = make_int4(__shfl(lane_tab, kLaneFrame + blk) + in_block, y, x, 0);
+      const int last_frame = div_by(rows_end - 1, a.plane, a.per_plane, &in_plane);
+      const int to_y = a.pairs_t, to_x = a.pairs_t + a.pairs_h, pairs_w = 64 - to_x;
+      // quads of a frame, row and column; where those of frame 0, row y0 and column 0 begin, less the quads before their first
+      const int of_t = (to_y + 3) >> 2, of_y = ((to_x + 3) >> 2) - (to_y >> 2), of_x = 16 - (to_x >> 2);
+      const int in_y = a.tab_f * of_t - (to_y >> 2), in_x = a.tab_f * of_t + a.tab_y * of_y - (to_x >> 2);
+      const int rows_on = y - y0 + (y < y0 ? a.grid_h : 0);
+      pos[lane] = make_int4(16 * frames * of_t, 16 * (in_y + rows_on * of_y), 16 * (in_x + x * of_x), 0);
+      // The entries, shared out to the threads: pairs of the frames, of the rows, of the columns.  Pairs 0 and 1 of a quad lie in
+      // one half of the table, 2 and 3 in the other, so that the 16 lanes of a row read neighbouring 16 bytes.
+      uint8_t* const trig = lds + kTrigArea;
+      const int n_t = a.tab_f * to_y, n_ty = n_t + a.tab_y * a.pairs_h, n_all = n_ty + a.grid_w * pairs_w;
+      const float inv_t = __builtin_amdgcn_rcpf(float(to_y)), inv_p = __builtin_amdgcn_rcpf(float(a.pairs_h)), inv_q = __builtin_amdgcn_rcpf(float(pairs_w));
+      // entry e of the table (uniform: the lanes of a wave exchange values)
+#define CA_FILL(e0)                                                                                                            \
+      {                                                                                                                        \
+        const int e = (e0) + tid;                                                                                              \
+        const bool on_t = e < n_t, on_y = e < n_ty;                                                                            \
+        const int k = e - (on_t ? 0 : (on_y ? n_t : n_ty)), v = div_small(k, on_t ? inv_t : (on_y ? inv_p : inv_q));           \
+        const int pair = (on_t ? 0 : (on_y ? to_y : to_x)) + k - v * (on_t ? to_y : (on_y ? a.pairs_h : pairs_w));             \
+        const int t_pos = frame_pos(min(frame0 + v, last_frame)), y_pos = y0 + v - (y0 + v >= a.grid_h ? a.grid_h : 0);        \
+        const float at = float(on_t ? t_pos : (on_y ? y_pos : v)), k_hi = __shfl(pair_hi, pair), k_lo = __shfl(pair_lo, pair); \
+        const float rev = __builtin_amdgcn_fractf(at * k_hi) + at * k_lo;                                                      \
+        const int quad = (on_t ? 0 : (on_y ? in_y : in_x)) + v * (on_t ? of_t : (on_y ? of_y : of_x)) + (pair >> 2);           \
+        if (e < n_all)                                                                                                         \
+          *reinterpret_cast<float2*>(trig + 16 * (quad + ((pair >> 1) & 1 ? a.tab_quads : 0)) + 8 * (pair & 1)) =              \
+              make_float2(__builtin_amdgcn_cosf(rev), __builtin_amdgcn_sinf(rev));                                             \
+      }
+      load_q<4, 8>(v, q_at, q_end, q_step, rows_end - first);
+      CA_FILL(0)
+      load_q<8, 12>(v, q_at, q_end, q_step, rows_end - first);
+      if (n_all > 256) CA_FILL(256)
+      load_q<12, 16>(v, q_at, q_end, q_step, rows_end - first);
+#pragma unroll 2
+      for (int e0 = 512; e0 < n_all; e0 += 256) CA_FILL(e0)
+#undef CA_FILL
     }
   }
   // Q has landed (and is taken note of as such before other loads are on their way, which the compiler does not count)
 #pragma unroll
   for (int i = 0; i < 16; ++i) asm volatile("" : "+v"(v[i]));
-  // ---- the first K and V page on their way into the first slots of their rings
+  // ---- the first K and V page on their way into the first slots of their rings (beside the rotation where there is one:
+  // the 16 loads take the 1000 cycles that their addresses take)
   const uint32_t lane_off = wave * 1024 + lane * 16;   // this lane's 16 bytes inside each 4 KB slice of a page
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
-  {
-    const int slot0 = __builtin_amdgcn_readlane(lane_tab, kLaneSlot + kb0);
-    const uint64_t k0 = reinterpret_cast<uint64_t>(a.pool) +
-                        ((uint64_t(slot0) * a.pages_per_block + pg0) * a.heads + h) * uint64_t(kPairBytes);
+  const int slot0 = __builtin_amdgcn_readlane(lane_tab, kLaneSlot + kb0);
+  const uint64_t k0 = reinterpret_cast<uint64_t>(a.pool) +
+                      ((uint64_t(slot0) * a.pages_per_block + pg0) * a.heads + h) * uint64_t(kPairBytes);
+  if (!kRopeQ || a.tab_y == 0)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const uint32_t m0 = lds0 + wave * 1024 + (i & 7) * 4096 + (i >> 3) * kVRing;
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                   :: "s"(m0), "v"(lane_off + (i & 7) * 4096), "s"(k0 + (i >> 3) * uint64_t(kPageBytes)) : "memory", "m0");
-    }
-  }
+    for (int i = 0; i < 16; ++i) load_page_piece(lds0 + wave * 1024, lane_off, k0, i);
   // ---- rotate, scale by c (scores then leave the matrix pipe in log2 units), round once, park the rows
   // in the second ring slots (rows 0..127 in K's, the others in V's), chunks swizzled as in a page
+  int end_again = rows_end;            // (compared anew: 16 masks kept from the loads would not fit the scalar registers)
+  asm volatile("" : "+s"(end_again));
   if (kRopeQ) {
     bool on_t[4], on_y[4];
 #pragma unroll
@@ -300,37 +341,69 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
     }
     if (a.tab_y > 0) {
       asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");       // the table is there (page loads stay in flight)
-      const uint8_t* const entry = lds + kTrigArea + 32 * c16;
-      // eight rows at a time, so that their reads wait together
+      // Each of a lane's four pairs has an entry of its own axis.  A lane's first two are of one axis, and so are its last two but
+      // in a lane where an axis ends behind the third pair, which has the fourth one read apart, ahead of the others (`ends`).  The
+      // reads of a row stand two rows before its products, so that the two run side by side, and a row's share of the page loads
+      // behind it.  Cycles of this part: 5200 with all reads first, of which 1700 wait for LDS, 4500 with four reads of 8 bytes.
+      const uint8_t* entry[4];
+      const int* place[4];
 #pragma unroll
-      for (int i0 = 0; i0 < 16; i0 += 8) {
-        float2 e[8][4];
+      for (int j = 0; j < 4; ++j) {
+        entry[j] = lds + kTrigArea + 16 * (c16 + (j >> 1) * a.tab_quads) + 8 * (j & 1);
+        place[j] = reinterpret_cast<const int*>(pos + r4) + (on_t[j] ? 0 : (on_y[j] ? 1 : 2));
+      }
+      auto rotated = [&](int i, const float2 (&t)[4]) {
+        const float c = row0 + wave * 64 + r4 + 4 * i < end_again ? a.c : 0.f;       // rows past the end are zeros
+        u32x4 out;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int4 p = pos[r4 + 4 * (i0 + i)];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) e[i][j].x = __int_as_float(on_t[j] ? p.x : (on_y[j] ? p.y : p.z));
+        for (int j = 0; j < 4; ++j) {
+          const uint32_t x = v[i][j];
+          const float u = __uint_as_float(x << 16), w = __uint_as_float(x & 0xffff0000u);
+          out[j] = pack2((u * t[j].x - w * t[j].y) * c, (u * t[j].y + w * t[j].x) * c);
         }
+        return out;
+      };
+      constexpr int kAhead = 2;
+      if ((a.pairs_t & 3) != 1 && ((a.pairs_t + a.pairs_h) & 3) != 1) {
+        const bool ends = place[3] != place[2];
+        int at[16][3];
+        float2 fourth[16];
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < 16; ++i) at[i][2] = place[3][16 * i], at[i][0] = place[0][16 * i], at[i][1] = place[2][16 * i];
+        if (ends) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) e[i][j] = *reinterpret_cast<const float2*>(entry + __float_as_int(e[i][j].x) + 8 * j);
+          for (int i = 0; i < 16; ++i) fourth[i] = *reinterpret_cast<const float2*>(entry[3] + at[i][2]);
+        }
+        float4 e[kAhead + 1][2];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int r = r4 + 4 * (i0 + i);
-          u32x4 out;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const uint32_t x = v[i0 + i][j];
-            const float u = __uint_as_float(x << 16), w = __uint_as_float(x & 0xffff0000u);
-            out[j] = pack2((u * e[i][j].x - w * e[i][j].y) * a.c, (u * e[i][j].y + w * e[i][j].x) * a.c);
+        for (int i = 0; i < 16 + kAhead; ++i) {
+          if (i < 16) {
+            e[i % (kAhead + 1)][0] = *reinterpret_cast<const float4*>(entry[0] + at[i][0]);
+            e[i % (kAhead + 1)][1] = *reinterpret_cast<const float4*>(entry[2] + at[i][1]);
           }
-          if (row0 + wave * 64 + r >= rows_end) out = u32x4{0, 0, 0, 0};
-          *reinterpret_cast<u32x4*>(parked + r * 256 + ((c16 ^ (r & 15)) << 4)) = out;
+          if (i < kAhead) continue;
+          const int k = i - kAhead;
+          const float4 lo = e[k % (kAhead + 1)][0], hi4 = e[k % (kAhead + 1)][1];
+          const float2 t[4] = {make_float2(lo.x, lo.y), make_float2(lo.z, lo.w), make_float2(hi4.x, hi4.y),
+                               make_float2(ends ? fourth[k].x : hi4.z, ends ? fourth[k].y : hi4.w)};
+          *reinterpret_cast<u32x4*>(park[k & 3] + (k >> 2) * 4096) = rotated(k, t);
+          load_page_piece(lds0 + wave * 1024, lane_off, k0, k);
+        }
+      } else {                                             // an axis ends behind a lane's first pair: four reads
+        float2 e[kAhead + 1][4];
+#pragma unroll
+        for (int i = 0; i < 16 + kAhead; ++i) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (i < 16) e[i % (kAhead + 1)][j] = *reinterpret_cast<const float2*>(entry[j] + place[j][16 * i]);
+          if (i < kAhead) continue;
+          const int k = i - kAhead;
+          *reinterpret_cast<u32x4*>(park[k & 3] + (k >> 2) * 4096) = rotated(k, e[k % (kAhead + 1)]);
+          load_page_piece(lds0 + wave * 1024, lane_off, k0, k);
         }
       }
     } else {
-      const float4 hi4 = *reinterpret_cast<const float4*>(a.rev_hi + 4 * c16), lo4 = *reinterpret_cast<const float4*>(a.rev_lo + 4 * c16);
+      const float4 hi4 = *reinterpret_cast<const float4*>(args.rev_hi + 4 * c16), lo4 = *reinterpret_cast<const float4*>(args.rev_lo + 4 * c16);
       const float rev_hi[4] = {hi4.x, hi4.y, hi4.z, hi4.w}, rev_lo[4] = {lo4.x, lo4.y, lo4.z, lo4.w};
       wave_lds_fence();
 #pragma unroll
@@ -347,8 +420,8 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
           const float u = __uint_as_float(x << 16), w = __uint_as_float(x & 0xffff0000u);
           out[j] = pack2((u * cs - w * sn) * a.c, (u * sn + w * cs) * a.c);
         }
-        if (row0 + wave * 64 + r >= rows_end) out = u32x4{0, 0, 0, 0};
-        *reinterpret_cast<u32x4*>(parked + r * 256 + ((c16 ^ (r & 15)) << 4)) = out;
+        if (row0 + wave * 64 + r >= end_again) out = u32x4{0, 0, 0, 0};
+        *reinterpret_cast<u32x4*>(park[i & 3] + (i >> 2) * 4096) = out;
       }
     }
   } else {
@@ -359,8 +432,8 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
 #pragma unroll
       for (int j = 0; j < 4; ++j)
         out[j] = pack2(__uint_as_float(v[i][j] << 16) * a.c, __uint_as_float(v[i][j] & 0xffff0000u) * a.c);
-      if (row0 + wave * 64 + r >= rows_end) out = u32x4{0, 0, 0, 0};
-      *reinterpret_cast<u32x4*>(parked + r * 256 + ((c16 ^ (r & 15)) << 4)) = out;
+      if (row0 + wave * 64 + r >= end_again) out = u32x4{0, 0, 0, 0};
+      *reinterpret_cast<u32x4*>(park[i & 3] + (i >> 2) * 4096) = out;
     }
   }
   wave_lds_fence();
@@ -544,17 +617,18 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs a) {
 // four register groups of one row of the attention kernel's tiles, and a lane keeps the place it had
 // there, so that every read of a partial tile is 1 KB of contiguous memory.
 template <bool kCore16>
-__global__ __launch_bounds__(256) void merge_partials_kernel(AttnArgs a) {
+__global__ __launch_bounds__(256) void merge_partials_kernel(AttnArgs args) {
+  const AttnHead a = load_head();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l31 = lane & 31, hi = lane >> 5, l15 = lane & 15, grp = lane >> 4;
-  const int lane_tab = a.lanes[lane];
-  const int xcd = blockIdx.x / a.split_items, sidx = blockIdx.x % a.split_items;
+  int sidx;
+  const int xcd = div_by(blockIdx.x, a.split_items, a.per_split_items, &sidx);
   const int wrow = blockIdx.y >> 1;                            // the attention kernel's wave
   // 16x16x32: query tile t, accumulators j0 .. j0+3 (dims 16 j0 ..); 32x32x16: column tile nt, accumulator 2 mt + nt
   const int t = 2 * (blockIdx.y & 1) + (wave & 1), j0 = 4 * (wave >> 1);
   const int nt = blockIdx.y & 1, mt = wave;
   const int first = kCore16 ? 16 * t : 32 * nt;
   const int row_in_tile = wrow * 64 + first + (kCore16 ? l15 : l31);
-  const float* tile = a.partials + size_t(xcd * a.split_items + sidx) * a.split * kPartialFloats;
+  const float* tile = args.partials + size_t(xcd * a.split_items + sidx) * a.split * kPartialFloats;
   const float* ml = tile + kPartialMl + 2 * row_in_tile;
   constexpr int kStep = kCore16 ? 4 * 64 : 64;                 // from one of the four groups to the next
   const float4* part = reinterpret_cast<const float4*>(tile) + (wrow * 32 + (kCore16 ? 4 * j0 + t : 4 * (2 * mt + nt))) * 64 + lane;
@@ -579,7 +653,7 @@ __global__ __launch_bounds__(256) void merge_partials_kernel(AttnArgs a) {
   };
   request(0);
   __builtin_amdgcn_sched_barrier(0);
-  const WorkItem wi = decode_item(a, lane_tab, xcd, a.full_items + sidx);
+  const WorkItem wi = decode_item(a, xcd, a.full_items + sidx);
   if (wi.h < 0) return;
   const int row = wi.row0 + row_in_tile;
   if (wi.row0 + wrow * 64 + first >= wi.rows_end) return;
@@ -607,7 +681,7 @@ __global__ __launch_bounds__(256) void merge_partials_kernel(AttnArgs a) {
   }
   if (row >= wi.rows_end) return;
   const float inv = 1.0f / l;
-  uint16_t* op = a.o + (int64_t(row) * a.heads + wi.h) * 128 + (kCore16 ? 16 * j0 + 4 * grp : 32 * mt + 4 * hi);
+  uint16_t* op = args.o + (int64_t(row) * a.heads + wi.h) * 128 + (kCore16 ? 16 * j0 + 4 * grp : 32 * mt + 4 * hi);
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
     u32x2 w;
@@ -679,24 +753,21 @@ int32_t plan_attn_bf16(const AttnPlan& p, int variant, const void* q, void* out,
   for (int i = 0; i < p.n_kv; ++i) a.lanes[kLaneSlot + i] = p.kv_slot[i];
   // Query segments: rows sharing one visible prefix are tiled together.  A bidirectional
   // cascade is one segment; block-causal gives one segment per in-flight block.
-  int tiles = 0;
   if (p.uniform) {
     a.n_seg = 1;
-    a.lanes[kLaneRow0] = 0;
-    a.lanes[kLaneRows] = p.n_q_blocks * p.block_tokens;
-    a.lanes[kLaneNvis] = p.n_vis[0];
-    tiles = (a.lanes[kLaneRows] + kRowsPerWg - 1) / kRowsPerWg;
+    a.seg_first = 0;
+    a.seg_rows = p.n_q_blocks * p.block_tokens;
+    a.vis_first = p.n_vis[0];
   } else {
     // one segment per query block, the longest prefix (latest block) first
     a.n_seg = p.n_q_blocks;
-    for (int j = 0; j < p.n_q_blocks; ++j) {
-      const int i = p.n_q_blocks - 1 - j;
-      a.lanes[kLaneRow0 + j] = i * p.block_tokens;
-      a.lanes[kLaneRows + j] = p.block_tokens;
-      a.lanes[kLaneNvis + j] = p.n_vis[i];
-    }
-    tiles = (p.block_tokens + kRowsPerWg - 1) / kRowsPerWg;
+    a.seg_first = (p.n_q_blocks - 1) * p.block_tokens;
+    a.seg_rows = p.block_tokens;
+    a.vis_first = p.n_vis[p.n_q_blocks - 1];
+    for (int i = 0; i + 1 < p.n_q_blocks; ++i)                 // a later block sees one more (CacheMeta::plan_forward)
+      if (p.n_vis[i + 1] != p.n_vis[i] + 1) return CA_EINVAL;
   }
+  const int tiles = (a.seg_rows + kRowsPerWg - 1) / kRowsPerWg;
   a.tiles_per_seg = tiles;
   a.total_cols = tiles * p.heads;
   a.cols_per_xcd = (a.total_cols + 7) / 8;
@@ -739,11 +810,11 @@ int32_t plan_attn_bf16(const AttnPlan& p, int variant, const void* q, void* out,
     }
   }
   *core16 = takes_core16(a, max_pages, n_cu);
-  a.inv_cols = 1.0f / float(a.cols_per_xcd);
-  a.inv_tiles = 1.0f / float(a.tiles_per_seg);
-  a.inv_pages = 1.0f / float(a.pages_per_block);
-  a.inv_split = 1.0f / float(a.split);
-  a.inv_split_items = 1.0f / float(a.split_items > 0 ? a.split_items : 1);
+  a.per_cols = reciprocal(a.cols_per_xcd);
+  a.per_tiles = reciprocal(a.tiles_per_seg);
+  a.per_pages = reciprocal(a.pages_per_block);
+  a.per_split = reciprocal(a.split);
+  a.per_split_items = reciprocal(a.split_items);
   return CA_OK;
 }
 
@@ -804,16 +875,20 @@ int32_t launch_attn_bf16_rope(const AttnPlan& p, const QRopePlan& rp, int varian
   a.grid_h = rp.geom.grid_h;
   a.grid_w = rp.geom.grid_w;
   a.plane = rp.geom.grid_h * rp.geom.grid_w;
-  a.inv_plane = 1.0f / float(a.plane);
-  a.inv_grid_w = 1.0f / float(a.grid_w);
+  a.per_plane = reciprocal(a.plane);
+  a.per_grid_w = reciprocal(a.grid_w);
   a.frames_per_block = p.block_tokens / a.plane;
-  a.inv_frames = 1.0f / float(a.frames_per_block);
   // what the 256 consecutive rows of a tile can meet: that many frames, rows (from the first one's on, round the
   // end), all columns
   a.tab_f = kRowsPerWg / a.plane + 2;
   a.tab_y = kRowsPerWg / a.grid_w + 2 < a.grid_h ? kRowsPerWg / a.grid_w + 2 : a.grid_h;
-  const int64_t entries = int64_t(a.tab_f) * a.pairs_t + int64_t(a.tab_y) * a.pairs_h + int64_t(a.grid_w) * (64 - a.pairs_t - a.pairs_h);
-  if (entries > kTrigEntries) a.tab_y = 0;
+  // no table where it does not fit, and where a quad has pairs of all three axes
+  const int to_y = a.pairs_t, to_x = a.pairs_t + a.pairs_h;
+  const int64_t quads = int64_t(a.tab_f) * ((to_y + 3) / 4) + int64_t(a.tab_y) * ((to_x + 3) / 4 - to_y / 4) + int64_t(a.grid_w) * (16 - to_x / 4);
+  if (quads > kTrigQuads || (to_y < to_x && to_x < 64 && to_y / 4 == to_x / 4 && to_y % 4 != 0))
+    a.tab_y = 0;
+  else
+    a.tab_quads = int32_t(quads);
   for (int i = 0; i < p.n_q_blocks; ++i) {
     // positions must stay below 4096 for the exact head product (frames are the only axis that grows)
     if (rp.first_frame[i] < 0 || rp.first_frame[i] + p.block_tokens / a.plane >= 4096) return CA_EUNSUPPORTED;

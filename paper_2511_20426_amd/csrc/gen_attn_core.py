@@ -117,9 +117,10 @@ class Emitter:
 
 
 # ---------------------------------------------------------------------------- building blocks
-def mfma_qk(first, s_base, nt, frag, ks):
+def mfma_qk(first, s_base, nt, frag, ks, start=None):
+    """start: what the sums begin with in place of -m_ref"""
     d = V(s_base + 16 * nt, 16)
-    c = V(NT[nt], 16) if first else d
+    c = (start or V(NT[nt], 16)) if first else d
     return f"v_mfma_f32_32x32x16_bf16 {d}, {V(FR + 4 * (frag % 8), 4)}, {A(128 + 4 * (8 * nt + ks), 4)}, {c}"
 
 
@@ -245,19 +246,19 @@ def finite_reference_lines(m, tmp):
 
 def emit_first_reference(E, s_base):
     """The exponent reference of a row starts as the maximum of its first tile (at s_base, its
-    per-lane maxima in MX): the tile and the -m_ref operand move by it.  Nothing has been
+    per-lane maxima in MX): the tile moves by it and -m_ref becomes known.  Nothing has been
     accumulated yet, so there is nothing to rescale."""
-    E.e("s_nop 15\ns_nop 15\ns_nop 15")                   # every MFMA issued so far has written back
     for nt in range(2):
-        t, other, delta = V(MX[nt]), V(RT[3]), V(RT[4])
-        E.e(f"ds_bpermute_b32 {other}, {V(XLANE)}, {t}")             # the partner lane's (lane ^ 32) maximum
-        E.e("s_waitcnt lgkmcnt(0)")
-        E.e(f"v_max_f32 {delta}, {t}, {other}")
-        for ln in finite_reference_lines(delta, other):
+        E.e(f"ds_bpermute_b32 {V(RT[3 + nt])}, {V(XLANE)}, {V(MX[nt])}")   # the partner lane's (lane ^ 32) maximum
+    for nt in range(2):
+        t, other = V(MX[nt]), V(RT[3 + nt])
+        E.e(f"s_waitcnt lgkmcnt({1 - nt})")
+        E.e(f"v_max_f32 {t}, {t}, {other}")
+        for ln in finite_reference_lines(t, other):
             E.e(ln)
         for i in range(16):
-            E.e(f"v_sub_f32 {V(NT[nt] + i)}, {V(NT[nt] + i)}, {delta}")
-            E.e(f"v_sub_f32 {V(s_base + 16 * nt + i)}, {V(s_base + 16 * nt + i)}, {delta}")
+            E.e(f"v_sub_f32 {V(NT[nt] + i)}, 0, {t}")
+            E.e(f"v_sub_f32 {V(s_base + 16 * nt + i)}, {V(s_base + 16 * nt + i)}, {t}")
 
 
 def emit_mask_check(E, s_base, pg_sreg, sub):
@@ -593,20 +594,26 @@ def emit_clear(E):
         E.e(f"v_mov_b32 {V(LACC + r)}, 0")
     for nt in range(2):
         E.e(f"v_mov_b32 {V(TS[nt])}, 0")
-    for nt in range(2):                                   # m_ref = 0 until tile 0 has been seen
-        for i in range(16):
-            E.e(f"v_mov_b32 {V(NT[nt] + i)}, 0")
+
+
+def clear_accumulator_lines(n):
+    """a[0:127] = 0, dealt out to the n MFMAs of the first tile, beside which there is room"""
+    lines = [f"v_accvgpr_write_b32 {A(r)}, 0" for r in range(128)]
+    return (lines[k * len(lines) // n:(k + 1) * len(lines) // n] for k in range(n))
 
 
 def emit_first_tile(E):
-    """S tile of step 0 into tile A, its mask, max and reference"""
+    """S tile of step 0 into tile A, its mask, max and reference; K(1) is requested beside it"""
     for f in range(8):
         E.e(f"ds_read_b128 {V(FR + 4 * f, 4)}, {V(XOK + f)} offset:0")
     E.e("s_waitcnt lgkmcnt(0)")
+    clear, page = clear_accumulator_lines(16), [ln for i in range(8) for ln in page_load_lines(i, PAGE, 0)]
     for f in range(8):
         for nt in range(2):
-            E.e(mfma_qk(f == 0, S_TILE["A"], nt, f, f))
-    E.e("s_nop 15\ns_nop 15\ns_nop 15")
+            E.e(mfma_qk(f == 0, S_TILE["A"], nt, f, f, "0"))
+            E.e(page.pop(0))                               # an M0 write or, behind other instructions, the load that takes it
+            E.lines += next(clear)
+    E.e("s_nop 15\ns_nop 7")
     for op in tile_max_ops(S_TILE["A"]):
         E.e(op)
     emit_mask_check(E, S_TILE["A"], S_PGCUR, 0)
@@ -673,17 +680,17 @@ def generate(core=None, tails=False):
         E.e(f"s_cmp_le_u32 s{S_LASTV}, 64")
         E.e(f"s_cselect_b32 s{S_SHORT}, s{S_PM1}, -1")
     # ---- K(0) and V(0) are in flight already (requested by the code around this block, oldest first);
-    # K(1) joins them, the accumulators are cleared meanwhile; wait for the first two, publish
+    # K(1) joins them, here or beside the first tile; wait for the first two, publish
     for grp in page_advance_lines():
         for ln in grp:
             E.e(ln)
-    emit_issue_page(E, 0, PAGE)
-    for r in range(128):
-        E.e(f"v_accvgpr_write_b32 {A(r)}, 0")
+    k1_here = hasattr(core, "emit_idle")                   # (waves without rows take no part in the first tile)
+    if k1_here:
+        emit_issue_page(E, 0, PAGE)
     core.emit_clear(E)
     for r in range(16):
         E.e(f"v_mov_b32 {V(P_TILE['B'] + r)}, 0")
-    E.e("s_waitcnt vmcnt(8) lgkmcnt(0)")
+    E.e(f"s_waitcnt vmcnt({8 if k1_here else 0}) lgkmcnt(0)")
     E.e("s_barrier")
     done = E.label("DONE")
     vmcnt = wait_counts(core)

@@ -82,9 +82,10 @@ def o_reg(dt, qt, i=0):
     return 16 * dt + 4 * qt + i
 
 
-def mfma_qk(s_base, kt, qt, ks):
+def mfma_qk(s_base, kt, qt, ks, start=None):
+    """start: what the sums begin with in place of -m_ref"""
     d = V(s_reg(s_base, kt, qt), 4)
-    c = V(NT[qt], 4) if ks == 0 else d
+    c = (start or V(NT[qt], 4)) if ks == 0 else d
     return f"v_mfma_f32_16x16x32_bf16 {d}, {V(FR + 4 * (4 * kt + ks), 4)}, {A(128 + 4 * (4 * qt + ks), 4)}, {c}"
 
 
@@ -170,7 +171,7 @@ def emit_mask(E, s_base, valid_sreg):
 
 def emit_first_reference(E, s_base):
     """The exponent reference of a row starts as the maximum of its first tile (at s_base, its
-    per-lane maxima in MX): the tile and the -m_ref operand move by it.  Nothing has been
+    per-lane maxima in MX): the tile moves by it and -m_ref becomes known.  Nothing has been
     accumulated yet, so there is nothing to rescale."""
     E.e("s_nop 15\ns_nop 15\ns_nop 15")                   # every MFMA issued so far has written back
     for qt in range(QT):
@@ -178,7 +179,7 @@ def emit_first_reference(E, s_base):
         for ln in across_lanes_lines(m, V(RT[3])) + base.finite_reference_lines(m, V(RT[3])):
             E.e(ln)
         for i in range(4):
-            E.e(f"v_sub_f32 {V(NT[qt] + i)}, {V(NT[qt] + i)}, {m}")
+            E.e(f"v_sub_f32 {V(NT[qt] + i)}, 0, {m}")
         for r in row_regs(s_base, qt):
             E.e(f"v_sub_f32 {V(r)}, {V(r)}, {m}")
 
@@ -416,8 +417,6 @@ def emit_clear(E):
     for qt in range(QT):
         E.e(f"v_mov_b32 {V(LACC + qt)}, 0")
         E.e(f"v_mov_b32 {V(TS[qt])}, 0")
-    for r in range(4 * QT):
-        E.e(f"v_mov_b32 {V(NT[0] + r)}, 0")               # m_ref = 0 until tile 0 has been seen
 
 
 def emit_first_tile(E):
@@ -425,8 +424,10 @@ def emit_first_tile(E):
     for f in range(8):
         E.e(ds_read_frag(f, k_source(0, 0, f)))
     E.e("s_waitcnt lgkmcnt(0)")
+    clear = base.clear_accumulator_lines(32)
     for x in qk_order():
-        E.e(mfma_qk(S_TILE["A"], *x))
+        E.e(mfma_qk(S_TILE["A"], *x, "0"))
+        E.lines += next(clear)
     E.e("s_nop 15\ns_nop 15\ns_nop 15")
     for op in tile_max_ops(S_TILE["A"]):
         E.e(op)
