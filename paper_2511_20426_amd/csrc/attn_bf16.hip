@@ -136,18 +136,18 @@ __device__ __forceinline__ int div_small(int n, float inv) { return int((float(n
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
 struct WorkItem {
-  int h, row0, rows_end, n_kvb;     // h < 0: no such item (the last XCD may own fewer columns)
+  int h, row0, rows_end, seg;       // h < 0: no such item (the last XCD may own fewer columns)
 };
 
-__device__ __forceinline__ WorkItem decode_item(const AttnHead& a, int xcd, int item) {
+template <typename Args>
+__device__ __forceinline__ WorkItem decode_item(const Args& a, int xcd, int item) {
   WorkItem w;
   int in_seg, t;
-  const int seg = div_by(item, a.cols_per_xcd, a.per_cols, &in_seg), col = xcd * a.cols_per_xcd + in_seg;
+  const int seg = w.seg = div_by(item, a.cols_per_xcd, a.per_cols, &in_seg), col = xcd * a.cols_per_xcd + in_seg;
   w.h = div_by(col, a.tiles_per_seg, a.per_tiles, &t);
   const int row0 = a.seg_first - seg * a.seg_rows;
   w.row0 = row0 + t * kRowsPerWg;
   w.rows_end = row0 + a.seg_rows;
-  w.n_kvb = a.vis_first - seg;
   if (col >= a.total_cols) w.h = -1;
   return w;
 }
@@ -236,7 +236,7 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs args) {
   }
   const WorkItem wi = decode_item(a, xcd, item);
   if (wi.h < 0) return;
-  const int h = wi.h, row0 = wi.row0, rows_end = wi.rows_end, n_kvb = wi.n_kvb;
+  const int h = wi.h, row0 = wi.row0, rows_end = wi.rows_end, n_kvb = a.vis_first - wi.seg;
   const int all_pages = n_kvb * a.pages_per_block;
   int page_lo = 0, page_hi = all_pages, in_block, rem;
   if (n_chunks > 1) {
@@ -616,9 +616,17 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs args) {
 // to the largest of their exponent references, summed and normalised.  Eight workgroups per tile: a wave takes
 // four register groups of one row of the attention kernel's tiles, and a lane keeps the place it had
 // there, so that every read of a partial tile is 1 KB of contiguous memory.
+struct MergeArgs {                     // as in AttnHead; 64 bytes: a launch with more takes the host up to 1 us longer
+  const float* partials;
+  uint16_t* o;
+  int32_t heads, tiles_per_seg, total_cols, cols_per_xcd, seg_first, seg_rows;
+  int32_t split, split_items, full_items;
+  uint32_t per_cols, per_tiles, per_split_items;
+};
+static_assert(sizeof(MergeArgs) == 64, "one cache line");
+
 template <bool kCore16>
-__global__ __launch_bounds__(256) void merge_partials_kernel(AttnArgs args) {
-  const AttnHead a = load_head();
+__global__ __launch_bounds__(256) void merge_partials_kernel(MergeArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l31 = lane & 31, hi = lane >> 5, l15 = lane & 15, grp = lane >> 4;
   int sidx;
   const int xcd = div_by(blockIdx.x, a.split_items, a.per_split_items, &sidx);
@@ -628,7 +636,7 @@ __global__ __launch_bounds__(256) void merge_partials_kernel(AttnArgs args) {
   const int nt = blockIdx.y & 1, mt = wave;
   const int first = kCore16 ? 16 * t : 32 * nt;
   const int row_in_tile = wrow * 64 + first + (kCore16 ? l15 : l31);
-  const float* tile = args.partials + size_t(xcd * a.split_items + sidx) * a.split * kPartialFloats;
+  const float* tile = a.partials + size_t(xcd * a.split_items + sidx) * a.split * kPartialFloats;
   const float* ml = tile + kPartialMl + 2 * row_in_tile;
   constexpr int kStep = kCore16 ? 4 * 64 : 64;                 // from one of the four groups to the next
   const float4* part = reinterpret_cast<const float4*>(tile) + (wrow * 32 + (kCore16 ? 4 * j0 + t : 4 * (2 * mt + nt))) * 64 + lane;
@@ -681,7 +689,7 @@ __global__ __launch_bounds__(256) void merge_partials_kernel(AttnArgs args) {
   }
   if (row >= wi.rows_end) return;
   const float inv = 1.0f / l;
-  uint16_t* op = args.o + (int64_t(row) * a.heads + wi.h) * 128 + (kCore16 ? 16 * j0 + 4 * grp : 32 * mt + 4 * hi);
+  uint16_t* op = a.o + (int64_t(row) * a.heads + wi.h) * 128 + (kCore16 ? 16 * j0 + 4 * grp : 32 * mt + 4 * hi);
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
     u32x2 w;
@@ -823,9 +831,12 @@ int32_t enqueue_attn_bf16(const AttnArgs& a, void* stream) {
   const dim3 grid((unsigned)((a.full_items + a.split_items * a.split) * 8));
   const auto kernel = attn_bf16_kernel<kRopeQ, kCore16, kTails>;
   hipLaunchKernelGGL(kernel, grid, dim3(256), kAttnLds, static_cast<hipStream_t>(stream), a);
-  if (a.split > 1)
+  if (a.split > 1) {
+    const MergeArgs m{a.partials, a.o, a.heads, a.tiles_per_seg, a.total_cols, a.cols_per_xcd, a.seg_first, a.seg_rows,
+                      a.split, a.split_items, a.full_items, a.per_cols, a.per_tiles, a.per_split_items};
     hipLaunchKernelGGL(merge_partials_kernel<kCore16>, dim3((unsigned)(8 * a.split_items), kRowsPerWg / 32), dim3(256), 0,
-                       static_cast<hipStream_t>(stream), a);
+                       static_cast<hipStream_t>(stream), m);
+  }
   return finish_launch("attn_bf16.hip");
 }
 

@@ -16,6 +16,8 @@
 //   Workgroups are numbered so that the 32 running together on one XCD share rows of X and W in its L2 (tile_of_workgroup).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "ca_internal.hpp"
 
 namespace ca {
@@ -54,7 +56,7 @@ struct GemmArgs {
   uint16_t* y;                                    // publishing: the packed queries [M][heads * 128]
   int32_t M, N, K;
   int64_t ldx, ldw, ldy;                          // row strides in elements
-  int32_t tiles_m, tiles_n, xcd_tiles;            // xcd_tiles: gemm_tile_kernel's tiles of an XCD
+  int32_t tiles_m, tiles_n, more;                 // as in LinearArgs
   int32_t block_cols;                             // columns of 8 x 4 blocks where tiles go by blocks (publishing), or 0
   // Row tiles are counted inside row blocks of block_rows rows, tiles_per_block each (the last
   // one ragged): one block spanning all of M for the plain product, one per in-flight block when
@@ -300,8 +302,11 @@ using Tile128 = TileShape<128, 128, 2, 4, 4>;
 using Tile64 = TileShape<64, 64, 2, 2, 4>;
 using Tile64Wide = TileShape<64, 64, 2, 4, 6>;
 
+template <bool kPublish>
+using TileArgs = std::conditional_t<kPublish, GemmArgs, LinearArgs>;
+
 template <typename T, bool kPublish>
-__global__ __launch_bounds__(T::kThreads) void gemm_tile_kernel(GemmArgs a) {
+__global__ __launch_bounds__(T::kThreads) void gemm_tile_kernel(TileArgs<kPublish> a) {
   constexpr int BM = T::kBm, BN = T::kBn, kWavesM = T::kWavesAlongM, kStages = T::kRing;
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -309,13 +314,16 @@ __global__ __launch_bounds__(T::kThreads) void gemm_tile_kernel(GemmArgs a) {
   const int wm = wave % kWavesM, wn = wave / kWavesM;
   // XCD x takes a contiguous range of the tiles.  Dealing them as gemm_bf16_kernel does costs a short kernel its longer
   // set-up: 220 x 2696 x 3072 12.0 us, 12.7 dealt; 2868 x 992 x 512 7.5, 7.6.
-  const int nth = int(blockIdx.x & 7) * a.xcd_tiles + int(blockIdx.x >> 3);
+  const int nth = int(blockIdx.x & 7) * a.more + int(blockIdx.x >> 3);
   if (nth >= a.tiles_m * a.tiles_n) return;
   int tm, tn;
   tile_at(a.tiles_m, a.tiles_n, nth, &tm, &tn);
-  const int blk = tm / a.tiles_per_block, tile_in_blk = tm - blk * a.tiles_per_block;
-  const int m0 = blk * a.block_rows + tile_in_blk * BM, n0 = tn * BN;
-  const int m_end = min((blk + 1) * a.block_rows, a.M);
+  int blk = 0, tile_in_blk = tm, m0 = tm * BM, m_end = a.M;
+  if constexpr (kPublish) {
+    blk = tm / a.tiles_per_block, tile_in_blk = tm - blk * a.tiles_per_block;
+    m0 = blk * a.block_rows + tile_in_blk * BM, m_end = min((blk + 1) * a.block_rows, a.M);
+  }
+  const int n0 = tn * BN;
 
   // as in gemm_bf16_kernel: load i of a wave brings 8 whole 128-byte rows, chunks swizzled by the row
   uint32_t offw[T::kLoadsW], offx[T::kLoadsX];
@@ -397,8 +405,8 @@ __global__ __launch_bounds__(T::kThreads) void gemm_tile_kernel(GemmArgs a) {
   }
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");     // the ring is free
 
-  const bool v_section = kPublish && n0 / (a.pub.heads * 128) == 2;
-  const int pitch = kPublish ? (v_section ? kEpiRowV : kEpiRow) : T::kPitch;
+  int pitch = T::kPitch;
+  if constexpr (kPublish) pitch = n0 / (a.pub.heads * 128) == 2 ? kEpiRowV : kEpiRow;
 #pragma unroll
   for (int i = 0; i < T::kTn; ++i)
 #pragma unroll
@@ -475,8 +483,13 @@ int32_t enqueue_gemm_tiles(GemmArgs& a, void* stream) {
   a.tiles_per_block = (a.block_rows + BM - 1) / BM;
   a.tiles_m = (a.M / a.block_rows) * a.tiles_per_block;
   a.tiles_n = (a.N + BN - 1) / BN;
-  a.xcd_tiles = (a.tiles_m * a.tiles_n + 7) / 8;
-  hipLaunchKernelGGL((gemm_tile_kernel<T, kPublish>), dim3(unsigned(a.xcd_tiles) * 8), dim3(T::kThreads), T::kLds, static_cast<hipStream_t>(stream), a);
+  a.more = (a.tiles_m * a.tiles_n + 7) / 8;
+  TileArgs<kPublish> args;
+  if constexpr (kPublish)
+    args = a;
+  else
+    args = LinearArgs{a.x, a.w, a.y, a.ldy, a.M, a.N, a.K, int32_t(a.ldx), int32_t(a.ldw), a.tiles_m, a.tiles_n, a.more};
+  hipLaunchKernelGGL((gemm_tile_kernel<T, kPublish>), dim3(unsigned(a.more) * 8), dim3(T::kThreads), T::kLds, static_cast<hipStream_t>(stream), args);
   return finish_launch("gemm_bf16.hip");
 }
 

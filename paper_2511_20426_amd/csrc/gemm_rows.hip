@@ -17,22 +17,12 @@ constexpr int kRowsLds = 160 * 1024;              // 3 stages of W, 2 of X
 constexpr int kFormThrough = 1, kFormPast = 2;    // results written through L2, past the caches; 0: left in L2
 constexpr int kList = 64;                         // tiles of a workgroup: one to a lane
 
-struct RowsArgs {
-  const uint16_t* x;
-  const uint16_t* w;
-  uint16_t* y;
-  int32_t M, N, K;
-  int64_t ldx, ldw, ldy;                          // row strides in elements
-  int32_t tiles_m, tiles_n;
-  int32_t form;                                   // how results are written: a kForm, that of a workgroup's last tile times four
-};
-
 // kMt: 16-row sub-tiles of X to a wave; a tile of Y has 32 kMt rows and 256 columns.
 // Tiles are numbered down bands of eight row tiles and dealt to the XCDs (workgroup b runs on b % 8) 32 at a time, what is
 // left for the last round by last_round_share; tile i of workgroup b of a group of 256 is the one that workgroup 256 i + b
 // would have if each took one.
 template <int kMt>
-__global__ __launch_bounds__(256, 1) void gemm_rows_kernel(RowsArgs a) {
+__global__ __launch_bounds__(256, 1) void gemm_rows_kernel(LinearArgs a) {
   constexpr int kTileRows = 32 * kMt, kWaveRows = 16 * kMt;
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, grp = lane >> 4;
@@ -66,7 +56,7 @@ __global__ __launch_bounds__(256, 1) void gemm_rows_kernel(RowsArgs a) {
       [y_lo] "s"(uint32_t(y)), [y_hi] "s"(uint32_t(y >> 32)), [tile_x] "s"(ldx2 * kTileRows),                          \
       [tile_w] "s"(ldw2 * kTileCols), [tile_y_lo] "s"(uint32_t(tile_y)), [tile_y_hi] "s"(uint32_t(tile_y >> 32)),      \
       [row8_lo] "s"(uint32_t(row8)), [row8_hi] "s"(uint32_t(row8 >> 32)), [ldw2] "s"(ldw2), [ldx2] "s"(ldx2),      \
-      [M] "s"(a.M), [N] "s"(a.N), [n_stages] "s"(a.K / 64), [tiles] "s"(tiles), [form] "s"(a.form), [wave] "s"(wave), [lds0] "s"(lds0),    \
+      [M] "s"(a.M), [N] "s"(a.N), [n_stages] "s"(a.K / 64), [tiles] "s"(tiles), [form] "s"(a.more), [wave] "s"(wave), [lds0] "s"(lds0),    \
       [list_m] "v"(list_m), [list_n] "v"(list_n), [roww] "v"(roww), [rowx] "v"(rowx), [chunkw] "v"(chunkw),            \
       [chunkx] "v"(chunkx), [aw0] "v"(aw0), [ax0] "v"(ax0), [row] "v"(row), [col] "v"(col),                            \
       [ylane_lo] "v"(uint32_t(ylane)), [ylane_hi] "v"(uint32_t(ylane >> 32))
@@ -86,7 +76,7 @@ __global__ __launch_bounds__(256, 1) void gemm_rows_kernel(RowsArgs a) {
 }
 
 template <int kMt>
-int32_t enqueue_gemm_rows(RowsArgs& a, void* stream) {
+int32_t enqueue_gemm_rows(LinearArgs& a, void* stream) {
   a.tiles_m = (a.M + 32 * kMt - 1) / (32 * kMt);
   a.tiles_n = (a.N + kTileCols - 1) / kTileCols;
   const int64_t total = int64_t(a.tiles_m) * a.tiles_n, rounds = (total + 255) / 256;
@@ -99,7 +89,7 @@ int32_t enqueue_gemm_rows(RowsArgs& a, void* stream) {
   // 23400 x 5128 x 256 78.1 / 81.2 / 117.4 / 111.1, 23400 x 5128 x 1536 281.1 / 286.1 / 317.5 / 286.0, one round 2340 x 4616 x 512
   // 16.0 / 15.5 / 15.4 / 15.5, 4680 x 3080 x 512 19.4 / 19.5 / 19.5 / 19.5.
   const bool whole_lines = a.ldy % 64 == 0 && reinterpret_cast<uintptr_t>(a.y) % 128 == 0;
-  a.form = whole_lines ? kFormPast | kFormThrough << 2 : (rounds <= 1 ? kFormThrough << 2 : 0);
+  a.more = whole_lines ? kFormPast | kFormThrough << 2 : (rounds <= 1 ? kFormThrough << 2 : 0);
   const auto kernel = gemm_rows_kernel<kMt>;
   hipLaunchKernelGGL(kernel, dim3(workgroups), dim3(256), kRowsLds, static_cast<hipStream_t>(stream), a);
   return finish_launch("gemm_rows.hip");
@@ -116,12 +106,12 @@ int32_t gemm_rows_ready() {
 
 int32_t launch_gemm_rows(int tile_rows, const void* x, const void* w, void* y, int32_t M, int32_t N, int32_t K,
                          int64_t ldx, int64_t ldw, int64_t ldy, void* stream) {
-  RowsArgs a{};
+  LinearArgs a{};
   a.x = static_cast<const uint16_t*>(x);
   a.w = static_cast<const uint16_t*>(w);
   a.y = static_cast<uint16_t*>(y);
   a.M = M; a.N = N; a.K = K;
-  a.ldx = ldx; a.ldw = ldw; a.ldy = ldy;
+  a.ldx = int32_t(ldx); a.ldw = int32_t(ldw); a.ldy = ldy;          // (below 2^22: check_gemm_shape)
   if (tile_rows == 256) return enqueue_gemm_rows<8>(a, stream);
   if (tile_rows == 192) return enqueue_gemm_rows<6>(a, stream);
   return enqueue_gemm_rows<4>(a, stream);

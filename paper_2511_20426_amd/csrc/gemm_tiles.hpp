@@ -1,8 +1,21 @@
-// How the tiles of a linear map are numbered and dealt to the XCDs, shared by its kernels.
+// The arguments of a plain linear map, and how its tiles are numbered and dealt to the XCDs, shared by its kernels.
 // (Included inside namespace ca { namespace { ... } }.)
 #pragma once
 
 constexpr int kBandRows = 8;                      // row tiles of a band
+
+// 64 bytes, because a launch with more takes the host longer: 2.6 us with up to 64 bytes of arguments, 3.3 with 128 to 256, 3.7
+// with 384 to 1024 (small products are bound by it: 257 x 768 x 1024 5.82 -> 5.56 us a call).
+struct LinearArgs {
+  const uint16_t* x;
+  const uint16_t* w;
+  uint16_t* y;
+  int64_t ldy;                                    // row strides in elements
+  int32_t M, N, K, ldx, ldw;
+  int32_t tiles_m, tiles_n;
+  int32_t more;                                   // gemm_rows_kernel: how results are written; gemm_tile_kernel: tiles of an XCD
+};
+static_assert(sizeof(LinearArgs) == 64, "one cache line");
 
 // Tiles are numbered down bands of eight row tiles.
 __device__ __forceinline__ void tile_at(int tiles_m, int tiles_n, int nth, int* tm, int* tn) {
