@@ -1,10 +1,12 @@
-"""Builds libcascade_attn.so (gfx950) in-tree with hipcc.  Used by __graft_entry__.build()."""
+"""Builds libcascade_attn.so (gfx950) in-tree with hipcc, and the Python extension beside it.  Used by __graft_entry__.build()."""
 from __future__ import annotations
 
+import importlib.util
 import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -12,6 +14,8 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.environ.get("CASCADE_ATTN_LIB") or os.path.join(PKG, "libcascade_attn.so")
 
 SOURCES = ["ca_meta.cpp", "ca_api.cpp", "ca_sched.cpp", "rope_cache.hip", "attn_f32.hip", "attn_bf16.hip", "mfma_peak.hip", "gemm_bf16.hip", "gemm_rows.hip"]
+
+CALLS = os.path.join(PKG, "_calls.so")           # Python extension: csrc/py_calls.cpp
 
 # packed fp32 instructions are kept off for all device code
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
@@ -22,6 +26,16 @@ def hipcc() -> str:
     if not os.path.exists(exe):
         raise RuntimeError("hipcc not found")
     return exe
+
+
+def calls_command() -> list:
+    """The extension holds no device code: g++ against the headers of torch and of HIP's host side."""
+    torch = importlib.util.find_spec("torch").submodule_search_locations[0]
+    return [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            "-I", os.path.join(ROOT, "include"), "-I", os.path.join(torch, "include"),
+            "-I", os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), "-I", sysconfig.get_paths()["include"],
+            os.path.join(CSRC, "py_calls.cpp"), "-L", os.path.join(torch, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
+            "-o", CALLS]
 
 
 def build(verbose: bool = False, extra=(), bdir: str | None = None) -> str:
@@ -42,10 +56,11 @@ def build(verbose: bool = False, extra=(), bdir: str | None = None) -> str:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
+    procs.append(("py_calls.cpp", subprocess.Popen(calls_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for src, p in procs:
         out, _ = p.communicate()
         if p.returncode != 0:
-            raise RuntimeError(f"hipcc failed on {src}:\n{out}")
+            raise RuntimeError(f"the compiler failed on {src}:\n{out}")
         if verbose and out.strip():
             print(out)
     cmd = [hipcc(), "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB] + objs

@@ -66,7 +66,8 @@ class CascadeAttnError(RuntimeError):
 
 
 def _load() -> C.CDLL:
-    if not os.path.exists(LIB_PATH) and "CASCADE_ATTN_LIB" not in os.environ:
+    calls = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_calls.so")
+    if not os.path.exists(calls) or not os.path.exists(LIB_PATH) and "CASCADE_ATTN_LIB" not in os.environ:
         # nothing built yet (a fresh checkout): build once, in-tree; there is no other path
         import importlib.util
         spec = importlib.util.spec_from_file_location(
@@ -151,6 +152,18 @@ def _load() -> C.CDLL:
 
 
 lib = _load()
+
+
+def _load_calls():
+    """The extension that takes the calls of runner.py's methods, on the entry points of the library loaded here."""
+    from . import _calls
+    _calls.bind(*(C.cast(f, C.c_void_p).value for f in (
+        lib.kv_cache_append_batch, lib.rope3d_apply_strided, lib.cascade_attn_forward, lib.cascade_attn_forward_share,
+        lib.cascade_attn_forward_rope, lib.layer_qkv_publish, lib.layer_linear_bf16)))
+    return _calls
+
+
+calls = _load_calls()
 
 
 def strerror(code: int) -> str:

@@ -12,8 +12,10 @@ import torch
 from . import binding as B
 
 
-# Small calls are bound by the host (a launch alone takes 3.5 - 4 us): checks read a tensor's shape and strides once,
-# as tuples, and no ctypes object is made for an address, for each look or object costs 0.1 us.
+# Small calls are bound by the host: a call whose arguments are all as they should be is taken by the extension (binding.calls), which
+# checks them and calls the library.  What it does not take (it returns None then) goes on in Python, which raises or, for
+# instance for integers of numpy, converts.  In the checks below a tensor's shape and strides are read once, as tuples, and no
+# ctypes object is made for an address, for each look or object costs 0.1 us.
 _BF16 = torch.bfloat16
 
 
@@ -50,6 +52,8 @@ class CascadePool:
         self.frames_per_block = frames_per_block
         self.heads, self.head_dim = heads, head_dim
         self._torch_dtype = torch_dtype(dtype)
+        index = self.device.index
+        self._shape = (heads, head_dim, self.block_tokens, int(dtype == "f32"), -1 if index is None else index)
 
     @classmethod
     def for_workload(cls, w, device="cuda:0"):
@@ -75,6 +79,13 @@ class CascadePool:
     def append_batch(self, block_ids: Sequence[int], timesteps: Sequence[int], epoch: int,
                      ks: Sequence[torch.Tensor], vs: Sequence[torch.Tensor]) -> list[int]:
         """All blocks of one cascade iteration in one launch; the tensors share their strides."""
+        h = self.ctx._h
+        if h:
+            r = B.calls.append_batch(h.value, self._shape, block_ids, timesteps, epoch, ks, vs)
+            if r.__class__ is list:
+                return r
+            if r is not None:
+                B._check(r, "kv_cache_append_batch")
         stride = ks[0].stride()
         for k, v in zip(ks, vs):
             self._check(k); self._check(v)
@@ -87,6 +98,13 @@ class CascadePool:
     def rope(self, x: torch.Tensor, first_frame: int, out: torch.Tensor | None = None) -> torch.Tensor:
         """Rotate x [n, H, D] (any token / head strides) into `out` (its own strides; default: a new
         contiguous tensor).  x is out is allowed."""
+        h = self.ctx._h
+        if h:
+            r = B.calls.rope(h.value, self._shape, x, first_frame, out)
+            if r.__class__ is int:
+                B._check(r, "rope3d_apply_strided")
+            if r is not None:
+                return r
         self._check(x)
         y = torch.empty(x.shape, dtype=x.dtype, device=x.device) if out is None else out
         self._check(y)
@@ -103,6 +121,13 @@ class CascadePool:
         first .. first+count-1 of `inflight` (q_rot and the result then hold just those);
         static_scratch: through cascade_attn_forward_static (`out` must then be given: that call
         is for callers that do not allocate)."""
+        h = self.ctx._h
+        if h and not static_scratch:
+            r = B.calls.forward(h.value, self._shape, q_rot, inflight, mode, out, share)
+            if r.__class__ is int:
+                B._check(r, "cascade_attn_forward" if share is None else "cascade_attn_forward_share")
+            if r is not None:
+                return r
         self._check(q_rot)
         n_q = len(inflight) if share is None else share[1]
         assert q_rot.is_contiguous() and q_rot.shape[0] == n_q * self.block_tokens
@@ -123,6 +148,13 @@ def _forward_rope(self, q_raw: torch.Tensor, inflight: Sequence[int], mode: int,
                   out: torch.Tensor | None = None) -> torch.Tensor:
     """Attention on queries that are not rotated yet (cascade_attn_forward_rope): q_raw [C*L, H, D]
     with any token / head strides; the result is a contiguous tensor of that shape."""
+    h = self.ctx._h
+    if h:
+        r = B.calls.forward_rope(h.value, self._shape, q_raw, inflight, mode, out)
+        if r.__class__ is int:
+            B._check(r, "cascade_attn_forward_rope")
+        if r is not None:
+            return r
     self._check(q_raw)
     assert q_raw.shape[0] == len(inflight) * self.block_tokens
     o = torch.empty(q_raw.shape, dtype=q_raw.dtype, device=q_raw.device) if out is None else out
@@ -139,6 +171,13 @@ def _qkv_publish(self, x: torch.Tensor, w_qkv: torch.Tensor, block_ids: Sequence
                  epoch: int, q_out: torch.Tensor | None = None) -> torch.Tensor:
     """QKV projection of the blocks in flight with their K/V published to the pool by the same
     launch (layer_qkv_publish); returns the packed, unrotated queries [C*L, H, D]."""
+    h = self.ctx._h
+    if h:
+        r = B.calls.qkv_publish(h.value, self._shape, x, w_qkv, block_ids, timesteps, epoch, q_out)
+        if r.__class__ is int:
+            B._check(r, "layer_qkv_publish")
+        if r is not None:
+            return r
     n = len(block_ids) * self.block_tokens
     width = self.heads * self.head_dim
     assert x.is_cuda and x.dtype == torch.bfloat16 and x.dim() == 2 and x.shape[0] == n and x.stride(1) == 1
@@ -156,6 +195,11 @@ CascadePool.qkv_publish = _qkv_publish
 def linear(x: torch.Tensor, w: torch.Tensor, out: torch.Tensor | None = None) -> torch.Tensor:
     """y = x @ w.T through layer_linear_bf16: x [M, K], w [N, K], y [M, N], bf16, rows may be
     strided (last dimension contiguous)."""
+    r = B.calls.linear(x, w, out)
+    if r.__class__ is int:
+        B._check(r, "layer_linear_bf16")
+    if r is not None:
+        return r
     assert x.is_cuda and w.is_cuda and x.dtype == _BF16 and w.dtype == _BF16
     xs, ws, sx, sw = x.shape, w.shape, x.stride(), w.stride()
     assert len(xs) == 2 and len(ws) == 2 and xs[1] == ws[1] and sx[1] == 1 and sw[1] == 1
