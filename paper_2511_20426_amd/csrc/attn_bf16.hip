@@ -63,20 +63,24 @@ struct AttnHead {
   float* partials;                     // [xcd][split item][chunk][kPartialFloats]
   // Query segments: rows that share one visible prefix (one segment in a bidirectional cascade,
   // one per query block in a block-causal one, longest prefix first); all have tiles_per_seg row
-  // tiles.  A "column" is a (head, row tile) pair; XCD x owns columns [x*cols_per_xcd,
-  // (x+1)*cols_per_xcd) and works through them segment by segment: item i of an XCD is segment
-  // i / cols_per_xcd of column i % cols_per_xcd.  Workgroups that run together on an XCD then
+  // tiles.  A "column" is a (head, row tile) pair, a work item a segment of a column.  Counted column by column the items
+  // are shared out to the XCDs in eight ranges of one length, so that an XCD's first and last column may be its own in some
+  // segments only; an XCD works through its range segment by segment (decode_item).  Workgroups that run together on an XCD then
   // walk KV prefixes of one length, start and finish together, and stay in step on the same pages
   // of the same few heads, which is what keeps those pages in the XCD's L2.
+  // With whole columns to an XCD, 60 columns were 8 for seven of them and 4 for the last, 9 columns 2 for four and none for three.  Whole
+  // block-causal steps of five blocks, us, whole columns / ranges of items: 12 heads of 4680 tokens 4392 / 3998 (143 items an XCD
+  // instead of 145 leave 15 for the last round, which can then be halved), of 1170 323 / 307; 3 heads of 540 58.5 / 42.8; four
+  // blocks of 2 heads of 1200 84 / 59.
   // Segment i has rows seg_first - i seg_rows .. and sees the first vis_first - i KV blocks.
   int32_t heads, pages_per_block, last_valid, n_seg;
-  int32_t tiles_per_seg, total_cols, cols_per_xcd, work_per_xcd;   // work_per_xcd = cols_per_xcd * n_seg
+  int32_t tiles_per_seg, items, work_per_xcd;   // work_per_xcd: of the XCDs with the most, items / 8 rounded up
   // Splitting: the last `split_items` work items of every XCD's range have their KV walk cut
   // into `split` page ranges, one workgroup each; their partial results meet in
   // merge_partials_kernel.
   int32_t split, split_items, full_items;   // per XCD: full_items + split_items == work_per_xcd
   float c;                             // log2(e) / sqrt(head_dim)
-  uint32_t per_cols, per_tiles, per_pages, per_split, per_split_items;   // reciprocal() of those
+  uint32_t per_seg, per_tiles, per_pages, per_split, per_split_items;   // reciprocal() of n_seg and those
   int64_t q_tok_stride, q_head_stride;
   // Rotary embedding of the queries (attn_bf16_kernel<true, ..> only).  Angles are formed in revolutions:
   // pair j turns by pos * freq[j] / 2pi; that factor is split into a 12-bit head and a tail so that
@@ -90,7 +94,7 @@ struct AttnHead {
   // every lane evaluates its own
   int32_t tab_f, tab_y, tab_quads;     // tab_quads: of the table
   int32_t seg_first, seg_rows, vis_first;
-  int32_t spare[4];
+  int32_t spare[5];
 };
 static_assert(sizeof(AttnHead) == 192, "three loads of 64 bytes");
 
@@ -136,19 +140,30 @@ __device__ __forceinline__ int div_small(int n, float inv) { return int((float(n
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
 struct WorkItem {
-  int h, row0, rows_end, seg;       // h < 0: no such item (the last XCD may own fewer columns)
+  int h, row0, rows_end, seg;       // h < 0: no such item (an XCD may own one less than another)
 };
+
+// Item `item` of an XCD, longest walks first.
 
 template <typename Args>
 __device__ __forceinline__ WorkItem decode_item(const Args& a, int xcd, int item) {
   WorkItem w;
-  int in_seg, t;
-  const int seg = w.seg = div_by(item, a.cols_per_xcd, a.per_cols, &in_seg), col = xcd * a.cols_per_xcd + in_seg;
+  // columns from .. to - 1, in the first `to_segs` segments column `to` too, in the first `from_segs` not column `from`
+  int from_segs, to_segs, t, seg = 0;
+  const int from = div_by((xcd * a.items) >> 3, a.n_seg, a.per_seg, &from_segs);
+  const int to = div_by(((xcd + 1) * a.items) >> 3, a.n_seg, a.per_seg, &to_segs);
+  int col = from + (from_segs > 0) + item, end = to + (to_segs > 0);
+  while (col >= end && ++seg < a.n_seg) {
+    col -= end;
+    col += from + (seg < from_segs);
+    end = to + (seg < to_segs);
+  }
+  w.seg = seg;
   w.h = div_by(col, a.tiles_per_seg, a.per_tiles, &t);
   const int row0 = a.seg_first - seg * a.seg_rows;
   w.row0 = row0 + t * kRowsPerWg;
   w.rows_end = row0 + a.seg_rows;
-  if (col >= a.total_cols) w.h = -1;
+  if (seg == a.n_seg) w.h = -1;
   return w;
 }
 
@@ -619,9 +634,9 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs args) {
 struct MergeArgs {                     // as in AttnHead; 64 bytes: a launch with more takes the host up to 1 us longer
   const float* partials;
   uint16_t* o;
-  int32_t heads, tiles_per_seg, total_cols, cols_per_xcd, seg_first, seg_rows;
+  int32_t heads, tiles_per_seg, items, n_seg, seg_first, seg_rows;
   int32_t split, split_items, full_items;
-  uint32_t per_cols, per_tiles, per_split_items;
+  uint32_t per_seg, per_tiles, per_split_items;
 };
 static_assert(sizeof(MergeArgs) == 64, "one cache line");
 
@@ -732,7 +747,7 @@ int split_of_small_launch(int items_per_xcd, int cus_per_xcd, int items, int min
 // few go the other way by little: 200 x 14 48.3 / 49.1, 152 x 74 168 / 159.
 bool takes_core16(const AttnArgs& a, int max_pages, int n_cu) {
   const bool alone = a.full_items == 0;                        // all items cut
-  const int64_t workgroups = int64_t(a.total_cols) * a.n_seg * (alone ? a.split : 1);
+  const int64_t workgroups = int64_t(a.items) * (alone ? a.split : 1);
   return 3 * workgroups >= 2 * int64_t(n_cu) && max_pages / (alone ? a.split : 1) >= 10;
 }
 
@@ -777,9 +792,8 @@ int32_t plan_attn_bf16(const AttnPlan& p, int variant, const void* q, void* out,
   }
   const int tiles = (a.seg_rows + kRowsPerWg - 1) / kRowsPerWg;
   a.tiles_per_seg = tiles;
-  a.total_cols = tiles * p.heads;
-  a.cols_per_xcd = (a.total_cols + 7) / 8;
-  a.work_per_xcd = a.cols_per_xcd * a.n_seg;
+  a.items = tiles * p.heads * a.n_seg;
+  a.work_per_xcd = (a.items + 7) / 8;
   a.c = 1.4426950408889634f / sqrtf(float(p.head_dim));
   a.q_tok_stride = int64_t(p.heads) * 128;       // rotated queries are contiguous
   a.q_head_stride = 128;
@@ -808,7 +822,7 @@ int32_t plan_attn_bf16(const AttnPlan& p, int variant, const void* q, void* out,
       if (split > 8) split = 8;
       while (split > 1 && (min_pages < 8 * split || (adapt && 8 * rem * split > capacity))) --split;
     } else {
-      split = split_of_small_launch(rem, cus_per_xcd, a.total_cols * a.n_seg, min_pages, max_pages, capacity);
+      split = split_of_small_launch(rem, cus_per_xcd, a.items, min_pages, max_pages, capacity);
     }
     if (split > 1) {
       a.split = split;
@@ -818,7 +832,7 @@ int32_t plan_attn_bf16(const AttnPlan& p, int variant, const void* q, void* out,
     }
   }
   *core16 = takes_core16(a, max_pages, n_cu);
-  a.per_cols = reciprocal(a.cols_per_xcd);
+  a.per_seg = reciprocal(a.n_seg);
   a.per_tiles = reciprocal(a.tiles_per_seg);
   a.per_pages = reciprocal(a.pages_per_block);
   a.per_split = reciprocal(a.split);
@@ -832,8 +846,8 @@ int32_t enqueue_attn_bf16(const AttnArgs& a, void* stream) {
   const auto kernel = attn_bf16_kernel<kRopeQ, kCore16, kTails>;
   hipLaunchKernelGGL(kernel, grid, dim3(256), kAttnLds, static_cast<hipStream_t>(stream), a);
   if (a.split > 1) {
-    const MergeArgs m{a.partials, a.o, a.heads, a.tiles_per_seg, a.total_cols, a.cols_per_xcd, a.seg_first, a.seg_rows,
-                      a.split, a.split_items, a.full_items, a.per_cols, a.per_tiles, a.per_split_items};
+    const MergeArgs m{a.partials, a.o, a.heads, a.tiles_per_seg, a.items, a.n_seg, a.seg_first, a.seg_rows,
+                      a.split, a.split_items, a.full_items, a.per_seg, a.per_tiles, a.per_split_items};
     hipLaunchKernelGGL(merge_partials_kernel<kCore16>, dim3((unsigned)(8 * a.split_items), kRowsPerWg / 32), dim3(256), 0,
                        static_cast<hipStream_t>(stream), m);
   }
