@@ -721,13 +721,14 @@ int32_t attn_bf16_variant_ok(int variant) { return variant == 0 || variant == 1 
 
 namespace {
 
-// How many page ranges the items of a launch that leaves CUs idle are cut into.  A walk of n pages cut
-// in s takes ceil(n / s) page times of 1.95 us; against that stand the merge launch, about one page time,
-// and every partial result that is written and read again (135 KB), 1/40 of one.  Measured, whole
-// forwards: 1 item of 14 pages 37.7 us whole, 26.7 in two, 18.8 in seven; 15 of 20 pages 54.8 whole, 41.1 / 30.1 /
+// How many page ranges the items are cut into that leave CUs idle: all of a launch, or what a launch of more than one round
+// leaves for its last.  A walk of n pages cut in s takes ceil(n / s) page times of 1.95 us; against that stand the merge
+// launch, about one page time, and every partial result that is written and read again (135 KB), 1/40 of one.
+// Measured, whole forwards: 1 item of 14 pages 37.7 us whole, 26.7 in two, 18.8 in seven; 15 of 20 pages 54.8 whole, 41.1 / 30.1 /
 // 32.3 in 2 / 5 / 8; 64 of 14 pages 42.0 whole, 33.9 in four; 38 of 259 pages 473 whole, 141 in six; 120 of 14 pages
-// 44.9 whole, 44.2 in two.
-int split_of_small_launch(int items_per_xcd, int cus_per_xcd, int items, int min_pages, int max_pages, int capacity) {
+// 44.9 whole, 44.2 in two.  Last rounds, whole steps: 8 of 264 items, 21 pages, 106.6 in 2, 92.8 in 11; 24 of 280, 16 pages, 90.7
+// in 2, 84.9 in 4; 16 of 272, 34 pages, 139.4 in 4, 132.4 in 9.
+int split_of_idle_round(int items_per_xcd, int cus_per_xcd, int items, int min_pages, int max_pages, int capacity) {
   int best = 1, best_cost = 40 * max_pages;                    // in 40ths of a page time
   for (int s = 2; s <= kMaxSplit && s * items_per_xcd <= cus_per_xcd && s <= min_pages; ++s) {
     if (8 * items_per_xcd * s > capacity) break;
@@ -799,7 +800,7 @@ int32_t plan_attn_bf16(const AttnPlan& p, int variant, const void* q, void* out,
   a.q_head_stride = 128;
   // Splitting.  One workgroup occupies a CU, an XCD has n_cu/8 of them, and all items of a
   // launch take about the same time: after floor(items / cus) full rounds, `rem` items would run
-  // alone while the other CUs idle.  Their KV walks are cut into split = floor(cus / rem) ranges.
+  // alone while the other CUs idle.  Their KV walks (the shortest of the launch) are cut into up to floor(cus / rem) ranges.
   // A launch that does not give every CU an item has all of them cut.
   int n_cu = 0;
   if (const int32_t rc = device_cu_count(&n_cu); rc != CA_OK) return rc;
@@ -818,11 +819,19 @@ int32_t plan_attn_bf16(const AttnPlan& p, int variant, const void* q, void* out,
   if (partials_dev && variant == 0 && rem > 0) {
     int split = 1;
     if (a.work_per_xcd > cus_per_xcd) {
-      split = cus_per_xcd / rem;
-      if (split > 8) split = 8;
-      while (split > 1 && (min_pages < 8 * split || (adapt && 8 * rem * split > capacity))) --split;
+      // With walks of several lengths CUs come to the last items one after the other, and what those could gain is less: ranges
+      // of at least eight pages, and as many as there are CUs.  (With the rule for walks of one length 64 of 320 items with walks
+      // of 14 to 42 pages go from 120.5 us to 128.7, from whole to three ranges; with an estimate of when the CUs come 48 of 300
+      // with 70 to 110 pages from 304 to 310, from five ranges to four.)
+      if (a.n_seg == 1) {
+        split = split_of_idle_round(rem, cus_per_xcd, 8 * rem, min_pages, max_pages, adapt ? capacity : INT32_MAX);
+      } else {
+        split = cus_per_xcd / rem;
+        if (split > 8) split = 8;
+        while (split > 1 && (min_pages < 8 * split || (adapt && 8 * rem * split > capacity))) --split;
+      }
     } else {
-      split = split_of_small_launch(rem, cus_per_xcd, a.items, min_pages, max_pages, capacity);
+      split = split_of_idle_round(rem, cus_per_xcd, a.items, min_pages, max_pages, capacity);
     }
     if (split > 1) {
       a.split = split;

@@ -140,6 +140,23 @@ def test_bf16_split_launch_that_fills_the_chip(nc, ni, mode):
         Hn.assert_close(out[:, heads], ref, "bf16", f"cut launch on many workgroups nc={nc} ni={ni} mode={mode} {form.__name__}", bound=bound)
 
 
+# What launches of more than one round leave for the last: 8 of 264 items in eleven ranges of one or two pages, 24 of 280 in four, 16 of
+# 272 in nine.  Each of an XCD's first heads has none of these items, its last one has.
+@pytest.mark.parametrize("heads,gh,gw,nc,ni", [(24, 20, 43, 0, 1), (40, 15, 9, 0, 4), (16, 21, 33, 0, 2)])
+def test_bf16_split_last_round(heads, gh, gw, nc, ni):
+    w = W.small_variant(W.CONFIGS["c3_wan1p3b_cascade5"], heads=heads, grid_h=gh, grid_w=gw, n_cached=nc, n_inflight=ni)
+    cached, infl = list(range(nc)), list(range(nc, nc + ni))
+    q, k, v = W.draw_config(w, seed=8)
+    pool = Hn.gpu_setup(w, k, v, cached, infl)
+    some = [0, heads // 8 - 1, heads - 1]
+    ref, bound = (np.concatenate(x) for x in Hn.oracle_forward_bounded(w, q, k, v, cached, infl, BI, heads=some))
+    pool.pool[pool.pool.numel() - (256 * 256 * 132 * 4):].fill_(0xFF)       # partial results start as NaN
+    print(f"last round heads={heads} grid={gh}x{gw}", flush=True)
+    out = Hn.gpu_forward(w, pool, q, infl, BI)
+    assert np.isfinite(out).all()
+    Hn.assert_close(out[:, some], ref, "bf16", f"last round heads={heads} grid={gh}x{gw}", bound=bound)
+
+
 # Tiles of the linear map: one row, a tile and one row, column counts that end inside a tile, the shortest and
 # longer walks over k, several tiles per band and XCD.  (Two stages are fewer than any ring holds.)
 @pytest.mark.parametrize("M,N,K", [(1, 8, 128), (65, 72, 128), (129, 200, 768), (1100, 1400, 256), (2050, 1160, 128), (1345, 3000, 256),
