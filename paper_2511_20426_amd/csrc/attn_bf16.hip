@@ -78,6 +78,9 @@ struct AttnHead {
   // Splitting: the last `split_items` work items of every XCD's range have their KV walk cut
   // into `split` page ranges, one workgroup each; their partial results meet in
   // merge_partials_kernel.
+  // With `range` > 0 all items of a launch with walks of several lengths are cut into ranges of that many pages (the last
+  // one of a walk is what is left), and a walk of one range is not cut: range_segs has, four bits each, in how many segments
+  // walks have a first, second .. range.  A workgroup has a place of its own for its partial result then.
   int32_t split, split_items, full_items;   // per XCD: full_items + split_items == work_per_xcd
   float c;                             // log2(e) / sqrt(head_dim)
   uint32_t per_seg, per_tiles, per_pages, per_split, per_split_items;   // reciprocal() of n_seg and those
@@ -94,7 +97,8 @@ struct AttnHead {
   // every lane evaluates its own
   int32_t tab_f, tab_y, tab_quads;     // tab_quads: of the table
   int32_t seg_first, seg_rows, vis_first;
-  int32_t spare[5];
+  int32_t range, spare[2];
+  uint64_t range_segs;
 };
 static_assert(sizeof(AttnHead) == 192, "three loads of 64 bytes");
 
@@ -106,6 +110,7 @@ constexpr int kLaneFrame = 0, kLaneSlot = 32;
 static_assert(kMaxInflight == 8 && kMaxKvBlocks == 32, "AttnArgs::lanes");
 
 constexpr int kMaxSplit = 16;          // page ranges of a walk
+constexpr int kPartialsPerXcd = kMaxPartials / 8;   // of launches with `range`
 
 typedef __attribute__((ext_vector_type(16))) uint32_t u32x16;
 
@@ -143,20 +148,32 @@ struct WorkItem {
   int h, row0, rows_end, seg;       // h < 0: no such item (an XCD may own one less than another)
 };
 
-// Item `item` of an XCD, longest walks first.
+// An XCD's items: columns from .. to - 1, in the first `to_segs` segments column `to` too, in the first `from_segs` not column
+// `from`.
+struct Share {
+  int from, from_segs, to, to_segs;
+  __device__ __forceinline__ int first(int seg) const { return from + (seg < from_segs); }
+  __device__ __forceinline__ int end(int seg) const { return to + (seg < to_segs); }
+  // items of the first n segments
+  __device__ __forceinline__ int count(int n) const { return n * (to - from) + min(n, to_segs) - min(n, from_segs); }
+};
 
 template <typename Args>
-__device__ __forceinline__ WorkItem decode_item(const Args& a, int xcd, int item) {
+__device__ __forceinline__ Share share_of(const Args& a, int xcd) {
+  Share s;
+  s.from = div_by((xcd * a.items) >> 3, a.n_seg, a.per_seg, &s.from_segs);
+  s.to = div_by(((xcd + 1) * a.items) >> 3, a.n_seg, a.per_seg, &s.to_segs);
+  return s;
+}
+
+// Item `item` of an XCD, longest walks first.
+template <typename Args>
+__device__ __forceinline__ WorkItem decode_item(const Args& a, const Share& share, int item) {
   WorkItem w;
-  // columns from .. to - 1, in the first `to_segs` segments column `to` too, in the first `from_segs` not column `from`
-  int from_segs, to_segs, t, seg = 0;
-  const int from = div_by((xcd * a.items) >> 3, a.n_seg, a.per_seg, &from_segs);
-  const int to = div_by(((xcd + 1) * a.items) >> 3, a.n_seg, a.per_seg, &to_segs);
-  int col = from + (from_segs > 0) + item, end = to + (to_segs > 0);
+  int t, seg = 0, col = share.first(0) + item, end = share.end(0);
   while (col >= end && ++seg < a.n_seg) {
-    col -= end;
-    col += from + (seg < from_segs);
-    end = to + (seg < to_segs);
+    col += share.first(seg) - end;
+    end = share.end(seg);
   }
   w.seg = seg;
   w.h = div_by(col, a.tiles_per_seg, a.per_tiles, &t);
@@ -242,19 +259,31 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs args) {
   // ---- which (head, row tile, page range): XCD x takes its own work_per_xcd items; inside an XCD
   // the full items come first, then the split ones, all their first page ranges, then the second ...
   const int xcd = blockIdx.x & 7, nth = blockIdx.x >> 3;
+  const Share share = share_of(a, xcd);
   int item = nth, chunk = 0, n_chunks = 1;
-  if (nth >= a.full_items) {
+  if (a.range > 0) {                                       // all first ranges, then the second ones of the walks that have one ..
+    uint64_t segs = a.range_segs;
+    for (int n; item >= (n = share.count(int(segs & 15)));) {
+      item -= n;
+      segs >>= 4;
+      ++chunk;
+      if (segs == 0) return;
+    }
+  } else if (nth >= a.full_items) {
     int in_chunk;
     chunk = div_by(nth - a.full_items, a.split_items, a.per_split_items, &in_chunk);
     item = a.full_items + in_chunk;
     n_chunks = a.split;
   }
-  const WorkItem wi = decode_item(a, xcd, item);
+  const WorkItem wi = decode_item(a, share, item);
   if (wi.h < 0) return;
   const int h = wi.h, row0 = wi.row0, rows_end = wi.rows_end, n_kvb = a.vis_first - wi.seg;
   const int all_pages = n_kvb * a.pages_per_block;
   int page_lo = 0, page_hi = all_pages, in_block, rem;
-  if (n_chunks > 1) {
+  if (a.range > 0) {
+    page_lo = chunk * a.range;
+    page_hi = min(page_lo + a.range, all_pages);
+  } else if (n_chunks > 1) {
     page_lo = div_by(all_pages * chunk, n_chunks, a.per_split, &rem);
     page_hi = div_by(all_pages * (chunk + 1), n_chunks, a.per_split, &rem);
   }
@@ -494,7 +523,8 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs args) {
   // The loop leaves few scalar registers: what the epilogue needs waits in LDS, or is read again from
   // the arguments, through a pointer the compiler cannot see to be the same.
   if (tid == 0) {
-    const int part_index = n_chunks > 1 ? (xcd * a.split_items + (item - a.full_items)) * n_chunks + chunk : -1;
+    const int part_index = a.range > 0 ? (all_pages > a.range ? xcd * kPartialsPerXcd + nth : -1)
+                           : n_chunks > 1 ? (xcd * a.split_items + (item - a.full_items)) * n_chunks + chunk : -1;
     *reinterpret_cast<int4*>(lds + kPosArea) = make_int4(h, row0, rows_end, part_index);
   }
   typedef const __attribute__((address_space(4))) AttnArgs* ArgPtr;
@@ -634,27 +664,49 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs args) {
 struct MergeArgs {                     // as in AttnHead; 64 bytes: a launch with more takes the host up to 1 us longer
   const float* partials;
   uint16_t* o;
+  uint64_t range_segs;                 // 0: every item has `split` ranges, side by side
   int32_t heads, tiles_per_seg, items, n_seg, seg_first, seg_rows;
-  int32_t split, split_items, full_items;
-  uint32_t per_seg, per_tiles, per_split_items;
+  int32_t split_and_items, full_items; // split + 256 split_items
+  uint32_t per_seg, per_tiles;
 };
 static_assert(sizeof(MergeArgs) == 64, "one cache line");
 
-template <bool kCore16>
+template <bool kCore16, bool kRanges>
 __global__ __launch_bounds__(256) void merge_partials_kernel(MergeArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l31 = lane & 31, hi = lane >> 5, l15 = lane & 15, grp = lane >> 4;
-  int sidx;
-  const int xcd = div_by(blockIdx.x, a.split_items, a.per_split_items, &sidx);
-  const int wrow = blockIdx.y >> 1;                            // the attention kernel's wave
+  const int xcd = blockIdx.y, sidx = blockIdx.x, piece = blockIdx.z;   // (on the XCD that wrote the partials: 1 % slower steps)
+  WorkItem wi;
+  int split = a.split_and_items & 255;
+  uint32_t place[kMaxSplit];                                   // of range c, counted in partial results from `first_part` on
+  const float* first_part = a.partials;
+  if (kRanges) {
+    const Share share = share_of(a, xcd);
+    wi = decode_item(a, share, sidx);
+    if (wi.h < 0) return;
+    uint64_t segs = a.range_segs;
+    uint32_t at = xcd * kPartialsPerXcd + sidx;
+    split = 0;
+#pragma unroll
+    for (int c = 0; c < kMaxSplit; ++c, segs >>= 4) {
+      place[c] = at;
+      at += share.count(int(segs & 15));
+      split += int(segs & 15) > wi.seg;
+    }
+    if (split < 2) return;                                     // written by its workgroup
+  } else {
+    first_part += size_t(xcd * (a.split_and_items >> 8) + sidx) * split * kPartialFloats;
+#pragma unroll
+    for (int c = 0; c < kMaxSplit; ++c) place[c] = c;
+  }
+  const int wrow = piece >> 1;                            // the attention kernel's wave
   // 16x16x32: query tile t, accumulators j0 .. j0+3 (dims 16 j0 ..); 32x32x16: column tile nt, accumulator 2 mt + nt
-  const int t = 2 * (blockIdx.y & 1) + (wave & 1), j0 = 4 * (wave >> 1);
-  const int nt = blockIdx.y & 1, mt = wave;
+  const int t = 2 * (piece & 1) + (wave & 1), j0 = 4 * (wave >> 1);
+  const int nt = piece & 1, mt = wave;
   const int first = kCore16 ? 16 * t : 32 * nt;
   const int row_in_tile = wrow * 64 + first + (kCore16 ? l15 : l31);
-  const float* tile = a.partials + size_t(xcd * a.split_items + sidx) * a.split * kPartialFloats;
-  const float* ml = tile + kPartialMl + 2 * row_in_tile;
+  const float* ml = first_part + kPartialMl + 2 * row_in_tile;
   constexpr int kStep = kCore16 ? 4 * 64 : 64;                 // from one of the four groups to the next
-  const float4* part = reinterpret_cast<const float4*>(tile) + (wrow * 32 + (kCore16 ? 4 * j0 + t : 4 * (2 * mt + nt))) * 64 + lane;
+  const float4* part = reinterpret_cast<const float4*>(first_part) + (wrow * 32 + (kCore16 ? 4 * j0 + t : 4 * (2 * mt + nt))) * 64 + lane;
   // All references and row sums are requested together and with them the accumulators of the first
   // kBatch partials: a launch of this kernel is two or three memory latencies long.  With one range after the other
   // 6.0 us for 15 tiles in seven ranges and 9.2 for 60 in six, now 4.4 and 8.1.
@@ -662,22 +714,24 @@ __global__ __launch_bounds__(256) void merge_partials_kernel(MergeArgs a) {
 #pragma unroll
   for (int c = 0; c < kMaxSplit; ++c) {
     y[c] = make_float2(-INFINITY, 0.f);
-    if (c < a.split) y[c] = *reinterpret_cast<const float2*>(ml + c * kPartialFloats);
+    if (c < split) y[c] = *reinterpret_cast<const float2*>(ml + size_t(place[c]) * kPartialFloats);
   }
   constexpr int kBatch = 4;
   float4 x[kBatch][4], acc[4];
   auto request = [&](int c0) {
 #pragma unroll
     for (int b = 0; b < kBatch; ++b)
-      if (c0 + b < a.split) {
+      if (c0 + b < split) {
 #pragma unroll
-        for (int g = 0; g < 4; ++g) x[b][g] = part[(c0 + b) * (kPartialFloats / 4) + g * kStep];
+        for (int g = 0; g < 4; ++g) x[b][g] = part[size_t(place[c0 + b]) * (kPartialFloats / 4) + g * kStep];
       }
   };
   request(0);
   __builtin_amdgcn_sched_barrier(0);
-  const WorkItem wi = decode_item(a, xcd, a.full_items + sidx);
-  if (wi.h < 0) return;
+  if (!kRanges) {
+    wi = decode_item(a, share_of(a, xcd), a.full_items + sidx);
+    if (wi.h < 0) return;
+  }
   const int row = wi.row0 + row_in_tile;
   if (wi.row0 + wrow * 64 + first >= wi.rows_end) return;
   float m = y[0].x, l = 0.f;
@@ -688,12 +742,12 @@ __global__ __launch_bounds__(256) void merge_partials_kernel(MergeArgs a) {
 #pragma unroll
   for (int c0 = 0; c0 < kMaxSplit; c0 += kBatch) {
     if (c0 > 0) {
-      if (a.split <= c0) break;
+      if (split <= c0) break;
       request(c0);
     }
 #pragma unroll
     for (int b = 0; b < kBatch; ++b) {
-      if (c0 + b >= a.split) break;
+      if (c0 + b >= split) break;
       const float wgt = __builtin_amdgcn_exp2f(y[c0 + b].x - m);
       l += wgt * y[c0 + b].y;
 #pragma unroll
@@ -741,6 +795,40 @@ int split_of_idle_round(int items_per_xcd, int cus_per_xcd, int items, int min_p
   return best;
 }
 
+// The same for launches with walks of several lengths that leave CUs idle: ranges of one length for all of them, since the
+// longest range is what counts.  Fills in `range`, `range_segs`, `split` (of the longest walk) and, as full_items, the workgroups
+// of an XCD.  Whole block-causal steps with each walk in as many ranges, and so: 12 heads, two
+// blocks of 924 tokens over one 48.2 / 44.9 us; six, five of 756 over three 72.7 / 60.9; three, five of 1596 over one 101 / 84;
+// eight, five of 252 28.5 / 25.9; three, five of 390 over two 28.7 / 28.6.
+void ranges_of_idle_launch(AttnArgs& a, int cus_per_xcd) {
+  const int most = cus_per_xcd < kPartialsPerXcd ? cus_per_xcd : kPartialsPerXcd, max_pages = a.vis_first * a.pages_per_block;
+  int64_t best_cost = 40 * int64_t(max_pages);                 // in 40ths of a page time
+  for (int s = 2; s <= kMaxSplit && s <= max_pages; ++s) {
+    const int range = (max_pages + s - 1) / s;
+    if ((max_pages + range - 1) / range != s) continue;
+    // an XCD has whole columns and of one column, at most, its first (longest) walks
+    int whole = 0, first = 0;
+    for (int i = 0; i < a.n_seg; ++i) {
+      const int n = ((a.vis_first - i) * a.pages_per_block + range - 1) / range;
+      whole += n;
+      if (i < a.work_per_xcd % a.n_seg) first += n;
+    }
+    const int ranges = a.work_per_xcd / a.n_seg * whole + first;
+    if (ranges > most) continue;
+    const int64_t cost = 40 * int64_t(range + 1) + 8 * ranges;
+    if (cost >= best_cost) continue;
+    best_cost = cost;
+    a.range = range;
+    a.split = s;
+    a.full_items = ranges;
+  }
+  for (int c = 0; a.range > 0 && c < a.split; ++c) {           // a walk has range c if it is longer than c ranges
+    int segs = 0;
+    while (segs < a.n_seg && (a.vis_first - segs) * a.pages_per_block > c * a.range) ++segs;
+    a.range_segs |= uint64_t(segs) << (4 * c);
+  }
+}
+
 // The loop on the 16x16x32 instruction draws less power a flop, the one on 32x32x16 needs fewer cycles: where most
 // CUs work at once and long enough, power decides.  Whole forwards, us, 32x32x16 / 16x16x32, by workgroups of a round
 // x pages of a walk: 171 x 259 545 / 528, 228 x 259 658 / 610, 228 x 43 135 / 129, 250 x 14 54.4 / 51.7, 200 x 10
@@ -748,8 +836,8 @@ int split_of_idle_round(int items_per_xcd, int cus_per_xcd, int items, int min_p
 // few go the other way by little: 200 x 14 48.3 / 49.1, 152 x 74 168 / 159.
 bool takes_core16(const AttnArgs& a, int max_pages, int n_cu) {
   const bool alone = a.full_items == 0;                        // all items cut
-  const int64_t workgroups = int64_t(a.items) * (alone ? a.split : 1);
-  return 3 * workgroups >= 2 * int64_t(n_cu) && max_pages / (alone ? a.split : 1) >= 10;
+  const int64_t workgroups = a.range > 0 ? 8 * int64_t(a.full_items) : int64_t(a.items) * (alone ? a.split : 1);
+  return 3 * workgroups >= 2 * int64_t(n_cu) && (a.range > 0 ? a.range : max_pages / (alone ? a.split : 1)) >= 10;
 }
 
 // Which launches take the loops with short pages: two steps instead of four are walked of a block's last page, and
@@ -830,6 +918,9 @@ int32_t plan_attn_bf16(const AttnPlan& p, int variant, const void* q, void* out,
         if (split > 8) split = 8;
         while (split > 1 && (min_pages < 8 * split || (adapt && 8 * rem * split > capacity))) --split;
       }
+    } else if (a.n_seg > 1 && capacity >= kMaxPartials) {
+      ranges_of_idle_launch(a, cus_per_xcd);
+      if (a.range > 0) *partials_needed = kMaxPartials;
     } else {
       split = split_of_idle_round(rem, cus_per_xcd, a.items, min_pages, max_pages, capacity);
     }
@@ -855,10 +946,11 @@ int32_t enqueue_attn_bf16(const AttnArgs& a, void* stream) {
   const auto kernel = attn_bf16_kernel<kRopeQ, kCore16, kTails>;
   hipLaunchKernelGGL(kernel, grid, dim3(256), kAttnLds, static_cast<hipStream_t>(stream), a);
   if (a.split > 1) {
-    const MergeArgs m{a.partials, a.o, a.heads, a.tiles_per_seg, a.items, a.n_seg, a.seg_first, a.seg_rows,
-                      a.split, a.split_items, a.full_items, a.per_seg, a.per_tiles, a.per_split_items};
-    hipLaunchKernelGGL(merge_partials_kernel<kCore16>, dim3((unsigned)(8 * a.split_items), kRowsPerWg / 32), dim3(256), 0,
-                       static_cast<hipStream_t>(stream), m);
+    const int cut = a.range > 0 ? a.work_per_xcd : a.split_items;        // items of an XCD
+    const MergeArgs m{a.partials, a.o, a.range_segs, a.heads, a.tiles_per_seg, a.items, a.n_seg, a.seg_first, a.seg_rows,
+                      a.split + 256 * cut, a.full_items, a.per_seg, a.per_tiles};
+    const auto merge = a.range > 0 ? merge_partials_kernel<kCore16, true> : merge_partials_kernel<kCore16, false>;
+    hipLaunchKernelGGL(merge, dim3((unsigned)cut, 8, kRowsPerWg / 32), dim3(256), 0, static_cast<hipStream_t>(stream), m);
   }
   return finish_launch("attn_bf16.hip");
 }

@@ -32,6 +32,54 @@ def test_every_item_once_and_longest_walks_first(n_seg):
         assert sorted(seen) == [(s, c) for s in range(n_seg) for c in range(cols)]
 
 
+def _ranges(cols, n_seg, longest, ppb, cus=32):
+    """ranges_of_idle_launch: pages of a range and workgroups of an XCD, or None."""
+    work, best = (cols * n_seg + 7) // 8, (40 * longest * ppb, None)
+    pages = [(longest - i) * ppb for i in range(n_seg)]
+    for s in range(2, min(16, pages[0]) + 1):
+        r = -(-pages[0] // s)
+        n = [-(-p // r) for p in pages]
+        groups = work // n_seg * sum(n) + sum(n[:work % n_seg])
+        if n[0] == s and groups <= cus:
+            best = min(best, (40 * (r + 1) + 8 * groups, (r, groups)), key=lambda b: b[0])
+    return best[1]
+
+
+@pytest.mark.parametrize("n_seg", range(2, 9))
+def test_every_page_in_one_range(n_seg):
+    """A workgroup's item and pages as attn_bf16_kernel finds them, and where merge_partials_kernel looks for its result."""
+    cut = 0
+    for cols in range(1, 256 // n_seg):
+        for longest in (n_seg, n_seg + 2, n_seg + 7):
+            for ppb in (1, 3, 13):
+                plan, items = _ranges(cols, n_seg, longest, ppb), cols * n_seg
+                if plan is None:
+                    continue
+                cut += 1
+                (r, groups), pages = plan, [(longest - i) * ppb for i in range(n_seg)]
+                segs = [sum(p > c * r for p in pages) for c in range(16)]
+                found, slots = {}, {}
+                for xcd in range(8):
+                    own = (xcd + 1) * items // 8 - xcd * items // 8
+                    seg_of = [_item(items, n_seg, xcd, i)[0] for i in range(own)]
+                    count = [sum(s < n for s in seg_of) for n in segs]
+                    assert sum(count) <= groups <= 32
+                    for nth in range(groups):
+                        item, c = nth, 0
+                        while c < 16 and item >= count[c]:
+                            item, c = item - count[c], c + 1
+                        if c < 16:
+                            seg, col = _item(items, n_seg, xcd, item)
+                            found.setdefault((seg, col), []).append((c * r, min(c * r + r, pages[seg])))
+                            slots[seg, col, c] = 32 * xcd + nth
+                    for i in range(own):
+                        seg, col = _item(items, n_seg, xcd, i)
+                        assert all(slots[seg, col, c] == 32 * xcd + i + sum(count[:c]) for c in range(sum(n > seg for n in segs)))
+                assert len(found) == items and len(set(slots.values())) == len(slots) and max(slots.values()) < 256
+                assert all([x for lo, hi in f for x in range(lo, hi)] == list(range(pages[seg])) for (seg, _), f in found.items())
+    assert cut > 20
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("heads,gh,gw,inflight", [(1, 4, 5, 1), (1, 4, 5, 5), (1, 11, 13, 3), (3, 11, 13, 5), (5, 9, 10, 2), (9, 11, 13, 5), (12, 7, 13, 4),
                                                   (15, 11, 13, 5)])
