@@ -135,7 +135,8 @@ FORMS = ("", " sc1", " nt")     # how results are written: left in L2, written t
 
 def result_lines(mt):
     """A tile's sums leave, rounded to bf16, 16 bytes of a row to a lane, in the form that %[form] has for the last tile of the
-    workgroup or for the others, and start from zero again if there is a next tile."""
+    workgroup or for the others, and start from zero again if there is a next tile.  (Between a vector instruction that writes VCC
+    or a scalar register and one that reads it stand two wait states, as the compiler has it for gfx950.)"""
     a = S_T
     out = ["s_nop 15", "s_nop 15",                         # the last MFMAs have written back
            f"v_readlane_b32 s{a}, %[list_m], s{S_YT}", f"v_readlane_b32 s{a + 1}, %[list_n], s{S_YT}", "s_nop 3",
@@ -143,8 +144,8 @@ def result_lines(mt):
            f"s_mul_i32 s{a + 2}, s{a}, %[tile_y_lo]", f"s_mul_hi_u32 s{a + 3}, s{a}, %[tile_y_lo]", f"s_mul_i32 s{a + 4}, s{a}, %[tile_y_hi]",
            f"s_add_u32 s{a + 3}, s{a + 3}, s{a + 4}", f"s_add_u32 s{a + 2}, s{a + 2}, %[y_lo]", f"s_addc_u32 s{a + 3}, s{a + 3}, %[y_hi]",
            f"s_lshl_b32 s{a + 4}, s{a + 1}, 9", f"s_add_u32 s{a + 2}, s{a + 2}, s{a + 4}", f"s_addc_u32 s{a + 3}, s{a + 3}, 0",
-           f"v_mov_b32 {V(VT)}, s{a + 3}",
-           f"v_add_co_u32 {V(YROW)}, vcc, s{a + 2}, %[ylane_lo]", f"v_addc_co_u32 {V(YROW + 1)}, vcc, {V(VT)}, %[ylane_hi], vcc",
+           f"v_add_co_u32 {V(YROW)}, vcc, s{a + 2}, %[ylane_lo]", f"v_mov_b32 {V(VT)}, s{a + 3}", "s_nop 0",
+           f"v_addc_co_u32 {V(YROW + 1)}, vcc, {V(VT)}, %[ylane_hi], vcc",
            # what exists of the tile
            f"s_mul_i32 s{a + 4}, s{a}, {32 * mt}", f"s_sub_u32 s{S_ROWS}, %[M], s{a + 4}",
            f"s_lshl_b32 s{a + 4}, s{a + 1}, 8", f"s_sub_u32 s{S_NCOL}, %[N], s{a + 4}"]
@@ -178,7 +179,7 @@ def result_lines(mt):
                             f"global_store_dwordx4 {V(YROW, 2)}, {V(pack + 8 * c + 4 * half, 4)}, off offset:{128 * c}{form}"]
                 out.append("s_mov_b64 exec, -1")
                 if tj < mt - 1 or half == 0:
-                    out += [f"v_mov_b32 {V(VT)}, %[row8_hi]", f"v_add_co_u32 {V(YROW)}, vcc, %[row8_lo], {V(YROW)}",
+                    out += [f"v_add_co_u32 {V(YROW)}, vcc, %[row8_lo], {V(YROW)}", f"v_mov_b32 {V(VT)}, %[row8_hi]", "s_nop 0",
                             f"v_addc_co_u32 {V(YROW + 1)}, vcc, {V(VT)}, {V(YROW + 1)}, vcc"]
         if k < 2:
             out.append("s_branch LEFT_%=")
