@@ -229,6 +229,7 @@ def emit_mask(E, s_base, valid_sreg):
         const = 8 * (i >> 2) + (i & 3)
         E.e(f"s_sub_i32 s{S_T}, s{valid_sreg}, {const}")
         E.e(f"v_cmp_lt_i32 vcc, {V(KIDX)}, s{S_T}")                 # key row < valid
+        E.e("s_nop 1")                                              # (vcc is read by a vector instruction)
         for nt in range(2):
             r = V(s_base + 16 * nt + i)
             E.e(f"v_cndmask_b32 {r}, {V(RT[0])}, {r}, vcc")
@@ -241,7 +242,7 @@ def finite_reference_lines(m, tmp):
     """m = NO_SCORE where it is -inf (the difference to it would be NaN): such keys get weight 0, and the first score above moves
     the reference as any other does.  (A score 126 or more below NO_SCORE, in log2 units, would then count for nothing: at that size
     the bf16 operands alone leave it several units off.)"""
-    return [f"v_mov_b32 {tmp}, {NO_SCORE}", f"v_cmp_gt_f32 vcc, 0xff7fffff, {m}", f"v_cndmask_b32 {m}, {m}, {tmp}, vcc"]
+    return [f"v_cmp_gt_f32 vcc, 0xff7fffff, {m}", f"v_mov_b32 {tmp}, {NO_SCORE}", "s_nop 0", f"v_cndmask_b32 {m}, {m}, {tmp}, vcc"]
 
 
 def emit_first_reference(E, s_base):

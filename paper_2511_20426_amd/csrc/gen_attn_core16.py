@@ -164,6 +164,7 @@ def emit_mask(E, s_base, valid_sreg):
         for i in range(4):
             E.e(f"s_sub_i32 s{S_T}, s{valid_sreg}, {8 * kt + i}")
             E.e(f"v_cmp_lt_i32 vcc, {V(KIDX)}, s{S_T}")             # key row < valid
+            E.e("s_nop 1")                                          # (vcc is read by a vector instruction)
             for qt in range(QT):
                 r = V(s_reg(s_base, kt, qt, i))
                 E.e(f"v_cndmask_b32 {r}, {V(RT[0])}, {r}, vcc")

@@ -17,7 +17,7 @@ def _load(name):
     return mod
 
 
-rows = _load("gen_gemm_rows")
+attn, attn16, gemm, rows = (_load(name) for name in ("gen_attn_core", "gen_attn_core16", "gen_gemm_core", "gen_gemm_rows"))
 TRANS = ("v_exp", "v_log", "v_rcp", "v_rsq", "v_sqrt", "v_sin", "v_cos")
 
 
@@ -93,9 +93,10 @@ def too_close(text):
     return found
 
 
-@pytest.mark.parametrize("program", [lambda mt=mt: rows.generate(mt) for mt in (8, 6, 4)], ids=["rows256", "rows192", "rows128"])
-def test_generated_programs_keep_the_wait_states(program):
-    assert too_close(program()) == []
+@pytest.mark.parametrize("gen,kw", [(attn, {}), (attn, {"tails": True}), (attn16, {}), (attn16, {"tails": True}), (gemm, {}), (gemm, {"mt": 4}),
+                                    (rows, {}), (rows, {"mt": 6}), (rows, {"mt": 4})])
+def test_generated_programs_keep_the_wait_states(gen, kw):
+    assert too_close(gen.generate(**kw)) == []
 
 
 def test_the_follower_sees_what_stands_too_close():
