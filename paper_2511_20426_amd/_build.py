@@ -28,17 +28,41 @@ def hipcc() -> str:
     return exe
 
 
-def calls_command() -> list:
+def calls_command(out: str) -> list:
     """The extension holds no device code: g++ against the headers of torch and of HIP's host side."""
     torch = importlib.util.find_spec("torch").submodule_search_locations[0]
     return [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
             "-I", os.path.join(ROOT, "include"), "-I", os.path.join(torch, "include"),
             "-I", os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), "-I", sysconfig.get_paths()["include"],
             os.path.join(CSRC, "py_calls.cpp"), "-L", os.path.join(torch, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
-            "-o", CALLS]
+            "-o", out]
 
 
-def build(verbose: bool = False, extra=(), bdir: str | None = None) -> str:
+def _finish(src: str, p: subprocess.Popen, verbose: bool = False) -> None:
+    out, _ = p.communicate()
+    if p.returncode != 0:
+        raise RuntimeError(f"the compiler failed on {src}:\n{out}")
+    if verbose and out.strip():
+        print(out)
+
+
+def build_calls(beside=None) -> None:
+    """The Python extension, while `beside` runs if it is given; the file takes its place when it is whole."""
+    part = f"{CALLS}.{os.getpid()}.part"
+    p = subprocess.Popen(calls_command(part), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    try:
+        if beside:
+            beside()
+        _finish("py_calls.cpp", p)
+        os.replace(part, CALLS)
+    finally:
+        if p.returncode is None:
+            p.communicate()
+        if os.path.exists(part):
+            os.remove(part)
+
+
+def build_library(verbose: bool = False, extra=(), bdir: str | None = None) -> None:
     objs = []
     bdir = bdir or os.path.join(PKG, "_build")
     os.makedirs(bdir, exist_ok=True)
@@ -56,17 +80,16 @@ def build(verbose: bool = False, extra=(), bdir: str | None = None) -> str:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
-    procs.append(("py_calls.cpp", subprocess.Popen(calls_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for src, p in procs:
-        out, _ = p.communicate()
-        if p.returncode != 0:
-            raise RuntimeError(f"the compiler failed on {src}:\n{out}")
-        if verbose and out.strip():
-            print(out)
+        _finish(src, p, verbose)
     cmd = [hipcc(), "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB] + objs
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stdout)
+
+
+def build(verbose: bool = False, extra=(), bdir: str | None = None) -> str:
+    build_calls(beside=lambda: build_library(verbose, extra, bdir))
     return LIB
 
 

@@ -65,17 +65,20 @@ class CascadeAttnError(RuntimeError):
         self.code = code
 
 
+def _build(what: str) -> None:
+    """build_library or build_calls of _build.py, for a fresh checkout."""
+    import importlib.util
+    spec = importlib.util.spec_from_file_location("_cascade_attn_build", os.path.join(_PKG, "_build.py"))
+    builder = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(builder)
+    getattr(builder, what)()
+
+
 def _load() -> C.CDLL:
-    calls = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_calls.so")
-    if not os.path.exists(calls) or not os.path.exists(LIB_PATH) and "CASCADE_ATTN_LIB" not in os.environ:
+    if not os.path.exists(LIB_PATH) and "CASCADE_ATTN_LIB" not in os.environ:
         # nothing built yet (a fresh checkout): build once, in-tree; there is no other path
-        import importlib.util
-        spec = importlib.util.spec_from_file_location(
-            "_cascade_attn_build", os.path.join(os.path.dirname(os.path.abspath(__file__)), "_build.py"))
-        builder = importlib.util.module_from_spec(spec)
         try:
-            spec.loader.exec_module(builder)
-            builder.build()
+            _build("build_library")
         except Exception as e:  # no hipcc, compile error, ...
             raise ImportError(f"{LIB_PATH} is missing and could not be built: {e}") from e
     if not os.path.exists(LIB_PATH):
@@ -155,7 +158,10 @@ lib = _load()
 
 
 def _load_calls():
-    """The extension that takes the calls of runner.py's methods, on the entry points of the library loaded here."""
+    """The extension that takes the calls of runner.py's methods, on the entry points of the library loaded here.  It is built by
+    itself where it is missing: the library, which may be a file of the user's, stays as it is."""
+    if not os.path.exists(os.path.join(_PKG, "_calls.so")):
+        _build("build_calls")
     from . import _calls
     _calls.bind(*(C.cast(f, C.c_void_p).value for f in (
         lib.kv_cache_append_batch, lib.rope3d_apply_strided, lib.cascade_attn_forward, lib.cascade_attn_forward_share,

@@ -316,6 +316,38 @@ def test_missing_library_is_an_import_error_not_a_fallback():
     assert r.returncode == 7 and "is missing" in r.stdout, (r.returncode, r.stdout, r.stderr)
 
 
+def _bare_copy(tmp_path):
+    """The package as a checkout has it: sources, nothing built."""
+    import shutil
+    src = os.path.join(ROOT, "paper_2511_20426_amd")
+    shutil.copytree(src, tmp_path / "paper_2511_20426_amd", ignore=shutil.ignore_patterns("*.so", "_build", "__pycache__"))
+    shutil.copytree(os.path.join(ROOT, "include"), tmp_path / "include")
+
+
+def _import_in(path, env, code=""):
+    import subprocess
+    import sys
+    return subprocess.run([sys.executable, "-c", "import paper_2511_20426_amd.binding as B\n" + code], cwd=path, env=dict(os.environ, **env), capture_output=True,
+                          text=True, timeout=300)
+
+
+def test_import_leaves_a_library_of_the_users_alone(tmp_path):
+    """CASCADE_ATTN_LIB names the library to load.  A missing extension is no reason to build that."""
+    _bare_copy(tmp_path)
+    theirs = tmp_path / "theirs.so"
+    theirs.write_bytes(b"not ours\n")
+    r = _import_in(tmp_path, {"CASCADE_ATTN_LIB": str(theirs)})
+    assert r.returncode != 0 and "theirs.so" in r.stderr, r.stderr              # no library at all, which the loader says
+    assert theirs.read_bytes() == b"not ours\n"
+    # with one that can be loaded: the extension is built beside it, the library is not touched
+    import shutil
+    shutil.copyfile(os.path.join(ROOT, "paper_2511_20426_amd", "libcascade_attn.so"), theirs)
+    before = (theirs.stat().st_mtime_ns, theirs.stat().st_ino)
+    r = _import_in(tmp_path, {"CASCADE_ATTN_LIB": str(theirs)}, "assert B.LIB_PATH.endswith('theirs.so') and B.calls.linear(1, 2, 3) is None\n")
+    assert r.returncode == 0, r.stderr
+    assert (theirs.stat().st_mtime_ns, theirs.stat().st_ino) == before and not list(tmp_path.rglob("libcascade_attn.so"))
+
+
 def test_append_batch_is_the_sequence_of_appends_or_nothing():
     """kv_cache_append_batch on a metadata-only context: same slots and tags as one call per
     entry in order; any failing entry leaves everything as it was."""
