@@ -1,7 +1,6 @@
 """Builds libcascade_attn.so (gfx950) in-tree with hipcc, and the Python extension beside it.  Used by __graft_entry__.build()."""
 from __future__ import annotations
 
-import importlib.util
 import os
 import shutil
 import subprocess
@@ -15,8 +14,6 @@ LIB = os.environ.get("CASCADE_ATTN_LIB") or os.path.join(PKG, "libcascade_attn.s
 
 SOURCES = ["ca_meta.cpp", "ca_api.cpp", "ca_sched.cpp", "rope_cache.hip", "attn_f32.hip", "attn_bf16.hip", "mfma_peak.hip", "gemm_bf16.hip", "gemm_rows.hip"]
 
-CALLS = os.path.join(PKG, "_calls.so")           # Python extension: csrc/py_calls.cpp
-
 # packed fp32 instructions are kept off for all device code
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
@@ -28,9 +25,16 @@ def hipcc() -> str:
     return exe
 
 
+def calls_path() -> str:
+    """The Python extension (csrc/py_calls.cpp) fits one Python and one torch, which its name says."""
+    import torch
+    return os.path.join(PKG, f"_calls.{sys.implementation.cache_tag}.torch-{torch.__version__}.so")
+
+
 def calls_command(out: str) -> list:
     """The extension holds no device code: g++ against the headers of torch and of HIP's host side."""
-    torch = importlib.util.find_spec("torch").submodule_search_locations[0]
+    import torch
+    torch = torch.__path__[0]
     return [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
             "-I", os.path.join(ROOT, "include"), "-I", os.path.join(torch, "include"),
             "-I", os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), "-I", sysconfig.get_paths()["include"],
@@ -48,13 +52,14 @@ def _finish(src: str, p: subprocess.Popen, verbose: bool = False) -> None:
 
 def build_calls(beside=None) -> None:
     """The Python extension, while `beside` runs if it is given; the file takes its place when it is whole."""
-    part = f"{CALLS}.{os.getpid()}.part"
+    path = calls_path()
+    part = f"{path}.{os.getpid()}.part"
     p = subprocess.Popen(calls_command(part), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     try:
         if beside:
             beside()
         _finish("py_calls.cpp", p)
-        os.replace(part, CALLS)
+        os.replace(part, path)
     finally:
         if p.returncode is None:
             p.communicate()

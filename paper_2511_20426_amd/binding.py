@@ -157,16 +157,37 @@ def _load() -> C.CDLL:
 lib = _load()
 
 
+class _NoCalls:
+    """In place of the extension: takes no call, so that all of them go through the Python code."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 def _load_calls():
     """The extension that takes the calls of runner.py's methods, on the entry points of the library loaded here.  It is built by
-    itself where it is missing: the library, which may be a file of the user's, stays as it is."""
-    if not os.path.exists(os.path.join(_PKG, "_calls.so")):
-        _build("build_calls")
-    from . import _calls
-    _calls.bind(*(C.cast(f, C.c_void_p).value for f in (
-        lib.kv_cache_append_batch, lib.rope3d_apply_strided, lib.cascade_attn_forward, lib.cascade_attn_forward_share,
-        lib.cascade_attn_forward_rope, lib.layer_qkv_publish, lib.layer_linear_bf16)))
-    return _calls
+    itself where there is none for this Python and this torch: the library, which may be a file of the user's, stays as it is.
+    What it does the Python code does too, in more host time, so that a machine that cannot build it (no compiler, no headers of
+    torch) goes without."""
+    import importlib.util
+    import sys
+    import warnings
+
+    import torch
+    path = os.path.join(_PKG, f"_calls.{sys.implementation.cache_tag}.torch-{torch.__version__}.so")
+    try:
+        if not os.path.exists(path):
+            _build("build_calls")
+        spec = importlib.util.spec_from_file_location(f"{__package__}._calls", path)
+        ext = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(ext)
+        ext.bind(*(C.cast(f, C.c_void_p).value for f in (
+            lib.kv_cache_append_batch, lib.rope3d_apply_strided, lib.cascade_attn_forward, lib.cascade_attn_forward_share,
+            lib.cascade_attn_forward_rope, lib.layer_qkv_publish, lib.layer_linear_bf16)))
+        return ext
+    except Exception as e:
+        warnings.warn(f"{path} cannot be used, calls take more host time without it: {e}", RuntimeWarning)
+        return _NoCalls()
 
 
 calls = _load_calls()

@@ -348,6 +348,23 @@ def test_import_leaves_a_library_of_the_users_alone(tmp_path):
     assert (theirs.stat().st_mtime_ns, theirs.stat().st_ino) == before and not list(tmp_path.rglob("libcascade_attn.so"))
 
 
+def test_without_a_usable_extension_the_python_code_takes_the_calls(tmp_path):
+    """No compiler, and an extension that is there but for another Python, or is none: the package works, and says so."""
+    import sys
+
+    import torch
+    _bare_copy(tmp_path)
+    env = {"CASCADE_ATTN_LIB": os.path.join(ROOT, "paper_2511_20426_amd", "libcascade_attn.so"), "PATH": ""}
+    code = ("assert B.calls.linear(1, 2, 3) is None and B.calls.rope() is None\n"
+            "assert B.Context(B.make_config(heads=2, head_dim=64, frames_per_block=1, grid_h=2, grid_w=3, rope_dims=(24, 20, 20), rope_theta=1e4,"
+            " sink_blocks=0, window_blocks=2, max_inflight=2, page_tokens=16, dtype='f32'), None, 0).kv_cache_append(0, 0, 0, None, None, 0, 0, None) == 0\n")
+    for name, there in (("_calls.so", b"another"), ("_calls.cpython-27.torch-1.0.so", b"another"),
+                        (f"_calls.{sys.implementation.cache_tag}.torch-{torch.__version__}.so", b"none")):
+        (tmp_path / "paper_2511_20426_amd" / name).write_bytes(there)
+        r = _import_in(tmp_path, env, code)
+        assert r.returncode == 0 and "RuntimeWarning" in r.stderr, r.stderr
+
+
 def test_append_batch_is_the_sequence_of_appends_or_nothing():
     """kv_cache_append_batch on a metadata-only context: same slots and tags as one call per
     entry in order; any failing entry leaves everything as it was."""
