@@ -91,6 +91,9 @@ bool fits(const Pool& p, const at::Tensor* t) {
   return t && t->is_cuda() && t->scalar_type() == p.dtype() && t->dim() == 3 && t->stride(2) == 1 && t->size(1) == p.heads && t->size(2) == p.head_dim;
 }
 
+// memory of the device that `like` is on (pinned host memory, which kernels reach too, is left to the Python code)
+bool beside(const at::Tensor& t, const at::Tensor& like) { return t.is_cuda() && t.device() == like.device(); }
+
 template <typename F>
 int32_t released(const F& call) {
   int32_t rc;
@@ -149,7 +152,7 @@ PyObject* linear(PyObject* const* a, Py_ssize_t n) {
   const int64_t m = x->size(0), cols = w->size(0), k = x->size(1);
   if (cols != int32_t(cols) || k != int32_t(k)) return not_taken();
   const at::Tensor& y = r.or_empty({m, cols}, *x);
-  if (y.dim() != 2 || y.size(0) != m || y.size(1) != cols || y.stride(1) != 1 || y.scalar_type() != at::kBFloat16) return not_taken();
+  if (y.dim() != 2 || y.size(0) != m || y.size(1) != cols || y.stride(1) != 1 || y.scalar_type() != at::kBFloat16 || !beside(y, *x)) return not_taken();
   void* const stream = c10::hip::getCurrentHIPStream(x->device().index()).stream();
   const void *xp = x->data_ptr(), *wp = w->data_ptr();
   void* const yp = y.data_ptr();
@@ -214,7 +217,7 @@ PyObject* forward(PyObject* const* a, Py_ssize_t n) {
   const at::Tensor* q = plain(a[2]);
   if (!fits(p, q) || !q->is_contiguous() || q->size(0) != (part ? share[1] : blocks) * p.block_tokens) return not_taken();
   const at::Tensor& o = r.or_empty(q->sizes(), *q);
-  if (!o.is_contiguous() || o.sizes() != q->sizes()) return not_taken();
+  if (!o.is_contiguous() || o.sizes() != q->sizes() || !fits(p, &o) || !beside(o, *q)) return not_taken();
   void *const stream = p.stream(), *const op = o.data_ptr();
   const void* const qp = q->data_ptr();
   return r.give(released([&] {
@@ -233,7 +236,7 @@ PyObject* forward_rope(PyObject* const* a, Py_ssize_t n) {
   const at::Tensor* q = plain(a[2]);
   if (blocks < 1 || !fits(p, q) || q->size(0) != blocks * p.block_tokens) return not_taken();
   const at::Tensor& o = r.or_empty(q->sizes(), *q);
-  if (!o.is_contiguous() || o.sizes() != q->sizes()) return not_taken();
+  if (!o.is_contiguous() || o.sizes() != q->sizes() || !fits(p, &o) || !beside(o, *q)) return not_taken();
   void *const stream = p.stream(), *const op = o.data_ptr();
   const void* const qp = q->data_ptr();
   const int64_t tok = q->stride(0), head = q->stride(1);
@@ -252,10 +255,12 @@ PyObject* qkv_publish(PyObject* const* a, Py_ssize_t n) {
   const int64_t rows = blocks * p.block_tokens, width = p.heads * p.head_dim;
   if (blocks < 1 || all<int32_t, whole32>(a[5], ts) != blocks || !x || !w || !x->is_cuda() || x->scalar_type() != at::kBFloat16 || x->dim() != 2 ||
       x->size(0) != rows || x->stride(1) != 1 || x->size(1) != int32_t(x->size(1)) || w->dim() != 2 || w->size(0) != 3 * width ||
-      w->size(1) != x->size(1) || w->stride(1) != 1 || w->scalar_type() != at::kBFloat16)
+      w->size(1) != x->size(1) || w->stride(1) != 1 || w->scalar_type() != at::kBFloat16 || !beside(*w, *x))
     return not_taken();
   const at::Tensor& q = r.or_empty({rows, p.heads, p.head_dim}, *x);
-  if (q.dim() != 3 || !q.is_contiguous() || q.size(0) != rows || q.size(1) != p.heads || q.size(2) != p.head_dim) return not_taken();
+  if (q.dim() != 3 || !q.is_contiguous() || q.size(0) != rows || q.size(1) != p.heads || q.size(2) != p.head_dim || q.scalar_type() != at::kBFloat16 ||
+      !beside(q, *x))
+    return not_taken();
   void *const stream = p.stream(), *const qp = q.data_ptr();
   const void *const xp = x->data_ptr(), *const wp = w->data_ptr();
   const int64_t ldx = x->stride(0), ldw = w->stride(0);

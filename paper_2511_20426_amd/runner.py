@@ -30,6 +30,11 @@ def _current_stream(device: torch.device) -> int:
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
 
 
+def _reachable(t: torch.Tensor, like: torch.Tensor) -> bool:
+    """t's memory is there for a kernel that works on `like`: the same device's, or pinned host memory."""
+    return t.device == like.device or t.is_pinned()
+
+
 class CascadePool:
     """A ca_ctx over a pool tensor allocated with torch on the current device."""
 
@@ -132,7 +137,7 @@ class CascadePool:
         n_q = len(inflight) if share is None else share[1]
         assert q_rot.is_contiguous() and q_rot.shape[0] == n_q * self.block_tokens
         o = torch.empty_like(q_rot) if out is None else out
-        assert o.is_contiguous() and o.shape == q_rot.shape
+        assert o.is_contiguous() and o.shape == q_rot.shape and o.dtype == q_rot.dtype and _reachable(o, q_rot)
         if static_scratch:
             assert share is None and out is not None
             self.ctx.cascade_attn_forward_static(q_rot.data_ptr(), list(inflight), mode, o.data_ptr(), self._stream())
@@ -158,7 +163,7 @@ def _forward_rope(self, q_raw: torch.Tensor, inflight: Sequence[int], mode: int,
     self._check(q_raw)
     assert q_raw.shape[0] == len(inflight) * self.block_tokens
     o = torch.empty(q_raw.shape, dtype=q_raw.dtype, device=q_raw.device) if out is None else out
-    assert o.is_contiguous() and o.shape == q_raw.shape
+    assert o.is_contiguous() and o.shape == q_raw.shape and o.dtype == q_raw.dtype and _reachable(o, q_raw)
     self.ctx.cascade_attn_forward_rope(q_raw.data_ptr(), q_raw.stride(0), q_raw.stride(1), list(inflight), mode,
                                        o.data_ptr(), self._stream())
     return o
@@ -181,9 +186,9 @@ def _qkv_publish(self, x: torch.Tensor, w_qkv: torch.Tensor, block_ids: Sequence
     n = len(block_ids) * self.block_tokens
     width = self.heads * self.head_dim
     assert x.is_cuda and x.dtype == torch.bfloat16 and x.dim() == 2 and x.shape[0] == n and x.stride(1) == 1
-    assert w_qkv.shape == (3 * width, x.shape[1]) and w_qkv.stride(1) == 1 and w_qkv.dtype == torch.bfloat16
+    assert w_qkv.shape == (3 * width, x.shape[1]) and w_qkv.stride(1) == 1 and w_qkv.dtype == torch.bfloat16 and _reachable(w_qkv, x)
     q = torch.empty((n, self.heads, self.head_dim), dtype=torch.bfloat16, device=x.device) if q_out is None else q_out
-    assert q.is_contiguous() and q.shape == (n, self.heads, self.head_dim)
+    assert q.is_contiguous() and q.shape == (n, self.heads, self.head_dim) and q.dtype == torch.bfloat16 and _reachable(q, x)
     self.ctx.layer_qkv_publish(list(block_ids), list(timesteps), epoch, x.data_ptr(), x.stride(0), w_qkv.data_ptr(),
                                w_qkv.stride(0), x.shape[1], q.data_ptr(), self._stream())
     return q
@@ -206,7 +211,7 @@ def linear(x: torch.Tensor, w: torch.Tensor, out: torch.Tensor | None = None) ->
     shape, device = (xs[0], ws[0]), x.device
     y = torch.empty(shape, dtype=_BF16, device=device) if out is None else out
     sy = y.stride()
-    assert y.shape == shape and sy[1] == 1 and y.dtype == _BF16
+    assert y.shape == shape and sy[1] == 1 and y.dtype == _BF16 and _reachable(y, x)
     B.layer_linear_bf16(x.data_ptr(), w.data_ptr(), y.data_ptr(), xs[0], ws[0], xs[1], sx[0], sw[0], sy[0],
                         _current_stream(device))
     return y

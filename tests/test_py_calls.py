@@ -89,6 +89,41 @@ def test_what_was_refused_is_refused():
         p.rope(q, 0)
 
 
+def _outs(like):
+    """Results that a launch must not be given: of another type (a larger and a smaller one), in pageable host memory, of another shape."""
+    return [torch.empty_like(like, dtype=torch.float32), torch.empty_like(like, dtype=torch.uint8), torch.empty_like(like, device="cpu"),
+            torch.empty_like(like[:-1])]
+
+
+@pytest.mark.gpu
+def test_results_of_another_type_or_in_host_memory_are_refused():
+    """... before anything is launched, by the extension (which leaves them to the Python code) and by the Python code."""
+    from paper_2511_20426_amd.runner import linear
+    p = _pool()
+    g = torch.Generator(device="cuda:0").manual_seed(4)
+    rand = lambda *s: torch.randn(s, generator=g, device="cuda:0").to(torch.bfloat16)  # noqa: E731
+    q, x, w, xq, wq = rand(60, 2, 128), rand(33, 256), rand(24, 256), rand(60, 256), rand(768, 256)
+    p.append_batch([0], [0], 0, [q], [q])
+    calls = ((lambda a, out: p.forward(a, [0], 0, out=out), q), (lambda a, out: p.forward(a, [0], 0, out=out, share=(0, 1)), q),
+             (lambda a, out: p.forward(a, [0], 0, out=out, static_scratch=True), q), (lambda a, out: p.forward_rope(a, [0], 0, out=out), q),
+             (lambda a, out: p.qkv_publish(a, wq, [0], [0], 0, q_out=out), xq), (lambda a, out: linear(a, w, out=out), x))
+    for call, a in calls:
+        good = torch.empty((33, 24), dtype=torch.bfloat16, device="cuda:0") if a is x else torch.empty_like(q)
+        for as_given in (a, a.as_subclass(_Sub)):
+            for out in _outs(good):
+                with pytest.raises(AssertionError):
+                    call(as_given, out)
+            assert call(as_given, good) is good
+        # memory that kernels reach, on the host: taken as before
+        pinned = torch.empty(good.shape, dtype=good.dtype, pin_memory=True)
+        assert call(a, pinned) is pinned
+        torch.cuda.synchronize()
+        assert torch.equal(pinned.view(torch.int16), good.cpu().view(torch.int16))
+    for bad in (wq.cpu(), wq.float()):
+        with pytest.raises(AssertionError):
+            p.qkv_publish(xq, bad, [0], [0], 0)
+
+
 @pytest.mark.gpu
 def test_streams_and_threads():
     """A call goes to the calling thread's stream of the moment."""
