@@ -7,6 +7,7 @@
 // A function here takes a call only if everything is as it should be (plain tensors, exact integers, lists or tuples, shapes and
 // strides that fit); otherwise it returns None and has done nothing, and the Python code does what it does: checks one by one and
 // raises.  It returns the result, or the library's code where that is not CA_OK.
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <ATen/ops/empty.h>
@@ -131,14 +132,17 @@ struct Result {
   }
 };
 
-// Anything that throws (a tensor whose memory cannot be looked at, no memory for a result) is left to the Python code.
+// Anything that throws (a tensor whose memory cannot be looked at, no memory for a result) is left to the Python code, but for
+// what Python code raised in here (a dispatch mode around the allocation), which is the caller's to see.
 template <PyObject* (*call)(PyObject* const*, Py_ssize_t)>
 PyObject* guarded(PyObject*, PyObject* const* a, Py_ssize_t n) {
   try {
     return call(a, n);
+  } catch (python_error& e) {
+    e.restore();
   } catch (...) {
-    return not_taken();
   }
+  return PyErr_Occurred() ? nullptr : not_taken();
 }
 
 // linear(x, w, out)

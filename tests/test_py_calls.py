@@ -157,3 +157,20 @@ def test_streams_and_threads():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(y, want)
+
+
+@pytest.mark.gpu
+def test_what_an_allocation_raises_comes_through():
+    """An error that a dispatch mode raises inside the extension's torch.empty is the caller's to see."""
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    from paper_2511_20426_amd.runner import linear
+
+    class Refuses(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            raise ValueError("no memory for you")
+
+    x, w = torch.zeros(4, 128, dtype=torch.bfloat16, device="cuda:0"), torch.zeros(8, 128, dtype=torch.bfloat16, device="cuda:0")
+    with Refuses(), pytest.raises(ValueError, match="no memory for you"):
+        linear(x, w)
+    assert linear(x, w).shape == (4, 8)
