@@ -62,7 +62,7 @@ struct GemmArgs {
   // one ragged): one block spanning all of M for the plain product, one per in-flight block when
   // publishing.
   int32_t block_rows, tiles_per_block;
-  PublishArgs pub;                                // read by gemm_bf16_kernel<true> only
+  PublishArgs pub;                                // publishing only
 };
 
 constexpr int kTrigBytes = 12288;                 // per 128-token page; two pages per workgroup behind the staging area
@@ -513,39 +513,32 @@ int32_t enqueue_gemm_tiles(GemmArgs& a, void* stream) {
 // instead of rows, which the largest tiles pay for most: of 23400 x 768 x 256, 34.0 us with 256 x 256, 33.5 with 128
 // x 256, 26.6 with 256 x 128, 29.4 with 128 x 128; 23400 x 3072 x 1024 163 / 176 / 182 / 206; 7920 x 2304 x 768 52 /
 // 45 / 49 / 46.
-enum GemmTile { kTile256, kTile192, kTile256x128, kTile128x256, kTile128, kTile64, kTile64Wide };
+enum GemmTile { kTile256, kTile256x128, kTile128x256, kTile128, kTile64, kTile64Wide };
 
-// compiled, compiled_cost: the cheapest of the tiles of compiled code that do not publish, if asked for
-int32_t pick_gemm_tile(const GemmArgs& a, bool publish, GemmTile* tile, GemmTile* compiled, int64_t* compiled_cost) {
-  // fixed_publish: 0 where the tile does not publish
+// the cheapest tile and, in nanoseconds, what it costs
+GemmTile pick_gemm_tile(const GemmArgs& a, bool publish, int n_cu, int64_t* cost) {
+  // fixed, fixed_publish: 0 where a plain product, a publishing one does not take the tile
   static constexpr struct { int bm, bn, per_cu, threads, stage, full, fixed, fixed_publish; } kModel[] = {
-      {256, 256, 1, 256, 1000, 1190, 11000, 12500}, {192, 256, 1, 256, 820, 970, 8250, 0},
-      {256, 128, 1, 512, 850, 870, 5800, 6250},    {128, 256, 1, 256, 580, 660, 7000, 9250},
-      {128, 128, 1, 512, 430, 430, 5000, 4500},    {64, 64, 2, 256, 310, 310, 4000, 0},
-      {64, 64, 1, 512, 165, 165, 4000, 0}};
-  int n_cu = 0;
-  if (const int32_t rc = device_cu_count(&n_cu); rc != CA_OK) return rc;
+      {256, 256, 1, 256, 1000, 1190, 0, 12500}, {256, 128, 1, 512, 850, 870, 5800, 6250}, {128, 256, 1, 256, 580, 660, 0, 9250},
+      {128, 128, 1, 512, 430, 430, 5000, 4500}, {64, 64, 2, 256, 310, 310, 4000, 0},      {64, 64, 1, 512, 165, 165, 4000, 0}};
   const int64_t blocks = a.M / a.block_rows, stages = a.K / 64;
-  int64_t best = 0;
+  GemmTile tile = kTile128;
+  *cost = INT64_MAX;
   for (int i = 0; i < int(sizeof(kModel) / sizeof(kModel[0])); ++i) {
     const auto& m = kModel[i];
-    if (publish && m.fixed_publish == 0) continue;
+    const int64_t fixed = publish ? m.fixed_publish : m.fixed;
+    if (fixed == 0) continue;
     const int64_t tiles = blocks * ((a.block_rows + m.bm - 1) / m.bm) * ((a.N + m.bn - 1) / m.bn);
-    if (i > 0 && tiles * m.threads >= (int64_t(1) << 31)) continue;      // a launch may have 2^32 threads
-    const int64_t slots = int64_t(n_cu) * m.per_cu;
-    const int64_t left = tiles % slots, fixed = publish ? m.fixed_publish : m.fixed;        // left: tiles of a last round
+    if (i != kTile256 && tiles * m.threads >= (int64_t(1) << 31)) continue;      // a launch may have 2^32 threads
+    const int64_t slots = int64_t(n_cu) * m.per_cu, left = tiles % slots;        // left: tiles of a last round
     const int64_t stage = m.stage + (2 * left > slots ? (m.full - m.stage) * (2 * left - slots) / slots : 0);
-    const int64_t cost = tiles / slots * (stages * m.full + fixed) + (left > 0 ? stages * stage + fixed : 0);
-    if (i == 0 || cost < best) {
-      best = cost;
-      *tile = GemmTile(i);
-    }
-    if (compiled && i != kTile256 && i != kTile192 && i != kTile128x256 && cost < *compiled_cost) {
-      *compiled = GemmTile(i);
-      *compiled_cost = cost;
+    const int64_t of_tile = tiles / slots * (stages * m.full + fixed) + (left > 0 ? stages * stage + fixed : 0);
+    if (of_tile < *cost) {
+      *cost = of_tile;
+      tile = GemmTile(i);
     }
   }
-  return CA_OK;
+  return tile;
 }
 
 // Tile height of gemm_rows.hip that a plain product takes, or 0 where one of the tiles of compiled code is cheaper.  A
@@ -574,8 +567,10 @@ int rows_tile(const GemmArgs& a, int n_cu, int64_t compiled, GemmTile by) {
 }
 
 int32_t dispatch_gemm_publish(GemmArgs& a, void* stream) {
-  GemmTile tile = kTile256;
-  if (const int32_t rc = pick_gemm_tile(a, true, &tile, nullptr, nullptr); rc != CA_OK) return rc;
+  int64_t cost = 0;
+  int n_cu = 0;
+  if (const int32_t rc = device_cu_count(&n_cu); rc != CA_OK) return rc;
+  const GemmTile tile = pick_gemm_tile(a, true, n_cu, &cost);
   const KernelLds kernels[] = {{reinterpret_cast<const void*>(gemm_bf16_kernel<8>), kGemmLds},
                                {reinterpret_cast<const void*>(gemm_bf16_kernel<4>), kGemmLds},
                                {reinterpret_cast<const void*>(gemm_tile_kernel<Tile256x128, true>), Tile256x128::kLds},
@@ -588,11 +583,10 @@ int32_t dispatch_gemm_publish(GemmArgs& a, void* stream) {
 }
 
 int32_t dispatch_gemm_plain(GemmArgs& a, void* stream) {
-  GemmTile tile = kTile256, compiled = kTile128;
-  int64_t cost = INT64_MAX;
+  int64_t cost = 0;
   int n_cu = 0;
-  if (const int32_t rc = pick_gemm_tile(a, false, &tile, &compiled, &cost); rc != CA_OK) return rc;
   if (const int32_t rc = device_cu_count(&n_cu); rc != CA_OK) return rc;
+  const GemmTile compiled = pick_gemm_tile(a, false, n_cu, &cost);
   const KernelLds kernels[] = {{reinterpret_cast<const void*>(gemm_tile_kernel<Tile256x128, false>), Tile256x128::kLds},
                                {reinterpret_cast<const void*>(gemm_tile_kernel<Tile128, false>), Tile128::kLds},
                                {reinterpret_cast<const void*>(gemm_tile_kernel<Tile64, false>), Tile64::kLds},

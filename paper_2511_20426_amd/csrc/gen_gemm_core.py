@@ -1,9 +1,9 @@
 #!/usr/bin/env python3
-"""Emits gemm_core_gfx950.inc: the main loop of the bf16 GEMM  Y[M,N] = X[M,K] . W[N,K]^T  used
-for the projections either side of the attention (fp32 accumulation in AGPRs).
+"""Emits gemm_core_gfx950.inc: the main loop of the bf16 GEMM  Y[M,N] = X[M,K] . W[N,K]^T  of the
+projection that publishes K/V (fp32 accumulation in AGPRs; gen_gemm_rows.py has the plain products').
 
-Three loops, for tiles of 256, 192 and 128 rows of X by 256 rows of W (MT = 8, 6, 4 sub-tiles of 16 rows to a wave); what follows
-describes the first, in the others a wave's part of X, and with it the products of a stage, is MT / 8 of that.
+Two loops, for tiles of 256 and 128 rows of X by 256 rows of W (MT = 8, 4 sub-tiles of 16 rows to a wave); what follows
+describes the first, in the other a wave's part of X, and with it the products of a stage, is MT / 8 of that.
 
 Workgroup = 4 waves = a 256 x 256 tile of Y; wave (wm, wn) owns 128 x 128 of it as 8 x 8 MFMA
 tiles of 16 x 16 (v_mfma_f32_16x16x32_bf16, A = rows of W, B = rows of X, so that a lane ends up

@@ -87,29 +87,49 @@ def attention_element_bound(o, p, q_rot, k_rot, v, logit_roundings: int = 3):
     return 1.01 * 2.0 ** -8 * np.abs(o) + N_SIGMA * np.sqrt(np.maximum(var_o, 0.0)) + 1e-30
 
 
-# --------------------------------------------------------------------------- tile of a linear map
+# --------------------------------------------------------------------------- kernel of a linear map
 
-def gemm_tile(M: int, N: int, K: int, block_rows: int | None = None, publish: bool = False) -> str:
-    """The tile that pick_gemm_tile takes for a product on 256 CUs, from the cost model as gemm_bf16.hip holds it."""
+def _gemm_models():
+    """The cost models as gemm_bf16.hip holds them: names and rows of the tiles, rows of gemm_rows.hip's heights."""
     source = open(os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2511_20426_amd", "csrc",
                                "gemm_bf16.hip")).read()
-    table = re.search(r"kModel\[\] = \{(.*?)\};", source, re.S).group(1)
-    names = re.search(r"enum GemmTile \{(.*?)\};", source).group(1).split(",")
-    rows = [[int(x) for x in r.split(",")] for r in re.findall(r"\{([\d, ]+)\}", table)]
-    assert len(rows) == len(names)
-    block_rows, best = block_rows or M, None
-    for name, (bm, bn, per_cu, _threads, stage, full, fixed, fixed_publish) in zip(names, rows):
-        if publish and fixed_publish == 0:
-            continue
-        tiles, slots = M // block_rows * -(-block_rows // bm) * -(-N // bn), 256 * per_cu
-        whole, left = divmod(tiles, slots)
+    tables = [[[int(x) for x in r.split(",")] for r in re.findall(r"\{([\d, ]+)\}", re.search(name + r"\[\] = \{(.*?)\};", source, re.S).group(1))]
+              for name in ("kModel", "kRows")]
+    names = [t.strip() for t in re.search(r"enum GemmTile \{(.*?)\};", source).group(1).split(",")]
+    assert len(tables[0]) == len(names)
+    return names, *tables
+
+
+def _gemm_tile(M, N, K, block_rows, publish):
+    best = None
+    for name, (bm, bn, per_cu, _threads, stage, full, fixed, fixed_publish) in zip(*_gemm_models()[:2]):
         fixed = fixed_publish if publish else fixed
-        if 2 * left > slots:
-            stage += (full - stage) * (2 * left - slots) // slots
+        if fixed == 0:
+            continue
+        whole, left = divmod(M // block_rows * -(-block_rows // bm) * -(-N // bn), 256 * per_cu)
+        stage += (full - stage) * max(0, 2 * left - 256 * per_cu) // (256 * per_cu)
         cost = whole * (K // 64 * full + fixed) + (K // 64 * stage + fixed if left else 0)
         if best is None or cost < best[0]:
-            best = (cost, name.strip())
-    return best[1]
+            best = (cost, name)
+    return best
+
+
+def publish_tile(M: int, N: int, K: int, block_rows: int) -> str:
+    """The tile that dispatch_gemm_publish takes on 256 CUs for blocks of block_rows rows."""
+    return _gemm_tile(M, N, K, block_rows, True)[1]
+
+
+def linear_kernel(M: int, N: int, K: int):
+    """What dispatch_gemm_plain takes on 256 CUs: a height of gemm_rows.hip's or the name of a tile."""
+    cost, kernel = _gemm_tile(M, N, K, M, False)
+    limit = cost - (cost // 14 if kernel == "kTile256x128" else 0)
+    for height, start, stage, full, tile in _gemm_models()[2]:
+        whole, left = divmod(-(-M // height) * -(-N // 256), 256)
+        stage += (full - stage) * max(0, 2 * left - 256) // 256
+        cost = start + whole * (K // 64 * full + tile) + (K // 64 * stage + tile if left else 0)
+        if cost < limit:
+            limit, kernel = cost, height
+    return kernel
 
 
 # --------------------------------------------------------------------------- oracle side

@@ -295,30 +295,6 @@ def test_rows_loop_over_tiles(mt, shape, tiles, pad, form):
 
 # --------------------------------------------------------------------------- which kernel, and what it computes
 
-def kernel_of(M, N, K):
-    """What dispatch_gemm_plain takes on 256 CUs, from the two cost models as gemm_bf16.hip holds them: a height of
-    gemm_rows.hip or the name of a compiled tile."""
-    src = open(os.path.join(CSRC, "gemm_bf16.hip")).read()
-    table = lambda name: [[int(x) for x in r.split(",")] for r in re.findall(r"\{([\d, ]+)\}", re.search(name + r"\[\] = \{(.*?)\};", src, re.S).group(1))]  # noqa: E731
-    names = [t.strip() for t in re.search(r"enum GemmTile \{(.*?)\};", src).group(1).split(",")]
-    stages, best = K // 64, None
-    for name, (bm, bn, per_cu, _threads, stage, full, fixed, _publish) in zip(names, table("kModel")):
-        if name in ("kTile256", "kTile192", "kTile128x256"):
-            continue
-        whole, left = divmod(-(-M // bm) * -(-N // bn), 256 * per_cu)
-        stage += (full - stage) * max(0, 2 * left - 256 * per_cu) // (256 * per_cu)
-        cost = whole * (stages * full + fixed) + (stages * stage + fixed if left else 0)
-        best = min(best or (cost, name), (cost, name))
-    limit, kernel = best[0] - (best[0] // 14 if best[1] == "kTile256x128" else 0), best[1]
-    for height, start, stage, full, tile in table("kRows"):
-        whole, left = divmod(-(-M // height) * -(-N // 256), 256)
-        stage += (full - stage) * max(0, 2 * left - 256) // 256
-        cost = start + whole * (stages * full + tile) + (stages * stage + tile if left else 0)
-        if cost < limit:
-            limit, kernel = cost, height
-    return kernel
-
-
 # kernel, rows, columns, k, columns of Y's rows: one to three rounds, last row tiles of one row, last column tiles of eight columns, the
 # shortest walk; rows of Y that are whole lines (a multiple of 64 columns) and rows that share them
 CASES = [(256, 769, 13064, 128, 13064), (256, 769, 13064, 128, 13120), (256, 4097, 3592, 768, 3648), (256, 6145, 6920, 128, 6920), (256, 6145, 6920, 128, 6976),
@@ -328,7 +304,13 @@ CASES = [(256, 769, 13064, 128, 13064), (256, 769, 13064, 128, 13120), (256, 409
 
 
 def test_every_kernel_has_a_case():
-    assert [kernel_of(*c[1:4]) for c in CASES] == [c[0] for c in CASES]
+    """... which is the one that the dispatch takes for it (in the names of the GPU tests' products too)."""
+    from tests import test_gpu_edges as E
+    assert [Hn.linear_kernel(*c[1:4]) for c in CASES] == [c[0] for c in CASES]
+    assert [Hn.linear_kernel(*c[1:]) for c in E.LINEAR_TILES] == [c[0] for c in E.LINEAR_TILES]
+    names, model, heights = Hn._gemm_models()
+    kernels = {h[0] for h in heights} | {n for n, m in zip(names, model) if m[6]}
+    assert {c[0] for c in CASES} == {c[0] for c in E.LINEAR_TILES} == kernels == {256, 192, 128, "kTile256x128", "kTile128", "kTile64", "kTile64Wide"}
 
 
 @pytest.mark.gpu

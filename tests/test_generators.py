@@ -657,7 +657,7 @@ def test_attention_walks_every_step_of_its_pages(core, tails):
                 assert idle.traffic == w.traffic and not idle.k_tiles and not idle.v_steps
 
 
-@pytest.mark.parametrize("mt", [8, 6, 4])
+@pytest.mark.parametrize("mt", [8, 4])
 @pytest.mark.parametrize("n_stages", [2, 4, 6, 14])
 def test_gemm_loops_multiply_every_stage(mt, n_stages):
     """The whole program of a tile, followed on the CPU: every product takes the fragments of its stage and k-step, read from a ring slot whose

@@ -216,18 +216,18 @@ def test_publish_tall_tiles(heads, gh, gw, k_in):
     test_publish_tiles(heads, 1, gh, gw, (1, 2, 3, 4, 5), k_in)
 
 
-# Every tile by name (the cost model may send the products above elsewhere): last row and column tiles of one row and
-# eight columns, the shortest walk and a longer one; 256 x 256 also with a short last round of 6 and of 18 tiles
-# behind six whole ones.
-LINEAR_TILES = [("kTile256", 769, 13064, 128), ("kTile256", 4097, 3592, 768), ("kTile256", 65537, 1288, 512), ("kTile256", 66049, 1288, 512),
-                ("kTile192", 1537, 4872, 128), ("kTile192", 2881, 2824, 384), ("kTile128x256", 513, 11016, 128),
-                ("kTile256x128", 1025, 3720, 128), ("kTile256x128", 4680, 1544, 384), ("kTile128", 2050, 1160, 128),
+# Every kernel by name (the cost models may send the products above elsewhere), assembly loops by their rows: last row and column
+# tiles of one row and eight columns, the shortest walk and a longer one; 256 rows also with a short last round of 6 and of 18
+# tiles behind six whole ones.
+LINEAR_TILES = [(256, 769, 13064, 128), (256, 4097, 3592, 768), (256, 65537, 1288, 512), (256, 66049, 1288, 512),
+                (192, 1537, 4872, 128), (192, 2881, 2824, 384), (128, 513, 11016, 128), (128, 1025, 3720, 128),
+                ("kTile256x128", 16385, 264, 128), ("kTile256x128", 4680, 1544, 384), ("kTile128", 2050, 1160, 128),
                 ("kTile64", 1100, 1400, 256), ("kTile64Wide", 129, 200, 768)]
 
 
-@pytest.mark.parametrize("tile,M,N,K", LINEAR_TILES)
-def test_linear_tile_by_name(tile, M, N, K):
-    assert Hn.gemm_tile(M, N, K) == tile
+@pytest.mark.parametrize("kernel,M,N,K", LINEAR_TILES)
+def test_linear_tile_by_name(kernel, M, N, K):
+    assert Hn.linear_kernel(M, N, K) == kernel
     test_linear_tiles(M, N, K)
 
 
@@ -239,7 +239,7 @@ PUBLISH_TILES = [("kTile256", 18, 10, 13, 5, 128), ("kTile256", 8, 57, 27, 5, 12
 
 @pytest.mark.parametrize("tile,heads,gh,gw,blocks,k_in", PUBLISH_TILES)
 def test_publish_tile_by_name(tile, heads, gh, gw, blocks, k_in):
-    assert Hn.gemm_tile(blocks * gh * gw, 3 * heads * 128, k_in, gh * gw, publish=True) == tile
+    assert Hn.publish_tile(blocks * gh * gw, 3 * heads * 128, k_in, gh * gw) == tile
     test_publish_tiles(heads, 1, gh, gw, tuple(range(1, 1 + blocks)), k_in)
 
 

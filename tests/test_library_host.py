@@ -461,14 +461,11 @@ def test_linear_map_kernels_do_not_spill(tmp_path):
     assert len(kernels) == len(spilled) >= 8 and not any(spilled), list(zip(kernels, spilled))
 
 
-def test_every_tile_of_the_linear_maps_is_tested():
-    """The cost model sends the products of the GPU tests to the tiles they are meant for, and no tile is without one."""
+def test_every_tile_of_the_publishing_projection_is_tested():
+    """The cost model sends the projections of the GPU tests to the tiles they are meant for, and no tile is without one (the plain
+    products': test_gemm_rows.py)."""
     from tests import _harness as Hn
     from tests import test_gpu_edges as E
-    assert [Hn.gemm_tile(*c[1:]) for c in E.LINEAR_TILES] == [c[0] for c in E.LINEAR_TILES]
-    assert [Hn.gemm_tile(n * gh * gw, 3 * h * 128, k, gh * gw, publish=True) for _, h, gh, gw, n, k in E.PUBLISH_TILES] == \
-        [c[0] for c in E.PUBLISH_TILES]
-    source = open(os.path.join(ROOT, "paper_2511_20426_amd", "csrc", "gemm_bf16.hip")).read()
-    tiles = {t.strip() for t in re.search(r"enum GemmTile \{(.*?)\};", source).group(1).split(",")}
-    assert {c[0] for c in E.LINEAR_TILES} == tiles
-    assert {c[0] for c in E.PUBLISH_TILES} == {"kTile256", "kTile256x128", "kTile128x256", "kTile128"}
+    assert [Hn.publish_tile(n * gh * gw, 3 * h * 128, k, gh * gw) for _, h, gh, gw, n, k in E.PUBLISH_TILES] == [c[0] for c in E.PUBLISH_TILES]
+    names, model, _ = Hn._gemm_models()
+    assert {c[0] for c in E.PUBLISH_TILES} == {n for n, m in zip(names, model) if m[7]} == {"kTile256", "kTile256x128", "kTile128x256", "kTile128"}
