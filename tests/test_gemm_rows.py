@@ -293,6 +293,33 @@ def test_rows_loop_over_tiles(mt, shape, tiles, pad, form):
         assert accs[::2] == accs[1::2] and len(set(accs)) == 8 * mt
 
 
+# --------------------------------------------------------------------------- which tiles a workgroup takes
+
+def _share(left):
+    """last_round_share"""
+    return 16 if 0 < left <= 64 else (left + 7) >> 3
+
+
+@pytest.mark.parametrize("tiles_m,tiles_n", [(1, 1), (1, 63), (64, 1), (13, 5), (17, 15), (32, 8), (257, 1), (9, 29), (40, 13), (127, 129), (128, 128), (16385, 1),
+                                             (5, 3277), (255, 64), (33, 993), (8, 4097), (1, 49157)])
+def test_every_tile_goes_to_one_workgroup(tiles_m, tiles_n):
+    """gemm_rows_kernel's lists over the grid that enqueue_gemm_rows launches: rounds that end inside a group of 256 workgroups, lists of 63
+    to 65 tiles, several groups."""
+    total, rounds = tiles_m * tiles_n, -(-tiles_m * tiles_n // 256)
+    workgroups = 8 * _share(total) if total < 256 else 256 * -(-rounds // 64)
+    full, left = divmod(total, 256)
+    share, taken = _share(left), []
+    for b in range(workgroups):
+        xcd, j, first = b & 7, b >> 3 & 31, (b >> 8) * 64
+        mine = full + (j < share and xcd * share + j < left)
+        for r in range(first, first + max(0, min(mine - first, 64))):
+            nth = r * 256 + xcd * 32 + j if r < full else full * 256 + xcd * share + j
+            band, in_band = divmod(nth, 8 * tiles_n)                 # tile_at
+            height = min(8, tiles_m - band * 8)
+            taken.append((band * 8 + in_band % height, in_band // height))
+    assert len(taken) == total and set(taken) == {(m, n) for m in range(tiles_m) for n in range(tiles_n)}
+
+
 # --------------------------------------------------------------------------- which kernel, and what it computes
 
 # kernel, rows, columns, k, columns of Y's rows: one to three rounds, last row tiles of one row, last column tiles of eight columns, the
@@ -334,3 +361,25 @@ def test_products(kernel, M, N, K, ldy):
     ref = orc.layer_linear(xf, wf)
     bound = np.abs(ref) * 2.0 ** -8 + 1e-5 * orc.layer_linear(np.abs(xf), np.abs(wf)) + 1e-30
     assert (np.abs(got[rows_, :N].astype(np.float64) - ref) <= bound).all(), f"{M}x{N}x{K}"
+
+
+@pytest.mark.gpu
+def test_lists_of_more_than_64_tiles():
+    """A second group of workgroups (more than 64 rounds of 256 tiles): every element against the product in fp32."""
+    import torch
+    from paper_2511_20426_amd.runner import linear
+    M, N, K = 256 * 256 * 64 + 256 + 1, 256, 128
+    assert Hn.linear_kernel(M, N, K) == 256
+    gen = torch.Generator(device="cuda:0").manual_seed(8)
+    x, w = (torch.randn((n, K), generator=gen, device="cuda:0", dtype=torch.bfloat16) for n in (M, N))
+    y = torch.full((M + 1, N), 7.0, dtype=torch.bfloat16, device="cuda:0")
+    print(f"product {M}x{N}x{K}", flush=True)
+    linear(x, w, out=y[:M])
+    torch.cuda.synchronize()
+    assert (y[M] == 7.0).all()
+    wf = w.float()
+    for at in range(0, M, 1 << 18):
+        xf, got = x[at:at + (1 << 18)].float(), y[at:min(M, at + (1 << 18))].float()
+        ref = xf @ wf.T
+        # one rounding to bf16 (2^-9 relative) and the order of 128 products in fp32 on both sides
+        assert ((got - ref).abs() <= ref.abs() * 2.0 ** -8 + 2e-5 * (xf.abs() @ wf.abs().T) + 1e-30).all(), at
