@@ -354,7 +354,6 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs args) {
       load_q<8, 12>(v, q_at, q_end, q_step, rows_end - first);
       if (n_all > 256) CA_FILL(256)
       load_q<12, 16>(v, q_at, q_end, q_step, rows_end - first);
-#pragma unroll 2
       for (int e0 = 512; e0 < n_all; e0 += 256) CA_FILL(e0)
 #undef CA_FILL
     }
