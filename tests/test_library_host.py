@@ -440,8 +440,11 @@ def test_addresses_are_integers(host):
                 pass
 
 
-def test_linear_map_kernels_do_not_spill(tmp_path):
-    """The assembly loops leave few vector registers: what lives across them has to fit, a spilled value is fetched from memory in the
+# file, the generated loops in it, its kernels
+@pytest.mark.parametrize("file,cores,kernels", [("gemm_bf16", ("gemm_core",), 8), ("gemm_rows", ("gemm_rows",), 3),
+                                                ("attn_bf16", ("attn_core", "attn_core16"), 12)])
+def test_kernels_with_assembly_loops_do_not_spill(tmp_path, file, cores, kernels):
+    """The assembly loops leave few registers: what lives across them has to fit, a spilled value is fetched from memory in the
     epilogue of every tile.  (The kernels are compiled here; nothing is run.)"""
     import importlib.util
     import subprocess
@@ -449,16 +452,16 @@ def test_linear_map_kernels_do_not_spill(tmp_path):
     spec = importlib.util.spec_from_file_location("_flags", os.path.join(ROOT, "paper_2511_20426_amd", "_build.py"))
     build = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(build)
-    subprocess.run([sys.executable, os.path.join(build.CSRC, "gen_gemm_core.py"), str(tmp_path / "gemm_core_gfx950.inc")], check=True,
-                   capture_output=True)
-    out = tmp_path / "gemm.s"
-    subprocess.run([build.hipcc(), "-x", "hip", "-S", "--offload-device-only", os.path.join(build.CSRC, "gemm_bf16.hip"), "-o", str(out), "-O3",
+    for core in cores:
+        subprocess.run([sys.executable, os.path.join(build.CSRC, f"gen_{core}.py"), str(tmp_path / f"{core}_gfx950.inc")], check=True, capture_output=True)
+    out = tmp_path / "out.s"
+    subprocess.run([build.hipcc(), "-x", "hip", "-S", "--offload-device-only", os.path.join(build.CSRC, file + ".hip"), "-o", str(out), "-O3",
                     "-std=c++17", "--offload-arch=gfx950", "-I", os.path.join(ROOT, "include"), "-I", build.CSRC, "-I", str(tmp_path)] +
                    build.DEVICE_FLAGS, check=True, capture_output=True)
     text = out.read_text()
-    kernels = re.findall(r"\.name:\s*(\S*gemm_\S*)", text)
-    spilled = [int(n) for n in re.findall(r"\.vgpr_spill_count:\s*(\d+)", text)]
-    assert len(kernels) == len(spilled) >= 8 and not any(spilled), list(zip(kernels, spilled))
+    names = re.findall(r"\.name:\s*(\S*_kernel\S*)", text)
+    spilled = [int(n) for n in re.findall(r"\.[sv]gpr_spill_count:\s*(\d+)", text)]
+    assert len(names) == kernels and len(spilled) == 2 * kernels and not any(spilled), list(zip(names, spilled[::2], spilled[1::2]))
 
 
 def test_every_tile_of_the_publishing_projection_is_tested():
