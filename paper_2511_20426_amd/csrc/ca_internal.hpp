@@ -125,6 +125,10 @@ int32_t launch_gemm_bf16(const void* x, const void* w, void* y, int64_t M, int32
 int32_t launch_gemm_rows(int tile_rows, const void* x, const void* w, void* y, int32_t M, int32_t N, int32_t K,
                          int64_t ldx, int64_t ldw, int64_t ldy, void* stream);
 int32_t gemm_rows_ready();
+// ... in a compiled tile (a GemmTile of up to 128 columns), each workgroup one
+int32_t launch_gemm_tile(int tile, const void* x, const void* w, void* y, int32_t M, int32_t N, int32_t K,
+                         int64_t ldx, int64_t ldw, int64_t ldy, void* stream);
+int32_t gemm_tiles_ready();
 // The QKV projection of n_blocks blocks (x rows: block b at b * block_tokens; w rows: q|k|v, head,
 // dim) with the publication of K/V to the blocks' slots fused into its epilogue; q_out gets the
 // packed, unrotated queries [n_blocks * block_tokens][heads * 128].

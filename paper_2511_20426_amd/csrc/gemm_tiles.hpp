@@ -2,6 +2,8 @@
 // (Included inside namespace ca { namespace { ... } }.)
 #pragma once
 
+enum GemmTile { kTile256, kTile256x128, kTile128x256, kTile128, kTile64, kTile64Wide };
+
 constexpr int kBandRows = 8;                      // row tiles of a band
 
 // 64 bytes, because a launch with more takes the host longer: 2.6 us with up to 64 bytes of arguments, 3.3 with 128 to 256, 3.7

@@ -90,12 +90,12 @@ def attention_element_bound(o, p, q_rot, k_rot, v, logit_roundings: int = 3):
 # --------------------------------------------------------------------------- kernel of a linear map
 
 def _gemm_models():
-    """The cost models as gemm_bf16.hip holds them: names and rows of the tiles, rows of gemm_rows.hip's heights."""
-    source = open(os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2511_20426_amd", "csrc",
-                               "gemm_bf16.hip")).read()
+    """The cost models as gemm_bf16.hip holds them: names (gemm_tiles.hpp) and rows of the tiles, rows of gemm_rows.hip's heights."""
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2511_20426_amd", "csrc")
+    source, header = (open(os.path.join(csrc, f)).read() for f in ("gemm_bf16.hip", "gemm_tiles.hpp"))
     tables = [[[int(x) for x in r.split(",")] for r in re.findall(r"\{([\d, ]+)\}", re.search(name + r"\[\] = \{(.*?)\};", source, re.S).group(1))]
               for name in ("kModel", "kRows")]
-    names = [t.strip() for t in re.search(r"enum GemmTile \{(.*?)\};", source).group(1).split(",")]
+    names = [t.strip() for t in re.search(r"enum GemmTile \{(.*?)\};", header).group(1).split(",")]
     assert len(tables[0]) == len(names)
     return names, *tables
 

@@ -440,11 +440,11 @@ def test_addresses_are_integers(host):
                 pass
 
 
-# file, the generated loops in it, its kernels
-@pytest.mark.parametrize("file,cores,kernels", [("gemm_bf16", ("gemm_core",), 8), ("gemm_rows", ("gemm_rows",), 3),
+# file, the generated loops in it, its kernels (gemm_tiles.hip's loops are compiled ones)
+@pytest.mark.parametrize("file,cores,kernels", [("gemm_bf16", ("gemm_core",), 4), ("gemm_rows", ("gemm_rows",), 3), ("gemm_tiles", (), 4),
                                                 ("attn_bf16", ("attn_core", "attn_core16"), 12)])
-def test_kernels_with_assembly_loops_do_not_spill(tmp_path, file, cores, kernels):
-    """The assembly loops leave few registers: what lives across them has to fit, a spilled value is fetched from memory in the
+def test_kernels_of_the_matrix_instructions_do_not_spill(tmp_path, file, cores, kernels):
+    """The loops leave few registers: what lives across them has to fit, a spilled value is fetched from memory in the
     epilogue of every tile.  (The kernels are compiled here; nothing is run.)"""
     import importlib.util
     import subprocess
@@ -457,11 +457,15 @@ def test_kernels_with_assembly_loops_do_not_spill(tmp_path, file, cores, kernels
     out = tmp_path / "out.s"
     subprocess.run([build.hipcc(), "-x", "hip", "-S", "--offload-device-only", os.path.join(build.CSRC, file + ".hip"), "-o", str(out), "-O3",
                     "-std=c++17", "--offload-arch=gfx950", "-I", os.path.join(ROOT, "include"), "-I", build.CSRC, "-I", str(tmp_path)] +
-                   build.DEVICE_FLAGS, check=True, capture_output=True)
+                   build.DEVICE_FLAGS + build.FILE_FLAGS.get(file + ".hip", []), check=True, capture_output=True)
     text = out.read_text()
     names = re.findall(r"\.name:\s*(\S*_kernel\S*)", text)
     spilled = [int(n) for n in re.findall(r"\.[sv]gpr_spill_count:\s*(\d+)", text)]
     assert len(names) == kernels and len(spilled) == 2 * kernels and not any(spilled), list(zip(names, spilled[::2], spilled[1::2]))
+    if file == "gemm_tiles":                  # where the loops begin (_build.py)
+        bodies = re.split(r"^_ZN\S*gemm_tile_kernel\S*:", text, flags=re.M)[1:]
+        loops = [re.findall(r"(\S+)\s*\n\.LBB\S+:[^\n]*Loop Header", b.split(".Lfunc_end")[0]) for b in bodies]
+        assert len(loops) == 4 and all(at[:1] == ["6"] for at in loops), loops      # (the first loop is the products')
 
 
 def test_every_tile_of_the_publishing_projection_is_tested():
