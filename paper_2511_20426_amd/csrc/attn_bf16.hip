@@ -184,6 +184,9 @@ __device__ __forceinline__ WorkItem decode_item(const Args& a, const Share& shar
   return w;
 }
 
+// u a + w b, the product with w rounded: written out, because the compiler joins either product to the sum, not the same in each place
+__device__ __forceinline__ float turned(float u, float w, float a, float b) { return __builtin_fmaf(u, a, w * b); }
+
 __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
   f32x2 f = {lo, hi};
   bf16x2 b = __builtin_convertvector(f, bf16x2);   // v_cvt_pk_bf16_f32, round to nearest even
@@ -402,7 +405,7 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs args) {
         for (int j = 0; j < 4; ++j) {
           const uint32_t x = v[i][j];
           const float u = __uint_as_float(x << 16), w = __uint_as_float(x & 0xffff0000u);
-          out[j] = pack2((u * t[j].x - w * t[j].y) * c, (u * t[j].y + w * t[j].x) * c);
+          out[j] = pack2(turned(u, w, t[j].x, -t[j].y) * c, turned(u, w, t[j].y, t[j].x) * c);
         }
         return out;
       };
@@ -461,7 +464,7 @@ __global__ __launch_bounds__(256, 1) void attn_bf16_kernel(AttnArgs args) {
           const float cs = __builtin_amdgcn_cosf(rev), sn = __builtin_amdgcn_sinf(rev);
           const uint32_t x = v[i][j];
           const float u = __uint_as_float(x << 16), w = __uint_as_float(x & 0xffff0000u);
-          out[j] = pack2((u * cs - w * sn) * a.c, (u * sn + w * cs) * a.c);
+          out[j] = pack2(turned(u, w, cs, -sn) * a.c, turned(u, w, sn, cs) * a.c);
         }
         if (row0 + wave * 64 + r >= end_again) out = u32x4{0, 0, 0, 0};
         *reinterpret_cast<u32x4*>(park[i & 3] + (i >> 2) * 4096) = out;

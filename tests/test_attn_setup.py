@@ -97,3 +97,33 @@ def test_axes_that_end_inside_a_lane(dims):
         rot = torch.cat([pool.rope(qt[i * L:(i + 1) * L], fpb * g) for i, g in enumerate(infl)])
         ref = Hn.from_torch(pool.forward(rot, list(infl), mode), "bf16")
         assert np.isfinite(got).all() and Hn.rel_l2(got, ref) < 8e-3, (dims, mode, Hn.rel_l2(got, ref))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("axis", range(3))
+def test_a_pair_is_rotated_the_same_wherever_axes_end(axis):
+    """The first pair of an axis turns by the position on it in every geometry.  With nothing else in Q and K the outputs are the same to
+    the last bit, whichever of its lane's four pairs it is and whether their factors come from the table in pairs, one by
+    one, or without a table: about one rotated value in 2^15 rounds the other way to bf16 if the two products of a rotation
+    are joined in another order."""
+    import torch
+    from paper_2511_20426_amd.runner import CascadePool
+    gen = torch.Generator(device="cuda:0").manual_seed(12)
+    H, D, L = 12, 128, 3 * 30 * 52
+    pairs = [torch.randn((n, H, 2), generator=gen, device="cuda:0").to(torch.bfloat16) for n in (2 * L, 3 * L)]
+    v = torch.randn((3 * L, H, D), generator=gen, device="cuda:0").to(torch.bfloat16)
+    outs = []
+    for dims in ((44, 42, 42), (42, 44, 42), (42, 42, 44), (46, 40, 42), (40, 42, 46), (6, 60, 62), (124, 2, 2), (60, 2, 66)):
+        w = W.small_variant(W.CONFIGS["c3_wan1p3b_cascade5"], heads=H, grid_h=30, grid_w=52, rope_dims=dims, n_cached=1, n_inflight=2)
+        first = sum(dims[:axis])
+        q, k = (torch.zeros((p.shape[0], H, D), dtype=torch.bfloat16, device="cuda:0") for p in pairs)
+        q[..., first:first + 2], k[..., first:first + 2] = pairs
+        print(f"axis {axis} of {dims}", flush=True)
+        pool = CascadePool.for_workload(w)
+        for i in range(3):
+            pool.append(i, 0, 0, k[i * L:(i + 1) * L], v[i * L:(i + 1) * L])
+            if i == 0:
+                pool.ctx.kv_cache_promote(0)
+        outs.append(pool.forward_rope(q, [1, 2], orc.BIDIRECTIONAL))
+        print("rows that differ", int((outs[0] != outs[-1]).any(-1).sum()), flush=True)
+    assert all(torch.equal(outs[0].view(torch.int16), o.view(torch.int16)) for o in outs[1:])
