@@ -264,7 +264,7 @@ def bench_linear(args, torch, W, B) -> int:
         "unit": "TFLOP/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "bf16", "data": "synthetic",
         "config": {"workload": args.workload, "m_rows": M, "n_out": N, "k_in": K, "flops_per_step": flops},
-        "roofline": {"bound": "mfma", "kernel": "gemm_bf16_kernel", "achieved": flops / kms / 1e9,
+        "roofline": {"bound": "mfma", "kernel": "gemm_rows_kernel<8>", "achieved": flops / kms / 1e9,
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": flops / kms / 1e9 / PEAK_BF16_TFLOPS,
                      "avg_launch_ms": kms, "traffic": None},
     }

@@ -800,8 +800,9 @@ int split_of_idle_round(int items_per_xcd, int cus_per_xcd, int items, int min_p
 // The same for launches with walks of several lengths that leave CUs idle: ranges of one length for all of them, since the
 // longest range is what counts.  Fills in `range`, `range_segs`, `split` (of the longest walk) and, as full_items, the workgroups
 // of an XCD.  Whole block-causal steps with each walk in as many ranges, and so: 12 heads, two
-// blocks of 924 tokens over one 48.2 / 44.9 us; six, five of 756 over three 72.7 / 60.9; three, five of 1596 over one 101 / 84;
-// eight, five of 252 28.5 / 25.9; three, five of 390 over two 28.7 / 28.6.
+// blocks of 924 tokens over one 49.8 / 47.2 us; six, five of 756 over three 74.4 / 63.4; three, five of 1596 over one 102.5 /
+// 82.8; eight, five of 252 32.1 / 30.0; two, two of 4680 over two 135.2 / 133.4; the other way three, five of 390 over two 31.3 /
+// 32.4; four, three of 1200 over three 56.2 / 57.2.
 void ranges_of_idle_launch(AttnArgs& a, int cus_per_xcd) {
   const int most = cus_per_xcd < kPartialsPerXcd ? cus_per_xcd : kPartialsPerXcd, max_pages = a.vis_first * a.pages_per_block;
   int64_t best_cost = 40 * int64_t(max_pages);                 // in 40ths of a page time

@@ -154,7 +154,7 @@ __device__ __forceinline__ void publish_tile(const Args& a, const uint8_t* tile,
 // now 23; 9360 x 5120 x 5120 404 / 332, 14040 x 15360 x 5120 1500 / 1465.  Where it does not they are up to 1 %
 // ahead, within the noise: 23400 x 15360 x 5120 2454 / 2471, 18720 x 15360 x 5120 1983 / 2001, 23400 x 5120 x 5120
 // 881 / 879, 16128 x 15360 x 5120 1688 / 1685.  One contiguous range per XCD keeps the XCDs apart (23400 x 15360 x
-// 5120 2740).
+// 5120 2740).  (Plain products, of a time when these had a workgroup to a tile as well.)
 __device__ __forceinline__ bool tile_of_workgroup(const GemmArgs& a, int* tm, int* tn) {
   const int xcd = int(blockIdx.x & 7), j = int(blockIdx.x >> 3), total = a.tiles_m * a.tiles_n;
   if (a.block_cols > 0) {
@@ -330,22 +330,18 @@ int32_t enqueue_gemm_tiles(GemmArgs& a, void* stream) {
 // same matrix instruction over k in steps of 32), so the choice is the cheapest by a model of what was measured:
 // rounds of workgroups over the CUs times (stages of 64 k x time of a stage + set-up and epilogue).  A stage takes
 // longer when most CUs work (`full`, from half of them on in proportion: the last round has its own).  Microseconds
-// (fixed: plain, publishing; the plain ones of 256 columns are of a workgroup that ends with its tile: such products go on
-// to rows_tile, which weighs gemm_rows.hip's against the cheapest of the others):
-//   256 x 256 (asm loops)   stage 1.0 .. 1.19, fixed 11, 12.5     256 x 128   stage 0.85 .. 0.87, fixed 5.8, 6.25
-//   192 x 256               0.82 .. 0.97, 8.25                    128 x 128   0.43, 5, 4.5
-//   128 x 256               0.58 .. 0.66, 7, 9.25                 64 x 64     two a CU 0.31, 4; one a CU 0.165, 4
-// Over 270 products the pick is 0.4 % slower than the fastest tile in the geometric mean, 9 % at the worst (8987 x 4592
-// x 256).  Whole calls, us, 256 x 256 first and then what is taken: 257 x 768 x 1024 (6 tiles of 256 x 256) 22.7
-// -> 8.1, 64 x 128 x 5120 80 -> 17, 1200 x 1400 x 1152 27.7 -> 10.1, 23400 x 128 x 5120 86 -> 39 (128 x 128), 4680 x
-// 1536 x 1536 32.7 -> 22.2 (128 x 256), 4680 x 4608 x 1536 69.8 -> 58.7 (192), 3000 x 3000 x 2944 56.2 -> 47.3 (192),
-// 1170 x 15360 x 5120 191 -> 157 (192); 256 x 256 stays where its tiles fill the chip: 23400 x 15360 x 5120 2440
-// against 2540, 8192^3 670 against 750.  256 x 128, of compiled code, is for column counts that 256 does not divide
-// well (an odd number of heads): 14040 x 1152 x 384 19.6 against 23.0 with 192, 23400 x 640 x 640 25.8 / 29.7, 17961
-// x 328 x 2432 36.1 / 38.8.  The publishing epilogue needs whole pages and heads: 128 or 256 rows.  It writes pages
-// instead of rows, which the largest tiles pay for most: of 23400 x 768 x 256, 34.0 us with 256 x 256, 33.5 with 128
-// x 256, 26.6 with 256 x 128, 29.4 with 128 x 128; 23400 x 3072 x 1024 163 / 176 / 182 / 206; 7920 x 2304 x 768 52 /
-// 45 / 49 / 46.
+// (fixed: plain, publishing; plain products in tiles of 256 columns are rows_tile's):
+//   256 x 256 (asm loop)    stage 1.0 .. 1.19, fixed -, 12.5      256 x 128   stage 0.85 .. 0.87, fixed 5.8, 6.25
+//   128 x 256 (asm loop)    0.58 .. 0.66, -, 9.25                 128 x 128   0.43, 5, 4.5
+//                                                                 64 x 64     two a CU 0.31, 4, -; one a CU 0.165, 4, -
+// Plain calls, us, by what is taken: 64 x 64, one a CU: 257 x 768 x 1024 5.8 (two a CU 6.3, 128 x 128 9.6, 128 x 256 14.4), 64 x 128 x 5120 16.6 (19.7, 34,
+// 48); two a CU: 1200 x 1400 x 1152 9.8 (one a CU 11.9, 128 x 128 11.7); 128 x 128: 23400 x 128 x 5120 39.6 (64 x 64 58, 256 x 128 62),
+// 1560 x 1536 x 1536 14.0 (18.1, 22.2).  256 x 128 is for column counts that 256 does not divide well (an odd number of
+// heads): 14040 x 1152 x 384 19.7 (192 x 256 21.2), 23400 x 640 x 640 26.3 (27.6), 17961 x 328 x 2432 35.9 (37.8).  The
+// publishing epilogue needs whole pages and heads: 128 or 256 rows.  It writes pages instead of rows, which the largest
+// tiles pay for most: of 23400 x 768 x 256, 34.0 us with 256 x 256, 33.5 with 128 x 256, 26.6 with 256 x 128, 29.4 with 128
+// x 128; 23400 x 3072 x 1024 163 / 176 / 182 / 206; 7920 x 2304 x 768 52 / 45 / 49 / 46.
+
 // the cheapest tile and, in nanoseconds, what it costs
 GemmTile pick_gemm_tile(const GemmArgs& a, bool publish, int n_cu, int64_t* cost) {
   // fixed, fixed_publish: 0 where a plain product, a publishing one does not take the tile
@@ -375,10 +371,13 @@ GemmTile pick_gemm_tile(const GemmArgs& a, bool publish, int n_cu, int64_t* cost
 // Tile height of gemm_rows.hip that a plain product takes, or 0 where one of the tiles of compiled code is cheaper.  A
 // workgroup goes on from tile to tile there, so that a round costs its stages and the results' way out, and a launch its
 // set-up once: nanoseconds by stages of 64 k = start + whole rounds x (stages x full + tile) + last round (stages x stage +
-// tile), stage up to full from half of the CUs on.  Fitted to 254 products; the pick is 0.14 % slower than the fastest of
-// them, 7 % at the worst (3737 x 15120 x 384).  Whole calls, us, as pick_gemm_tile has it with a tile to a workgroup / now: 23400 x
-// 5120 x 256 101 / 80, 10709 x 4200 x 256 43.8 / 30.5, 5882 x 8776 x 640 82 / 63, 4680 x 3072 x 512 19.1 / 17.5, 4680 x 4608 x 1536 59 /
-// 55, 23400 x 15360 x 5120 2583 / 2453.  The 256 x 128 tile stays ahead of an equal cost (14040 x 1152 x 384 20.1, 192 x 256 21.5).
+// tile), stage up to full from half of the CUs on.  Fitted to 254 products; over 130 others (64 to 23400 rows, up to 15360 columns, k up to
+// 5120) the pick is 0.2 % slower than the fastest of all seven kernels in the geometric mean, 16 % at the worst (6658 x 6736 x 128,
+// 28.8 us for 24.9).  Whole calls, us, with a tile to a workgroup and the result through LDS / now: 23400 x 5120 x 256 102 / 78, 10709 x
+// 4200 x 256 46 / 34, 5882 x 8776 x 640 87 / 71, 4680 x 3072 x 512 19.0 / 17.3, 4680 x 4608 x 1536 59.4 / 54.5, 23400 x 15360
+// x 5120 2423 / 2352; the other way 8192 x 8192 x 8064 673 / 696, whole rounds of long walks.  By height, 256 / 192 / 128: 4680 x 4608 x 1536 66.0
+// / 54.1 / 60.7, 23400 x 15360 x 5120 2341 / 2461 / 2752, 4680 x 1536 x 1536 32.8 / 26.9 / 22.4.  The 256 x 128 tile stays ahead of an
+// equal cost (14040 x 1152 x 384 19.7, 192 x 256 21.2).
 int rows_tile(const GemmArgs& a, int n_cu, int64_t compiled, GemmTile by) {
   static constexpr struct { int rows, start, stage, full, tile; } kRows[] = {
       {256, 2260, 960, 1325, 5100}, {192, 2280, 754, 1070, 3900}, {128, 2840, 594, 785, 2410}};

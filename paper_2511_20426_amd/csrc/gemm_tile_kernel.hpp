@@ -52,7 +52,7 @@ __global__ __launch_bounds__(T::kThreads) void gemm_tile_kernel(typename TileArg
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l15 = lane & 15, grp = lane >> 4;
   const int wm = wave % kWavesM, wn = wave / kWavesM;
-  // XCD x takes a contiguous range of the tiles.  Dealing them as gemm_bf16_kernel does costs a short kernel its longer
+  // XCD x takes a contiguous range of the tiles.  Dealing them as gemm_rows_kernel does costs a short kernel its longer
   // set-up: 220 x 2696 x 3072 12.0 us, 12.7 dealt; 2868 x 992 x 512 7.5, 7.6.
   const int nth = int(blockIdx.x & 7) * a.more + int(blockIdx.x >> 3);
   if (nth >= a.tiles_m * a.tiles_n) return;

@@ -96,8 +96,8 @@ def mfma_pv(dt, qt, p_base):
 
 def pv_order(p_base):
     """the query tiles forth and back, so that where a V fragment ends the next MFMA keeps its P operand: 2178 TFLOP/s in a loop of
-    nothing but these MFMAs and QK's, 2148 with the tiles always in one order; 14B step of five blocks 15.71 -> 15.59 ms, 1.3B
-    rollout step 4820 -> 4786 us, one 1.3B block 646 -> 643"""
+    nothing but these MFMAs and QK's, 2148 with the tiles always in one order; whole steps gain under 1 %, which the noise of a
+    run hides at the 14B shape"""
     return [mfma_pv(dt, qt if dt % 2 == 0 else QT - 1 - qt, p_base) for dt in range(8) for qt in range(QT)]
 
 

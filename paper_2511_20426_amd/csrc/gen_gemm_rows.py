@@ -5,8 +5,8 @@ one tile of 256, 192 or 128 rows by 256 columns after the other (MT = 8, 6, 4 su
 Tile, waves, stages of 64 k, rings in LDS and barriers are those of gen_gemm_core.py, which says why they are so.  Here a
 workgroup does not end with its tile: the stream of stages goes on with the next tile's, so that nothing is requested twice
 and nothing waited for between tiles, and the results leave straight from registers, without LDS, which the next tile's
-stages are filling by then.  What a tile costs outside its products went from 25 000 cycles (set-up, first fill, transposition
-through LDS, two barriers) to about 3000.
+stages are filling by then.  What a tile of 256 rows costs outside its products went from 11 us (set-up, first fill, transposition
+through LDS, two barriers) to 5.1, by the cost models fitted to either (rows_tile in gemm_bf16.hip).
 
 Results from registers.  With W as the A operand a lane ends up with four consecutive rows of W, that is four columns of one
 row of Y.  The 16 rows of W that sub-tile ti = 2 c + b multiplies are picked as 32 c + 8 g + 4 b + r (lane group g, accumulator

@@ -2,7 +2,7 @@
 // and pass on, without a Python object for every look at a tensor.  Small calls are bound by the host (a launch alone takes 2.6
 // us).  Host time of a call, through ctypes and here: a linear map 5.2 and 3.3 us, a cache write 7.1 and 3.9, a rotation 5.1 and
 // 3.8, attention on rotated queries 5.1 and 3.5, on raw ones 8.6 and 7.2 (its launches take most of that); the smallest
-// rollout step in fp32 19.9 -> 15.1 us, a linear map of 257 x 768 x 1024 5.76 -> 5.53.
+// rollout step in fp32 18 to 20 -> 15.1 us, a linear map of 257 x 768 x 1024 5.76 -> 5.53.
 //
 // A function here takes a call only if everything is as it should be (plain tensors, exact integers, lists or tuples, shapes and
 // strides that fit); otherwise it returns None and has done nothing, and the Python code does what it does: checks one by one and
