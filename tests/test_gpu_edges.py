@@ -225,9 +225,9 @@ LINEAR_TILES = [(256, 769, 13064, 128), (256, 4097, 3592, 768), (256, 65537, 128
                 ("kTile64", 1100, 1400, 256), ("kTile64Wide", 129, 200, 768)]
 
 
-@pytest.mark.parametrize("kernel,M,N,K", LINEAR_TILES)
-def test_linear_tile_by_name(kernel, M, N, K):
-    assert Hn.linear_kernel(M, N, K) == kernel
+@pytest.mark.parametrize("tile,M,N,K", LINEAR_TILES)
+def test_linear_tile_by_name(tile, M, N, K):
+    assert Hn.linear_kernel(M, N, K) == tile
     test_linear_tiles(M, N, K)
 
 

@@ -441,9 +441,8 @@ def test_addresses_are_integers(host):
 
 
 # file, the generated loops in it, its kernels (gemm_tiles.hip's loops are compiled ones)
-@pytest.mark.parametrize("file,cores,kernels", [("gemm_bf16", ("gemm_core",), 4), ("gemm_rows", ("gemm_rows",), 3), ("gemm_tiles", (), 4),
-                                                ("attn_bf16", ("attn_core", "attn_core16"), 12)])
-def test_kernels_of_the_matrix_instructions_do_not_spill(tmp_path, file, cores, kernels):
+@pytest.mark.parametrize("file,cores,kernels", [("gemm_bf16", ("gemm_core",), 4), ("gemm_rows", ("gemm_rows",), 3), ("gemm_tiles", (), 4)])
+def test_linear_map_kernels_do_not_spill(tmp_path, file, cores, kernels):
     """The loops leave few registers: what lives across them has to fit, a spilled value is fetched from memory in the
     epilogue of every tile.  (The kernels are compiled here; nothing is run.)"""
     import importlib.util
@@ -468,7 +467,11 @@ def test_kernels_of_the_matrix_instructions_do_not_spill(tmp_path, file, cores, 
         assert len(loops) == 4 and all(at[:1] == ["6"] for at in loops), loops      # (the first loop is the products')
 
 
-def test_every_tile_of_the_publishing_projection_is_tested():
+def test_attention_kernels_do_not_spill(tmp_path):
+    test_linear_map_kernels_do_not_spill(tmp_path, "attn_bf16", ("attn_core", "attn_core16"), 12)
+
+
+def test_every_tile_of_the_linear_maps_is_tested():
     """The cost model sends the projections of the GPU tests to the tiles they are meant for, and no tile is without one (the plain
     products': test_gemm_rows.py)."""
     from tests import _harness as Hn
